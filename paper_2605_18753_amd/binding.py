@@ -91,11 +91,20 @@ def _check(rc: int, what: str):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # a plain int (or None): the declared argument types convert it
+    return None if t is None else t.data_ptr()
+
+
+# The current stream's handle without building a torch.cuda.Stream object: 0.2 us instead of
+# 2.7 us, which a decode step of a short cache would notice.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is not None and _device is not None and torch.cuda.is_initialized():
+        return _raw_stream(_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def make_params(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, o: Optional[torch.Tensor],
@@ -137,7 +146,7 @@ def alloc_workspace(p: dash_params, device) -> torch.Tensor:
 def _ws_ptr(ws: torch.Tensor):
     base = ws.data_ptr()
     aligned = (base + 255) & ~255
-    return ctypes.c_void_p(aligned), ws.numel() - (aligned - base)
+    return aligned, ws.numel() - (aligned - base)
 
 
 @dataclass
@@ -164,7 +173,7 @@ class Lists:
 
 def dash_kbar_compress(p: dash_params, k: torch.Tensor, kbar: torch.Tensor,
                        first_chunk: int = 0, n_chunks: int = -1) -> None:
-    _check(load_library().dash_kbar_compress(ctypes.byref(p), _ptr(k), _ptr(kbar), first_chunk, n_chunks,
+    _check(load_library().dash_kbar_compress(p, _ptr(k), _ptr(kbar), first_chunk, n_chunks,
                                              _stream()), "dash_kbar_compress")
 
 
@@ -184,27 +193,27 @@ def dash_kbar_summarize(p: dash_params, k: torch.Tensor, qbar: torch.Tensor, kba
     """qbar: fp32 tensor [h_kv, d] (one summary query per kv-head), [h_kv, T_c, d]
     or [batch, h_kv, T_c, d] (one per chunk); only the strides are passed on."""
     arr = _qbar_strides(qbar)
-    _check(load_library().dash_kbar_summarize(ctypes.byref(p), _ptr(k), _ptr(qbar), arr, _ptr(kbar),
+    _check(load_library().dash_kbar_summarize(p, _ptr(k), _ptr(qbar), arr, _ptr(kbar),
                                               first_chunk, n_chunks, _stream()), "dash_kbar_summarize")
 
 
 def dash_stage1_route(p, q, kbar, lists: Lists, ws: torch.Tensor) -> None:
     wp, wn = _ws_ptr(ws)
-    _check(load_library().dash_stage1_route(ctypes.byref(p), _ptr(q), _ptr(kbar), _ptr(lists.mask),
+    _check(load_library().dash_stage1_route(p, _ptr(q), _ptr(kbar), _ptr(lists.mask),
                                             _ptr(lists.cnt), _ptr(lists.idx), _ptr(lists.bias),
                                             _ptr(lists.tau), wp, wn, _stream()), "dash_stage1_route")
 
 
 def dash_stage2_attend(p, q, k, v, o, lists: Lists, ws: torch.Tensor) -> None:
     wp, wn = _ws_ptr(ws)
-    _check(load_library().dash_stage2_attend(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), _ptr(o),
+    _check(load_library().dash_stage2_attend(p, _ptr(q), _ptr(k), _ptr(v), _ptr(o),
                                              _ptr(lists.mask), _ptr(lists.bias), wp, wn, _stream()),
            "dash_stage2_attend")
 
 
 def dash_attn_prefill(p, q, k, v, o, kbar, lists: Lists, ws: torch.Tensor) -> None:
     wp, wn = _ws_ptr(ws)
-    _check(load_library().dash_attn_prefill(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(kbar),
+    _check(load_library().dash_attn_prefill(p, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(kbar),
                                             _ptr(lists.mask), _ptr(lists.cnt), _ptr(lists.idx),
                                             _ptr(lists.bias), _ptr(lists.tau), wp, wn, _stream()),
            "dash_attn_prefill")
@@ -212,7 +221,7 @@ def dash_attn_prefill(p, q, k, v, o, kbar, lists: Lists, ws: torch.Tensor) -> No
 
 def dash_attn_decode(p, q, k_cache, v_cache, kbar_cache, o, lists: Lists, ws: torch.Tensor) -> None:
     wp, wn = _ws_ptr(ws)
-    _check(load_library().dash_attn_decode(ctypes.byref(p), _ptr(q), _ptr(k_cache), _ptr(v_cache),
+    _check(load_library().dash_attn_decode(p, _ptr(q), _ptr(k_cache), _ptr(v_cache),
                                            _ptr(kbar_cache), _ptr(o), _ptr(lists.mask), _ptr(lists.cnt),
                                            _ptr(lists.idx), _ptr(lists.bias), _ptr(lists.tau), wp, wn,
                                            _stream()), "dash_attn_decode")
@@ -220,7 +229,7 @@ def dash_attn_decode(p, q, k_cache, v_cache, kbar_cache, o, lists: Lists, ws: to
 
 def dash_attn_decode_static(p, q, k_cache, v_cache, kbar_cache, o, lists: Lists) -> None:
     """dash_attn_decode on the library's built-in scratch (no workspace, no allocation)."""
-    _check(load_library().dash_attn_decode_static(ctypes.byref(p), _ptr(q), _ptr(k_cache), _ptr(v_cache),
+    _check(load_library().dash_attn_decode_static(p, _ptr(q), _ptr(k_cache), _ptr(v_cache),
                                                   _ptr(kbar_cache), _ptr(o), _ptr(lists.mask), _ptr(lists.cnt),
                                                   _ptr(lists.idx), _ptr(lists.bias), _ptr(lists.tau), _stream()),
            "dash_attn_decode_static")
@@ -230,7 +239,7 @@ def dash_attn_decode_ragged(p, q, k_cache, v_cache, kbar_cache, seq_lens: torch.
                             ws: torch.Tensor, update_cache: bool = True) -> None:
     assert seq_lens.dtype == torch.int32 and seq_lens.is_contiguous() and seq_lens.numel() == p.batch
     wp, wn = _ws_ptr(ws)
-    _check(load_library().dash_attn_decode_ragged(ctypes.byref(p), _ptr(q), _ptr(k_cache), _ptr(v_cache),
+    _check(load_library().dash_attn_decode_ragged(p, _ptr(q), _ptr(k_cache), _ptr(v_cache),
                                                   _ptr(kbar_cache), _ptr(seq_lens), int(update_cache), _ptr(o),
                                                   _ptr(lists.mask), _ptr(lists.cnt), _ptr(lists.idx),
                                                   _ptr(lists.bias), _ptr(lists.tau), wp, wn, _stream()),
@@ -239,7 +248,7 @@ def dash_attn_decode_ragged(p, q, k_cache, v_cache, kbar_cache, seq_lens: torch.
 
 def dense_attn(p, q, k, v, o, ws: torch.Tensor) -> None:
     wp, wn = _ws_ptr(ws)
-    _check(load_library().dense_attn(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), _ptr(o), wp, wn, _stream()),
+    _check(load_library().dense_attn(p, _ptr(q), _ptr(k), _ptr(v), _ptr(o), wp, wn, _stream()),
            "dense_attn")
 
 
@@ -260,7 +269,7 @@ def dash_attn_backward(p, q, k, v, d_o, kbar, lists: Lists, dq, dk, dv, ws: torc
     wp, wn = _ws_ptr(ws)
     if dkbar is not None:
         assert dkbar.dtype == torch.float32 and dkbar.is_contiguous() and tuple(dkbar.shape) == kbar_shape(p)
-    _check(load_library().dash_attn_backward(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), _ptr(d_o),
+    _check(load_library().dash_attn_backward(p, _ptr(q), _ptr(k), _ptr(v), _ptr(d_o),
                                              _ptr(kbar), _ptr(lists.mask), _ptr(lists.bias), _ptr(lists.tau),
                                              _ptr(dq), _ptr(dk), _ptr(dv), _ptr(dkbar), wp, wn, _stream()),
            "dash_attn_backward")
@@ -271,7 +280,7 @@ def dash_kbar_summarize_backward(p, k, qbar: torch.Tensor, dkbar: torch.Tensor, 
     strides = _qbar_strides(qbar)
     assert dkbar.dtype == torch.float32 and dkbar.is_contiguous() and tuple(dkbar.shape) == kbar_shape(p)
     assert dqbar.dtype == torch.float32 and dqbar.is_contiguous() and tuple(dqbar.shape) == kbar_shape(p)
-    _check(load_library().dash_kbar_summarize_backward(ctypes.byref(p), _ptr(k), _ptr(qbar), strides, _ptr(dkbar),
+    _check(load_library().dash_kbar_summarize_backward(p, _ptr(k), _ptr(qbar), strides, _ptr(dkbar),
                                                        _ptr(dk), _ptr(dqbar), _stream()),
            "dash_kbar_summarize_backward")
 

@@ -14,6 +14,8 @@ MICROBENCH_LIB = os.path.join(HERE, "libdash_microbench.so")
 SOURCES = [(s, [], s.replace(".hip", ".o")) for s in
            ["api.hip", "compress.hip", "stage1.hip", "stage2.hip", "stage2_decode.hip", "stage2_f32.hip", "backward.hip"]]
 SOURCES += [("stage1_regs.hip", [f"-DDASH_S1R_G={g}"], f"stage1_regs_g{g}.o") for g in (1, 2, 4, 8, 16)]
+# ... the decode step once per entmax exponent mode
+SOURCES += [("decode_route.hip", [f"-DDASH_DEC_MODE={m}"], f"decode_route_m{m}.o") for m in range(5)]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-w",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -76,8 +76,8 @@ int make_layout(const dash_params* p, Layout* L, bool routing) {
   int splits = 1;
   if (decode_mfma) {
     const int pairs = p->batch * p->h_kv;
-    const int target = 512;   // workgroups per launch: two per CU
-    splits = (target + pairs - 1) / pairs;
+    const int target = 512;   // workgroups per launch: two per CU, all resident at once
+    splits = target / pairs;
     if (splits > 64) splits = 64;
     if (splits > L->t_all) splits = L->t_all;
     if (splits < 1) splits = 1;
@@ -95,6 +95,12 @@ int make_layout(const dash_params* p, Layout* L, bool routing) {
     off += align256((size_t)p->batch * p->h_q * p->n_q * (L->t_c > 0 ? L->t_c : 1) * 4);
   L->off_part = off;
   if (decode_mfma) off += align256((size_t)p->batch * p->h_kv * splits * g * (p->head_dim + 2) * 4);
+  L->off_flags = off;
+  if (decode_mfma) off += align256((size_t)p->batch * p->h_kv * splits * 8);
+  L->total_min = off > 0 ? off : 256;
+  L->off_dec_scores = off;
+  L->dec_scores = decode_scores_apart(*p, *L);
+  if (L->dec_scores) off += align256((size_t)p->batch * p->h_q * decode_scores_ld(*L) * 4);
   L->total = off > 0 ? off : 256;
   if (p->dtype == DASH_BF16) {
     // the bf16 kernels address one (batch, kv-head) slice of every tensor with 32-bit byte
@@ -109,8 +115,8 @@ int make_layout(const dash_params* p, Layout* L, bool routing) {
   return DASH_OK;
 }
 
-static int check_ws(const Layout& L, void* ws, size_t bytes) {
-  if (!ws || ((uintptr_t)ws & 255) != 0 || bytes < L.total) return DASH_EWORKSPACE;
+static int check_ws(size_t need, void* ws, size_t bytes) {
+  if (!ws || ((uintptr_t)ws & 255) != 0 || bytes < need) return DASH_EWORKSPACE;
   return DASH_OK;
 }
 
@@ -143,7 +149,7 @@ static int run_stage2(const dash_params* p, const Layout& L, const void* q, cons
   hipError_t e;
   if (p->dtype == DASH_F32) e = launch_s2_f32(*p, L, q, k, v, o, m, bb, dense, st);
   else if (p->n_q == 1)
-    e = launch_decode_s2(*p, L, q, k, v, o, m, bb, reinterpret_cast<float*>(ws + L.off_part), dense, st);
+    e = launch_decode_s2(*p, L, q, k, v, o, m, bb, ws, dense, st);
   else e = launch_s2_mfma(*p, L, q, k, v, o, m, bb, dense, st);
   return e == hipSuccess ? DASH_OK : DASH_ELAUNCH;
 }
@@ -209,7 +215,7 @@ int dash_stage1_route(const dash_params* p, const void* q, const float* kbar, ui
   int rc = make_layout(p, &L);
   if (rc != DASH_OK) return rc;
   if (!q || (!kbar && L.t_c > 0)) return DASH_EINVAL;
-  if ((rc = check_ws(L, workspace, workspace_bytes)) != DASH_OK) return rc;
+  if ((rc = check_ws(L.total, workspace, workspace_bytes)) != DASH_OK) return rc;
   return run_stage1(p, L, q, kbar, mask, blk_cnt, blk_idx, blk_bias, tau, (char*)workspace,
                     (hipStream_t)stream);
 }
@@ -221,7 +227,7 @@ int dash_stage2_attend(const dash_params* p, const void* q, const void* k, const
   int rc = make_layout(p, &L);
   if (rc != DASH_OK) return rc;
   if (!q || !k || !v || !o) return DASH_EINVAL;
-  if ((rc = check_ws(L, workspace, workspace_bytes)) != DASH_OK) return rc;
+  if ((rc = check_ws(L.total, workspace, workspace_bytes)) != DASH_OK) return rc;
   return run_stage2(p, L, q, k, v, o, mask, blk_bias, (char*)workspace, false, (hipStream_t)stream);
 }
 
@@ -233,7 +239,7 @@ int dash_attn_prefill(const dash_params* p, const void* q, const void* k, const 
   int rc = make_layout(p, &L);
   if (rc != DASH_OK) return rc;
   if (!q || !k || !v || !o || (!kbar && L.t_c > 0)) return DASH_EINVAL;
-  if ((rc = check_ws(L, workspace, workspace_bytes)) != DASH_OK) return rc;
+  if ((rc = check_ws(L.total, workspace, workspace_bytes)) != DASH_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   if (launch_kbar_compress(*p, L, k, kbar, 0, L.t_c, st) != hipSuccess) return DASH_ELAUNCH;
   rc = run_stage1(p, L, q, kbar, mask, blk_cnt, blk_idx, blk_bias, tau, (char*)workspace, st);
@@ -244,16 +250,25 @@ int dash_attn_prefill(const dash_params* p, const void* q, const void* k, const 
 static int decode_impl(const dash_params* p, const void* q, const void* k_cache, const void* v_cache,
                        float* kbar_cache, const int32_t* seq_lens, bool update_cache, void* o,
                        uint32_t* mask, int32_t* blk_cnt, int32_t* blk_idx, float* blk_bias, float* tau,
-                       void* workspace, size_t workspace_bytes, void* stream) {
+                       void* workspace, size_t workspace_bytes, void* stream, bool built_in = false) {
   Layout L;
   int rc = make_layout(p, &L);
   if (rc != DASH_OK) return rc;
   if (p->n_q != 1 || !p->causal) return DASH_EINVAL;
   if (!q || !k_cache || !v_cache || (!kbar_cache && L.t_c > 0) || !o) return DASH_EINVAL;
   if (seq_lens && p->dtype != DASH_BF16) return DASH_EUNSUPPORTED;
-  if ((rc = check_ws(L, workspace, workspace_bytes)) != DASH_OK) return rc;
+  // the built-in scratch may lack the room for score rows of their own
+  if ((rc = check_ws(built_in ? L.total_min : L.total, workspace, workspace_bytes)) != DASH_OK) return rc;
   L.seq_lens = seq_lens;
   hipStream_t st = (hipStream_t)stream;
+  if (decode_route_applicable(*p, L, workspace_bytes)) {
+    S1Out out;
+    out.mask = mask; out.cnt = blk_cnt; out.idx = blk_idx; out.bias = blk_bias; out.tau = tau;
+    return launch_decode_route(*p, L, q, k_cache, v_cache, o, kbar_cache, update_cache, out, (char*)workspace,
+                               workspace_bytes, st) == hipSuccess ? DASH_OK : DASH_ELAUNCH;
+  }
+  // fp32 tensors, and score rows that neither the LDS nor the scratch has room for: routing and
+  // attention one after the other
   // a current token that completes a chunk: that chunk is summarised now, by extra workgroups
   // of the Stage-1 launch; it becomes a candidate only for later positions
   rc = run_stage1(p, L, q, kbar_cache, mask, blk_cnt, blk_idx, blk_bias, tau, (char*)workspace, st,
@@ -276,11 +291,11 @@ int dash_attn_decode_static(const dash_params* p, const void* q, const void* k_c
   Layout L;
   int rc = make_layout(p, &L);
   if (rc != DASH_OK) return rc;
-  if (L.total > kStaticScratchBytes) return DASH_EWORKSPACE;   // larger than the built-in scratch
+  if (L.total_min > kStaticScratchBytes) return DASH_EWORKSPACE;   // larger than the built-in scratch
   void* ws = nullptr;
   if ((rc = static_scratch(&ws)) != DASH_OK) return rc;
   return decode_impl(p, q, k_cache, v_cache, kbar_cache, nullptr, true, o, mask, blk_cnt, blk_idx,
-                     blk_bias, tau, ws, kStaticScratchBytes, stream);
+                     blk_bias, tau, ws, kStaticScratchBytes, stream, true);
 }
 
 int dash_attn_decode_ragged(const dash_params* p, const void* q, const void* k_cache,
@@ -299,7 +314,7 @@ int dense_attn(const dash_params* p, const void* q, const void* k, const void* v
   int rc = make_layout(p, &L, false);
   if (rc != DASH_OK) return rc;
   if (!q || !k || !v || !o) return DASH_EINVAL;
-  if ((rc = check_ws(L, workspace, workspace_bytes)) != DASH_OK) return rc;
+  if ((rc = check_ws(L.total, workspace, workspace_bytes)) != DASH_OK) return rc;
   return run_stage2(p, L, q, k, v, o, nullptr, nullptr, (char*)workspace, true, (hipStream_t)stream);
 }
 

@@ -24,7 +24,9 @@ struct Layout {
   bool use_mfma;    // bf16 prefill path (split summaries + MFMA Stage 1/2)
   const int32_t* seq_lens;   // decode with per-sequence lengths: device array [batch], else null
   // workspace offsets in bytes (256-aligned); 0-sized regions share offsets
-  size_t off_ksplit, off_mask, off_bias, off_scores, off_part, total;
+  size_t off_ksplit, off_mask, off_bias, off_scores, off_part, off_flags, off_dec_scores, total;
+  bool dec_scores;     // decode: the workspace has room for score rows of a launch of their own
+  size_t total_min;    // decode: without that room (total otherwise)
 };
 
 // Validates p and fills L.  Returns a dash_status.  routing = false skips the
@@ -85,8 +87,15 @@ hipError_t launch_backward(const dash_params& p, const Layout& L, const void* q,
 hipError_t launch_kbar_summarize_bwd(const dash_params& p, const Layout& L, const void* k, const float* qbar,
                                      const int64_t* qs, const float* dkbar, void* dk, float* dqbar,
                                      hipStream_t st);
+// bf16 decode (n_q = 1): attention over given lists / dense; the whole step with its routing; where
+// its scores are computed (stage2_decode.hip)
 hipError_t launch_decode_s2(const dash_params& p, const Layout& L, const void* q, const void* k,
                             const void* v, void* o, const uint32_t* mask, const float* bias,
-                            float* partials, bool dense, hipStream_t st);
+                            char* ws, bool dense, hipStream_t st);
+bool decode_scores_apart(const dash_params& p, const Layout& L);
+int decode_scores_ld(const Layout& L);
+bool decode_route_applicable(const dash_params& p, const Layout& L, size_t ws_bytes);
+hipError_t launch_decode_route(const dash_params& p, const Layout& L, const void* q, const void* k, const void* v, void* o,
+                               float* kbar, bool update, const S1Out& out, char* ws, size_t ws_bytes, hipStream_t st);
 
 }  // namespace dash

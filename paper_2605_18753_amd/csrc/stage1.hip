@@ -27,6 +27,7 @@
 #include "compress_body.h"
 #include "dash_internal.h"
 #include "stage1_common.h"
+#include "stage1_solve.h"
 
 namespace dash {
 
@@ -39,12 +40,7 @@ static bool s1_regs_applicable(const dash_params& p, const Layout& L, int max_ca
 }
 
 static hipError_t launch_s1_regs(const dash_params& p, const Layout& L, const S1Args& a, int max_cand, hipStream_t st) {
-  int mode;
-  if (a.pexp < 1.f) mode = MODE_BISECT;
-  else if (a.pexp == 1.f) mode = MODE_P1;
-  else if (a.pexp == 2.f) mode = MODE_P2;
-  else if (a.pexp == 4.f) mode = MODE_P4;
-  else mode = MODE_GEN;
+  const int mode = s1_mode(a.pexp);
   switch (L.g_q) {
     case 1: return launch_s1_regs_g1(a, p.head_dim, mode, max_cand, st);
     case 2: return launch_s1_regs_g2(a, p.head_dim, mode, max_cand, st);
@@ -54,98 +50,27 @@ static hipError_t launch_s1_regs(const dash_params& p, const Layout& L, const S1
   }
 }
 
-// Solve RB rows at once (interleaved for ILP).  Row values live in registers:
-// lane l holds chunks l, l+64, ...  On exit the rows of S hold the per-head
-// entmax probabilities.
+// Solve RB rows at once.  Row values live in registers: lane l holds chunks l, l+64, ...
+// On exit the rows of S hold the per-head entmax probabilities.
 template <int NJ, int RB, int MODE>
 __device__ __forceinline__ void solve_rows(float* S, int ld, int row0, int n_cand, float alpha,
                                            float p, int lane, float* tau_out /*[RB]*/) {
-  float v[RB][NJ], mx[RB], lo[RB], hi[RB], tau[RB];
-  bool done[RB];
+  float v[RB][NJ];
 #pragma unroll
-  for (int rb = 0; rb < RB; rb++) {
-    float m = -INFINITY;
+  for (int rb = 0; rb < RB; rb++)
 #pragma unroll
     for (int j = 0; j < NJ; j++) {
       const int c = lane + 64 * j;
       v[rb][j] = c < n_cand ? S[(row0 + 4 * rb) * ld + c] : -INFINITY;
-      m = fmaxf(m, v[rb][j]);
     }
-    mx[rb] = wave_max(m);
-    lo[rb] = mx[rb] - 1.f;
-    hi[rb] = mx[rb] - exp2f(-(alpha - 1.f) * log2f((float)n_cand));
-    tau[rb] = lo[rb];
-    done[rb] = false;
-  }
-  if constexpr (MODE != MODE_BISECT) {
-    // warm start on the 64 lane maxima (a subset: its root and every Newton
-    // iterate from the left on it are lower bounds of tau)
+  solve_rows_regs<NJ, RB, MODE>(v, n_cand, alpha, p, tau_out);
 #pragma unroll
-    for (int rb = 0; rb < RB; rb++) {
-      float ml = -INFINITY;
-#pragma unroll
-      for (int j = 0; j < NJ; j++) ml = fmaxf(ml, v[rb][j]);
-      for (int it = 0; it < 5; it++) {
-        float f, g;
-        pow_terms<MODE>(fmaxf(ml - tau[rb], 0.f), p, f, g);
-        const float F = wave_sum(f), G = wave_sum(g);
-        if (F > 1.f && G > 0.f) tau[rb] += (F - 1.f) / (p * G);
-      }
-      tau[rb] = fmaxf(tau[rb], lo[rb]);
-      if (!(tau[rb] < hi[rb])) tau[rb] = lo[rb];
-    }
-  }
-  for (int it = 0; it < 64; it++) {
-    bool all_done = true;
-#pragma unroll
-    for (int rb = 0; rb < RB; rb++) {
-      float F = 0.f, G = 0.f;
-#pragma unroll
-      for (int j = 0; j < NJ; j++) {
-        float f, g;
-        pow_terms<MODE>(fmaxf(v[rb][j] - tau[rb], 0.f), p, f, g);
-        F += f; G += g;
-      }
-      F = wave_sum(F);
-      G = wave_sum(G);
-      if (!done[rb]) {
-        const float f = F - 1.f;
-        if (f == 0.f) {
-          done[rb] = true;
-        } else {
-          if (f > 0.f) lo[rb] = tau[rb]; else hi[rb] = tau[rb];
-          const float mid = 0.5f * (lo[rb] + hi[rb]);
-          float cand = (MODE == MODE_BISECT || !(G > 0.f)) ? mid : tau[rb] + f / (p * G);
-          if (MODE != MODE_BISECT && cand == tau[rb]) {
-            done[rb] = true;                       // Newton step below the fp32 spacing of tau
-          } else {
-            if (!(cand > lo[rb] && cand < hi[rb])) cand = mid;
-            if (!(cand > lo[rb] && cand < hi[rb])) {
-              done[rb] = true;                     // bracket closed: adjacent floats
-              tau[rb] = lo[rb];
-            } else {
-              if (MODE == MODE_P2 && f > 0.f && cand != mid) {   // see solve_rows16
-                const float st = cand - tau[rb];
-                if ((float)n_cand * st * st < 4e-8f * G) done[rb] = true;
-              }
-              tau[rb] = cand;
-            }
-          }
-        }
-      }
-      all_done = all_done && done[rb];
-    }
-    if (all_done) break;
-  }
-#pragma unroll
-  for (int rb = 0; rb < RB; rb++) {
+  for (int rb = 0; rb < RB; rb++)
 #pragma unroll
     for (int j = 0; j < NJ; j++) {
       const int c = lane + 64 * j;
-      if (c < n_cand) S[(row0 + 4 * rb) * ld + c] = pow_p<MODE>(fmaxf(v[rb][j] - tau[rb], 0.f), p);
+      if (c < n_cand) S[(row0 + 4 * rb) * ld + c] = v[rb][j];
     }
-    tau_out[rb] = tau[rb];
-  }
 }
 
 // Rows are dealt to the four waves round robin (wave w: rows w, w+4, ...), so a
@@ -565,12 +490,7 @@ __global__ __launch_bounds__(256) void s1_route_kernel(S1Args a) {
 
   const int nj = (n_cand + 63) >> 6;
   if (n_cand > 0) {
-    int mode;
-    if (a.pexp < 1.f) mode = MODE_BISECT;
-    else if (a.pexp == 1.f) mode = MODE_P1;
-    else if (a.pexp == 2.f) mode = MODE_P2;
-    else if (a.pexp == 4.f) mode = MODE_P4;
-    else mode = MODE_GEN;
+    const int mode = s1_mode(a.pexp);
 #define DASH_SOLVE(NJ_)                                                                          \
   switch (mode) {                                                                                \
     case MODE_P1: solve_wave_rows<NJ_, MODE_P1>(S, a, wave, ROWS, n_cand, lane, b, r, tok0); break; \
@@ -788,12 +708,7 @@ __global__ __launch_bounds__(1024) void s1_decode_kernel(S1Args a) {
 
   const int nj = (n_cand + 63) >> 6;
   if (n_cand > 0) {
-    int mode;
-    if (a.pexp < 1.f) mode = MODE_BISECT;
-    else if (a.pexp == 1.f) mode = MODE_P1;
-    else if (a.pexp == 2.f) mode = MODE_P2;
-    else if (a.pexp == 4.f) mode = MODE_P4;
-    else mode = MODE_GEN;
+    const int mode = s1_mode(a.pexp);
     if (n_cand <= 512) {
       // four rows per wave, one per DPP row: waves 0..3 cover the 16 rows
       if (wave < 4) {

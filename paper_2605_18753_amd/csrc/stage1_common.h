@@ -25,6 +25,12 @@ struct S1Args {
 };
 
 enum { MODE_P1 = 0, MODE_P2 = 1, MODE_P4 = 2, MODE_GEN = 3, MODE_BISECT = 4 };
+__host__ __device__ inline int s1_mode(float pexp) {
+  if (pexp < 1.f) return MODE_BISECT;
+  if (pexp == 1.f) return MODE_P1;
+  if (pexp == 2.f) return MODE_P2;
+  return pexp == 4.f ? MODE_P4 : MODE_GEN;
+}
 
 // u^p and u^(p-1) for u >= 0 (0 -> 0, and 0 for the derivative term as well)
 template <int MODE>
