@@ -1,0 +1,639 @@
+// Attention for fp32 tensors, forward (Stage 2 of Alg. 3 / Proposition 1 and the dense
+// reference of Eq. 1) and backward, in fp32 throughout on the fp32 matrix cores
+// (v_mfma_f32_16x16x4_f32: fp32 products, fp32 sums; 256 flop per clock and CU).
+//
+// Tiles.  A 16-row tile holds the g_q heads of 16 / g_q consecutive tokens of one kv-head; keys
+// go by 16 as well.  Both kinds of product read their operands straight from global memory (L2)
+// with 16-byte loads and need no shuffle in between:
+//   first kind, contraction over d (S = K Q^T, dP = V dO^T): lane (m = lane % 16, kq = lane / 16)
+//     loads d = 16 s + 4 kq .. + 3 of its row m, for both operands; element e of load s is one
+//     MFMA.  The result, lane (n, hq), is column n (of the B operand) at A rows 4 hq .. + 3.
+//   second kind, contraction over the A rows of the first (O^T = V^T P^T, dQ^T = K^T dZ^T, dV^T =
+//     dO^T P, dK^T = Q^T dZ): step t contracts the rows 4 kq + t, so lane (n, kq) supplies its own
+//     accumulator register t; the other operand's lane (m, kq) loads d = 64 nv + 4 m .. + 3 of row
+//     4 kq + t, element e being the d-tile {64 nv + 4 m + e}.  Result: d = 64 nv + 16 hq + 4 v + e.
+// A wave owns whole chunks (row kernels) or whole 16-row tiles (key kernel) and the waves of a
+// workgroup add their results through LDS, so that the bias gradient of a chunk is one wave's and
+// the launch is wide enough for a single head.
+//
+// What bounds it: at one head, 1024 tokens, d = 64, latency and launches (a wave has one chunk or
+// two); at many heads the fp32 matrix rate.  Before (plain VALU kernels, dK / dV by one atomic
+// per key and element): forward 138 us, backward rows 526 us, summary gradient 286 us on that shape.
+#include <math.h>
+
+#include "backward_args.h"
+#include "common.h"
+#include "dash_internal.h"
+
+namespace dash {
+
+template <int D> struct F32Cfg {
+  static constexpr int NS = D / 16;     // 16-byte loads of a row, first kind
+  static constexpr int NV = D / 64;     // 16-byte loads of a row, second kind
+  static constexpr int LD = D + 4;      // LDS row of a result tile (floats)
+};
+
+template <int D> __device__ __forceinline__ void load_row(const float* row, int kq, f32x4 (&v)[D / 16]) {
+#pragma unroll
+  for (int s = 0; s < D / 16; s++) v[s] = *reinterpret_cast<const f32x4*>(row + 16 * s + 4 * kq);
+}
+// first kind: 16 A rows x 16 B rows
+template <int D> __device__ __forceinline__ f32x4 mma_dot(const f32x4 (&a)[D / 16], const f32x4 (&b)[D / 16]) {
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < D / 16; s++)
+#pragma unroll
+    for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][e], b[s][e], acc, 0, 0, 0);
+  return acc;
+}
+// second kind, one step t: acc[4 nv + e] += (row's d 64 nv + 4 m + e) * w
+template <int D> __device__ __forceinline__ void mma_outer(const f32x4 (&row)[D / 64], float w, f32x4 (&acc)[D / 16]) {
+#pragma unroll
+  for (int nv = 0; nv < D / 64; nv++)
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      acc[4 * nv + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(row[nv][e], w, acc[4 * nv + e], 0, 0, 0);
+}
+template <int D> __device__ __forceinline__ void load_row2(const float* row, int m, f32x4 (&v)[D / 64]) {
+#pragma unroll
+  for (int nv = 0; nv < D / 64; nv++) v[nv] = *reinterpret_cast<const f32x4*>(row + 64 * nv + 4 * m);
+}
+// a second-kind result into LDS row n of a [16][LD] tile
+template <int D> __device__ __forceinline__ void put_tile(float* tile, int n, int hq, const f32x4 (&acc)[D / 16], float w) {
+#pragma unroll
+  for (int nv = 0; nv < D / 64; nv++)
+#pragma unroll
+    for (int v = 0; v < 4; v++) {
+      const f32x4 x = {acc[4 * nv][v] * w, acc[4 * nv + 1][v] * w, acc[4 * nv + 2][v] * w, acc[4 * nv + 3][v] * w};
+      *reinterpret_cast<f32x4*>(tile + n * F32Cfg<D>::LD + 64 * nv + 16 * hq + 4 * v) = x;
+    }
+}
+__device__ __forceinline__ float quad_rows_max(float x) {   // over the four lanes of a column n
+  x = fmaxf(x, __shfl_xor(x, 16));
+  return fmaxf(x, __shfl_xor(x, 32));
+}
+__device__ __forceinline__ float quad_rows_sum(float x) {
+  x += __shfl_xor(x, 16);
+  return x + __shfl_xor(x, 32);
+}
+
+// The chunk list of a 16-row tile: union of its tokens' masks and, per token, the number of
+// entries before each mask word (the bias lists are addressed by rank).
+struct TileLists {
+  uint32_t* uni;      // LDS [64]
+  uint32_t* word;     // LDS [16][64]
+  uint16_t* before;   // LDS [16][64]
+  static constexpr size_t BYTES = 64 * 4 + 16 * 64 * 4 + 16 * 64 * 2;
+  __device__ __forceinline__ TileLists(char* p)
+      : uni((uint32_t*)p), word((uint32_t*)(p + 256)), before((uint16_t*)(p + 256 + 4096)) {}
+  // mask: row of token 0 of the tile; ntok valid tokens.  Ends with a barrier.
+  __device__ __forceinline__ void build(const uint32_t* mask, int words, int ntok, int tid, int nthr) {
+    const int wave = tid >> 6, lane = tid & 63, nw = nthr >> 6;
+    for (int t = wave; t < ntok; t += nw) {
+      const uint32_t w = lane < words ? mask[(int64_t)t * words + lane] : 0u;
+      int incl = __popc(w);
+      const int mine = incl;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(incl, o);
+        if (lane >= o) incl += x;
+      }
+      word[t * 64 + lane] = w;
+      before[t * 64 + lane] = (uint16_t)(incl - mine);
+    }
+    __syncthreads();
+    if (tid < 64) {
+      uint32_t u = 0u;
+      for (int t = 0; t < ntok; t++) u |= word[t * 64 + tid];
+      uni[tid] = u;
+    }
+    __syncthreads();
+  }
+  __device__ __forceinline__ bool has(int t, int c) const { return (word[t * 64 + (c >> 5)] >> (c & 31)) & 1u; }
+  __device__ __forceinline__ int rank(int t, int c) const {
+    return before[t * 64 + (c >> 5)] + __popc(word[t * 64 + (c >> 5)] & ((1u << (c & 31)) - 1u));
+  }
+};
+
+// Walks the set bits of the union that belong to worker `who` of `of` (every of-th entry).
+struct ListWalk {
+  const uint32_t* uni;
+  int words, wi, skip, of;
+  uint32_t bits;
+  __device__ __forceinline__ ListWalk(const uint32_t* u, int words_, int who, int of_)
+      : uni(u), words(words_), wi(-1), skip(who), of(of_), bits(0u) {}
+  __device__ __forceinline__ int next() {     // chunk id, or -1 (wave-uniform)
+    for (;;) {
+      while (bits == 0u) {
+        if (++wi >= words) return -1;
+        bits = __builtin_amdgcn_readfirstlane(uni[wi]);
+      }
+      const int c = wi * 32 + __builtin_ctz(bits);
+      bits &= bits - 1u;
+      if (skip-- == 0) { skip = of - 1; return c; }
+    }
+  }
+};
+
+// ---------------------------------------------------------------------------
+// Forward
+// ---------------------------------------------------------------------------
+struct S2FArgs {
+  const float* q; const float* k; const float* v; float* o;
+  const uint32_t* mask; const float* bias;
+  int h_kv, g_q, n_q, n_kv, block, t_all, words, pos0, causal, hb, n_tiles;
+  int64_t qs_b, qs_h, qs_t, ks_b, ks_h, ks_t, vs_b, vs_h, vs_t, os_b, os_h, os_t;
+  float c1;
+};
+
+template <int D, bool DENSE>
+__global__ __launch_bounds__(512) void s2_f32_kernel(S2FArgs a) {
+  using C = F32Cfg<D>;
+  constexpr int NWV = 8;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  float* tiles = reinterpret_cast<float*>(lds);                       // [8][16][LD]
+  float* ms = tiles + NWV * 16 * C::LD;                               // [8][16]
+  float* ls = ms + NWV * 16;                                          // [8][16]
+  TileLists tl(reinterpret_cast<char*>(ls + NWV * 16));
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, hq = lane >> 4;
+  const int hbi = blockIdx.x % a.hb, tile = a.n_tiles - 1 - blockIdx.x / a.hb;   // longest rows first
+  const int r = hbi % a.h_kv, b = hbi / a.h_kv;
+  const int tokt = 16 / a.g_q, tok0 = tile * tokt, ntok = min(tokt, a.n_q - tok0);
+  const int t_n = min(n / a.g_q, ntok - 1), tok = tok0 + t_n;          // this lane's row (padding repeats the last token)
+  const int pos = a.pos0 + tok, cw = (a.pos0 + tok0) / a.block;       // all tokens of a tile lie in one chunk
+  const int nsub = a.block >> 4;
+  const int64_t base = ((int64_t)b * a.h_kv + r) * a.n_q + tok0;
+  if (DENSE) {
+    if (tid < 64) {
+      const int last = a.causal ? cw : a.t_all - 1, lo = tid * 32;
+      tl.uni[tid] = last < lo ? 0u : (last - lo >= 31 ? 0xffffffffu : (2u << (last - lo)) - 1u);
+    }
+    __syncthreads();
+  } else {
+    tl.build(a.mask + base * a.words, a.words, ntok, tid, 512);
+  }
+  f32x4 qf[C::NS];
+  load_row<D>(a.q + b * a.qs_b + (int64_t)(r * a.g_q + n % a.g_q) * a.qs_h + (int64_t)tok * a.qs_t, hq, qf);
+  const float* kb = a.k + b * a.ks_b + r * a.ks_h;
+  const float* vb = a.v + b * a.vs_b + r * a.vs_h;
+  float m_run = -INFINITY, l_run = 0.f;       // l_run: this lane's keys only
+  f32x4 o[C::NS];
+#pragma unroll
+  for (int i = 0; i < C::NS; i++) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  ListWalk it(tl.uni, DENSE ? 64 : a.words, wave, NWV);
+  for (int c = it.next(); c >= 0; c = it.next()) {
+    const bool diag = a.causal && c == cw;
+    float bias = 0.f;
+    if (!DENSE && !diag) bias = tl.has(t_n, c) ? a.bias[(base + t_n) * a.t_all + tl.rank(t_n, c)] * kLog2e : -INFINITY;
+    // SUB sub-tiles of 16 keys per step: all K loads of a step are in flight together, and its V loads
+    // are issued before the softmax that they wait behind
+    constexpr int SUB = D == 64 ? 4 : 2;
+    for (int st0 = 0; st0 < nsub; st0 += SUB) {
+      const int kpos0 = c * a.block + st0 * 16;
+      if (kpos0 >= a.n_kv || (diag && kpos0 > a.pos0 + tok0 + ntok - 1)) break;
+      f32x4 kf[SUB][C::NS], vr[SUB][4][C::NV], s[SUB];
+#pragma unroll
+      for (int st = 0; st < SUB; st++) load_row<D>(kb + (int64_t)min(kpos0 + 16 * st + n, a.n_kv - 1) * a.ks_t, hq, kf[st]);
+#pragma unroll
+      for (int st = 0; st < SUB; st++)
+#pragma unroll
+        for (int t = 0; t < 4; t++) load_row2<D>(vb + (int64_t)min(kpos0 + 16 * st + 4 * hq + t, a.n_kv - 1) * a.vs_t, n, vr[st][t]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int st = 0; st < SUB; st++) s[st] = mma_dot<D>(kf[st], qf);
+      // dead keys: after the row's position, past the end of the sequence
+      const int lim = min(diag ? pos : 0x7fffffff, a.n_kv - 1) - kpos0 - 4 * hq;
+      float mx = -INFINITY;
+#pragma unroll
+      for (int st = 0; st < SUB; st++)
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+          s[st][v] = 16 * st + v > lim ? -INFINITY : fmaf(s[st][v], a.c1, bias);
+          mx = fmaxf(mx, s[st][v]);
+        }
+      const float m_new = fmaxf(m_run, quad_rows_max(mx));
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;
+      const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
+      m_run = m_new;
+      l_run *= corr;
+#pragma unroll
+      for (int i = 0; i < C::NS; i++) o[i] *= corr;
+#pragma unroll
+      for (int st = 0; st < SUB; st++)
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+          const float p = __builtin_amdgcn_exp2f(s[st][t] - m_use);
+          l_run += p;
+          mma_outer<D>(vr[st][t], p, o);
+        }
+    }
+  }
+  // ---- add up the waves: rows weighted by 2^(m_wave - M) --------------------------------------
+  const float l_tot = quad_rows_sum(l_run);
+  if (hq == 0) { ms[wave * 16 + n] = m_run; ls[wave * 16 + n] = l_tot; }
+  __syncthreads();
+  float M = -INFINITY, den = 0.f;
+#pragma unroll
+  for (int w = 0; w < NWV; w++) M = fmaxf(M, ms[w * 16 + n]);
+#pragma unroll
+  for (int w = 0; w < NWV; w++) den = fmaf(ms[w * 16 + n] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms[w * 16 + n] - M), ls[w * 16 + n], den);
+  put_tile<D>(tiles + wave * 16 * C::LD, n, hq, o, m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - M) / den);
+  __syncthreads();
+  for (int i = tid; i < 16 * D / 4; i += 512) {
+    const int row = i / (D / 4), d4 = (i % (D / 4)) * 4;
+    if (row / a.g_q >= ntok) continue;
+    f32x4 x = *reinterpret_cast<const f32x4*>(tiles + row * C::LD + d4);
+#pragma unroll
+    for (int w = 1; w < NWV; w++) x += *reinterpret_cast<const f32x4*>(tiles + (w * 16 + row) * C::LD + d4);
+    *reinterpret_cast<f32x4*>(a.o + b * a.os_b + (int64_t)(r * a.g_q + row % a.g_q) * a.os_h +
+                              (int64_t)(tok0 + row / a.g_q) * a.os_t + d4) = x;
+  }
+}
+
+template <int D, bool DENSE> static hipError_t launch_s2_f32_t(const S2FArgs& a, hipStream_t st) {
+  constexpr size_t lds = (size_t)(8 * 16 * F32Cfg<D>::LD + 2 * 8 * 16) * 4 + TileLists::BYTES;
+  auto kern = s2_f32_kernel<D, DENSE>;
+  static LdsOptIn opt_in;
+  if (hipError_t e = allow_dyn_lds((const void*)kern, lds, opt_in); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(a.n_tiles * a.hb)), dim3(512), lds, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_s2_f32(const dash_params& p, const Layout& L, const void* q, const void* k,
+                         const void* v, void* o, const uint32_t* mask, const float* bias,
+                         bool dense, hipStream_t st) {
+  S2FArgs a;
+  a.q = (const float*)q; a.k = (const float*)k; a.v = (const float*)v; a.o = (float*)o;
+  a.mask = mask; a.bias = bias;
+  a.h_kv = p.h_kv; a.g_q = L.g_q; a.n_q = p.n_q; a.n_kv = p.n_kv; a.block = p.block_size;
+  a.t_all = L.t_all; a.words = L.words; a.pos0 = L.pos0; a.causal = p.causal;
+  a.hb = p.h_kv * p.batch;
+  const int tokt = 16 / L.g_q;
+  a.n_tiles = (p.n_q + tokt - 1) / tokt;
+  a.qs_b = p.q_stride[0]; a.qs_h = p.q_stride[1]; a.qs_t = p.q_stride[2];
+  a.ks_b = p.k_stride[0]; a.ks_h = p.k_stride[1]; a.ks_t = p.k_stride[2];
+  a.vs_b = p.v_stride[0]; a.vs_h = p.v_stride[1]; a.vs_t = p.v_stride[2];
+  a.os_b = p.o_stride[0]; a.os_h = p.o_stride[1]; a.os_t = p.o_stride[2];
+  a.c1 = L.scale * kLog2e;
+  if (p.head_dim == 128) return dense ? launch_s2_f32_t<128, true>(a, st) : launch_s2_f32_t<128, false>(a, st);
+  return dense ? launch_s2_f32_t<64, true>(a, st) : launch_s2_f32_t<64, false>(a, st);
+}
+
+// ---------------------------------------------------------------------------
+// Backward (n_q == n_kv; see backward.hip for the chain)
+// ---------------------------------------------------------------------------
+// Row kernel, one workgroup of 4 waves per (16-row tile, part of its chunk list).
+//   GRAD = false: log-sum-exp and D per row, or, of several parts, (max, sum, sum of exponentials
+//     times dP) of the part's keys into `scratch`; also clears what the later kernels add to (dq32, and dk, dv, dkbar if `clear_kv`).
+//   GRAD = true: log-sum-exp and D (from the parts' records); bias gradient and a copy of the bias
+//     by chunk id; dq (attention part) added to dq32.
+struct RowF32 {
+  int parts, n_tiles, clear_kv;
+  int64_t rows;         // batch * h_q * n_q
+  float* scratch;       // parts > 1: [parts][rows][3]
+};
+
+template <int D, bool GRAD>
+__global__ __launch_bounds__(256) void bwd_f32_row_kernel(BwdArgs a, RowF32 x) {
+  using C = F32Cfg<D>;
+  constexpr int NWV = 4;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  TileLists tl(lds);
+  float* red = reinterpret_cast<float*>(lds + TileLists::BYTES);      // GRAD: [4][16][LD]; else [4][16][3]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, hq = lane >> 4;
+  const int hbi = blockIdx.x % a.hb, tile = x.n_tiles - 1 - blockIdx.x / a.hb, part = blockIdx.y;
+  const int r = hbi % a.h_kv, b = hbi / a.h_kv;
+  const int tokt = 16 / a.g_q, tok0 = tile * tokt, ntok = min(tokt, a.n_q - tok0);
+  const int t_n = min(n / a.g_q, ntok - 1), tok = tok0 + t_n, head = r * a.g_q + n % a.g_q;
+  const int cw = tok0 / a.block, nsub = a.block >> 4;
+  const int64_t base = ((int64_t)b * a.h_kv + r) * a.n_q + tok0;
+  const bool row_ok = n / a.g_q < ntok;
+  const int64_t row_n = ((int64_t)b * a.h_q + head) * a.n_q + tok;
+  if (!GRAD) {
+    const int64_t step = (int64_t)gridDim.x * gridDim.y * 256, i0 = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + tid;
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    const int64_t nq4 = (int64_t)a.hb * a.g_q * a.n_q * (D / 4);
+    for (int64_t i = i0; i < nq4; i += step) reinterpret_cast<f32x4*>(a.dq32)[i] = z;
+    if (x.clear_kv) {
+      const int64_t nk4 = (int64_t)a.hb * a.n_kv * (D / 4);
+      for (int64_t i = i0; i < nk4; i += step) {
+        const int64_t row = i / (D / 4);
+        const int key = (int)(row % a.n_kv), e = (int)(i % (D / 4)) * 4;
+        const int64_t bb = row / a.n_kv / a.h_kv, rr = row / a.n_kv % a.h_kv;
+        *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.dk) + bb * a.ks_b + rr * a.ks_h + (int64_t)key * a.ks_t + e) = z;
+        *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.dv) + bb * a.vs_b + rr * a.vs_h + (int64_t)key * a.vs_t + e) = z;
+      }
+      if (a.dkbar_out) {
+        const int64_t nb4 = (int64_t)a.hb * a.t_c * (D / 4);
+        for (int64_t i = i0; i < nb4; i += step) reinterpret_cast<f32x4*>(a.dkbar_out)[i] = z;
+      }
+    }
+  }
+  tl.build(a.mask + base * a.words, a.words, ntok, tid, 256);
+  f32x4 qf[C::NS], of[C::NS];
+  load_row<D>(reinterpret_cast<const float*>(a.q) + b * a.qs_b + head * a.qs_h + (int64_t)tok * a.qs_t, hq, qf);
+  load_row<D>(reinterpret_cast<const float*>(a.d_o) + b * a.os_b + head * a.os_h + (int64_t)tok * a.os_t, hq, of);
+  const float* kb = reinterpret_cast<const float*>(a.k) + b * a.ks_b + r * a.ks_h;
+  const float* vb = reinterpret_cast<const float*>(a.v) + b * a.vs_b + r * a.vs_h;
+  float m_run = -INFINITY, l_run = 0.f, dn_run = 0.f;     // of this lane's keys
+  float lse2 = 0.f, dsum = 0.f;
+  f32x4 dq[GRAD ? C::NS : 1];
+  if constexpr (GRAD) {
+#pragma unroll
+    for (int i = 0; i < C::NS; i++) dq[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (x.parts == 1) {
+      lse2 = a.lse[row_n];
+      dsum = a.dsum[row_n];
+    } else {
+      const float* rec = x.scratch + row_n * 3;
+      float M = -INFINITY, l = 0.f, dn = 0.f;
+      for (int p = 0; p < x.parts; p++) M = fmaxf(M, rec[p * x.rows * 3]);
+      for (int p = 0; p < x.parts; p++) {
+        const float* rp = rec + p * x.rows * 3;
+        const float w = rp[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(rp[0] - M);
+        l = fmaf(w, rp[1], l);
+        dn = fmaf(w, rp[2], dn);
+      }
+      lse2 = M + __builtin_amdgcn_logf(l);      // v_log_f32: log2
+      dsum = dn / l;
+      if (part == 0 && wave == 0 && hq == 0 && row_ok) { a.lse[row_n] = lse2; a.dsum[row_n] = dsum; }
+    }
+  }
+  ListWalk it(tl.uni, a.words, part * NWV + wave, x.parts * NWV);
+  for (int c = it.next(); c >= 0; c = it.next()) {
+    const bool diag = a.causal && c == cw, mine = tl.has(t_n, c);
+    float bias = 0.f, db = 0.f;
+    if (!diag) bias = mine ? a.bias[(base + t_n) * a.t_all + tl.rank(t_n, c)] : -INFINITY;
+    const float bias2 = bias * kLog2e;
+    for (int st = 0; st < nsub; st++) {
+      const int kpos0 = c * a.block + st * 16;
+      if (kpos0 >= a.n_kv || (diag && kpos0 > tok0 + ntok - 1)) break;
+      f32x4 kf[C::NS], vf[C::NS], kr[GRAD ? 4 : 1][C::NV];     // one round trip per sub-tile
+      load_row<D>(kb + (int64_t)min(kpos0 + n, a.n_kv - 1) * a.ks_t, hq, kf);
+      load_row<D>(vb + (int64_t)min(kpos0 + n, a.n_kv - 1) * a.vs_t, hq, vf);
+      if constexpr (GRAD) {
+#pragma unroll
+        for (int t = 0; t < 4; t++) load_row2<D>(kb + (int64_t)min(kpos0 + 4 * hq + t, a.n_kv - 1) * a.ks_t, n, kr[t]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      f32x4 s = mma_dot<D>(kf, qf), dp = mma_dot<D>(vf, of);
+      const int lim = min(diag ? tok : 0x7fffffff, a.n_kv - 1) - kpos0 - 4 * hq;
+      if constexpr (!GRAD) {
+        float mx = m_run;
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+          s[v] = v > lim ? -INFINITY : fmaf(s[v], a.c1, bias2);
+          mx = fmaxf(mx, s[v]);
+        }
+        const float m_use = mx == -INFINITY ? 0.f : mx;
+        const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
+        m_run = mx;
+        l_run *= corr;
+        dn_run *= corr;
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+          const float p = __builtin_amdgcn_exp2f(s[v] - m_use);
+          l_run += p;
+          dn_run = fmaf(p, dp[v], dn_run);
+        }
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+          const float p = t > lim ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[t], a.c1, bias2 - lse2));
+          const float dz = p * (dp[t] - dsum);
+          db += dz;
+          mma_outer<D>(kr[t], dz, dq);
+        }
+      }
+    }
+    if constexpr (GRAD) {
+      // bias gradient: over the chunk's keys (four lanes of the row) and the group's heads (rows)
+      db = quad_rows_sum(db);
+      for (int o = 1; o < a.g_q; o <<= 1) db += __shfl_xor(db, o);
+      if (!diag && mine && row_ok && hq == 0 && n % a.g_q == 0) {
+        a.dbd[(base + t_n) * a.t_all + c] = db;
+        a.biasd[(base + t_n) * a.t_all + c] = bias;
+      }
+    }
+  }
+  if constexpr (!GRAD) {
+    const float M = quad_rows_max(m_run), w = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - M);
+    const float l = quad_rows_sum(l_run * w), dn = quad_rows_sum(dn_run * w);
+    if (hq == 0) { red[(wave * 16 + n) * 3] = M; red[(wave * 16 + n) * 3 + 1] = l; red[(wave * 16 + n) * 3 + 2] = dn; }
+    __syncthreads();
+    if (tid < 16) {
+      float Mt = -INFINITY, lt = 0.f, dt = 0.f;
+      for (int w_ = 0; w_ < NWV; w_++) Mt = fmaxf(Mt, red[(w_ * 16 + tid) * 3]);
+      for (int w_ = 0; w_ < NWV; w_++) {
+        const float e = red[(w_ * 16 + tid) * 3] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(red[(w_ * 16 + tid) * 3] - Mt);
+        lt = fmaf(e, red[(w_ * 16 + tid) * 3 + 1], lt);
+        dt = fmaf(e, red[(w_ * 16 + tid) * 3 + 2], dt);
+      }
+      if (row_ok) {     // wave 0, lane tid: row_n is row tid
+        if (x.parts == 1) {
+          a.lse[row_n] = Mt + __builtin_amdgcn_logf(lt);
+          a.dsum[row_n] = dt / lt;
+        } else {
+          float* rp = x.scratch + (part * x.rows + row_n) * 3;
+          rp[0] = Mt; rp[1] = lt; rp[2] = dt;
+        }
+      }
+    }
+  } else {
+    put_tile<D>(red + wave * 16 * C::LD, n, hq, dq, a.scale);
+    __syncthreads();
+    for (int i = tid; i < 16 * D; i += 256) {
+      const int row = i / D, d = i % D;
+      if (row / a.g_q >= ntok) continue;
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < NWV; w++) v += red[(w * 16 + row) * C::LD + d];
+      float* dst = a.dq32 + (((int64_t)b * a.h_q + r * a.g_q + row % a.g_q) * a.n_q + tok0 + row / a.g_q) * D + d;
+      if (x.parts == 1) *dst = v; else unsafeAtomicAdd(dst, v);
+    }
+  }
+}
+
+// Key kernel, one workgroup of 4 waves per (16-key tile, part of the rows that attend its chunk):
+// dK, dV and the chunk's summary gradient.  Several parts add to cleared outputs.
+template <int D>
+__global__ __launch_bounds__(256) void bwd_f32_key_kernel(BwdArgs a, int parts) {
+  using C = F32Cfg<D>;
+  constexpr int NWV = 4;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  float* red = reinterpret_cast<float*>(lds);                         // [4][16][LD]
+  float* kbs = red + NWV * 16 * C::LD;                                // [4][D]
+  uint32_t* bits = reinterpret_cast<uint32_t*>(kbs + NWV * D);        // [n_q / 32]: tokens that attend the chunk
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, hq = lane >> 4;
+  const int hbi = blockIdx.x % a.hb, ktile = blockIdx.x / a.hb, part = blockIdx.y;   // early keys (the most rows) first
+  const int r = hbi % a.h_kv, b = hbi / a.h_kv;
+  const int kpos0 = ktile * 16, c = kpos0 / a.block;
+  const int tokt = 16 / a.g_q;
+  const int64_t mrow = ((int64_t)b * a.h_kv + r) * a.n_q;
+  // the tokens of this part: whole 64-token groups, dealt out evenly over those that can attend the keys
+  const int g0 = a.causal ? kpos0 / 64 : 0, ng = (a.n_q + 63) / 64 - g0;
+  const int per = (ng + parts - 1) / parts;
+  const int gb = g0 + part * per, ge = min(gb + per, g0 + ng);
+  for (int g = gb + wave; g < ge; g += NWV) {
+    const int tk = g * 64 + lane;
+    const bool bit = tk < a.n_q && ((a.mask[(mrow + tk) * a.words + (c >> 5)] >> (c & 31)) & 1u);
+    const uint64_t bal = __ballot(bit);
+    if (lane == 0) { bits[2 * (g - gb)] = (uint32_t)bal; bits[2 * (g - gb) + 1] = (uint32_t)(bal >> 32); }
+  }
+  const int key = min(kpos0 + n, a.n_kv - 1);
+  f32x4 kf[C::NS], vf[C::NS];
+  load_row<D>(reinterpret_cast<const float*>(a.k) + b * a.ks_b + r * a.ks_h + (int64_t)key * a.ks_t, hq, kf);
+  load_row<D>(reinterpret_cast<const float*>(a.v) + b * a.vs_b + r * a.vs_h + (int64_t)key * a.vs_t, hq, vf);
+  __syncthreads();
+  const float* qb = reinterpret_cast<const float*>(a.q) + b * a.qs_b + (int64_t)r * a.g_q * a.qs_h;
+  const float* ob = reinterpret_cast<const float*>(a.d_o) + b * a.os_b + (int64_t)r * a.g_q * a.os_h;
+  f32x4 dk[C::NS], dv[C::NS], kbar[C::NV];
+#pragma unroll
+  for (int i = 0; i < C::NS; i++) { dk[i] = f32x4{0.f, 0.f, 0.f, 0.f}; dv[i] = dk[i]; }
+#pragma unroll
+  for (int i = 0; i < C::NV; i++) kbar[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int tpg = 64 / tokt;                  // row tiles per 64-token group
+  for (int T = gb * tpg + wave; T < ge * tpg; T += NWV) {
+    const int tok0 = T * tokt;
+    if (tok0 >= a.n_q) break;
+    const int lt = tok0 - gb * 64;
+    const uint32_t tb = (__builtin_amdgcn_readfirstlane(bits[lt >> 5]) >> (lt & 31)) & (tokt == 32 ? ~0u : (1u << tokt) - 1u);
+    if (tb == 0u) continue;                   // bits of tokens past the end are 0
+    // all loads of the row tile in flight together
+    const int64_t ra = min(tok0 + n / a.g_q, a.n_q - 1);
+    f32x4 qa[C::NS], oa[C::NS], qw[4][C::NV], ow[4][C::NV];
+    load_row<D>(qb + (n % a.g_q) * a.qs_h + ra * a.qs_t, hq, qa);
+    load_row<D>(ob + (n % a.g_q) * a.os_h + ra * a.os_t, hq, oa);
+#pragma unroll
+    for (int t = 0; t < 4; t++) {
+      const int row = 4 * hq + t;
+      const int64_t rt = min(tok0 + row / a.g_q, a.n_q - 1);
+      load_row2<D>(ob + (row % a.g_q) * a.os_h + rt * a.os_t, n, ow[t]);
+      load_row2<D>(qb + (row % a.g_q) * a.qs_h + rt * a.qs_t, n, qw[t]);
+    }
+    // per-row values: lane (m, kq) fetches one of the four of row m, then every lane takes its rows'
+    const int cdiag = tok0 / a.block;
+    const bool isdiag = a.causal && c == cdiag;
+    const int n_cand = a.causal ? max(cdiag - a.window, 0) : a.t_c;
+    float val = 0.f;
+    {
+      const int tk = min(tok0 + n / a.g_q, a.n_q - 1);
+      const int64_t hrow = ((int64_t)b * a.h_q + r * a.g_q + n % a.g_q) * a.n_q + tk;
+      const bool bit = (tb >> (n / a.g_q)) & 1u;
+      if (hq == 0) val = a.lse[hrow];
+      else if (hq == 1) val = a.dsum[hrow];
+      else if (hq == 2) { if (bit && !isdiag) val = a.biasd[(mrow + tk) * a.t_all + c]; }
+      else if (bit && c < n_cand) val = a.dxd[hrow * a.t_all + c];
+    }
+    float cmb[4], ds[4], dx[4];
+#pragma unroll
+    for (int v = 0; v < 4; v++) {
+      const int row = 4 * hq + v;
+      const float lse = __shfl(val, row), bs = __shfl(val, 32 + row);
+      ds[v] = __shfl(val, 16 + row);
+      dx[v] = __shfl(val, 48 + row);
+      cmb[v] = ((tb >> (row / a.g_q)) & 1u) ? fmaf(bs, kLog2e, -lse) : -INFINITY;
+    }
+    const f32x4 s = mma_dot<D>(qa, kf), dp = mma_dot<D>(oa, vf);
+#pragma unroll
+    for (int t = 0; t < 4; t++) {
+      const int row = 4 * hq + t, tk = tok0 + row / a.g_q;
+      const bool dead = a.causal && kpos0 + n > tk;
+      const float p = dead ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[t], a.c1, cmb[t]));
+      const float dz = p * (dp[t] - ds[t]);
+      mma_outer<D>(ow[t], p, dv);
+      mma_outer<D>(qw[t], dz, dk);
+#pragma unroll
+      for (int nv = 0; nv < C::NV; nv++) kbar[nv] += qw[t][nv] * dx[t];
+    }
+  }
+  // ---- add up the waves ------------------------------------------------------------------------
+#pragma unroll
+  for (int nv = 0; nv < C::NV; nv++)
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float t = quad_rows_sum(kbar[nv][e]);
+      if (hq == 0) kbs[wave * D + 64 * nv + 4 * n + e] = t;
+    }
+  put_tile<D>(red + wave * 16 * C::LD, n, hq, dk, a.scale);
+  __syncthreads();
+  const bool fold = c < a.t_c && !a.dkbar_out;
+  const float kscale = a.xscale / (float)a.block;
+  for (int i = tid; i < 16 * D; i += 256) {
+    const int row = i / D, d = i % D;
+    if (kpos0 + row >= a.n_kv) continue;
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < NWV; w++) v += red[(w * 16 + row) * C::LD + d];
+    // block-mean summaries: every key of a complete chunk receives 1/B of the chunk's dkbar
+    if (fold) v = fmaf((kbs[d] + kbs[D + d]) + (kbs[2 * D + d] + kbs[3 * D + d]), kscale, v);
+    float* dst = reinterpret_cast<float*>(a.dk) + b * a.ks_b + r * a.ks_h + (int64_t)(kpos0 + row) * a.ks_t + d;
+    if (parts == 1) *dst = v; else unsafeAtomicAdd(dst, v);
+  }
+  if (a.dkbar_out && c < a.t_c && kpos0 % a.block == 0) {
+    for (int d = tid; d < D; d += 256) {
+      const float v = ((kbs[d] + kbs[D + d]) + (kbs[2 * D + d] + kbs[3 * D + d])) * a.xscale;
+      float* dst = a.dkbar_out + (((int64_t)b * a.h_kv + r) * a.t_c + c) * D + d;
+      if (parts == 1) *dst = v; else unsafeAtomicAdd(dst, v);
+    }
+  }
+  __syncthreads();
+  put_tile<D>(red + wave * 16 * C::LD, n, hq, dv, 1.f);
+  __syncthreads();
+  for (int i = tid; i < 16 * D; i += 256) {
+    const int row = i / D, d = i % D;
+    if (kpos0 + row >= a.n_kv) continue;
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < NWV; w++) v += red[(w * 16 + row) * C::LD + d];
+    float* dst = reinterpret_cast<float*>(a.dv) + b * a.vs_b + r * a.vs_h + (int64_t)(kpos0 + row) * a.vs_t + d;
+    if (parts == 1) *dst = v; else unsafeAtomicAdd(dst, v);
+  }
+}
+
+static int clamp_int(int64_t x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : (int)x); }
+
+// Parts: enough workgroups for two per CU, while a wave keeps at least one chunk (rows) or a
+// part one 64-token group (keys).  The rows' records fit the score-gradient array they
+// are kept in until the routing kernel fills it: 3 floats per row and part of its t_all >= 4 parts.
+static int key_parts(const BwdArgs& a) {
+  const int ktiles = (a.n_kv + 15) / 16;
+  return clamp_int(512 / ((int64_t)ktiles * a.hb), 1, (a.n_q + 63) / 64);
+}
+
+template <int D> static hipError_t launch_rows_t(const BwdArgs& a, hipStream_t st) {
+  RowF32 x;
+  const int tokt = 16 / a.g_q;
+  x.n_tiles = (a.n_q + tokt - 1) / tokt;
+  x.parts = clamp_int(512 / ((int64_t)x.n_tiles * a.hb), 1, a.t_all >= 4 ? a.t_all / 4 : 1);
+  x.rows = (int64_t)a.hb * a.g_q * a.n_q;
+  x.clear_kv = key_parts(a) > 1;
+  x.scratch = a.dxd;
+  const dim3 grid((unsigned)(x.n_tiles * a.hb), (unsigned)x.parts), blk(256);
+  hipLaunchKernelGGL((bwd_f32_row_kernel<D, false>), grid, blk, TileLists::BYTES + 4 * 16 * 3 * 4, st, a, x);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  hipLaunchKernelGGL((bwd_f32_row_kernel<D, true>), grid, blk, TileLists::BYTES + 4 * 16 * F32Cfg<D>::LD * 4, st, a, x);
+  return hipGetLastError();
+}
+
+template <int D> static hipError_t launch_keys_t(const BwdArgs& a, hipStream_t st) {
+  const int parts = key_parts(a), ktiles = (a.n_kv + 15) / 16;
+  const size_t lds = (size_t)(4 * 16 * F32Cfg<D>::LD + 4 * D) * 4 + (size_t)((a.n_q + 63) / 64) * 8;
+  auto kern = bwd_f32_key_kernel<D>;
+  static LdsOptIn opt_in;
+  if (hipError_t e = allow_dyn_lds((const void*)kern, lds, opt_in); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(ktiles * a.hb), (unsigned)parts), dim3(256), lds, st, a, parts);
+  return hipGetLastError();
+}
+
+hipError_t launch_bwd_f32_rows(const BwdArgs& a, int head_dim, hipStream_t st) {
+  return head_dim == 128 ? launch_rows_t<128>(a, st) : launch_rows_t<64>(a, st);
+}
+hipError_t launch_bwd_f32_keys(const BwdArgs& a, int head_dim, hipStream_t st) {
+  return head_dim == 128 ? launch_keys_t<128>(a, st) : launch_keys_t<64>(a, st);
+}
+
+}  // namespace dash
