@@ -2,16 +2,7 @@
 // reference of Eq. 1) and backward, in fp32 throughout on the fp32 matrix cores
 // (v_mfma_f32_16x16x4_f32: fp32 products, fp32 sums; 256 flop per clock and CU).
 //
-// Tiles.  A 16-row tile holds the g_q heads of 16 / g_q consecutive tokens of one kv-head; keys
-// go by 16 as well.  Both kinds of product read their operands straight from global memory (L2)
-// with 16-byte loads and need no shuffle in between:
-//   first kind, contraction over d (S = K Q^T, dP = V dO^T): lane (m = lane % 16, kq = lane / 16)
-//     loads d = 16 s + 4 kq .. + 3 of its row m, for both operands; element e of load s is one
-//     MFMA.  The result, lane (n, hq), is column n (of the B operand) at A rows 4 hq .. + 3.
-//   second kind, contraction over the A rows of the first (O^T = V^T P^T, dQ^T = K^T dZ^T, dV^T =
-//     dO^T P, dK^T = Q^T dZ): step t contracts the rows 4 kq + t, so lane (n, kq) supplies its own
-//     accumulator register t; the other operand's lane (m, kq) loads d = 64 nv + 4 m .. + 3 of row
-//     4 kq + t, element e being the d-tile {64 nv + 4 m + e}.  Result: d = 64 nv + 16 hq + 4 v + e.
+// Tiles and operand layouts: f32_tiles.h.
 // A wave owns whole chunks (row kernels) or whole 16-row tiles (key kernel) and the waves of a
 // workgroup add their results through LDS, so that the bias gradient of a chunk is one wave's and
 // the launch is wide enough for a single head.
@@ -24,58 +15,14 @@
 #include "backward_args.h"
 #include "common.h"
 #include "dash_internal.h"
+#include "f32_tiles.h"
 
 namespace dash {
 
-template <int D> struct F32Cfg {
-  static constexpr int NS = D / 16;     // 16-byte loads of a row, first kind
-  static constexpr int NV = D / 64;     // 16-byte loads of a row, second kind
-  static constexpr int LD = D + 4;      // LDS row of a result tile (floats)
-};
-
-template <int D> __device__ __forceinline__ void load_row(const float* row, int kq, f32x4 (&v)[D / 16]) {
-#pragma unroll
-  for (int s = 0; s < D / 16; s++) v[s] = *reinterpret_cast<const f32x4*>(row + 16 * s + 4 * kq);
-}
-// first kind: 16 A rows x 16 B rows
-template <int D> __device__ __forceinline__ f32x4 mma_dot(const f32x4 (&a)[D / 16], const f32x4 (&b)[D / 16]) {
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int s = 0; s < D / 16; s++)
-#pragma unroll
-    for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][e], b[s][e], acc, 0, 0, 0);
-  return acc;
-}
-// second kind, one step t: acc[4 nv + e] += (row's d 64 nv + 4 m + e) * w
-template <int D> __device__ __forceinline__ void mma_outer(const f32x4 (&row)[D / 64], float w, f32x4 (&acc)[D / 16]) {
-#pragma unroll
-  for (int nv = 0; nv < D / 64; nv++)
-#pragma unroll
-    for (int e = 0; e < 4; e++)
-      acc[4 * nv + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(row[nv][e], w, acc[4 * nv + e], 0, 0, 0);
-}
-template <int D> __device__ __forceinline__ void load_row2(const float* row, int m, f32x4 (&v)[D / 64]) {
-#pragma unroll
-  for (int nv = 0; nv < D / 64; nv++) v[nv] = *reinterpret_cast<const f32x4*>(row + 64 * nv + 4 * m);
-}
-// a second-kind result into LDS row n of a [16][LD] tile
-template <int D> __device__ __forceinline__ void put_tile(float* tile, int n, int hq, const f32x4 (&acc)[D / 16], float w) {
-#pragma unroll
-  for (int nv = 0; nv < D / 64; nv++)
-#pragma unroll
-    for (int v = 0; v < 4; v++) {
-      const f32x4 x = {acc[4 * nv][v] * w, acc[4 * nv + 1][v] * w, acc[4 * nv + 2][v] * w, acc[4 * nv + 3][v] * w};
-      *reinterpret_cast<f32x4*>(tile + n * F32Cfg<D>::LD + 64 * nv + 16 * hq + 4 * v) = x;
-    }
-}
-__device__ __forceinline__ float quad_rows_max(float x) {   // over the four lanes of a column n
-  x = fmaxf(x, __shfl_xor(x, 16));
-  return fmaxf(x, __shfl_xor(x, 32));
-}
-__device__ __forceinline__ float quad_rows_sum(float x) {
-  x += __shfl_xor(x, 16);
-  return x + __shfl_xor(x, 32);
-}
+// e^(z - m) for logits in natural units: the difference is formed before the change of base, so a
+// strong prior's large biases are rounded once, key by key, as in the logit itself
+__device__ __forceinline__ float exp_diff(float z, float m) { return __builtin_amdgcn_exp2f((z - m) * kLog2e); }
+__device__ __forceinline__ float ln_of(float x) { return __builtin_amdgcn_logf(x) * 0.6931471805599453f; }   // v_log_f32: log2
 
 // The chunk list of a 16-row tile: union of its tokens' masks and, per token, the number of
 // entries before each mask word (the bias lists are addressed by rank).
@@ -143,7 +90,7 @@ struct S2FArgs {
   const uint32_t* mask; const float* bias;
   int h_kv, g_q, n_q, n_kv, block, t_all, words, pos0, causal, hb, n_tiles;
   int64_t qs_b, qs_h, qs_t, ks_b, ks_h, ks_t, vs_b, vs_h, vs_t, os_b, os_h, os_t;
-  float c1;
+  float scale;
 };
 
 template <int D, bool DENSE>
@@ -185,7 +132,7 @@ __global__ __launch_bounds__(512) void s2_f32_kernel(S2FArgs a) {
   for (int c = it.next(); c >= 0; c = it.next()) {
     const bool diag = a.causal && c == cw;
     float bias = 0.f;
-    if (!DENSE && !diag) bias = tl.has(t_n, c) ? a.bias[(base + t_n) * a.t_all + tl.rank(t_n, c)] * kLog2e : -INFINITY;
+    if (!DENSE && !diag) bias = tl.has(t_n, c) ? a.bias[(base + t_n) * a.t_all + tl.rank(t_n, c)] : -INFINITY;
     // SUB sub-tiles of 16 keys per step: all K loads of a step are in flight together, and its V loads
     // are issued before the softmax that they wait behind
     constexpr int SUB = D == 64 ? 4 : 2;
@@ -209,12 +156,12 @@ __global__ __launch_bounds__(512) void s2_f32_kernel(S2FArgs a) {
       for (int st = 0; st < SUB; st++)
 #pragma unroll
         for (int v = 0; v < 4; v++) {
-          s[st][v] = 16 * st + v > lim ? -INFINITY : fmaf(s[st][v], a.c1, bias);
+          s[st][v] = 16 * st + v > lim ? -INFINITY : fmaf(s[st][v], a.scale, bias);
           mx = fmaxf(mx, s[st][v]);
         }
       const float m_new = fmaxf(m_run, quad_rows_max(mx));
       const float m_use = m_new == -INFINITY ? 0.f : m_new;
-      const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
+      const float corr = exp_diff(m_run, m_use);
       m_run = m_new;
       l_run *= corr;
 #pragma unroll
@@ -223,13 +170,13 @@ __global__ __launch_bounds__(512) void s2_f32_kernel(S2FArgs a) {
       for (int st = 0; st < SUB; st++)
 #pragma unroll
         for (int t = 0; t < 4; t++) {
-          const float p = __builtin_amdgcn_exp2f(s[st][t] - m_use);
+          const float p = exp_diff(s[st][t], m_use);
           l_run += p;
           mma_outer<D>(vr[st][t], p, o);
         }
     }
   }
-  // ---- add up the waves: rows weighted by 2^(m_wave - M) --------------------------------------
+  // ---- add up the waves: rows weighted by e^(m_wave - M) --------------------------------------
   const float l_tot = quad_rows_sum(l_run);
   if (hq == 0) { ms[wave * 16 + n] = m_run; ls[wave * 16 + n] = l_tot; }
   __syncthreads();
@@ -237,8 +184,8 @@ __global__ __launch_bounds__(512) void s2_f32_kernel(S2FArgs a) {
 #pragma unroll
   for (int w = 0; w < NWV; w++) M = fmaxf(M, ms[w * 16 + n]);
 #pragma unroll
-  for (int w = 0; w < NWV; w++) den = fmaf(ms[w * 16 + n] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms[w * 16 + n] - M), ls[w * 16 + n], den);
-  put_tile<D>(tiles + wave * 16 * C::LD, n, hq, o, m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - M) / den);
+  for (int w = 0; w < NWV; w++) den = fmaf(ms[w * 16 + n] == -INFINITY ? 0.f : exp_diff(ms[w * 16 + n], M), ls[w * 16 + n], den);
+  put_tile<D>(tiles + wave * 16 * C::LD, n, hq, o, m_run == -INFINITY ? 0.f : exp_diff(m_run, M) / den);
   __syncthreads();
   for (int i = tid; i < 16 * D / 4; i += 512) {
     const int row = i / (D / 4), d4 = (i % (D / 4)) * 4;
@@ -275,7 +222,7 @@ hipError_t launch_s2_f32(const dash_params& p, const Layout& L, const void* q, c
   a.ks_b = p.k_stride[0]; a.ks_h = p.k_stride[1]; a.ks_t = p.k_stride[2];
   a.vs_b = p.v_stride[0]; a.vs_h = p.v_stride[1]; a.vs_t = p.v_stride[2];
   a.os_b = p.o_stride[0]; a.os_h = p.o_stride[1]; a.os_t = p.o_stride[2];
-  a.c1 = L.scale * kLog2e;
+  a.scale = L.scale;
   if (p.head_dim == 128) return dense ? launch_s2_f32_t<128, true>(a, st) : launch_s2_f32_t<128, false>(a, st);
   return dense ? launch_s2_f32_t<64, true>(a, st) : launch_s2_f32_t<64, false>(a, st);
 }
@@ -338,13 +285,13 @@ __global__ __launch_bounds__(256) void bwd_f32_row_kernel(BwdArgs a, RowF32 x) {
   const float* kb = reinterpret_cast<const float*>(a.k) + b * a.ks_b + r * a.ks_h;
   const float* vb = reinterpret_cast<const float*>(a.v) + b * a.vs_b + r * a.vs_h;
   float m_run = -INFINITY, l_run = 0.f, dn_run = 0.f;     // of this lane's keys
-  float lse2 = 0.f, dsum = 0.f;
+  float lse = 0.f, dsum = 0.f;
   f32x4 dq[GRAD ? C::NS : 1];
   if constexpr (GRAD) {
 #pragma unroll
     for (int i = 0; i < C::NS; i++) dq[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (x.parts == 1) {
-      lse2 = a.lse[row_n];
+      lse = a.lse[row_n];
       dsum = a.dsum[row_n];
     } else {
       const float* rec = x.scratch + row_n * 3;
@@ -352,13 +299,13 @@ __global__ __launch_bounds__(256) void bwd_f32_row_kernel(BwdArgs a, RowF32 x) {
       for (int p = 0; p < x.parts; p++) M = fmaxf(M, rec[p * x.rows * 3]);
       for (int p = 0; p < x.parts; p++) {
         const float* rp = rec + p * x.rows * 3;
-        const float w = rp[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(rp[0] - M);
+        const float w = rp[0] == -INFINITY ? 0.f : exp_diff(rp[0], M);
         l = fmaf(w, rp[1], l);
         dn = fmaf(w, rp[2], dn);
       }
-      lse2 = M + __builtin_amdgcn_logf(l);      // v_log_f32: log2
+      lse = M + ln_of(l);
       dsum = dn / l;
-      if (part == 0 && wave == 0 && hq == 0 && row_ok) { a.lse[row_n] = lse2; a.dsum[row_n] = dsum; }
+      if (part == 0 && wave == 0 && hq == 0 && row_ok) { a.lse[row_n] = lse; a.dsum[row_n] = dsum; }
     }
   }
   ListWalk it(tl.uni, a.words, part * NWV + wave, x.parts * NWV);
@@ -366,7 +313,6 @@ __global__ __launch_bounds__(256) void bwd_f32_row_kernel(BwdArgs a, RowF32 x) {
     const bool diag = a.causal && c == cw, mine = tl.has(t_n, c);
     float bias = 0.f, db = 0.f;
     if (!diag) bias = mine ? a.bias[(base + t_n) * a.t_all + tl.rank(t_n, c)] : -INFINITY;
-    const float bias2 = bias * kLog2e;
     for (int st = 0; st < nsub; st++) {
       const int kpos0 = c * a.block + st * 16;
       if (kpos0 >= a.n_kv || (diag && kpos0 > tok0 + ntok - 1)) break;
@@ -384,24 +330,24 @@ __global__ __launch_bounds__(256) void bwd_f32_row_kernel(BwdArgs a, RowF32 x) {
         float mx = m_run;
 #pragma unroll
         for (int v = 0; v < 4; v++) {
-          s[v] = v > lim ? -INFINITY : fmaf(s[v], a.c1, bias2);
+          s[v] = v > lim ? -INFINITY : fmaf(s[v], a.scale, bias);
           mx = fmaxf(mx, s[v]);
         }
         const float m_use = mx == -INFINITY ? 0.f : mx;
-        const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
+        const float corr = exp_diff(m_run, m_use);
         m_run = mx;
         l_run *= corr;
         dn_run *= corr;
 #pragma unroll
         for (int v = 0; v < 4; v++) {
-          const float p = __builtin_amdgcn_exp2f(s[v] - m_use);
+          const float p = exp_diff(s[v], m_use);
           l_run += p;
           dn_run = fmaf(p, dp[v], dn_run);
         }
       } else {
 #pragma unroll
         for (int t = 0; t < 4; t++) {
-          const float p = t > lim ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[t], a.c1, bias2 - lse2));
+          const float p = t > lim ? 0.f : exp_diff(fmaf(s[t], a.scale, bias), lse);
           const float dz = p * (dp[t] - dsum);
           db += dz;
           mma_outer<D>(kr[t], dz, dq);
@@ -419,7 +365,7 @@ __global__ __launch_bounds__(256) void bwd_f32_row_kernel(BwdArgs a, RowF32 x) {
     }
   }
   if constexpr (!GRAD) {
-    const float M = quad_rows_max(m_run), w = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - M);
+    const float M = quad_rows_max(m_run), w = m_run == -INFINITY ? 0.f : exp_diff(m_run, M);
     const float l = quad_rows_sum(l_run * w), dn = quad_rows_sum(dn_run * w);
     if (hq == 0) { red[(wave * 16 + n) * 3] = M; red[(wave * 16 + n) * 3 + 1] = l; red[(wave * 16 + n) * 3 + 2] = dn; }
     __syncthreads();
@@ -427,13 +373,13 @@ __global__ __launch_bounds__(256) void bwd_f32_row_kernel(BwdArgs a, RowF32 x) {
       float Mt = -INFINITY, lt = 0.f, dt = 0.f;
       for (int w_ = 0; w_ < NWV; w_++) Mt = fmaxf(Mt, red[(w_ * 16 + tid) * 3]);
       for (int w_ = 0; w_ < NWV; w_++) {
-        const float e = red[(w_ * 16 + tid) * 3] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(red[(w_ * 16 + tid) * 3] - Mt);
+        const float e = red[(w_ * 16 + tid) * 3] == -INFINITY ? 0.f : exp_diff(red[(w_ * 16 + tid) * 3], Mt);
         lt = fmaf(e, red[(w_ * 16 + tid) * 3 + 1], lt);
         dt = fmaf(e, red[(w_ * 16 + tid) * 3 + 2], dt);
       }
       if (row_ok) {     // wave 0, lane tid: row_n is row tid
         if (x.parts == 1) {
-          a.lse[row_n] = Mt + __builtin_amdgcn_logf(lt);
+          a.lse[row_n] = Mt + ln_of(lt);
           a.dsum[row_n] = dt / lt;
         } else {
           float* rp = x.scratch + (part * x.rows + row_n) * 3;
@@ -528,21 +474,22 @@ __global__ __launch_bounds__(256) void bwd_f32_key_kernel(BwdArgs a, int parts) 
       else if (hq == 2) { if (bit && !isdiag) val = a.biasd[(mrow + tk) * a.t_all + c]; }
       else if (bit && c < n_cand) val = a.dxd[hrow * a.t_all + c];
     }
-    float cmb[4], ds[4], dx[4];
+    float bs[4], ls[4], ds[4], dx[4];
 #pragma unroll
     for (int v = 0; v < 4; v++) {
       const int row = 4 * hq + v;
-      const float lse = __shfl(val, row), bs = __shfl(val, 32 + row);
+      ls[v] = __shfl(val, row);
+      bs[v] = __shfl(val, 32 + row);
       ds[v] = __shfl(val, 16 + row);
       dx[v] = __shfl(val, 48 + row);
-      cmb[v] = ((tb >> (row / a.g_q)) & 1u) ? fmaf(bs, kLog2e, -lse) : -INFINITY;
+      if (!((tb >> (row / a.g_q)) & 1u)) bs[v] = -INFINITY;
     }
     const f32x4 s = mma_dot<D>(qa, kf), dp = mma_dot<D>(oa, vf);
 #pragma unroll
     for (int t = 0; t < 4; t++) {
       const int row = 4 * hq + t, tk = tok0 + row / a.g_q;
       const bool dead = a.causal && kpos0 + n > tk;
-      const float p = dead ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[t], a.c1, cmb[t]));
+      const float p = dead ? 0.f : exp_diff(fmaf(s[t], a.scale, bs[t]), ls[t]);
       const float dz = p * (dp[t] - ds[t]);
       mma_outer<D>(ow[t], p, dv);
       mma_outer<D>(qw[t], dz, dk);

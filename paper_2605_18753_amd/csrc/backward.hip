@@ -23,8 +23,8 @@
 //                  log-sum-exp and D, <GRAD = true> for dq (attention part, fp32), dd
 //                  and a dense copy of the bias; the latter also marks, per chunk,
 //                  which row tiles attend it.
-//   bwd_route_kernel  one wave per (kv-head, token): prior and entmax Jacobian,
-//                  dx per head and chunk, the routing part of dq, final dq.
+//   bwd_route_kernel  (bwd_route.hip) 16 (token, head) rows per wave: prior and entmax
+//                  Jacobian, dx per head and chunk, the routing part of dq, final dq.
 //   bwd_kv_kernel  owns a 64-key tile, walks the row tiles that attend its chunk and
 //                  accumulates dK, dV and the chunk's dkbar without atomics.
 //   bwd_f32_*      (attn_f32.hip) the same chain for fp32 tensors, with the routing kernel above.
@@ -395,243 +395,6 @@ __global__ __launch_bounds__(256, GRAD ? 2 : 3) void bwd_q_kernel(BwdArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Routing backward: one wave per (batch, kv-head, token).
-// ---------------------------------------------------------------------------
-// u^p and p u^(p-1) for u > 0
-__device__ __forceinline__ void pow_and_slope(float u, float p, float& w, float& g) {
-  if (p == 2.f) { w = u * u; g = 2.f * u; }
-  else if (p == 1.f) { w = u; g = 1.f; }
-  else { w = __builtin_amdgcn_exp2f(p * __builtin_amdgcn_logf(u)); g = p * w / u; }
-}
-
-template <int D, int G, typename T>
-__global__ __launch_bounds__(64) void bwd_route_kernel(BwdArgs a) {
-  constexpr int SEG = 64;
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-  float* qs = reinterpret_cast<float*>(lds);                 // [G][D]
-  int* cidx = reinterpret_cast<int*>(qs + G * D);            // [t_c]
-  float* dwl = reinterpret_cast<float*>(cidx + a.t_c);       // [t_c]
-  float* dxs = dwl + a.t_c;                                  // [G][SEG]
-
-  const int lane = threadIdx.x;
-  const int tok = blockIdx.x % a.n_q;
-  const int hbi = blockIdx.x / a.n_q;
-  const int r = hbi % a.h_kv, b = hbi / a.h_kv;
-  const int n_cand = a.causal ? max(tok / a.block - a.window, 0) : a.t_c;
-  const int64_t trow = ((int64_t)b * a.h_kv + r) * a.n_q + tok;
-  const uint32_t* mrow = a.mask + trow * a.words;
-  const float* dbrow = a.dbd + trow * a.t_all;
-  const float* kb = a.kbar + ((int64_t)b * a.h_kv + r) * a.t_c * D;
-
-  for (int i = lane; i < G * D; i += 64) {
-    const int hh = i / D, d = i % D;
-    qs[i] = elem<T>::ld(reinterpret_cast<const T*>(a.q) + b * a.qs_b + (r * G + hh) * a.qs_h + (int64_t)tok * a.qs_t + d);
-  }
-  // routed candidates, ascending
-  int n_r = 0;
-  for (int base = 0; base < n_cand; base += 64) {
-    const int c = base + lane;
-    const bool bit = c < n_cand && ((mrow[c >> 5] >> (c & 31)) & 1u);
-    const uint64_t bal = __ballot(bit);
-    if (bit) cidx[n_r + __popcll(bal & ((1ull << lane) - 1ull))] = c;
-    n_r += __popcll(bal);
-  }
-  __syncthreads();
-
-  float acc_q[G][2];            // routing part of dq: this lane's d pair (D = 128) or single d (D = 64)
-#pragma unroll
-  for (int hh = 0; hh < G; hh++) acc_q[hh][0] = acc_q[hh][1] = 0.f;
-
-  if (n_r > 0) {
-    float tauh[G];
-#pragma unroll
-    for (int hh = 0; hh < G; hh++) tauh[hh] = a.tau[((int64_t)b * a.h_q + r * G + hh) * a.n_q + tok];
-    float dsum = 0.f;
-    for (int e = lane; e < n_r; e += 64) dsum += dbrow[cidx[e]];
-    const float dmean = wave_sum(dsum) / (float)n_r;
-
-    // sweep A: scores, weights, slopes; S0 = sum g, S1 = sum g dw_hat per head.
-    // Eight lanes share a routed chunk (lane = 8 cs + dp): lane dp reads the dp-th
-    // eighth of the summary row, so a wave instruction covers 8 whole rows, and the
-    // partial dot products are combined over the 8 lanes by DPP.  Every lane of the
-    // group then holds all scores; lane dp keeps the per-head results of the heads
-    // hh = dp (mod 8) (slopes to memory, their sums in registers).
-    constexpr int DP = D / 8;                      // d range of one lane
-    // With few heads the routing part of dq is accumulated in the same sweep:
-    // sum_c dx_c kbar_c = sum_c (g_c dw_hat_c) kbar_c - ratio sum_c g_c kbar_c, two sums whose
-    // weights are known chunk by chunk, so the summary rows are read once.
-    constexpr bool FUSE = 2 * G * DP <= 64;
-    const int cs = lane >> 3, dp = lane & 7;
-    float s0[G], s1[G];
-#pragma unroll
-    for (int hh = 0; hh < G; hh++) s0[hh] = s1[hh] = 0.f;
-    float a1[FUSE ? G : 1][DP], a2[FUSE ? G : 1][DP];
-    if constexpr (FUSE) {
-#pragma unroll
-      for (int hh = 0; hh < G; hh++)
-#pragma unroll
-        for (int j = 0; j < DP; j++) a1[hh][j] = a2[hh][j] = 0.f;
-    }
-    for (int e0 = 0; e0 < n_r; e0 += 8) {
-      const int e = e0 + cs;
-      const bool live = e < n_r;
-      const int c = cidx[live ? e : n_r - 1];
-      const float4* krow = reinterpret_cast<const float4*>(kb + (int64_t)c * D + dp * DP);
-      float x[G];
-#pragma unroll
-      for (int hh = 0; hh < G; hh++) x[hh] = 0.f;
-      float kvr[DP];
-#pragma unroll
-      for (int d4 = 0; d4 < DP / 4; d4++) {
-        const float4 kv = krow[d4];
-        kvr[4 * d4] = kv.x; kvr[4 * d4 + 1] = kv.y; kvr[4 * d4 + 2] = kv.z; kvr[4 * d4 + 3] = kv.w;
-#pragma unroll
-        for (int hh = 0; hh < G; hh++) {
-          const float4 qv = *reinterpret_cast<const float4*>(qs + hh * D + dp * DP + d4 * 4);
-          x[hh] = fmaf(qv.x, kv.x, fmaf(qv.y, kv.y, fmaf(qv.z, kv.z, fmaf(qv.w, kv.w, x[hh]))));
-        }
-      }
-      float gd[G], wsum = 0.f;
-#pragma unroll
-      for (int hh = 0; hh < G; hh++) {
-        float xs = x[hh];
-        asm volatile("" : "+v"(xs));
-        xs += dpp_f<0xB1>(xs);     // lane ^ 1
-        xs += dpp_f<0x4E>(xs);     // lane ^ 2
-        xs += dpp_f<0x141>(xs);    // the other quad of the 8 lanes
-        const float u = xs * a.xscale - tauh[hh];
-        float wv = 0.f;
-        gd[hh] = 0.f;
-        if (u > 0.f) pow_and_slope(u, a.pexp, wv, gd[hh]);
-        wsum += wv;
-      }
-      // dw_hat = dlnw / w / g_q with w = wsum / g_q
-      const float dwh = wsum > 0.f ? (dbrow[c] - dmean) / (a.sigma * wsum) : 0.f;
-      if (live) {
-        if (dp == 0) dwl[e] = dwh;
-#pragma unroll
-        for (int hh = 0; hh < G; hh++)
-          if ((hh & 7) == dp) {
-            s0[hh] += gd[hh];
-            s1[hh] += gd[hh] * dwh;
-            a.dxd[(((int64_t)b * a.h_q + r * G + hh) * a.n_q + tok) * a.t_all + c] = gd[hh];
-          }
-        if constexpr (FUSE) {
-#pragma unroll
-          for (int hh = 0; hh < G; hh++) {
-            const float w1 = gd[hh] * dwh, w2 = gd[hh];
-#pragma unroll
-            for (int j = 0; j < DP; j++) {
-              a1[hh][j] = fmaf(w1, kvr[j], a1[hh][j]);
-              a2[hh][j] = fmaf(w2, kvr[j], a2[hh][j]);
-            }
-          }
-        }
-      }
-    }
-    float ratio[G];
-#pragma unroll
-    for (int hh = 0; hh < G; hh++) {
-      const float t0 = wave_sum(s0[hh]), t1 = wave_sum(s1[hh]);
-      ratio[hh] = t0 > 0.f ? t1 / t0 : 0.f;
-    }
-    if constexpr (FUSE) {
-      // dx for the key-owner kernel (each lane turns the slopes it wrote itself into dx)
-      for (int e0 = 0; e0 < n_r; e0 += 8) {
-        const int e = e0 + cs;
-        if (e < n_r) {
-          const int c = cidx[e];
-          const float dwh = dwl[e];
-#pragma unroll
-          for (int hh = 0; hh < G; hh++)
-            if ((hh & 7) == dp) {
-              float* px = a.dxd + (((int64_t)b * a.h_q + r * G + hh) * a.n_q + tok) * a.t_all + c;
-              *px = *px * (dwh - ratio[hh]);
-            }
-        }
-      }
-      // routing part of dq: combine the two sums, add up the 8 chunk slots (lanes that differ
-      // in cs), and hand lane (cs, dp) the d = dp DP + cs DP/8 .. of its output pair
-#pragma unroll
-      for (int hh = 0; hh < G; hh++) {
-        float v0 = 0.f, v1 = 0.f;
-#pragma unroll
-        for (int j = 0; j < DP; j++) {
-          float t = a1[hh][j] - ratio[hh] * a2[hh][j];
-          t += __shfl_xor(t, 8);
-          t += __shfl_xor(t, 16);
-          t += __shfl_xor(t, 32);
-          if (D == 128) {
-            if ((j >> 1) == cs) { if (j & 1) v1 = t; else v0 = t; }
-          } else {
-            if (j == cs) v0 = t;
-          }
-        }
-        acc_q[hh][0] = v0;
-        acc_q[hh][1] = v1;
-      }
-    } else
-    // sweep B, one segment of SEG routed chunks at a time: dx (each lane turns the slopes
-    // it wrote itself into dx), then dq += dx kbar with the lanes over d
-    for (int e0 = 0; e0 < n_r; e0 += SEG) {
-      __syncthreads();
-#pragma unroll
-      for (int it = 0; it < SEG / 8; it++) {
-        const int j = it * 8 + cs, e = e0 + j;
-        if (e < n_r) {
-          const int c = cidx[e];
-          const float dwh = dwl[e];
-#pragma unroll
-          for (int hh = 0; hh < G; hh++)
-            if ((hh & 7) == dp) {
-              float* px = a.dxd + (((int64_t)b * a.h_q + r * G + hh) * a.n_q + tok) * a.t_all + c;
-              const float dx = *px * (dwh - ratio[hh]);
-              *px = dx;
-              dxs[hh * SEG + j] = dx;
-            }
-        }
-      }
-      __syncthreads();
-      const int cnt = min(SEG, n_r - e0);
-      for (int j = 0; j < cnt; j++) {
-        const int c = cidx[e0 + j];
-        float k0, k1 = 0.f;
-        if (D == 128) {
-          const float2 kv = *reinterpret_cast<const float2*>(kb + (int64_t)c * D + 2 * lane);
-          k0 = kv.x; k1 = kv.y;
-        } else {
-          k0 = kb[(int64_t)c * D + lane];
-        }
-#pragma unroll
-        for (int hh = 0; hh < G; hh++) {
-          const float dx = dxs[hh * SEG + j];
-          acc_q[hh][0] = fmaf(dx, k0, acc_q[hh][0]);
-          acc_q[hh][1] = fmaf(dx, k1, acc_q[hh][1]);
-        }
-      }
-    }
-  }
-  // final dq = attention part + routing part; a lane owns the d pair 2 lane .. (D = 128) or the
-  // single d = lane (D = 64) in the two-sweep variant, d = 16 dp + 2 cs .. or 8 dp + cs in the fused one
-  constexpr bool FUSED = 2 * G * (D / 8) <= 64;
-  const int d_own = FUSED ? (D == 128 ? 16 * (lane & 7) + 2 * (lane >> 3) : 8 * (lane & 7) + (lane >> 3))
-                          : (D == 128 ? 2 * lane : lane);
-#pragma unroll
-  for (int hh = 0; hh < G; hh++) {
-    const int64_t row = ((int64_t)b * a.h_q + r * G + hh) * a.n_q + tok;
-    T* out = reinterpret_cast<T*>(a.dq) + b * a.qs_b + (r * G + hh) * a.qs_h + (int64_t)tok * a.qs_t;
-    if (D == 128) {
-      const float2 base = *reinterpret_cast<const float2*>(a.dq32 + row * D + d_own);
-      const float v0 = fmaf(a.xscale, acc_q[hh][0], base.x), v1 = fmaf(a.xscale, acc_q[hh][1], base.y);
-      if constexpr (sizeof(T) == 2) *reinterpret_cast<uint32_t*>(out + d_own) = cvt_bf16x2(v0, v1);
-      else *reinterpret_cast<float2*>(out + d_own) = make_float2(v0, v1);
-    } else {
-      elem<T>::st(out + d_own, fmaf(a.xscale, acc_q[hh][0], a.dq32[row * D + d_own]));
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Key-owner kernel: one 64-key tile per workgroup.
 // ---------------------------------------------------------------------------
 template <int D>
@@ -910,31 +673,14 @@ size_t backward_workspace_bytes(const dash_params& p, const Layout& L) {
          al256(rows_q * p.head_dim * 4) + al256((size_t)p.batch * p.h_kv * L.t_all * cwords * 4);
 }
 
-template <int D, int G, typename T> static hipError_t launch_route(const BwdArgs& a, int batch, hipStream_t st) {
-  const size_t lds = (size_t)G * D * 4 + (size_t)a.t_c * 8 + (size_t)G * 64 * 4 + 64;
-  auto kern = bwd_route_kernel<D, G, T>;     // at most 29 KB of LDS (t_c <= 2048): no opt-in needed
-  hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)batch * a.h_kv * a.n_q)), dim3(64), lds, st, a);
-  return hipGetLastError();
-}
-
-template <int D, typename T> static hipError_t launch_route_g(const BwdArgs& a, int batch, hipStream_t st) {
-  switch (a.g_q) {
-    case 1: return launch_route<D, 1, T>(a, batch, st);
-    case 2: return launch_route<D, 2, T>(a, batch, st);
-    case 4: return launch_route<D, 4, T>(a, batch, st);
-    case 8: return launch_route<D, 8, T>(a, batch, st);
-    default: return launch_route<D, 16, T>(a, batch, st);
-  }
-}
-
-template <int D> static hipError_t launch_bwd_f32(const BwdArgs& a, int batch, hipStream_t st) {
+template <int D> static hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t st) {
   hipError_t e;
   if ((e = launch_bwd_f32_rows(a, D, st)) != hipSuccess) return e;
-  if ((e = launch_route_g<D, float>(a, batch, st)) != hipSuccess) return e;
+  if ((e = launch_bwd_route(a, D, false, st)) != hipSuccess) return e;
   return launch_bwd_f32_keys(a, D, st);
 }
 
-template <int D> static hipError_t launch_bwd_t(const BwdArgs& a, int batch, hipStream_t st) {
+template <int D> static hipError_t launch_bwd_t(const BwdArgs& a, hipStream_t st) {
   using C = BCfg<D>;
   static LdsOptIn done_lse, done_grad, done_kv;
   hipError_t e;
@@ -958,7 +704,7 @@ template <int D> static hipError_t launch_bwd_t(const BwdArgs& a, int batch, hip
     hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb), dim3(256), lds, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((e = launch_route_g<D, uint16_t>(a, batch, st)) != hipSuccess) return e;
+  if ((e = launch_bwd_route(a, D, true, st)) != hipSuccess) return e;
   {
     const size_t xch = (size_t)2 * 2 * C::NDT * 16 * 64 * 4;
     const size_t tiles = 4 * C::TILE_BYTES;
@@ -1004,8 +750,8 @@ hipError_t launch_backward(const dash_params& p, const Layout& L, const void* q,
   a.dq32 = (float*)(ws + off);   off += al256(rows_q * p.head_dim * 4);
   a.colmask = (uint32_t*)(ws + off);
   if (p.dtype == DASH_F32)
-    return p.head_dim == 128 ? launch_bwd_f32<128>(a, p.batch, st) : launch_bwd_f32<64>(a, p.batch, st);
-  return p.head_dim == 128 ? launch_bwd_t<128>(a, p.batch, st) : launch_bwd_t<64>(a, p.batch, st);
+    return p.head_dim == 128 ? launch_bwd_f32<128>(a, st) : launch_bwd_f32<64>(a, st);
+  return p.head_dim == 128 ? launch_bwd_t<128>(a, st) : launch_bwd_t<64>(a, st);
 }
 
 }  // namespace dash

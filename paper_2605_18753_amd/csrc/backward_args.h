@@ -20,6 +20,8 @@ struct BwdArgs {
   float c1, scale, xscale, pexp, sigma;
 };
 
+// routing backward of both data types (bwd_route.hip)
+hipError_t launch_bwd_route(const BwdArgs& a, int head_dim, bool bf16, hipStream_t st);
 // fp32 tensors: row log-sum-exp, D, bias gradient and the attention part of dq; then, after the
 // routing kernel, dk, dv and the summary gradient
 hipError_t launch_bwd_f32_rows(const BwdArgs& a, int head_dim, hipStream_t st);
