@@ -25,8 +25,8 @@
 //                  which row tiles attend it.
 //   bwd_route_kernel  (bwd_route.hip) 16 (token, head) rows per wave: prior and entmax
 //                  Jacobian, dx per head and chunk, the routing part of dq, final dq.
-//   bwd_kv_kernel  owns a 64-key tile, walks the row tiles that attend its chunk and
-//                  accumulates dK, dV and the chunk's dkbar without atomics.
+//   bwd_kbar_kernel, bwd_kv_kernel  (bwd_kv.hip) the summaries' gradient; dK, dV of 128-key tiles
+//                  over the row tiles that attend their chunks, without atomics.
 //   bwd_f32_*      (attn_f32.hip) the same chain for fp32 tensors, with the routing kernel above.
 // MFMA operand layouts are those of the forward kernel: every product is
 // arranged so that the accumulator of the first product is directly the
@@ -36,61 +36,12 @@
 #include <stdlib.h>
 
 #include "backward_args.h"
+#include "bwd_tiles.h"
 #include "common.h"
 #include "dash_internal.h"
 #include "lds_copy.h"
 
 namespace dash {
-
-template <int D> struct BCfg {
-  static constexpr int NCH = D / 8;
-  static constexpr int ROW_BYTES = D * 2;
-  static constexpr int TILE_BYTES = 64 * ROW_BYTES;
-  static constexpr int COPIES = TILE_BYTES / 16 / 256;
-  static constexpr int ROWS_PER_COPY = 256 / NCH;
-  static constexpr int NDT = D / 32;
-  static constexpr int NS = D / 8;
-};
-
-// Chunk permutation of a 64-row tile (position of logical 16-byte chunk c of row
-// `row` is c ^ swz(row)), chosen so that both kinds of operand reads are free of
-// bank conflicts: the A-operand read has 16 lanes on 16 consecutive rows at one
-// logical chunk (they must land in 16 different slots of a 256-byte bank window),
-// the transposing read has 16 lanes on 4 consecutive rows x 2 consecutive chunks
-// (rows r..r+3 must land in different 64-byte groups).
-template <int D> __device__ __forceinline__ int swz(int row) {
-  return D == 128 ? (((row & 3) << 2) | ((row >> 2) & 3)) : ((((row >> 1) & 1) << 2) | ((row >> 2) & 3));
-}
-// byte offset of element (row, d0) of a tile, d0 a multiple of 4
-template <int D> __device__ __forceinline__ uint32_t tile_off(int row, int d0) {
-  return (uint32_t)(row * BCfg<D>::ROW_BYTES + (((d0 >> 3) ^ swz<D>(row)) << 4) + ((d0 & 7) << 1));
-}
-
-// Operand addresses.  Because the chunk permutation is an XOR, the offsets of the
-// d slices of one row differ from the first one by an XOR with a constant, so a
-// lane keeps one base offset per kind of read instead of one register per slice.
-// A operand slice `i` (d slice ks = i / 2, 32-row half i % 2) of a row-major tile;
-// base = tile_off(row, 8 h): the slice starts at d = 16 ks + 8 h, chunk 2 ks + h
-template <int D> __device__ __forceinline__ bf16x8 read_a(const char* tile, uint32_t base, int i) {
-  return *reinterpret_cast<const bf16x8*>(tile + (base ^ (uint32_t)((i >> 1) << 5)) + (i & 1) * 32 * BCfg<D>::ROW_BYTES);
-}
-// transposed A operand: contraction step g (16 tile rows), d-tile t; lo / hi address the
-// two 8-row halves of step 0 at d-tile 0 (d-tile t starts 4 t chunks further)
-template <int D> __device__ __forceinline__ bf16x8 read_t(const char* tile, uint32_t lo, uint32_t hi, int g, int t) {
-  return lds_read_tr_pair(tile + (lo ^ (uint32_t)(t << 6)) + (16 * g) * BCfg<D>::ROW_BYTES,
-                          tile + (hi ^ (uint32_t)(t << 6)) + (16 * g) * BCfg<D>::ROW_BYTES);
-}
-
-// two fp32 -> packed bf16 (round to nearest even) with the hardware conversion
-__device__ __forceinline__ uint32_t cvt_bf16x2(float lo, float hi) {
-  const bf16x2 w = {(__bf16)lo, (__bf16)hi};
-  return __builtin_bit_cast(uint32_t, w);
-}
-
-__device__ __forceinline__ f32x16 zero16() {
-  const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  return z;
-}
 
 __global__ void bwd_fill_zero_kernel(uint32_t* p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
@@ -180,17 +131,18 @@ __global__ __launch_bounds__(256, GRAD ? 2 : 3) void bwd_q_kernel(BwdArgs a) {
       if (m) atomicOr(&wgmask[wi], m);
     }
   __syncthreads();
-  // tell the key-owner kernel which chunks this row tile attends
+  // tell the key side which chunks this wave's 32-row tile attends
   if constexpr (GRAD)
-  for (int wi = tid; wi < a.words; wi += 256) {
-    uint32_t m = wgmask[wi];
-    while (m) {
-      const int c = wi * 32 + __builtin_ctz(m);
-      m &= m - 1u;
-      if (c < a.t_all)
-        atomicOr(&a.colmask[((int64_t)hbi * a.t_all + c) * a.cwords + (tile >> 5)], 1u << (tile & 31));
+  if (wave_ok)
+    for (int wi = lane; wi < a.words; wi += 64) {
+      uint32_t m = wvmask[wave * 64 + wi];
+      const int T = tile * 4 + wave;
+      while (m) {
+        const int c = wi * 32 + __builtin_ctz(m);
+        m &= m - 1u;
+        if (c < a.t_all) atomicOr(&a.colmask[((int64_t)hbi * a.t_all + c) * a.cwords + (T >> 5)], 1u << (T & 31));
+      }
     }
-  }
 
   // ---- tile iterator ---------------------------------------------------------
   int it_wi = -1, it_sub = nsub - 1, it_u = -1;
@@ -395,282 +347,39 @@ __global__ __launch_bounds__(256, GRAD ? 2 : 3) void bwd_q_kernel(BwdArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Key-owner kernel: one 64-key tile per workgroup.
-// ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
-  using C = BCfg<D>;
-  extern __shared__ __attribute__((aligned(1024))) char lds[];
-  char* k_t = lds;                             // this workgroup's 64 keys (stationary)
-  char* v_t = lds + C::TILE_BYTES;             // and values
-  char* q_t = lds + 2 * C::TILE_BYTES;         // 64 query rows of the current step
-  char* d_t = lds + 3 * C::TILE_BYTES;         // and their dO rows
-  float* cmb_s = reinterpret_cast<float*>(lds + 4 * C::TILE_BYTES);   // [64] per-row scalars
-  float* dsum_s = cmb_s + 64;
-  float* dx_s = dsum_s + 64;
-  int* pos_s = reinterpret_cast<int*>(dx_s + 64);
-  float* redf = reinterpret_cast<float*>(pos_s + 64);                 // [D] dkbar of the chunk
-  float* red = redf + D;                                              // [RG][D] dkbar partials
-  constexpr int RG = 256 / C::NCH, RPG = 64 / RG;   // dkbar: row groups per workgroup, rows per group
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = lane & 31, h = lane >> 5;
-  const int kh = wave & 1, rh = wave >> 1;
-  const int hbi = blockIdx.x % a.hb;
-  const int ktile = blockIdx.x / a.hb;          // early key tiles (the most rows) first
-  const int r = hbi % a.h_kv, b = hbi / a.h_kv;
-  const int kpos0 = ktile * 64;
-  const int c = kpos0 / a.block;
-  const int tok_step = 64 / a.g_q;              // tokens per 64-row step
-  const int my_key = kpos0 + kh * 32 + n;
-
-  const u32x4 k_rs = make_rsrc(a.k + b * a.ks_b + r * a.ks_h, (((int64_t)a.n_kv - 1) * a.ks_t + D) * 2);
-  const u32x4 v_rs = make_rsrc(a.v + b * a.vs_b + r * a.vs_h, (((int64_t)a.n_kv - 1) * a.vs_t + D) * 2);
-  const u32x4 q_rs = make_rsrc(a.q + b * a.qs_b + (int64_t)r * a.g_q * a.qs_h,
-                               ((int64_t)(a.g_q - 1) * a.qs_h + ((int64_t)a.n_q - 1) * a.qs_t + D) * 2);
-  const u32x4 o_rs = make_rsrc(a.d_o + b * a.os_b + (int64_t)r * a.g_q * a.os_h,
-                               ((int64_t)(a.g_q - 1) * a.os_h + ((int64_t)a.n_q - 1) * a.os_t + D) * 2);
-  const uint32_t lds0 = lds_addr_of(lds);
-  const int c_row = (wave * 64 + lane) / C::NCH, c_pos = lane % C::NCH;
-  const uint32_t c_chunk = (uint32_t)((c_pos ^ swz<D>(c_row)) << 4);
-  const int c_tok = c_row / a.g_q, c_head = c_row % a.g_q;
-  const uint32_t q_off = (uint32_t)((c_tok * (int)a.qs_t + c_head * (int)a.qs_h) * 2) + c_chunk;
-  const uint32_t o_off = (uint32_t)((c_tok * (int)a.os_t + c_head * (int)a.os_h) * 2) + c_chunk;
-  const uint32_t q_step = (uint32_t)((C::ROWS_PER_COPY / a.g_q) * (int)a.qs_t * 2);
-  const uint32_t o_step = (uint32_t)((C::ROWS_PER_COPY / a.g_q) * (int)a.os_t * 2);
-  // the key and value tiles, once (rows past the end of the sequence read as zeros)
-  {
-    const uint32_t k_off = (uint32_t)(c_row * (int)a.ks_t * 2) + c_chunk;
-    const uint32_t v_off = (uint32_t)(c_row * (int)a.vs_t * 2) + c_chunk;
-#pragma unroll
-    for (int i = 0; i < C::COPIES; i++) {
-      const uint32_t la = lds0 + wave * 1024 + i * 4096;
-      copy16_to_lds(k_rs, la, k_off, (uint32_t)(kpos0 + i * C::ROWS_PER_COPY) * (uint32_t)a.ks_t * 2u);
-      copy16_to_lds(v_rs, la + C::TILE_BYTES, v_off, (uint32_t)(kpos0 + i * C::ROWS_PER_COPY) * (uint32_t)a.vs_t * 2u);
-    }
-  }
-
-  // operand read offsets: B operands (keys kh*32 + n) and A operands (rows rh*32 + n)
-  // share the row-major pattern; the transposing reads walk this wave's 32 rows
-  const uint32_t b_rd = tile_off<D>(kh * 32 + n, 8 * h), a_rd = tile_off<D>(rh * 32 + n, 8 * h);
-  const int s16 = lane & 15, a16 = (lane >> 4) & 1;
-  const uint32_t t_lo = tile_off<D>(rh * 32 + 4 * h + (s16 >> 2), 16 * a16 + 4 * (s16 & 3));
-  const uint32_t t_hi = tile_off<D>(rh * 32 + 8 + 4 * h + (s16 >> 2), 16 * a16 + 4 * (s16 & 3));
-
-  f32x16 dkacc[C::NDT], dvacc[C::NDT];
-#pragma unroll
-  for (int t = 0; t < C::NDT; t++) { dkacc[t] = zero16(); dvacc[t] = zero16(); }
-  float kbv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // dkbar partial: 8 d of this thread's rows
-
-  // Steps: the 64-row halves of the row tiles whose bit is set in this chunk's column
-  // mask, ascending.  The per-row scalars of a step (mask bit, bias, dx, log-sum-exp,
-  // D) are fetched one step ahead into registers, all addresses known up front, so
-  // that their latency overlaps the previous step instead of preceding the tile copies.
-  const uint32_t* cm = a.colmask + ((int64_t)hbi * a.t_all + c) * a.cwords;
-  int st_wi = -1, st_half = 1, st_T = 0;
-  uint32_t st_bits = 0u;
-  auto next_step = [&]() -> int {        // first token of the next step, or -1
-    for (;;) {
-      if (st_half == 0) { st_half = 1; }
-      else {
-        while (st_bits == 0u) {
-          if (++st_wi >= a.cwords) return -1;
-          st_bits = __builtin_amdgcn_readfirstlane(cm[st_wi]);
-        }
-        st_T = st_wi * 32 + __builtin_ctz(st_bits);
-        st_bits &= st_bits - 1u;
-        st_half = 0;
-      }
-      const int t0 = st_T * 2 * tok_step + st_half * tok_step;
-      if (t0 < a.n_q) return t0;
-    }
-  };
-  // this lane's row of a step (lanes 0..15 of each wave: row 16 wave + lane)
-  const int s_row = wave * 16 + (lane & 15);
-  const int s_head = r * a.g_q + s_row % a.g_q;
-  uint32_t f_mask = 0u;
-  float f_bias = 0.f, f_dx = 0.f, f_lse = 0.f, f_dsum = 0.f;
-  int f_tok = 0;
-  bool f_ok = false;
-  auto fetch = [&](int t0) {
-    const int tk = t0 + s_row / a.g_q;
-    f_ok = tk < a.n_q;
-    f_tok = f_ok ? tk : a.n_q - 1;
-    const int64_t trow = ((int64_t)b * a.h_kv + r) * a.n_q + f_tok;
-    const int64_t hrow = ((int64_t)b * a.h_q + s_head) * a.n_q + f_tok;
-    f_mask = a.mask[trow * a.words + (c >> 5)];
-    f_bias = a.biasd[trow * a.t_all + c];      // meaningful only where the mask bit is set
-    f_dx = a.dxd[hrow * a.t_all + c];          // and, for dx, where the chunk is a candidate
-    f_lse = a.lse[hrow];
-    f_dsum = a.dsum[hrow];
-  };
-  int tok0 = next_step();
-  if (tok0 >= 0 && lane < 16) fetch(tok0);
-  while (tok0 >= 0) {
-    __syncthreads();                    // the previous step is no longer read
-    int have = 0;
-    if (lane < 16) {
-      const bool bit = f_ok && ((f_mask >> (c & 31)) & 1u);
-      const int cdiag = f_tok / a.block;
-      const bool isdiag = a.causal && c == cdiag;
-      const int n_cand = a.causal ? max(cdiag - a.window, 0) : a.t_c;
-      // bias - log-sum-exp in base-2 units (-inf: the row does not attend the chunk)
-      cmb_s[s_row] = bit ? (isdiag ? 0.f : f_bias * kLog2e) - f_lse : -INFINITY;
-      dx_s[s_row] = (bit && c < n_cand) ? f_dx : 0.f;
-      dsum_s[s_row] = f_dsum;
-      pos_s[s_row] = a.causal ? f_tok : 0x7fffffff;
-      have = bit ? 1 : 0;
-    }
-    const int cur_tok0 = tok0;
-    tok0 = next_step();
-    if (tok0 >= 0 && lane < 16) fetch(tok0);
-    if (!__syncthreads_or(have)) continue;
-    // is the chunk a routing candidate of any row of this step?  (the candidate count
-    // grows with the position, so the step's last token decides)
-    const bool any_cand = c < (a.causal ? max(min(cur_tok0 + tok_step - 1, a.n_q - 1) / a.block - a.window, 0)
-                                        : a.t_c);
-    // the key mask matters only where the rows' own chunk is this one, or at the end of the sequence
-    const bool masked = (a.causal && (cur_tok0 + tok_step - 1) / a.block >= c && cur_tok0 / a.block <= c) ||
-                        kpos0 + 64 > a.n_kv;
-    const uint32_t soff_q = (uint32_t)cur_tok0 * (uint32_t)a.qs_t * 2u;
-    const uint32_t soff_o = (uint32_t)cur_tok0 * (uint32_t)a.os_t * 2u;
-#pragma unroll
-    for (int i = 0; i < C::COPIES; i++) {
-      const uint32_t la = lds0 + 2 * C::TILE_BYTES + wave * 1024 + i * 4096;
-      copy16_to_lds(q_rs, la, q_off, soff_q + i * q_step);
-      copy16_to_lds(o_rs, la + C::TILE_BYTES, o_off, soff_o + i * o_step);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-
-    // S = Q K^T and dP = dO V^T for this wave's 32 rows x 32 keys
-    // (the base offsets are made opaque here so that the per-slice offsets derived from
-    // them are formed next to their use instead of being kept in registers across steps)
-    uint32_t a_b = a_rd, b_b = b_rd, tl = t_lo, th = t_hi;
-    asm volatile("" : "+v"(a_b), "+v"(b_b), "+v"(tl), "+v"(th));
-    f32x16 s = zero16(), dp = zero16();
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) {
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_a<D>(q_t, a_b, 2 * ks), read_a<D>(k_t, b_b, 2 * ks), s, 0, 0, 0);
-      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_a<D>(d_t, a_b, 2 * ks), read_a<D>(v_t, b_b, 2 * ks), dp, 0, 0, 0);
-    }
-    u32x4 pp[2], pd[2];
-#pragma unroll
-    for (int q4 = 0; q4 < 4; q4++) {
-      const int row0 = rh * 32 + 8 * q4 + 4 * h;
-      const float4 d4 = *reinterpret_cast<const float4*>(dsum_s + row0);
-      const float4 b4 = *reinterpret_cast<const float4*>(cmb_s + row0);
-      int4 p4 = {0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff};
-      if (masked) p4 = *reinterpret_cast<const int4*>(pos_s + row0);
-      const float ds[4] = {d4.x, d4.y, d4.z, d4.w};
-      const float bs[4] = {b4.x, b4.y, b4.z, b4.w};
-      const int ps[4] = {p4.x, p4.y, p4.z, p4.w};
-      float pv[4], dv[4];
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int j = q4 * 4 + i;
-        const bool dead = masked && (my_key > ps[i] || my_key >= a.n_kv);
-        const float p = dead ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[j], a.c1, bs[i]));
-        pv[i] = p;
-        dv[i] = p * (dp[j] - ds[i]);
-      }
-      pp[q4 >> 1][(q4 & 1) * 2 + 0] = cvt_bf16x2(pv[0], pv[1]);
-      pp[q4 >> 1][(q4 & 1) * 2 + 1] = cvt_bf16x2(pv[2], pv[3]);
-      pd[q4 >> 1][(q4 & 1) * 2 + 0] = cvt_bf16x2(dv[0], dv[1]);
-      pd[q4 >> 1][(q4 & 1) * 2 + 1] = cvt_bf16x2(dv[2], dv[3]);
-    }
-    // dV^T += dO^T P,  dK^T += Q^T dS  (contraction over this wave's 32 rows)
-#pragma unroll
-    for (int g = 0; g < 2; g++)
-#pragma unroll
-      for (int t = 0; t < C::NDT; t++) {
-        dvacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_t<D>(d_t, tl, th, g, t),
-                                                           __builtin_bit_cast(bf16x8, pp[g]), dvacc[t], 0, 0, 0);
-        dkacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_t<D>(q_t, tl, th, g, t),
-                                                           __builtin_bit_cast(bf16x8, pd[g]), dkacc[t], 0, 0, 0);
-      }
-    // dkbar += sum_rows dx q: thread tid takes the 8 d of chunk tid % NCH and the RPG rows of group tid / NCH
-    if (any_cand) {
-      const int cs = tid % C::NCH, rg = tid / C::NCH;
-#pragma unroll
-      for (int rr = 0; rr < RPG; rr++) {
-        const int row = rg * RPG + rr;
-        const float dx = dx_s[row];
-        const bf16x8 qv = *reinterpret_cast<const bf16x8*>(q_t + tile_off<D>(row, 8 * cs));
-#pragma unroll
-        for (int e = 0; e < 8; e++) kbv[e] = fmaf(dx, (float)qv[e], kbv[e]);
-      }
-    }
-  }
-
-  // ---- combine the two row halves and write ------------------------------------
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // a workgroup without any step: its K / V copies
-  __syncthreads();
-  {
-    const int cs = tid % C::NCH, rg = tid / C::NCH;
-#pragma unroll
-    for (int e = 0; e < 8; e++) red[rg * D + 8 * cs + e] = kbv[e];
-  }
-  float* xch = reinterpret_cast<float*>(lds);          // [2 kh][2 tensors][NDT*16][64 lanes]
-  if (rh == 1) {
-#pragma unroll
-    for (int t = 0; t < C::NDT; t++)
-#pragma unroll
-      for (int j = 0; j < 16; j++) {
-        xch[((kh * 2 + 0) * C::NDT * 16 + t * 16 + j) * 64 + lane] = dkacc[t][j];
-        xch[((kh * 2 + 1) * C::NDT * 16 + t * 16 + j) * 64 + lane] = dvacc[t][j];
-      }
-  }
-  __syncthreads();
-  if (tid < D) {
-    float t = 0.f;
-    for (int g = 0; g < RG; g++) t += red[g * D + tid];
-    redf[tid] = t;
-  }
-  __syncthreads();
-  if (a.dkbar_out && tid < D && c < a.t_c && kpos0 % a.block == 0)
-    a.dkbar_out[(((int64_t)b * a.h_kv + r) * a.t_c + c) * D + tid] = redf[tid] * a.xscale;
-  if (rh == 0 && my_key < a.n_kv) {
-    // block-mean summaries: every key of a complete chunk receives 1/B of the chunk's dkbar
-    const float kscale = (c < a.t_c && !a.dkbar_out) ? a.xscale / (float)a.block : 0.f;
-    uint16_t* dkp = a.dk + b * a.ks_b + r * a.ks_h + (int64_t)my_key * a.ks_t;
-    uint16_t* dvp = a.dv + b * a.vs_b + r * a.vs_h + (int64_t)my_key * a.vs_t;
-#pragma unroll
-    for (int t = 0; t < C::NDT; t++)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; q4++) {
-        const int d0 = t * 32 + q4 * 8 + h * 4;
-        float kv[4], vv[4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          const int j = q4 * 4 + i;
-          const float kbar_g = redf[d0 + i];
-          kv[i] = (dkacc[t][j] + xch[((kh * 2 + 0) * C::NDT * 16 + t * 16 + j) * 64 + lane]) * a.scale +
-                  kbar_g * kscale;
-          vv[i] = dvacc[t][j] + xch[((kh * 2 + 1) * C::NDT * 16 + t * 16 + j) * 64 + lane];
-        }
-        uint2 w;
-        w.x = cvt_bf16x2(kv[0], kv[1]); w.y = cvt_bf16x2(kv[2], kv[3]);
-        *reinterpret_cast<uint2*>(dkp + d0) = w;
-        w.x = cvt_bf16x2(vv[0], vv[1]); w.y = cvt_bf16x2(vv[2], vv[3]);
-        *reinterpret_cast<uint2*>(dvp + d0) = w;
-      }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
 static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-size_t backward_workspace_bytes(const dash_params& p, const Layout& L) {
-  const size_t rows_q = (size_t)p.batch * p.h_q * p.n_q, rows_kv = (size_t)p.batch * p.h_kv * p.n_q;
+// Carves the workspace (ws may be null: sizes only) and fills the sizes of the arguments.  Returns
+// the bytes.
+static size_t carve_workspace(BwdArgs& a, const dash_params& p, const Layout& L, char* ws) {
+  a.h_q = p.h_q; a.h_kv = p.h_kv; a.g_q = L.g_q; a.n_q = p.n_q; a.n_kv = p.n_kv; a.block = p.block_size;
+  a.t_c = L.t_c; a.t_all = L.t_all; a.words = L.words; a.causal = p.causal; a.window = p.window;
+  a.hb = p.h_kv * p.batch;
   const int tok_tile = 4 * (32 / L.g_q);
-  const int n_tiles = (p.n_q + tok_tile - 1) / tok_tile;
-  const int cwords = (n_tiles + 31) / 32;
-  return 2 * al256(rows_q * 4) + 2 * al256(rows_kv * L.t_all * 4) + al256(rows_q * L.t_all * 4) +
-         al256(rows_q * p.head_dim * 4) + al256((size_t)p.batch * p.h_kv * L.t_all * cwords * 4);
+  a.n_tiles = (p.n_q + tok_tile - 1) / tok_tile;
+  a.cwords = (4 * a.n_tiles + 31) / 32;
+  bwd_kv_plan(a);
+  a.kb_stride *= p.head_dim;
+  const size_t rows_q = (size_t)p.batch * p.h_q * p.n_q, rows_kv = (size_t)p.batch * p.h_kv * p.n_q;
+  size_t off = 0;
+  auto take = [&](size_t bytes) { char* q = ws ? ws + off : nullptr; off += al256(bytes); return q; };
+  a.lse = (float*)take(rows_q * 4);
+  a.dsum = (float*)take(rows_q * 4);
+  a.biasd = (float*)take(rows_kv * L.t_all * 4);
+  a.dbd = (float*)take(rows_kv * L.t_all * 4);
+  a.dxd = (float*)take(rows_q * L.t_all * 4);
+  a.dq32 = (float*)take(rows_q * p.head_dim * 4);
+  a.colmask = (uint32_t*)take((size_t)a.hb * L.t_all * a.cwords * 4);
+  a.dkbar = (float*)take((size_t)a.kb_parts * a.kb_stride * 4);
+  a.kv_part = (float*)take(a.kv_max_parts > 1 ? (size_t)((p.n_kv + 127) / 128) * a.hb * a.kv_max_parts * 2 * 128 * p.head_dim * 4 : 0);
+  return off;
+}
+
+size_t backward_workspace_bytes(const dash_params& p, const Layout& L) {
+  BwdArgs a;
+  return carve_workspace(a, p, L, nullptr);
 }
 
 template <int D> static hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t st) {
@@ -682,7 +391,7 @@ template <int D> static hipError_t launch_bwd_f32(const BwdArgs& a, hipStream_t 
 
 template <int D> static hipError_t launch_bwd_t(const BwdArgs& a, hipStream_t st) {
   using C = BCfg<D>;
-  static LdsOptIn done_lse, done_grad, done_kv;
+  static LdsOptIn done_lse, done_grad;
   hipError_t e;
   {
     const size_t nwords = (size_t)a.hb * a.t_all * a.cwords;
@@ -705,18 +414,7 @@ template <int D> static hipError_t launch_bwd_t(const BwdArgs& a, hipStream_t st
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = launch_bwd_route(a, D, true, st)) != hipSuccess) return e;
-  {
-    const size_t xch = (size_t)2 * 2 * C::NDT * 16 * 64 * 4;
-    const size_t tiles = 4 * C::TILE_BYTES;
-    // tiles (reused for the end-of-kernel exchange), 4 per-row scalar arrays, dkbar and its partials
-    const size_t lds = (xch > tiles ? xch : tiles) + 4 * 64 * 4 + D * 4 + (size_t)(256 / C::NCH) * D * 4;
-    auto kern = bwd_kv_kernel<D>;
-    if ((e = allow_dyn_lds((const void*)kern, lds, done_kv)) != hipSuccess) return e;
-    const int ktiles = (a.n_kv + 63) / 64;
-    hipLaunchKernelGGL(kern, dim3(ktiles * a.hb), dim3(256), lds, st, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return launch_bwd_kv(a, D, st);
 }
 
 hipError_t launch_backward(const dash_params& p, const Layout& L, const void* q, const void* k, const void* v,
@@ -729,26 +427,12 @@ hipError_t launch_backward(const dash_params& p, const Layout& L, const void* q,
   a.d_o = (const uint16_t*)d_o;
   a.dq = (uint16_t*)dq; a.dk = (uint16_t*)dk; a.dv = (uint16_t*)dv;
   a.kbar = kbar; a.mask = mask; a.bias = bias; a.tau = tau;
-  a.h_q = p.h_q; a.h_kv = p.h_kv; a.g_q = L.g_q; a.n_q = p.n_q; a.n_kv = p.n_kv; a.block = p.block_size;
-  a.t_c = L.t_c; a.t_all = L.t_all; a.words = L.words; a.causal = p.causal; a.window = p.window;
-  a.hb = p.h_kv * p.batch;
-  const int tok_tile = 4 * (32 / L.g_q);
-  a.n_tiles = (p.n_q + tok_tile - 1) / tok_tile;
-  a.cwords = (a.n_tiles + 31) / 32;
+  carve_workspace(a, p, L, ws);
   a.qs_b = p.q_stride[0]; a.qs_h = p.q_stride[1]; a.qs_t = p.q_stride[2];
   a.ks_b = p.k_stride[0]; a.ks_h = p.k_stride[1]; a.ks_t = p.k_stride[2];
   a.vs_b = p.v_stride[0]; a.vs_h = p.v_stride[1]; a.vs_t = p.v_stride[2];
   a.os_b = p.o_stride[0]; a.os_h = p.o_stride[1]; a.os_t = p.o_stride[2];
   a.c1 = L.scale * kLog2e; a.scale = L.scale; a.xscale = L.xscale; a.pexp = L.pexp; a.sigma = p.sigma;
-  const size_t rows_q = (size_t)p.batch * p.h_q * p.n_q, rows_kv = (size_t)p.batch * p.h_kv * p.n_q;
-  size_t off = 0;
-  a.lse = (float*)(ws + off);    off += al256(rows_q * 4);
-  a.dsum = (float*)(ws + off);   off += al256(rows_q * 4);
-  a.biasd = (float*)(ws + off);  off += al256(rows_kv * L.t_all * 4);
-  a.dbd = (float*)(ws + off);    off += al256(rows_kv * L.t_all * 4);
-  a.dxd = (float*)(ws + off);    off += al256(rows_q * L.t_all * 4);
-  a.dq32 = (float*)(ws + off);   off += al256(rows_q * p.head_dim * 4);
-  a.colmask = (uint32_t*)(ws + off);
   if (p.dtype == DASH_F32)
     return p.head_dim == 128 ? launch_bwd_f32<128>(a, st) : launch_bwd_f32<64>(a, st);
   return p.head_dim == 128 ? launch_bwd_t<128>(a, st) : launch_bwd_t<64>(a, st);

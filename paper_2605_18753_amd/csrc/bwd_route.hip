@@ -3,18 +3,19 @@
 //
 // bf16 tensors: a wave owns 16 (token, head) rows: the g_q heads of 16 / g_q tokens, whose candidate sets are the
 // same.  It walks the candidates in tiles of 16 chunks, twice: margins u = xscale <q, kbar> - tau,
-// weights and slopes, and the row sums of the Jacobian; then dx and dq += dx kbar.  The margins
-// come from v_mfma_f64_16x16x4_f64 (half the fp32 rate): 1 / w and, for alpha > 2, the slope are
-// singular at u = 0, and the rounding of an fp32 dot product is what a row with a chunk next to
-// its threshold would show.  The second product runs on the fp32 matrix cores in the layout of
-// f32_tiles.h, lane (n, hq) with row n and chunks 4 hq .. + 3 being its operand.  The margins of the
-// first walk are kept in LDS, lane-private, for rows of up to 256 chunks and computed again
-// beyond.
+// weights and slopes, and the row sums of the Jacobian; then dx and dq += dx kbar.  Both products run
+// on the fp32 matrix cores in the layouts of f32_tiles.h, the accumulator of the first (lane
+// (n, hq): row n, chunks 4 hq .. + 3) being the operand of the second.  The margins of the first walk are
+// kept in LDS, lane-private, for rows of up to 256 chunks and computed again beyond.
 //
-// What bounds it: the fp64 matrix rate (64 clocks per instruction, 32 of them per 16 rows x 16
-// chunks at d = 128) and L2 reads of the summaries (16 KB per tile).  Training-shaped workload (4 x 16 heads x 8192 tokens): 1.33 ms with one wave
-// per token and fp32 FMAs on 8 lanes per summary row -> 0.53 ms
-// (fetching the next tile ahead costs the third wave per SIMD: 0.65 ms).
+// The gradient is singular at the threshold (1 / w, and for alpha > 2 the slope as well), so a
+// chunk next to it magnifies the rounding of its margin.  Margins below kNear therefore come from
+// one definition shared with the kernel for fp32 tensors (near_margin: fp32 FMAs in eight
+// partial sums), whatever the tiling; about one tile in twenty has one.
+//
+// What bounds it: L2 reads of the summaries (16 KB per 16 rows and 16 chunks at d = 128), and the
+// fp32 matrix rate.  Training-shaped workload (4 x 16 heads x 8192 tokens): 1.33 ms with one wave
+// per token and fp32 FMAs on 8 lanes per summary row -> 0.58 ms.
 #include <math.h>
 
 #include "backward_args.h"
@@ -271,6 +272,28 @@ __global__ __launch_bounds__(64) void bwd_route_f32_kernel(BwdArgs a) {
   }
 }
 
+constexpr float kNear = 1e-4f;
+
+// Margin of one (row, chunk) pair from fp32 FMAs: lane dp = lane % 8 sums the dp-th eighth of the
+// head dimension, the partial sums are added pairwise.  q and kbar rows are wave-uniform; all lanes
+// get the result.
+template <int D> __device__ __forceinline__ float near_margin(const uint16_t* q, const float* kbar, float xscale, float tau, int lane) {
+  constexpr int DP = D / 8;
+  const int dp = lane & 7;
+  float x = 0.f;
+#pragma unroll
+  for (int d4 = 0; d4 < DP / 4; d4++) {
+    const f32x4 kv = *reinterpret_cast<const f32x4*>(kbar + dp * DP + d4 * 4);
+    const uint2 w = *reinterpret_cast<const uint2*>(q + dp * DP + d4 * 4);
+    x = fmaf(bf16_lo(w.x), kv[0], fmaf(bf16_hi(w.x), kv[1], fmaf(bf16_lo(w.y), kv[2], fmaf(bf16_hi(w.y), kv[3], x))));
+  }
+  asm volatile("" : "+v"(x));
+  x += dpp_f<0xB1>(x);       // lane ^ 1
+  x += dpp_f<0x4E>(x);       // lane ^ 2
+  x += dpp_f<0x141>(x);      // the other quad of the 8 lanes
+  return fmaf(x, xscale, -tau);
+}
+
 constexpr int kKeepTiles = 16;   // margin tiles kept in LDS: 1 KB each and wave
 
 template <int D, int G, bool KEEP>
@@ -318,6 +341,19 @@ __global__ __launch_bounds__(256) void bwd_route_kernel(BwdArgs a, int n_tiles, 
     }
     return v;
   };
+  // dx of all candidates, zero where not routed (the summary gradient reads them all)
+  auto put_dx = [&](int ct, f32x4 dx) {
+    if (!row_ok) return;
+    float* p = dxrow + ct * 16 + 4 * hq;
+    const int left = n_cand - (ct * 16 + 4 * hq);
+    if (vec && left >= 4) {
+      *reinterpret_cast<f32x4*>(p) = dx;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+        if (i < left) p[i] = dx[i];
+    }
+  };
   float dsum = 0.f, cnt = 0.f;
   for (int ct = 0; ct < nct; ct++) {
     const uint32_t bits = bits_of(ct);
@@ -330,30 +366,34 @@ __global__ __launch_bounds__(256) void bwd_route_kernel(BwdArgs a, int n_tiles, 
   const float dmean = cnt > 0.f ? dsum / cnt : 0.f;
 
   if (__any(cnt > 0.f)) {
-    typedef double f64x4 __attribute__((ext_vector_type(4)));
-    double qf[C::NS][4];
+    f32x4 qf[C::NS];
+    const uint16_t* qrow = a.q + b * a.qs_b + (int64_t)r * G * a.qs_h;
     {
-      const uint16_t* qp = a.q + b * a.qs_b + (r * G + n % G) * a.qs_h + (int64_t)tok * a.qs_t + 4 * hq;
+      const uint16_t* qp = qrow + (n % G) * a.qs_h + (int64_t)tok * a.qs_t + 4 * hq;
 #pragma unroll
-      for (int s = 0; s < C::NS; s++)
-#pragma unroll
-        for (int e = 0; e < 4; e++) qf[s][e] = (double)bf16_bits_to_f32(qp[16 * s + e]);
+      for (int s = 0; s < C::NS; s++) {
+        const uint2 w = *reinterpret_cast<const uint2*>(qp + 16 * s);
+        qf[s] = f32x4{bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y)};
+      }
     }
-    const double tau = (double)a.tau[hrow], xs = (double)a.xscale;
-    // The fp64 accumulator has A row 4 i + hq in register i of lane (n, hq): operand lane m takes
-    // chunk 4 (m % 4) + m / 4, so that register i is chunk 4 hq + i as in the fp32 layout.
-    const int c_row = 4 * (n & 3) + (n >> 2);
-    auto margins = [&](int ct) -> f32x4 {
+    const float tau = a.tau[hrow];
+    auto margins = [&](int ct, uint32_t bits) -> f32x4 {
       f32x4 kf[C::NS];
-      load_row<D>(kb + (int64_t)min(ct * 16 + c_row, n_cand - 1) * D, hq, kf);
-      f64x4 acc = {0., 0., 0., 0.};
+      load_row<D>(kb + (int64_t)min(ct * 16 + n, n_cand - 1) * D, hq, kf);
+      f32x4 u = mma_dot<D>(kf, qf);
 #pragma unroll
-      for (int s = 0; s < C::NS; s++)
-#pragma unroll
-        for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kf[s][e], qf[s][e], acc, 0, 0, 0);
-      f32x4 u;
-#pragma unroll
-      for (int i = 0; i < 4; i++) u[i] = (float)fma(acc[i], xs, -tau);
+      for (int i = 0; i < 4; i++) {
+        u[i] = fmaf(u[i], a.xscale, -tau);
+        uint64_t near = __ballot(((bits >> i) & 1u) && fabsf(u[i]) < kNear);
+        while (near) {
+          const int l = __builtin_ctzll(near);
+          near &= near - 1ull;
+          const int row = l & 15, tk = min(tok0 + row / G, a.n_q - 1);
+          const float un = near_margin<D>(qrow + (row % G) * a.qs_h + (int64_t)tk * a.qs_t, kb + (int64_t)(ct * 16 + 4 * (l >> 4) + i) * D,
+                                          a.xscale, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tau), l)), lane);
+          if (lane == l) u[i] = un;
+        }
+      }
       return u;
     };
     // slopes g and dw_hat = dlnw / w / g_q (w = wsum / g_q) of this lane's four chunks
@@ -372,7 +412,7 @@ __global__ __launch_bounds__(256) void bwd_route_kernel(BwdArgs a, int n_tiles, 
     for (int ct = 0; ct < nct; ct++) {
       const uint32_t bits = bits_of(ct);
       if (!__any(bits != 0u)) continue;
-      const f32x4 db = db_of(ct, bits), u = margins(ct);
+      const f32x4 db = db_of(ct, bits), u = margins(ct, bits);
       if constexpr (KEEP) kept[ct * 64] = u;
       f32x4 g, dwh;
       terms(u, db, bits, g, dwh);
@@ -384,28 +424,23 @@ __global__ __launch_bounds__(256) void bwd_route_kernel(BwdArgs a, int n_tiles, 
     const float ratio = s0 > 0.f ? s1 / s0 : 0.f;
     for (int ct = 0; ct < nct; ct++) {
       const uint32_t bits = bits_of(ct);
-      if (!__any(bits != 0u)) continue;
+      if (!__any(bits != 0u)) { put_dx(ct, f32x4{0.f, 0.f, 0.f, 0.f}); continue; }
       f32x4 kr[4][C::NV];
 #pragma unroll
       for (int t = 0; t < 4; t++) load_row2<D>(kb + (int64_t)min(ct * 16 + 4 * hq + t, n_cand - 1) * D, n, kr[t]);
       const f32x4 db = db_of(ct, bits);
       f32x4 u, g, dwh, dx;
-      if constexpr (KEEP) u = kept[ct * 64]; else u = margins(ct);
+      if constexpr (KEEP) u = kept[ct * 64]; else u = margins(ct, bits);
       terms(u, db, bits, g, dwh);
 #pragma unroll
       for (int i = 0; i < 4; i++) dx[i] = g[i] * (dwh[i] - ratio);
-      if (row_ok && bits) {
-        float* p = dxrow + ct * 16 + 4 * hq;
-        if (vec) *reinterpret_cast<f32x4*>(p) = dx;     // entries of chunks that were not routed are not read
-        else {
-#pragma unroll
-          for (int i = 0; i < 4; i++)
-            if ((bits >> i) & 1u) p[i] = dx[i];
-        }
-      }
+      put_dx(ct, dx);
 #pragma unroll
       for (int t = 0; t < 4; t++) mma_outer<D>(kr[t], dx[t], dq);
     }
+  }
+  else {
+    for (int ct = 0; ct < nct; ct++) put_dx(ct, f32x4{0.f, 0.f, 0.f, 0.f});
   }
   // final dq = attention part + routing part
   if (!row_ok) return;
