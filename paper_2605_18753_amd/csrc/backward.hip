@@ -35,6 +35,8 @@
 #include <math.h>
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "backward_args.h"
 #include "bwd_tiles.h"
 #include "common.h"
@@ -51,17 +53,20 @@ __global__ void bwd_fill_zero_kernel(uint32_t* p, size_t n) {
 // ---------------------------------------------------------------------------
 // Row-owner kernel.
 // ---------------------------------------------------------------------------
-// GRAD = false: the first walk (row log-sum-exp and D into the workspace; few registers, dO
-// fragments in registers, three workgroups per CU).  GRAD = true: the second walk (dq, bias
-// gradient, column masks; dO rows as an LDS operand, two workgroups per CU).
+// GRAD = false: the first walk (row log-sum-exp and D into the workspace); GRAD = true: the second
+// (dq, bias gradient, column masks).  Both walk like the forward kernel (stage2.hip): two-stage K and V
+// rings filled by direct copies issued between the MFMAs of the tile before, one barrier per
+// tile, q and dO fragments in registers, two workgroups per CU, and the tile written slot by slot with
+// the vector work of one 32-key half behind the MFMAs of the next product.
+// What bounds it: the matrix and LDS pipes about equally (48 KB of operand reads per 48 MFMAs and
+// wave in the second walk).  Training-shaped workload (4 x 16 heads x 8192 tokens): 1.35 + 2.43 ms
+// with a single tile buffer (copy, wait, compute) and dO as an LDS operand -> 1.30 + 2.07 ms.
 template <int D, bool GRAD>
-__global__ __launch_bounds__(256, GRAD ? 2 : 3) void bwd_q_kernel(BwdArgs a) {
+__global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
   using C = BCfg<D>;
+  constexpr int KS = D / 16, NDT = C::NDT;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  char* k_t = lds;                            // K tile
-  char* v_t = lds + C::TILE_BYTES;            // V tile
-  char* do_t = lds + 2 * C::TILE_BYTES;       // GRAD: dO rows of the workgroup's 128 rows (stationary)
-  uint32_t* wgmask = reinterpret_cast<uint32_t*>(lds + (GRAD ? 4 : 2) * C::TILE_BYTES);   // [64]
+  uint32_t* wgmask = reinterpret_cast<uint32_t*>(lds + 4 * C::TILE_BYTES);   // [64], after the K ring [2] and the V ring [2]
   uint32_t* wvmask = wgmask + 64;                                            // [4][64]
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -82,32 +87,18 @@ __global__ __launch_bounds__(256, GRAD ? 2 : 3) void bwd_q_kernel(BwdArgs a) {
   const int cw = (tok_w0 < a.n_q ? tok_w0 : a.n_q - 1) / a.block;
   const bool wave_ok = tok_w0 < a.n_q;
 
-  // ---- row fragments as B operands: q in registers; dO in registers (first walk) or in LDS
-  // (second walk, each wave its own 32 rows)
-  bf16x8 qf[D / 16], dof[GRAD ? 1 : D / 16];
+  // ---- row fragments (B operands), complete before the tile loop -----------------
+  bf16x8 qf[KS], dof[KS];
   {
     const uint16_t* qp = a.q + b * a.qs_b + my_head * a.qs_h + (int64_t)row_tok * a.qs_t + h * 8;
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
-  }
-  if constexpr (!GRAD) {
     const uint16_t* dop = a.d_o + b * a.os_b + my_head * a.os_h + (int64_t)row_tok * a.os_t + h * 8;
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) dof[ks] = *reinterpret_cast<const bf16x8*>(dop + ks * 16);
-  } else {
-    const u32x4 o_rs = make_rsrc(a.d_o + b * a.os_b + (int64_t)r * a.g_q * a.os_h,
-                                 ((int64_t)(a.g_q - 1) * a.os_h + ((int64_t)a.n_q - 1) * a.os_t + D) * 2);
-    constexpr int RPI = 64 / C::NCH;             // rows one copy instruction covers
+    for (int ks = 0; ks < KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
 #pragma unroll
-    for (int i = 0; i < 32 / RPI; i++) {
-      const int rw = i * RPI + lane / C::NCH;    // row of this wave
-      const int tk = min(tok_w0 + rw / a.g_q, a.n_q - 1);
-      const uint32_t voff = (uint32_t)((tk * (int)a.os_t + (rw % a.g_q) * (int)a.os_h) * 2) +
-                            (uint32_t)(((lane % C::NCH) ^ swz<D>(wave * 32 + rw)) << 4);
-      copy16_to_lds(o_rs, lds_addr_of(do_t) + (wave * 32 + i * RPI) * C::ROW_BYTES, voff, 0u);
-    }
+    for (int ks = 0; ks < KS; ks++) dof[ks] = *reinterpret_cast<const bf16x8*>(dop + ks * 16);
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) asm volatile("" : "+v"(qf[ks]), "+v"(dof[ks]));
   }
-  const uint32_t do_rd = tile_off<D>(wave * 32 + n, 8 * h);
 
   // ---- chunk bitmaps ---------------------------------------------------------
   const int trk_tok = tok_w0 + lane;
@@ -168,6 +159,18 @@ __global__ __launch_bounds__(256, GRAD ? 2 : 3) void bwd_q_kernel(BwdArgs a) {
   const uint32_t v_off = (uint32_t)(c_row * (int)a.vs_t * 2 + ((c_pos ^ swz<D>(c_row)) << 4));
   const uint32_t k_step = (uint32_t)(C::ROWS_PER_COPY * (int)a.ks_t * 2);
   const uint32_t v_step = (uint32_t)(C::ROWS_PER_COPY * (int)a.vs_t * 2);
+  uint32_t cp_k = 0, cp_v = 0;   // scalar byte offsets of the tile being copied
+  auto copy_begin = [&](int u, int sub) {
+    cp_k = (uint32_t)(u * a.block + sub * 64) * (uint32_t)a.ks_t * 2u;
+    cp_v = (uint32_t)(u * a.block + sub * 64) * (uint32_t)a.vs_t * 2u;
+  };
+  auto copy_one = [&](int c, int slot) {
+    if (c < C::COPIES)
+      copy16_to_lds(k_rs, lds0 + slot * C::TILE_BYTES + wave * 1024 + c * 4096, k_off, cp_k + c * k_step);
+    else
+      copy16_to_lds(v_rs, lds0 + (2 + slot) * C::TILE_BYTES + wave * 1024 + (c - C::COPIES) * 4096, v_off,
+                    cp_v + (c - C::COPIES) * v_step);
+  };
 
   // ---- operand read offsets ------------------------------------------------------
   // A operand: lane (n, h) reads logical chunk 2 ks + h of rows n, 32 + n.
@@ -179,134 +182,175 @@ __global__ __launch_bounds__(256, GRAD ? 2 : 3) void bwd_q_kernel(BwdArgs a) {
   const uint32_t t_lo = tile_off<D>(4 * h + (s16 >> 2), 16 * a16 + 4 * (s16 & 3));
   const uint32_t t_hi = tile_off<D>(8 + 4 * h + (s16 >> 2), 16 * a16 + 4 * (s16 & 3));
 
-  // first walk (GRAD = false): running max, sum of exponentials and sum of exponentials
-  // times dP; D = <P, dP> = <dO, o> is taken from the latter two in fp32 (the stored bf16
-  // output would put its rounding error into every dz of the row).  Second walk: both
-  // come from the workspace.
-  float m_run = -INFINITY, l_run = 0.f, dn_run = 0.f, lse2 = 0.f, dsum = 0.f;
-  f32x16 dqacc[GRAD ? C::NDT : 1];
+  // first walk: running max, sum of exponentials and sum of exponentials times dP; D =
+  // <P, dP> = <dO, o> is taken from the latter two in fp32 (the stored bf16 output would
+  // put its rounding error into every dz of the row).  Second walk: both come from the workspace.
+  float m_run = -INFINITY, l_run = 0.f, dn_run = 0.f, lse2 = 0.f, dsum = 0.f, db_acc = 0.f;
+  f32x16 dqacc[GRAD ? NDT : 1];
 #pragma unroll
-  for (int t = 0; t < (GRAD ? C::NDT : 1); t++) dqacc[t] = zero16();
-  float db_acc = 0.f;
+  for (int t = 0; t < (GRAD ? NDT : 1); t++) dqacc[t] = zero16();
   if constexpr (GRAD) {
     const int64_t row = ((int64_t)b * a.h_q + my_head) * a.n_q + row_tok;
     lse2 = a.lse[row];
     dsum = a.dsum[row];
+    asm volatile("" : "+v"(lse2), "+v"(dsum));
   }
-
-  {
-    constexpr bool grad = GRAD;
-    float trk_next = (trk_ok && a.t_all > 0) ? trk_bias[0] : 0.f;
-    float bias_row = 0.f;
-    bool wave_on = false, diag = false;
-    while (advance()) {
-      const int cu = it_u, csub = it_sub;
-      const uint32_t soff_k = (uint32_t)(cu * a.block + csub * 64) * (uint32_t)a.ks_t * 2u;
-      const uint32_t soff_v = (uint32_t)(cu * a.block + csub * 64) * (uint32_t)a.vs_t * 2u;
-      __syncthreads();                      // the previous tile is no longer read
-#pragma unroll
-      for (int c = 0; c < C::COPIES; c++) {
-        copy16_to_lds(k_rs, lds0 + wave * 1024 + c * 4096, k_off, soff_k + c * k_step);
-        copy16_to_lds(v_rs, lds0 + C::TILE_BYTES + wave * 1024 + c * 4096, v_off, soff_v + c * v_step);
-      }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-
-      if (csub == 0) {
-        wave_on = wave_ok && ((__builtin_amdgcn_readfirstlane(wvmask[wave * 64 + (cu >> 5)]) >> (cu & 31)) & 1u);
-        diag = a.causal && cu == cw;
-        if (wave_on) {
-          float bt = 0.f;
-          trk_has = false;
-          if (!diag) {
-            bt = -INFINITY;
-            if (trk_ok) {
-              if ((cu >> 5) != trk_wi) { trk_wi = cu >> 5; trk_word = trk_mask[trk_wi]; }
-              if ((trk_word >> (cu & 31)) & 1u) {
-                trk_has = true;
-                bt = trk_next * kLog2e;
-                if (grad) a.biasd[trk_base * a.t_all + cu] = trk_next;
-                trk_rank++;
-                if (trk_rank < a.t_all) trk_next = trk_bias[trk_rank];
-              }
-            }
-          }
-          bias_row = __shfl(bt, n / a.g_q);
+  float trk_next = trk_ok ? trk_bias[0] : 0.f;
+  float bias_row = 0.f;
+  bool wave_on = false, diag = false;
+  auto begin_chunk = [&](int u) {
+    wave_on = wave_ok && ((__builtin_amdgcn_readfirstlane(wvmask[wave * 64 + (u >> 5)]) >> (u & 31)) & 1u);
+    diag = a.causal && u == cw;
+    if (!wave_on) return;
+    float bt = 0.f;
+    trk_has = false;
+    if (!diag) {
+      bt = -INFINITY;
+      if (trk_ok) {
+        if ((u >> 5) != trk_wi) { trk_wi = u >> 5; trk_word = trk_mask[trk_wi]; }
+        if ((trk_word >> (u & 31)) & 1u) {
+          trk_has = true;
+          bt = trk_next * kLog2e;
+          if (GRAD) a.biasd[trk_base * a.t_all + u] = trk_next;
+          trk_rank++;
+          if (trk_rank < a.t_all) trk_next = trk_bias[trk_rank];
         }
       }
-      if (!wave_on) continue;
-      const int kpos0 = cu * a.block + csub * 64;
+    }
+    bias_row = __shfl(bt, n / a.g_q);
+  };
 
-      // the tile in two halves of 32 keys (keeps one S^T and one dP^T accumulator live)
-      u32x4 pb[4];
-      float dssum = 0.f;
+  // ---- one 64-key tile, in two 32-key halves -----------------------------------------
+  auto tile_math = [&](auto p_tag, bool masked, int kpos0, bool more) {
+    constexpr int P = decltype(p_tag)::value;
+    const char* kb = lds + P * C::TILE_BYTES;
+    const char* vb = lds + (2 + P) * C::TILE_BYTES;
+    constexpr int AH = 2;
+    f32x16 s[2], dp[2];
+    // S^T = K Q^T or dP^T = V dO^T of half kt; after MFMA i: behind(i)
+    auto product = [&](const char* t, const bf16x8 (&rows)[KS], int kt, auto&& behind) -> f32x16 {
+      f32x16 acc;
+      bf16x8 op[KS];
+#pragma unroll
+      for (int i = 0; i < AH; i++) op[i] = read_a<D>(t, a_rd, 2 * i + kt);
+#pragma unroll
+      for (int i = 0; i < KS; i++) {
+        if (i + AH < KS) op[i + AH] = read_a<D>(t, a_rd, 2 * (i + AH) + kt);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[i], rows[i], i == 0 ? zero16() : acc, 0, 0, 0);
+        behind(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      return acc;
+    };
+    // quad index of slot i (four quads of 4 keys over KS slots)
+    auto quad_at = [](int i) -> int { return KS == 8 ? ((i & 1) ? i >> 1 : -1) : i; };
+    // key mask: causal inside the diagonal chunk, and the end of the sequence
+    auto mask_half = [&](int kt) {
+      if (masked) {
+        const int k0 = kpos0 + 32 * kt + 4 * h;
+        int lim = min(diag ? row_pos - k0 : 0x7fffffff, a.n_kv - 1 - k0);
+        asm volatile("" : "+v"(lim));
+#pragma unroll
+        for (int j = 0; j < 16; j++) {
+          const int c = (j >> 2) * 8 + (j & 3);
+          s[kt][j] = c > lim ? -INFINITY : s[kt][j];
+        }
+      }
+    };
+    // the copies of the next tile, one per slot, starting at slot `i0` of the tile
+    auto copies = [&](int i) {
+      if (i < 2 * C::COPIES && more) copy_one(i, P ^ 1);
+    };
+    if constexpr (!GRAD) {
+      s[0] = product(kb, qf, 0, [&](int i) { copies(i); });
+      s[1] = product(kb, qf, 1, [&](int i) { copies(KS + i); });
+      mask_half(0);
+      mask_half(1);
+      float mloc = -INFINITY;
+#pragma unroll
+      for (int kt = 0; kt < 2; kt++)
+#pragma unroll
+        for (int j = 0; j < 16; j += 2) mloc = fmaxf(fmaxf(mloc, s[kt][j]), s[kt][j + 1]);
+      mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+      const float m_new = fmaxf(m_run, fmaf(mloc, a.c1, bias_row));
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;
+      const float corr = __builtin_amdgcn_exp2f(m_run - m_use), off = bias_row - m_use;
+      m_run = m_new;
+      l_run *= corr;
+      dn_run *= corr;
+      auto e_quad = [&](int kt, int q4) {
+        if (q4 < 0) return;
+#pragma unroll
+        for (int j = 4 * q4; j < 4 * q4 + 4; j++) {
+          s[kt][j] = __builtin_amdgcn_exp2f(fmaf(s[kt][j], a.c1, off));
+          l_run += s[kt][j];
+        }
+      };
+      auto n_quad = [&](int kt, int q4) {
+        if (q4 < 0) return;
+#pragma unroll
+        for (int j = 4 * q4; j < 4 * q4 + 4; j++) dn_run = fmaf(s[kt][j], dp[kt][j], dn_run);
+      };
+      dp[0] = product(vb, dof, 0, [&](int i) { e_quad(0, quad_at(i)); });
+      dp[1] = product(vb, dof, 1, [&](int i) { e_quad(1, quad_at(i)); n_quad(0, quad_at(i)); });
+#pragma unroll
+      for (int q4 = 0; q4 < 4; q4++) n_quad(1, q4);
+    } else {
       const float off = bias_row - lse2;
+      u32x4 pb[4];
+      auto p_quad = [&](int kt, int q4) {
+        if (q4 < 0) return;
 #pragma unroll
-      for (int kt = 0; kt < 2; kt++) {
-        // S^T = K Q^T, dP^T = V dO^T
-        f32x16 s = zero16(), dp = zero16();
+        for (int j = 4 * q4; j < 4 * q4 + 4; j++) s[kt][j] = __builtin_amdgcn_exp2f(fmaf(s[kt][j], a.c1, off));
+      };
+      auto d_quad = [&](int kt, int q4) {     // dS^T = P^T (dP^T - D), packed as the B operand of the last product
+        if (q4 < 0) return;
+        float z[4];
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ks++) {
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_a<D>(k_t, a_rd, 2 * ks + kt), qf[ks], s, 0, 0, 0);
-          if constexpr (GRAD)
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_a<D>(v_t, a_rd, 2 * ks + kt),
-                                                         read_a<D>(do_t, do_rd, 2 * ks), dp, 0, 0, 0);
-          else
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_a<D>(v_t, a_rd, 2 * ks + kt), dof[ks], dp, 0, 0, 0);
-        }
-        // key mask: causal inside the diagonal chunk, and the end of the sequence
-        if (diag || kpos0 + 64 > a.n_kv) {
-          const int k0 = kpos0 + 32 * kt + 4 * h;
-          const int lim = min(diag ? row_pos - k0 : 0x7fffffff, a.n_kv - 1 - k0);
-#pragma unroll
-          for (int j = 0; j < 16; j++) {
-            const int c = (j >> 2) * 8 + (j & 3);
-            s[j] = c > lim ? -INFINITY : s[j];
-          }
-        }
-        if (!grad) {
-          float mloc = -INFINITY;
-#pragma unroll
-          for (int j = 0; j < 16; j++) mloc = fmaxf(mloc, s[j]);
-          mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-          const float tmax = fmaf(mloc, a.c1, bias_row);
-          const float m_new = fmaxf(m_run, tmax);
-          const float m_use = m_new == -INFINITY ? 0.f : m_new;
-          float lsum = 0.f, dnsum = 0.f;
-#pragma unroll
-          for (int j = 0; j < 16; j++) {
-            const float e = __builtin_amdgcn_exp2f(fmaf(s[j], a.c1, bias_row - m_use));
-            lsum += e;
-            dnsum = fmaf(e, dp[j], dnsum);
-          }
-          const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
-          l_run = l_run * corr + lsum;
-          dn_run = dn_run * corr + dnsum;
-          m_run = m_new;
-        } else {
-          // dS^T = P^T (dP^T - D), packed as the B operand of the second product
-#pragma unroll
-          for (int k = 0; k < 8; k++) {
-            const int g = 2 * kt + (k >> 2), j = 8 * (k >> 2) + 2 * (k & 3);
-            const float p0 = __builtin_amdgcn_exp2f(fmaf(s[j], a.c1, off));
-            const float p1 = __builtin_amdgcn_exp2f(fmaf(s[j + 1], a.c1, off));
-            const float d0 = p0 * (dp[j] - dsum);
-            const float d1 = p1 * (dp[j + 1] - dsum);
-            dssum += d0 + d1;
-            pb[g][k & 3] = cvt_bf16x2(d0, d1);
-          }
-        }
-      }
-      if constexpr (GRAD) {
-      db_acc += dssum;
+        for (int i = 0; i < 4; i++) z[i] = s[kt][4 * q4 + i] * (dp[kt][4 * q4 + i] - dsum);
+        db_acc += (z[0] + z[1]) + (z[2] + z[3]);
+        pb[2 * kt + (q4 >> 1)][(q4 & 1) * 2] = cvt_bf16x2(z[0], z[1]);
+        pb[2 * kt + (q4 >> 1)][(q4 & 1) * 2 + 1] = cvt_bf16x2(z[2], z[3]);
+      };
+      s[0] = product(kb, qf, 0, [&](int i) { copies(i); });
+      mask_half(0);
+      dp[0] = product(vb, dof, 0, [&](int i) { copies(KS + i); p_quad(0, quad_at(i)); });
+      s[1] = product(kb, qf, 1, [&](int i) { d_quad(0, quad_at(i)); });
+      mask_half(1);
+      dp[1] = product(vb, dof, 1, [&](int i) { p_quad(1, quad_at(i)); });
       // dQ^T += K^T dS^T
+      bf16x8 tr[4 * NDT];
 #pragma unroll
-      for (int i = 0; i < C::NS; i++) {
-        const int g = i / C::NDT, t = i % C::NDT;
-        dqacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_t<D>(k_t, t_lo, t_hi, g, t),
-                                                           __builtin_bit_cast(bf16x8, pb[g]), dqacc[t], 0, 0, 0);
+      for (int i = 0; i < AH; i++) tr[i] = read_t<D>(kb, t_lo, t_hi, i / NDT, i % NDT);
+#pragma unroll
+      for (int i = 0; i < 4 * NDT; i++) {
+        if (i + AH < 4 * NDT) tr[i + AH] = read_t<D>(kb, t_lo, t_hi, (i + AH) / NDT, (i + AH) % NDT);
+        dqacc[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr[i], __builtin_bit_cast(bf16x8, pb[i / NDT]), dqacc[i % NDT], 0, 0, 0);
+        if (i < 2 * NDT) d_quad(1, NDT == 4 ? ((i & 1) ? i >> 1 : -1) : i);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      if (csub == nsub - 1) {
+    }
+  };
+
+  // ---- main loop: as in the forward kernel ------------------------------------------------
+  bool have = advance();
+  if (have) {
+    copy_begin(it_u, it_sub);
+#pragma unroll
+    for (int c = 0; c < 2 * C::COPIES; c++) copy_one(c, 0);
+  }
+  auto iteration = [&](auto p_tag) {
+    constexpr int P = decltype(p_tag)::value;
+    const int cu = it_u, csub = it_sub;
+    const bool more = advance();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's copies of the tile have landed
+    __syncthreads();
+    if (csub == 0) begin_chunk(cu);
+    if (more) copy_begin(it_u, it_sub);
+    if (wave_on) {
+      const int kpos0 = cu * a.block + csub * 64;
+      tile_math(p_tag, diag || kpos0 + 64 > a.n_kv, kpos0, more);
+      if (GRAD && csub == nsub - 1) {
         // bias gradient of chunk cu: sum over the keys (both lane halves) and the
         // token's heads (adjacent lanes), written by the lane that tracks the token
         float tot = db_acc + __shfl_xor(db_acc, 32);
@@ -315,26 +359,32 @@ __global__ __launch_bounds__(256, GRAD ? 2 : 3) void bwd_q_kernel(BwdArgs a) {
         if (!diag && trk_ok && trk_has) a.dbd[trk_base * a.t_all + cu] = mine;
         db_acc = 0.f;
       }
-      }
+    } else if (more) {
+#pragma unroll
+      for (int c = 0; c < 2 * C::COPIES; c++) copy_one(c, P ^ 1);
     }
-    if constexpr (!GRAD) {
-      const float l_tot = l_run + __shfl_xor(l_run, 32);
-      const float dn_tot = dn_run + __shfl_xor(dn_run, 32);
-      lse2 = (m_run == -INFINITY ? 0.f : m_run) + __builtin_amdgcn_logf(l_tot);   // v_log_f32: log2
-      dsum = l_tot > 0.f ? dn_tot / l_tot : 0.f;
-    }
+    have = more;
+  };
+  while (have) {
+    iteration(std::integral_constant<int, 0>{});
+    if (!have) break;
+    iteration(std::integral_constant<int, 1>{});
   }
 
   // ---- outputs -----------------------------------------------------------------
-  if (row_ok) {
-    const int64_t row = ((int64_t)b * a.h_q + my_head) * a.n_q + my_tok;
-    if constexpr (!GRAD) {
-      if (h == 0) { a.lse[row] = lse2; a.dsum[row] = dsum; }
+  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  const float dn_tot = dn_run + __shfl_xor(dn_run, 32);
+  if (!row_ok) return;
+  const int64_t row = ((int64_t)b * a.h_q + my_head) * a.n_q + my_tok;
+  if constexpr (!GRAD) {
+    if (h == 0) {
+      a.lse[row] = (m_run == -INFINITY ? 0.f : m_run) + __builtin_amdgcn_logf(l_tot);   // v_log_f32: log2
+      a.dsum[row] = l_tot > 0.f ? dn_tot / l_tot : 0.f;
     }
+  } else {
     float* dq = a.dq32 + row * D;
-    if constexpr (GRAD)
 #pragma unroll
-    for (int t = 0; t < C::NDT; t++)
+    for (int t = 0; t < NDT; t++)
 #pragma unroll
       for (int q4 = 0; q4 < 4; q4++) {
         const int m0 = q4 * 8 + h * 4;
@@ -400,7 +450,7 @@ template <int D> static hipError_t launch_bwd_t(const BwdArgs& a, hipStream_t st
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   {
-    const size_t lds = 2 * C::TILE_BYTES + 5 * 64 * 4;
+    const size_t lds = 4 * C::TILE_BYTES + 5 * 64 * 4;
     auto kern = bwd_q_kernel<D, false>;
     if ((e = allow_dyn_lds((const void*)kern, lds, done_lse)) != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb), dim3(256), lds, st, a);
