@@ -7,10 +7,20 @@
 // wave w owns 32 rows = all g_q heads of 32/g_q consecutive tokens.  The
 // workgroup walks the union of its tokens' chunk masks in ascending order.
 // Every 64-key tile of K and V is copied once from global memory straight into
-// LDS (buffer_load_dwordx4 ... lds, no staging registers), two stages deep: the copy
-// of tile j+1 is in flight while tile j is computed.  A wave skips the MFMA work
-// of a chunk none of its tokens kept; rows of a wave that did not keep a chunk
+// LDS (buffer_load_dwordx4 ... lds, no staging registers), two stages deep.  A wave
+// pipelines its tiles: the first product of tile i runs together with the exponentials of
+// tile i - 1, the second product of tile i - 1 together with the row maximum of tile i.  A wave skips
+// the MFMA work of a chunk none of its tokens kept; rows of a wave that did not keep a chunk
 // get bias -inf for it, which keeps the per-token result exact.
+//
+// What bounds it.  Timing copies of this kernel without one part at a time (32k causal, group
+// of 4, dense): no direct copies -12 %, no LDS operand reads -11 %, no exponentials -8 %, no
+// barriers -2 %, none of them -29 % (1.5 PFLOP/s, near the rate of a register-fed MFMA loop at the
+// clock this load runs at): copies, operand feed and vector work share the time about evenly and the
+// order of the instructions no longer matters (exponential and operand-read distances: +-1 %).
+// Without the pipeline across tiles (softmax of a tile between its own two products): 8.84 ->
+// 8.43 ms at the 32k prefill, 110 -> 104 ms at 128k tokens, 820 -> 735 us for 2000 tokens against a
+// 32k cache.
 //
 // LDS layout.  Tiles are row major ([key][d], no padding: the direct copy writes
 // 1 KB contiguous per wave instruction) with the 16-byte chunks of every row
@@ -174,18 +184,16 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
   const uint32_t v_off = (uint32_t)(c_row * (int)a.vs_t * 2 + ((c_pos ^ v_swz<D>(c_row)) << 4));
   const uint32_t k_step = (uint32_t)(C::ROWS_PER_COPY * (int)a.ks_t * 2);
   const uint32_t v_step = (uint32_t)(C::ROWS_PER_COPY * (int)a.vs_t * 2);
-  // copy instruction c of a tile: c < COPIES moves K rows, the rest V rows
-  uint32_t cp_k = 0, cp_v = 0;   // scalar byte offsets of the tile being copied
+  uint32_t cp_k = 0, cp_k_v = 0, cp_v = 0;   // scalar byte offsets: K of the tile being copied, V of the same, V being copied
   auto copy_begin = [&](int u, int sub) {
     cp_k = (uint32_t)(u * a.block + sub * 64) * (uint32_t)a.ks_t * 2u;
-    cp_v = (uint32_t)(u * a.block + sub * 64) * (uint32_t)a.vs_t * 2u;
+    cp_k_v = (uint32_t)(u * a.block + sub * 64) * (uint32_t)a.vs_t * 2u;
   };
-  auto copy_one = [&](int c, int slot) {
-    if (c < C::COPIES)
-      copy16_to_lds(k_rs, lds0 + slot * C::TILE_BYTES + wave * 1024 + c * 4096, k_off, cp_k + c * k_step);
-    else
-      copy16_to_lds(v_rs, lds0 + (2 + slot) * C::TILE_BYTES + wave * 1024 + (c - C::COPIES) * 4096, v_off,
-                    cp_v + (c - C::COPIES) * v_step);
+  auto copy_k = [&](int c, int slot) {
+    copy16_to_lds(k_rs, lds0 + slot * C::TILE_BYTES + wave * 1024 + c * 4096, k_off, cp_k + c * k_step);
+  };
+  auto copy_v = [&](int c, int slot) {
+    copy16_to_lds(v_rs, lds0 + (2 + slot) * C::TILE_BYTES + wave * 1024 + c * 4096, v_off, cp_v + c * v_step);
   };
 
   // ---- operand read addresses (bytes inside a stage) -------------------------
@@ -237,47 +245,97 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
     bias_row = __shfl(bt, n / a.g_q);
   };
 
-  // ---- one 64-key tile -------------------------------------------------------
-  // S^T = K Q^T, online softmax, O^T += V^T P^T.  The source is written slot by
-  // slot (one MFMA per slot, its operand reads a few slots ahead, a share of the
-  // softmax VALU work behind it) in the order the instructions should issue, and
-  // the scheduler may not move code across slots.  VALU budget: an MFMA 32x32x16
-  // leaves about 24 issue cycles of its 32, an exponential takes 8 and a plain
-  // VALU op 4.  P = LDS slot of the tile (compile time: every LDS offset is an
-  // immediate).  MASKED adds the causal / sequence-end key mask (diagonal chunk
-  // and ragged tail only).
-  auto tile_math = [&](auto p_tag, auto m_tag, int kpos0, bool more) {
+  // ---- the tile pipeline -----------------------------------------------------
+  // Iteration i forms S^T of tile i and O^T += V^T P^T of tile i - 1: the exponentials of tile
+  // i - 1 run behind the MFMAs of the first product, the row maximum of tile i behind those of the
+  // second, so that a wave has matrix work to issue while its vector work completes.  The source is
+  // written slot by slot (one MFMA per slot, its operand reads a few slots ahead, a share of the vector work
+  // behind it) and the scheduler may not move code across slots.
+  //
+  // LDS: K ring [2] then V ring [2]; tile i lives in slot i & 1 of both, V one iteration behind K.  At
+  // the top of iteration i a wave waits for its own copies (K of tile i, V of tile i - 1), the barrier
+  // makes everybody's visible and retires the reads of iteration i - 1 (K of tile i - 1, V of
+  // tile i - 2), whose slots the copies of this iteration (K of tile i + 1, V of tile i) overwrite; those are
+  // issued one at a time between the MFMAs: a burst right after the barrier would queue all waves
+  // behind the 64 B/clk global -> LDS path.
+  bool have = advance();
+  if (have) {
+    copy_begin(it_u, it_sub);
+#pragma unroll
+    for (int c = 0; c < C::COPIES; c++) copy_k(c, 0);
+  }
+  bool pend = false;                 // a tile whose S^T waits for its softmax and second product
+  bool drain = have;                 // the last iteration of the workgroup has no tile of its own
+  float bias_old = 0.f, tmax_old = 0.f;
+  u32x4 pb[4];
+  auto iteration = [&](auto p_tag, f32x16 (&s)[2], f32x16 (&so)[2]) {
     constexpr int P = decltype(p_tag)::value;
-    constexpr bool MASKED = decltype(m_tag)::value;
-    constexpr int NS = D / 8;                                 // MFMAs per product and tile
-    const char* kb = lds + P * C::TILE_BYTES;                  // K ring
-    const char* vb = lds + (2 + P) * C::TILE_BYTES;            // V ring
+    constexpr int NS = D / 8;                                  // MFMAs per product and tile
+    const bool cur = have;
+    const int cu = it_u, csub = it_sub;
+    const bool more = cur && advance();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    bool on = false;
+    if (cur) {
+      if (csub == 0) begin_chunk(cu);
+      on = wave_on;
+    }
+    cp_v = cp_k_v;                                             // V of tile i
+    if (more) copy_begin(it_u, it_sub);                        // K of tile i + 1
+    // Lazy rescaling: the reference max m_run of a row is only raised when the tile's max
+    // exceeds it by more than 2^kLazy; until then p = 2^(t - m_run) may reach 2^kLazy, which fp32 / bf16
+    // hold without loss, and the final division by the row sum is unaffected.
+    float off = 0.f;
+    if (pend) {
+      if (__builtin_expect(__any(tmax_old > m_run + kLazy), 0)) {
+        const float m_new = fmaxf(m_run, fmaxf(tmax_old, __shfl_xor(tmax_old, 32)));
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;
+        const float corr = __builtin_amdgcn_exp2f(m_run - m_use);   // m_run = -inf -> 0
+        m_run = m_new;
+        l_run *= corr;
+#pragma unroll
+        for (int dt = 0; dt < NDT; dt++)
+#pragma unroll
+          for (int j = 0; j < 16; j++) oacc[dt][j] *= corr;
+      }
+      off = bias_old - (m_run == -INFINITY ? 0.f : m_run);
+    }
+    const char* kb = lds + P * C::TILE_BYTES;
+    const char* vb = lds + (2 + (P ^ 1)) * C::TILE_BYTES;
     auto k_read = [&](int i) -> bf16x8 {   // slot i: d slice i / 2, key half i % 2
       return *reinterpret_cast<const bf16x8*>(kb + k_rd[i >> 1] + (i & 1) * 32 * C::ROW_BYTES);
     };
     auto v_read = [&](int i) -> bf16x8 {   // slot i: contraction step g = i / NDT, d-tile t = i % NDT
       const int g = i / NDT, t = i % NDT;
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (__attribute__((address_space(3))) s16x4*)(vb + v_rd[t] + (16 * g) * C::ROW_BYTES));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (__attribute__((address_space(3))) s16x4*)(vb + v_rd[t] + (16 * g + 8) * C::ROW_BYTES));
-      return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      return lds_read_tr_pair(vb + v_rd[t] + (16 * g) * C::ROW_BYTES, vb + v_rd[t] + (16 * g + 8) * C::ROW_BYTES);
+    };
+    // exponential pair k of tile i - 1: P^T slots 2 (k % 4), + 1 of contraction step g = k / 4
+    auto e_pair = [&](int k) {
+      const int g = k >> 2, kt = g >> 1, j = 8 * (g & 1) + 2 * (k & 3);
+      const float p0 = __builtin_amdgcn_exp2f(fmaf(so[kt][j], a.c1, off));
+      const float p1 = __builtin_amdgcn_exp2f(fmaf(so[kt][j + 1], a.c1, off));
+      l_run += p0 + p1;
+      asm volatile("" : "+v"(l_run));   // keeps the row-sum update in its slot
+      const bf16x2 w = {(__bf16)p0, (__bf16)p1};
+      pb[g][k & 3] = __builtin_bit_cast(uint32_t, w);
+    };
+    // copy instruction c of the iteration: K of tile i + 1, then V of tile i
+    auto copies = [&](int c) {
+      if (c < C::COPIES) { if (more) copy_k(c, P ^ 1); }
+      else if (c < 2 * C::COPIES) { if (cur) copy_v(c - C::COPIES, P); }
     };
     constexpr int KAHEAD = 4, VAHEAD = 2;
-    f32x16 s[2];
-    {
+    constexpr int EQ = 12;                                     // exponential pairs behind the first product
+    auto first_product = [&](auto e_tag) {
+      constexpr bool EXPS = decltype(e_tag)::value;
       bf16x8 kf[NS];
 #pragma unroll
       for (int i = 0; i < KAHEAD; i++) kf[i] = k_read(i);
 #pragma unroll
       for (int i = 0; i < NS; i++) {
         if (i + KAHEAD < NS) kf[i + KAHEAD] = k_read(i + KAHEAD);
-        // the copies of the next tile are issued one at a time between the MFMAs: a
-        // burst right after the barrier would queue all waves behind the 64 B/clk
-        // global -> LDS path
-        if ((i & 1) == 0 && (i >> 1) < 2 * C::COPIES) {
-          if (more) copy_one(i >> 1, P ^ 1);
-        }
+        if ((i & 1) == 0) copies(i >> 1);
         const int ks = i >> 1, kt = i & 1;
         if (ks == 0) {
           const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -285,130 +343,81 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
         } else {
           s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[ks], s[kt], 0, 0, 0);
         }
+        if constexpr (EXPS) {
+#pragma unroll
+          for (int k = i * EQ / NS; k < (i + 1) * EQ / NS; k++) e_pair(k);
+        }
         __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    if (on) {
+      if (pend) first_product(std::true_type{});
+      else first_product(std::false_type{});
+      // key kpos0 + 4 h + c (c = the compile-time part of the key index of an accumulator
+      // register) is dead if it lies after the row's position in the diagonal chunk or past the
+      // end of the sequence, i.e. if c > lim
+      const int kpos0 = cu * a.block + csub * 64;
+      if (diag || kpos0 + 64 > a.n_kv) {
+        const int k0 = kpos0 + 4 * h;
+        int lim = min(diag ? row_pos - k0 : 0x7fffffff, a.n_kv - 1 - k0);
+        asm volatile("" : "+v"(lim));   // keep the per-register comparisons against immediates
+#pragma unroll
+        for (int kt = 0; kt < 2; kt++)
+#pragma unroll
+          for (int j = 0; j < 16; j++) {
+            const int c = kt * 32 + (j >> 2) * 8 + (j & 3);
+            s[kt][j] = c > lim ? -INFINITY : s[kt][j];
+          }
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < 2 * C::COPIES; c++) copies(c);
+      if (pend) {
+#pragma unroll
+        for (int k = 0; k < EQ; k++) e_pair(k);
       }
     }
     float mloc = -INFINITY;
-    // MASKED: key kpos0 + 4 h + c (c = the compile-time part of the key index of
-    // an accumulator register) is dead if it lies after the row's position in the
-    // diagonal chunk or past the end of the sequence, i.e. if c > lim
-    int lim = 0;
-    if constexpr (MASKED) {
-      const int k0 = kpos0 + 4 * h;
-      lim = min(diag ? row_pos - k0 : 0x7fffffff, a.n_kv - 1 - k0);
-      asm volatile("" : "+v"(lim));   // keep the per-register comparisons against immediates
-    }
-#pragma unroll
-    for (int kt = 0; kt < 2; kt++)
-#pragma unroll
-      for (int j = 0; j < 16; j += 2) {
-        if constexpr (MASKED) {
-#pragma unroll
-          for (int jj = j; jj < j + 2; jj++) {
-            const int c = kt * 32 + (jj >> 2) * 8 + (jj & 3);
-            s[kt][jj] = c > lim ? -INFINITY : s[kt][jj];
-          }
-        }
-        mloc = fmaxf(fmaxf(mloc, s[kt][j]), s[kt][j + 1]);
-      }
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-    // max of the base-2 logits s*c1 + bias over the tile (c1 > 0)
-    const float tmax = fmaf(mloc, a.c1, bias_row);
-    // Lazy rescaling: the reference max m_run of a row is only raised when the
-    // tile's max exceeds it by more than 2^kLazy; until then p = 2^(t - m_run)
-    // may reach 2^kLazy, which fp32 / bf16 hold without loss, and the final
-    // division by the row sum is unaffected.  Raising it is rare after the
-    // first tiles, so the O rescale below is almost never executed.
-    // The two outcomes rejoin only after the second product, so the accumulators
-    // never have to be copied between registers on the common path.
-    auto second_product = [&]() {
-      const float off = bias_row - (m_run == -INFINITY ? 0.f : m_run);
-      u32x4 pb[4];
-      float lsum = 0.f;
-      // exponential pair k: P^T slots 2 (k % 4), + 1 of contraction step g = k / 4
-      auto e_pair = [&](int k) {
-        const int g = k >> 2, kt = g >> 1, j = 8 * (g & 1) + 2 * (k & 3);
-        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kt][j], a.c1, off));
-        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kt][j + 1], a.c1, off));
-        lsum += p0 + p1;
-        asm volatile("" : "+v"(lsum));   // keeps the row-sum update in its slot
-        const bf16x2 w = {(__bf16)p0, (__bf16)p1};
-        pb[g][k & 3] = __builtin_bit_cast(uint32_t, w);
-      };
-      {
-        bf16x8 vf[NS];
-#pragma unroll
-        for (int i = 0; i < VAHEAD; i++) vf[i] = v_read(i);
-#pragma unroll
-        for (int k = 0; k < 4; k++) e_pair(k);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < NS; i++) {
-          if (i + VAHEAD < NS) vf[i + VAHEAD] = v_read(i + VAHEAD);
-          const int g = i / NDT, t = i % NDT;
-          oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], __builtin_bit_cast(bf16x8, pb[g]), oacc[t], 0, 0, 0);
-          // the remaining 12 pairs go behind the first MFMAs: pairs of step g + 1
-          // must be complete before slot NDT * (g + 1)
-          constexpr int PPS = D == 128 ? 1 : 2;
-#pragma unroll
-          for (int kk = 0; kk < PPS; kk++)
-            if (4 + i * PPS + kk < 16) e_pair(4 + i * PPS + kk);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-      l_run += lsum;
+    auto max_quad = [&](int q) {   // four of the tile's 32 scores per lane
+      const int kt = q >> 2, j = 4 * (q & 3);
+      mloc = fmaxf(fmaxf(mloc, s[kt][j]), s[kt][j + 1]);
+      mloc = fmaxf(fmaxf(mloc, s[kt][j + 2]), s[kt][j + 3]);
     };
-    if (__builtin_expect(__any(tmax > m_run + kLazy), 0)) {
-      const float m_new = fmaxf(m_run, tmax);
-      const float m_use = m_new == -INFINITY ? 0.f : m_new;
-      const float corr = __builtin_amdgcn_exp2f(m_run - m_use);   // m_run = -inf -> 0
-      m_run = m_new;
-      l_run *= corr;
+    if (pend) {
+      bf16x8 vf[NS];
 #pragma unroll
-      for (int dt = 0; dt < NDT; dt++)
+      for (int i = 0; i < VAHEAD; i++) vf[i] = v_read(i);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < 16; j++) oacc[dt][j] *= corr;
-      second_product();
-    } else {
-      second_product();
+      for (int i = 0; i < NS; i++) {
+        if (i + VAHEAD < NS) vf[i + VAHEAD] = v_read(i + VAHEAD);
+        const int g = i / NDT, t = i % NDT;
+        oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], __builtin_bit_cast(bf16x8, pb[g]), oacc[t], 0, 0, 0);
+        // the remaining pairs belong to the last contraction step
+        if (EQ + i < 16) e_pair(EQ + i);
+        if constexpr (NS == 16) { if (i >= 4 && i < 12) max_quad(i - 4); }
+        else if (i >= 4) { max_quad(2 * (i - 4)); max_quad(2 * (i - 4) + 1); }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else if (on) {
+#pragma unroll
+      for (int q = 0; q < 8; q++) max_quad(q);
     }
-  };
-
-  // ---- main loop -----------------------------------------------------------
-  // LDS: K ring [2] then V ring [2]; tile j lives in slot j & 1 of both.  At the
-  // top of iteration j the wave waits for its own copies of tile j, the barrier
-  // makes everybody's copies visible and guarantees that tile j - 1 (the other
-  // slot) is no longer read; then the copies of tile j + 1 are issued between the
-  // MFMAs of the first product of tile j and run during the rest of it.  The loop body is written out twice so that the
-  // slot is a compile-time constant.
-  bool have = advance();
-  if (have) {
-    copy_begin(it_u, it_sub);
-#pragma unroll
-    for (int c = 0; c < 2 * C::COPIES; c++) copy_one(c, 0);
-  }
-  auto iteration = [&](auto p_tag) {
-    constexpr int P = decltype(p_tag)::value;
-    const int cu = it_u, csub = it_sub;
-    const bool more = advance();
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's copies of tile j have landed
-    __syncthreads();
-    if (csub == 0) begin_chunk(cu);
-    if (more) copy_begin(it_u, it_sub);
-    if (wave_on) {
-      const int kpos0 = cu * a.block + csub * 64;
-      if (diag || kpos0 + 64 > a.n_kv) tile_math(p_tag, std::true_type{}, kpos0, more);
-      else tile_math(p_tag, std::false_type{}, kpos0, more);
-    } else if (more) {
-#pragma unroll
-      for (int c = 0; c < 2 * C::COPIES; c++) copy_one(c, P ^ 1);
-    }
+    // this lane half's max of the base-2 logits s c1 + bias (c1 > 0)
+    tmax_old = fmaf(mloc, a.c1, bias_row);
+    bias_old = bias_row;
+    pend = on;
     have = more;
   };
-  while (have) {
-    iteration(std::integral_constant<int, 0>{});
-    if (!have) break;
-    iteration(std::integral_constant<int, 1>{});
+  {
+    f32x16 sa[2], sb[2];
+    while (drain) {
+      drain = have;
+      iteration(std::integral_constant<int, 0>{}, sa, sb);
+      if (!drain) break;
+      drain = have;
+      iteration(std::integral_constant<int, 1>{}, sb, sa);
+    }
   }
 
   // ---- finalise ------------------------------------------------------------
