@@ -73,13 +73,16 @@ int make_layout(const dash_params* p, Layout* L, bool routing) {
   L->pexp = (float)(1.0 / ((double)p->alpha - 1.0));
   L->use_mfma = p->dtype == DASH_BF16 && p->n_q > 1;
   const bool decode_mfma = p->dtype == DASH_BF16 && p->n_q == 1;
+  const int pairs = p->batch * p->h_kv;
   int splits = 1;
+  int part_slots = 1;   // room for records per pair: rounded up, so that a workspace made for more pairs holds fewer
   if (decode_mfma) {
-    const int pairs = p->batch * p->h_kv;
     const int target = 512;   // workgroups per launch: two per CU, all resident at once
     splits = target / pairs;
-    if (splits > 64) splits = 64;
-    if (splits > L->t_all) splits = L->t_all;
+    part_slots = (target + pairs - 1) / pairs;
+    const int cap = L->t_all < 64 ? L->t_all : 64;
+    if (splits > cap) splits = cap;
+    if (part_slots > cap) part_slots = cap;
     if (splits < 1) splits = 1;
   }
   L->splits = splits;
@@ -94,10 +97,11 @@ int make_layout(const dash_params* p, Layout* L, bool routing) {
   if (!L->use_mfma && !(p->n_q == 1 && p->causal))
     off += align256((size_t)p->batch * p->h_q * p->n_q * (L->t_c > 0 ? L->t_c : 1) * 4);
   L->off_part = off;
-  if (decode_mfma) off += align256((size_t)p->batch * p->h_kv * splits * g * (p->head_dim + 2) * 4);
+  if (decode_mfma) off += align256((size_t)pairs * part_slots * g * (p->head_dim + 2) * 4);
   L->off_flags = off;
-  if (decode_mfma) off += align256((size_t)p->batch * p->h_kv * splits * 8);
+  if (splits > 1) off += align256((size_t)pairs * splits * 8);   // a single split writes no flag
   L->total_min = off > 0 ? off : 256;
+  if (decode_mfma && splits == 1) off += align256(512 * 8);       // see part_slots
   L->off_dec_scores = off;
   L->dec_scores = decode_scores_apart(*p, *L);
   if (L->dec_scores) off += align256((size_t)p->batch * p->h_q * decode_scores_ld(*L) * 4);
@@ -215,7 +219,7 @@ int dash_stage1_route(const dash_params* p, const void* q, const float* kbar, ui
   int rc = make_layout(p, &L);
   if (rc != DASH_OK) return rc;
   if (!q || (!kbar && L.t_c > 0)) return DASH_EINVAL;
-  if ((rc = check_ws(L.total, workspace, workspace_bytes)) != DASH_OK) return rc;
+  if ((rc = check_ws(L.total_min, workspace, workspace_bytes)) != DASH_OK) return rc;
   return run_stage1(p, L, q, kbar, mask, blk_cnt, blk_idx, blk_bias, tau, (char*)workspace,
                     (hipStream_t)stream);
 }
@@ -227,7 +231,7 @@ int dash_stage2_attend(const dash_params* p, const void* q, const void* k, const
   int rc = make_layout(p, &L);
   if (rc != DASH_OK) return rc;
   if (!q || !k || !v || !o) return DASH_EINVAL;
-  if ((rc = check_ws(L.total, workspace, workspace_bytes)) != DASH_OK) return rc;
+  if ((rc = check_ws(L.total_min, workspace, workspace_bytes)) != DASH_OK) return rc;
   return run_stage2(p, L, q, k, v, o, mask, blk_bias, (char*)workspace, false, (hipStream_t)stream);
 }
 
@@ -239,7 +243,7 @@ int dash_attn_prefill(const dash_params* p, const void* q, const void* k, const 
   int rc = make_layout(p, &L);
   if (rc != DASH_OK) return rc;
   if (!q || !k || !v || !o || (!kbar && L.t_c > 0)) return DASH_EINVAL;
-  if ((rc = check_ws(L.total, workspace, workspace_bytes)) != DASH_OK) return rc;
+  if ((rc = check_ws(L.total_min, workspace, workspace_bytes)) != DASH_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   if (launch_kbar_compress(*p, L, k, kbar, 0, L.t_c, st) != hipSuccess) return DASH_ELAUNCH;
   rc = run_stage1(p, L, q, kbar, mask, blk_cnt, blk_idx, blk_bias, tau, (char*)workspace, st);
@@ -250,15 +254,15 @@ int dash_attn_prefill(const dash_params* p, const void* q, const void* k, const 
 static int decode_impl(const dash_params* p, const void* q, const void* k_cache, const void* v_cache,
                        float* kbar_cache, const int32_t* seq_lens, bool update_cache, void* o,
                        uint32_t* mask, int32_t* blk_cnt, int32_t* blk_idx, float* blk_bias, float* tau,
-                       void* workspace, size_t workspace_bytes, void* stream, bool built_in = false) {
+                       void* workspace, size_t workspace_bytes, void* stream) {
   Layout L;
   int rc = make_layout(p, &L);
   if (rc != DASH_OK) return rc;
   if (p->n_q != 1 || !p->causal) return DASH_EINVAL;
   if (!q || !k_cache || !v_cache || (!kbar_cache && L.t_c > 0) || !o) return DASH_EINVAL;
   if (seq_lens && p->dtype != DASH_BF16) return DASH_EUNSUPPORTED;
-  // the built-in scratch may lack the room for score rows of their own
-  if ((rc = check_ws(built_in ? L.total_min : L.total, workspace, workspace_bytes)) != DASH_OK) return rc;
+  // a workspace made for a longer cache may lack the room for score rows of their own
+  if ((rc = check_ws(L.total_min, workspace, workspace_bytes)) != DASH_OK) return rc;
   L.seq_lens = seq_lens;
   hipStream_t st = (hipStream_t)stream;
   if (decode_route_applicable(*p, L, workspace_bytes)) {
@@ -295,7 +299,7 @@ int dash_attn_decode_static(const dash_params* p, const void* q, const void* k_c
   void* ws = nullptr;
   if ((rc = static_scratch(&ws)) != DASH_OK) return rc;
   return decode_impl(p, q, k_cache, v_cache, kbar_cache, nullptr, true, o, mask, blk_cnt, blk_idx,
-                     blk_bias, tau, ws, kStaticScratchBytes, stream, true);
+                     blk_bias, tau, ws, kStaticScratchBytes, stream);
 }
 
 int dash_attn_decode_ragged(const dash_params* p, const void* q, const void* k_cache,
@@ -314,7 +318,7 @@ int dense_attn(const dash_params* p, const void* q, const void* k, const void* v
   int rc = make_layout(p, &L, false);
   if (rc != DASH_OK) return rc;
   if (!q || !k || !v || !o) return DASH_EINVAL;
-  if ((rc = check_ws(L.total, workspace, workspace_bytes)) != DASH_OK) return rc;
+  if ((rc = check_ws(L.total_min, workspace, workspace_bytes)) != DASH_OK) return rc;
   return run_stage2(p, L, q, k, v, o, nullptr, nullptr, (char*)workspace, true, (hipStream_t)stream);
 }
 

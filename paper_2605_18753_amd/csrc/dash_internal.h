@@ -26,7 +26,7 @@ struct Layout {
   // workspace offsets in bytes (256-aligned); 0-sized regions share offsets
   size_t off_ksplit, off_mask, off_bias, off_scores, off_part, off_flags, off_dec_scores, total;
   bool dec_scores;     // decode: the workspace has room for score rows of a launch of their own
-  size_t total_min;    // decode: without that room (total otherwise)
+  size_t total_min;    // without that room: what a call has to have
 };
 
 // Validates p and fills L.  Returns a dash_status.  routing = false skips the

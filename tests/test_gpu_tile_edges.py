@@ -1,0 +1,118 @@
+"""GPU parity at the sizes where the tilings change: the ranges of the decode step's kernels, the
+128-key tiles and the cut row ranges of the backward pass, the 16-row tiles of the fp32 kernels.
+Oracle and tolerances are those of parity_util and test_gpu_backward."""
+import pytest
+import torch
+
+import parity_util as U
+import test_gpu_backward as TB
+from paper_2605_18753_amd import binding as B
+from paper_2605_18753_amd.inputs import Workload, make_inputs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+# One launch scores up to 640 chunks (320 for groups of 8 and 16) in the attention's workgroups when
+# a pair has several splits; beyond that the scores have a launch of their own.
+DECODE = [
+    # name, batch, h_q, h_kv, n_kv, d, block, extra
+    ("one_key", 2, 4, 2, 1, 128, 64, {}),
+    ("own_chunk_only", 1, 8, 1, 64, 64, 64, {}),
+    ("one_candidate", 1, 2, 2, 65, 128, 64, {}),
+    ("16_candidates_and_one", 1, 8, 2, 17 * 64 + 1, 128, 64, {}),
+    ("65_candidates_g1", 2, 2, 2, 65 * 64 + 33, 64, 64, {}),
+    ("640_chunks_in_place", 1, 4, 1, 640 * 64 + 5, 64, 64, {"gamma": 1.5}),
+    ("641_chunks_apart", 1, 4, 1, 641 * 64 + 5, 64, 64, {"gamma": 1.5}),
+    ("g16_320_chunks_in_place", 1, 16, 1, 320 * 64 + 63, 128, 64, {"gamma": 2.0}),
+    ("g8_321_chunks_apart", 1, 8, 1, 321 * 64 + 1, 128, 64, {"gamma": 2.0}),
+    ("g16_apart_d64_b128_alpha3", 1, 16, 1, 400 * 128, 64, 128, {"alpha": 3.0}),
+    ("2047_candidates_g2_alpha2", 1, 2, 1, 131072, 64, 64, {"alpha": 2.0, "gamma": 1.5}),
+    ("257_pairs_one_split", 257, 1, 1, 700, 64, 64, {}),
+    ("171_pairs_alpha125", 57, 12, 3, 1500, 64, 64, {"alpha": 1.25, "window": 1}),
+    ("alpha17_window8", 1, 4, 2, 3000, 128, 128, {"alpha": 1.7, "window": 8}),
+]
+
+
+@pytest.mark.parametrize("case", DECODE, ids=[c[0] for c in DECODE])
+def test_decode_step(case):
+    name, batch, h_q, h_kv, n_kv, d, block, extra = case
+    w = Workload("edge_" + name, batch, h_q, h_kv, 1, n_kv, d, block, offset_sigma=0.7, seed=41, **extra)
+    q, k, v = make_inputs(w, DEV)
+    run = U.run_decode(w, q, k, v)
+    heads = sorted({(b, r) for b in (0, batch // 2, batch - 1) for r in (0, h_kv - 1)})
+    U.check_against_oracle(w, q, k, v, run, rows=[(b, r, 0) for b, r in heads])
+
+
+@pytest.mark.parametrize("h_q,n_kv", [(16, 700 * 64 + 9), (4, 2000 * 64)])
+def test_decode_without_room_for_score_rows(h_q, n_kv):
+    """A workspace sized for a cache that keeps no score rows serves one that would: the step then
+    routes in a launch of its own."""
+    w = Workload("edge_small_ws", 1, h_q, 1, 1, n_kv, 64, 64, offset_sigma=0.7, gamma=1.5, seed=43)
+    q, k, v = make_inputs(w, DEV)
+    o = torch.full_like(q, float("nan"))
+    p = B.make_params(q, k, v, o, w.block, w.alpha, w.gamma, w.sigma, True)
+    kbar = torch.empty(B.kbar_shape(p), dtype=torch.float32, device=DEV)
+    B.dash_kbar_compress(p, k, kbar)
+    lists = B.Lists.allocate(p, DEV)
+    ws = B.alloc_workspace(p, DEV)
+    score_rows = h_q * ((n_kv // 64 + 15) // 16 * 16) * 4
+    B.dash_attn_decode(p, q, k, v, kbar, o, lists, ws[:ws.numel() - (score_rows + 255) // 256 * 256])
+    torch.cuda.synchronize()
+    U.check_against_oracle(w, q, k, v, U.HipRun(o, kbar, lists, p))
+
+
+def test_ragged_decode_replays_with_other_lengths():
+    """A captured step keeps the number its split flags carry: every replay, with other lengths
+    (other numbers of splits) each time, has to give what an uncaptured step gives."""
+    w = Workload("edge_graph", 6, 8, 2, 1, 6000, 128, 64, offset_sigma=0.7, seed=44)
+    q, k, v = make_inputs(w, DEV)
+    o, want = torch.empty_like(q), torch.empty_like(q)
+    p = B.make_params(q, k, v, o, w.block, w.alpha, w.gamma, w.sigma, True)
+    kbar = torch.empty(B.kbar_shape(p), dtype=torch.float32, device=DEV)
+    B.dash_kbar_compress(p, k, kbar)
+    ws, ws2 = B.alloc_workspace(p, DEV), B.alloc_workspace(p, DEV)
+    lens = torch.full((6,), 6000, dtype=torch.int32, device=DEV)
+    step = lambda out, scratch: B.dash_attn_decode_ragged(p, q, k, v, kbar, lens, out, B.Lists(), scratch, update_cache=False)
+    step(o, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(o, ws)
+    for i in range(6):
+        lens.copy_(torch.tensor([6000, 1 + 900 * i, 65 + i, 64 * (i + 1), 3000 - i, 5999], dtype=torch.int32))
+        o.fill_(float("nan"))
+        graph.replay()
+        step(want, ws2)
+        torch.cuda.synchronize()
+        assert torch.equal(o, want), i
+
+
+# 128-key tiles (the last one of 1, 64 and 65 keys), row ranges cut into parts, 16-row tiles of
+# the fp32 kernels with ragged ends
+BACKWARD = [
+    ("b_129", 1, 4, 2, 129, 128, 64, {"offset_sigma": 0.8}),
+    ("b_192_mha", 2, 2, 2, 192, 64, 64, {"offset_sigma": 0.8}),
+    ("b_193_b128", 1, 8, 1, 193, 128, 128, {"offset_sigma": 0.8}),
+    ("b_parts_g16_d64", 1, 16, 1, 1037, 64, 64, {"offset_sigma": 0.8, "gamma": 2.0}),
+    ("b_parts_noncausal_b128", 1, 4, 1, 1152, 128, 128, {"offset_sigma": 0.8, "causal": False}),
+    ("b_window3_alpha3_g2", 1, 2, 1, 831, 64, 64, {"offset_sigma": 0.8, "alpha": 3.0, "window": 3}),
+    ("f_17", 1, 2, 1, 17, 64, 64, {"dtype": "fp32"}),
+    ("f_g16_467_d128", 1, 16, 1, 467, 128, 64, {"dtype": "fp32", "offset_sigma": 0.8}),
+    ("f_g8_b128_331", 1, 8, 1, 331, 128, 128, {"dtype": "fp32", "offset_sigma": 0.8}),
+]
+
+
+@pytest.mark.parametrize("case", BACKWARD, ids=[c[0] for c in BACKWARD])
+def test_backward(case):
+    TB.test_backward_matches_the_oracle(case)
+
+
+# one, two and three 64-key tiles, waves without rows, a group of 16 whose waves skip chunks
+@pytest.mark.parametrize("h_q,h_kv,n,d,block,extra", [
+    (4, 1, 65, 128, 64, {}), (16, 1, 129, 64, 64, {"gamma": 3.0}), (16, 1, 577, 128, 64, {"gamma": 4.0, "offset_sigma": 1.0}),
+    (1, 1, 1025, 128, 128, {"gamma": 4.0, "offset_sigma": 1.0}), (2, 1, 999, 64, 64, {"window": 1, "sigma": 0.1})])
+def test_prefill(h_q, h_kv, n, d, block, extra):
+    w = Workload("edge_prefill", 1, h_q, h_kv, n, n, d, block, seed=45, **extra)
+    q, k, v = make_inputs(w, DEV)
+    U.check_against_oracle(w, q, k, v, U.run_prefill(w, q, k, v))
