@@ -934,11 +934,21 @@ hipError_t launch_s1_route(const dash_params& p, const Layout& L, const void* q,
     };
     int lds_from = 0;   // tokens from here on go to the LDS-row kernel
     if (mfma) {
+      // A range joins the next one where that costs its launch no further round of workgroups (256 at once,
+      // one per CU): the shorter rows then take the kernel of the longer ones.  65 tokens against a 32k cache
+      // (8 kv-heads, group of 4: 64 tokens with 512 candidates, one with 513) 74 -> 40 us; 300 against
+      // 16k 55 -> 33 us; 1000 against 32k 116 -> 81 us.
+      auto rounds = [&](int t0, int t1, int rows) {
+        const int tokt = rows / L.g_q;
+        return ((int64_t)((t1 - t0 + tokt - 1) / tokt) * p.h_kv * p.batch + 255) / 256;
+      };
       const int t256 = first_beyond(256);
-      if (t256 > 0 && t256 < p.n_q) bounds[nb++] = t256;
       const int t512 = first_beyond(512);
       const int t1536 = p.head_dim == 128 ? first_beyond(1536) : t512;
-      if (t512 > t256 && t512 < p.n_q) bounds[nb++] = t512;
+      if (t256 > 0 && t256 < p.n_q && rounds(0, t512, 128) > rounds(t256, t512, 128)) bounds[nb++] = t256;
+      if (t512 > t256 && t512 < p.n_q &&
+          (p.head_dim != 128 || rounds(bounds[nb - 1], t1536, 64) > rounds(t512, t1536, 64)))
+        bounds[nb++] = t512;
       if (t1536 > t512 && t1536 < p.n_q) bounds[nb++] = t1536;
       lds_from = t1536;
     }

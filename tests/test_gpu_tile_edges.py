@@ -127,13 +127,17 @@ def test_prefill(h_q, h_kv, n, d, block, extra):
     ("g1_window", 2, 2, 130, 64 * 70 + 130, 64, 64, {"window": 2}),
     ("g16_b128", 16, 1, 9, 128 * 40 + 64 + 9, 128, 128, {"gamma": 2.0}),
     ("g8_sparse", 8, 1, 33, 64 * 301 + 33, 64, 64, {"gamma": 4.0, "offset_sigma": 1.0}),
-    ("g2_nine_chunks", 4, 2, 63, 64 * 8 + 63, 128, 64, {"alpha": 2.0}),
+    ("g2_seventeen_chunks", 4, 2, 63, 64 * 16 + 63, 128, 64, {"alpha": 2.0}),
+    # rows of 255 .. 257, 511 .. 513 and 255 .. 513 candidates: the routing kernels' ranges, in one launch
+    ("rows_of_256", 4, 1, 130, 64 * 255 + 130, 64, 64, {"gamma": 2.0}),
+    ("rows_of_512", 8, 1, 130, 64 * 511 + 130, 128, 64, {"gamma": 2.0}),
+    ("rows_of_512_d64", 2, 1, 130, 64 * 511 + 130, 64, 64, {"gamma": 1.5}),
     ("noncausal", 4, 2, 1024, 1024, 128, 64, {"causal": False})])
 def test_prefill_cut_chunk_lists(name, h_q, h_kv, n_q, n_kv, d, block, extra):
     w = Workload("edge_cut_" + name, 1, h_q, h_kv, n_q, n_kv, d, block, seed=46, **extra)
     q, k, v = make_inputs(w, DEV)
     run = U.run_prefill(w, q, k, v)
-    rows = None if n_q < 200 else U.sample_rows(w, 60)
+    rows = None if n_q * n_kv < 1 << 20 else U.sample_rows(w, 60)
     U.check_against_oracle(w, q, k, v, run, rows=rows)
     # without room for the parts' records: uncut, the same up to the rounding of the results
     o = torch.full_like(q, float("nan"))
