@@ -16,11 +16,11 @@ namespace dash {
 template <typename T>
 __global__ __launch_bounds__(256) void kbar_compress_kernel(
     const T* __restrict__ k, float* __restrict__ kbar, int block,
-    int d, int t_c, int first_chunk, int64_t ks_b, int64_t ks_h, int64_t ks_t) {
+    int d, int t_c, int first_chunk, int64_t ks_b, int64_t ks_h, int64_t ks_t, uint16_t* __restrict__ ksplit) {
   __shared__ double sm[2048];
   const int c = first_chunk + blockIdx.x;
   const int r = blockIdx.y, b = blockIdx.z, h_kv = gridDim.y;
-  kbar_block_mean<T>(k, kbar, sm, block, d, t_c, c, r, b, h_kv, ks_b, ks_h, ks_t);
+  kbar_block_mean<T>(k, kbar, sm, block, d, t_c, c, r, b, h_kv, ks_b, ks_h, ks_t, ksplit);
 }
 
 
@@ -232,17 +232,17 @@ hipError_t launch_kbar_summarize_bwd(const dash_params& p, const Layout& L, cons
 }
 
 hipError_t launch_kbar_compress(const dash_params& p, const Layout& L, const void* k, float* kbar,
-                                int first_chunk, int n_chunks, hipStream_t st) {
+                                int first_chunk, int n_chunks, hipStream_t st, uint16_t* ksplit) {
   if (n_chunks <= 0) return hipSuccess;
   dim3 grid(n_chunks, p.h_kv, p.batch), blk(256);
   if (p.dtype == DASH_BF16)
     hipLaunchKernelGGL(kbar_compress_kernel<uint16_t>, grid, blk, 0, st, (const uint16_t*)k, kbar,
                        p.block_size, p.head_dim, L.t_c, first_chunk, p.k_stride[0],
-                       p.k_stride[1], p.k_stride[2]);
+                       p.k_stride[1], p.k_stride[2], ksplit);
   else
     hipLaunchKernelGGL(kbar_compress_kernel<float>, grid, blk, 0, st, (const float*)k, kbar,
                        p.block_size, p.head_dim, L.t_c, first_chunk, p.k_stride[0], p.k_stride[1],
-                       p.k_stride[2]);
+                       p.k_stride[2], (uint16_t*)nullptr);
   return hipGetLastError();
 }
 

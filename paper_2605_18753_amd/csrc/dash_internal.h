@@ -60,16 +60,16 @@ struct S1Out {
 };
 
 hipError_t launch_kbar_compress(const dash_params& p, const Layout& L, const void* k, float* kbar,
-                                int first_chunk, int n_chunks, hipStream_t st);
+                                int first_chunk, int n_chunks, hipStream_t st, uint16_t* ksplit = nullptr);
 hipError_t launch_kbar_summarize(const dash_params& p, const Layout& L, const void* k, const float* qbar,
                                  const int64_t* qs, float* kbar, int first_chunk, int n_chunks,
                                  hipStream_t st);
 hipError_t launch_s1_scores_f32(const dash_params& p, const Layout& L, const void* q,
                                 const float* kbar, float* scores, hipStream_t st);
-// ksplit != NULL: bf16 MFMA scorer (the split of kbar is written to ksplit first);
+// ksplit != NULL: bf16 MFMA scorer (the split of kbar is written to ksplit first, unless split_done);
 // otherwise the scores are read from `scores` (written by launch_s1_scores_f32).
 hipError_t launch_s1_route(const dash_params& p, const Layout& L, const void* q, const float* kbar,
-                           uint16_t* ksplit, const float* scores, const S1Out& out, hipStream_t st);
+                           uint16_t* ksplit, const float* scores, const S1Out& out, hipStream_t st, bool split_done = false);
 hipError_t launch_s1_decode(const dash_params& p, const Layout& L, const void* q, const float* kbar,
                             const S1Out& out, const void* k_upd, float* kbar_upd, hipStream_t st);
 hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, const void* k,

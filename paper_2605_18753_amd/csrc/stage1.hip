@@ -830,8 +830,7 @@ static hipError_t launch_route_k(const S1Args& a, dim3 grid, size_t lds, hipStre
   return hipGetLastError();
 }
 
-// Exact 3-way bf16 split of the fp32 summaries: x = hi + mid + lo with every piece
-// obtained by truncation (same sign, no rounding), laid out [chunk][3][d].
+// the split of all summaries (store_split, compress_body.h)
 __global__ __launch_bounds__(256) void ksplit_kernel(const float* __restrict__ kbar,
                                                      uint16_t* __restrict__ ksplit, int64_t n_rows,
                                                      int d) {
@@ -839,15 +838,7 @@ __global__ __launch_bounds__(256) void ksplit_kernel(const float* __restrict__ k
   if (i >= n_rows * d) return;
   const int64_t row = i / d;
   const int col = (int)(i % d);
-  const float x = kbar[i];
-  const uint32_t hi = __float_as_uint(x) & 0xffff0000u;
-  const float r1 = x - __uint_as_float(hi);
-  const uint32_t mid = __float_as_uint(r1) & 0xffff0000u;
-  const float r2 = r1 - __uint_as_float(mid);
-  uint16_t* o = ksplit + row * 3 * d + col;
-  o[0] = (uint16_t)(hi >> 16);
-  o[d] = (uint16_t)(mid >> 16);
-  o[2 * d] = (uint16_t)(__float_as_uint(r2) >> 16);
+  store_split(ksplit + row * 3 * d + col, d, kbar[i]);
 }
 
 static S1Args make_s1_args(const dash_params& p, const Layout& L, const void* q, const float* kbar, const S1Out& out) {
@@ -902,8 +893,8 @@ hipError_t launch_s1_decode(const dash_params& p, const Layout& L, const void* q
 }
 
 hipError_t launch_s1_route(const dash_params& p, const Layout& L, const void* q, const float* kbar,
-                           uint16_t* ksplit, const float* scores, const S1Out& out, hipStream_t st) {
-  if (ksplit != nullptr && L.t_c > 0) {
+                           uint16_t* ksplit, const float* scores, const S1Out& out, hipStream_t st, bool split_done) {
+  if (ksplit != nullptr && L.t_c > 0 && !split_done) {
     const int64_t n_rows = (int64_t)p.batch * p.h_kv * L.t_c;
     const int64_t n = n_rows * p.head_dim;
     hipLaunchKernelGGL(ksplit_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, kbar,
