@@ -113,14 +113,8 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
   for (int i = tid; i < 5 * 64; i += 256) wgmask[i] = 0u;
   __syncthreads();
   if (wave_ok)
-    for (int wi = lane; wi < a.words; wi += 64) {
-      uint32_t m = 0u;
-      for (int t = 0; t < tokw; t++)
-        if (tok_w0 + t < a.n_q)
-          m |= a.mask[(((int64_t)b * a.h_kv + r) * a.n_q + tok_w0 + t) * a.words + wi];
-      wvmask[wave * 64 + wi] = m;
-      if (m) atomicOr(&wgmask[wi], m);
-    }
+    or_mask_rows(a.mask + (((int64_t)b * a.h_kv + r) * a.n_q + tok_w0) * a.words, min(tokw, a.n_q - tok_w0) * a.words,
+                 a.words, wvmask + wave * 64, wgmask, lane);
   __syncthreads();
   // tell the key side which chunks this wave's 32-row tile attends
   if constexpr (GRAD)

@@ -77,4 +77,24 @@ __device__ __forceinline__ float row16_sum(float v) { return row16_reduce(v, OpA
 
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63u; }
 
+// One wave: ORs the mask rows of consecutive tokens (n = tokens * words consecutive words) into
+// own[words] and own into all[words], both in LDS and zeroed by an earlier barrier.  Eight loads are in
+// flight at a time: one token after the other, each load waited for, took 32 round trips to memory at 32
+// tokens per wave, before the first tile of a workgroup could be copied.
+__device__ __forceinline__ void or_mask_rows(const uint32_t* rows, int n, int words, uint32_t* own, uint32_t* all, int lane) {
+  for (int i0 = lane; i0 - lane < n; i0 += 8 * 64) {
+    uint32_t w[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) w[k] = i0 + 64 * k < n ? rows[i0 + 64 * k] : 0u;
+#pragma unroll
+    for (int k = 0; k < 8; k++)
+      if (w[k]) atomicOr(&own[(i0 + 64 * k) % words], w[k]);
+  }
+  asm volatile("" ::: "memory");              // a wave's LDS operations complete in order
+  for (int wi = lane; wi < words; wi += 64) {
+    const uint32_t m = own[wi];
+    if (m) atomicOr(&all[wi], m);
+  }
+}
+
 }  // namespace dash
