@@ -60,7 +60,7 @@ typedef enum dash_status {
   DASH_OK = 0,
   DASH_EINVAL = -1,       /* NULL pointer, non-positive size, h_q % h_kv != 0, alpha <= 1, ...   */
   DASH_EUNSUPPORTED = -2, /* a combination this build has no kernel for (see dash_params)         */
-  DASH_EWORKSPACE = -3,   /* workspace NULL / misaligned / smaller than dash_attn_workspace_bytes */
+  DASH_EWORKSPACE = -3,   /* workspace NULL / misaligned / smaller than the call needs (dash_attn_workspace_bytes suffices) */
   DASH_ELAUNCH = -4       /* the HIP runtime reported an error at launch                          */
 } dash_status;
 
@@ -102,7 +102,10 @@ int32_t dash_mask_words(const dash_params* p);
  * computation only).  The workspace must be 256-byte aligned.  One query serves every
  * call, dense_attn included, so it accepts what any of them accepts: a non-causal n_kv
  * that is not a multiple of block_size gets a size here and DASH_EINVAL from the
- * routing calls (a tail chunk has no summary), which dense_attn does not need. */
+ * routing calls (a tail chunk has no summary), which dense_attn does not need.
+ * The size includes room that only speeds some calls up (score rows of long decode steps, records
+ * of a prefill whose chunk lists are cut into parts); a call that has the rest of it but not that
+ * room runs without, so a workspace made for the largest call serves the smaller ones. */
 int dash_attn_workspace_bytes(const dash_params* p, size_t* out_bytes);
 
 /* Stage 0 (Eq. 3 at zero summary query = uniform mean; Alg. 1).
@@ -191,7 +194,7 @@ int dash_attn_decode(const dash_params* p, const void* q, const void* k_cache,
  * the same step with the same kernels and the same results, except that the scratch
  * (attended-chunk lists when not asked for, split-KV partial results)
  * lives in an 8 MiB array inside the library, one per GPU, held until the process ends.
- * The call allocates nothing.  DASH_EWORKSPACE if dash_attn_workspace_bytes(p) exceeds
+ * The call allocates nothing.  DASH_EWORKSPACE if lists and partial results exceed
  * 8 MiB (the 128k-token decode step of 16 sequences x 8 kv-heads needs 2.1 MiB).
  * Every call on a GPU uses that GPU's one array: calls that overlap on one GPU (different
  * streams or threads) race; nothing in it has to survive from one call to the next. */
