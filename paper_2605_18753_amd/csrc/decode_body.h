@@ -223,9 +223,11 @@ __global__ __launch_bounds__(256, 2) void s2_decode_kernel(DecArgs a) {
     r = pair % s.h_kv; b = pair / s.h_kv;
     split = blockIdx.x / pairs; ns = a.splits; rec0 = pair * ns; len = s.n_kv;
   } else {
-    // per-sequence lengths: sequence i gets 1 + floor(extra n_i / sum n) of the splits * batch
-    // slots of its kv-head, n_i = its chunks (at most 64, the flags one wave reads)
-    const int slots = a.splits * a.batch, extra = slots - a.batch;
+    // per-sequence lengths: half of the splits * batch slots of a kv-head are dealt evenly (the kept
+    // chunks grow more slowly than the length), the others by length: sequence i gets
+    // half + floor(extra N_{i+1} / N) - floor(extra N_i / N), N_i = the chunks of the sequences before it (at most
+    // 64, the flags one wave reads), so that no slot is left over
+    const int slots = a.splits * a.batch, half = max(a.splits >> 1, 1), extra = slots - half * a.batch;
     r = blockIdx.x % s.h_kv;
     const int slot = blockIdx.x / s.h_kv;
     int tot = 0;
@@ -237,14 +239,20 @@ __global__ __launch_bounds__(256, 2) void s2_decode_kernel(DecArgs a) {
       tot += t;
     }
     b = -1; split = 0; ns = 1;
-    int first = 0, base = 0;
+    int first = 0, base = 0, n_before = 0;
     for (int i0 = 0; i0 < a.batch && b < 0; i0 += 64) {
       const int i = i0 + lane;
-      int cnt = 0;
-      if (i < a.batch) {
-        const int nc = (min(max(s.seq_lens[i], 1), s.n_kv) - 1) / s.block + 1;
-        cnt = min(min(1 + (int)((int64_t)extra * nc / tot), 64), nc);
+      const int nc = i < a.batch ? (min(max(s.seq_lens[i], 1), s.n_kv) - 1) / s.block + 1 : 0;
+      int upto = nc;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(upto, o);
+        if (lane >= o) upto += t;
       }
+      upto += n_before;
+      n_before = __builtin_amdgcn_readlane(upto, 63);
+      const int share = half + (int)((int64_t)extra * upto / tot) - (int)((int64_t)extra * (upto - nc) / tot);
+      const int cnt = i < a.batch ? min(min(share, 64), nc) : 0;
       int incl = cnt;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {

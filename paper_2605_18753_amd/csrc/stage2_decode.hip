@@ -60,7 +60,7 @@ static int share_cap(const dash_params& p, const Layout& L) {
   if (!L.seq_lens) {
     cap = (L.t_all + L.splits - 1) / L.splits + 2;      // a share may start and end inside a chunk
   } else {
-    const int64_t extra = (int64_t)(L.splits - 1) * p.batch;
+    const int64_t extra = (int64_t)(L.splits - (L.splits >> 1)) * p.batch;   // splits > 1
     cap = (int)(((int64_t)p.batch * L.t_all + extra - 1) / extra) + 3;
     if (cap < (L.t_all + 63) / 64 + 2) cap = (L.t_all + 63) / 64 + 2;
   }
