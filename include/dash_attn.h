@@ -103,9 +103,8 @@ int32_t dash_mask_words(const dash_params* p);
  * call, dense_attn included, so it accepts what any of them accepts: a non-causal n_kv
  * that is not a multiple of block_size gets a size here and DASH_EINVAL from the
  * routing calls (a tail chunk has no summary), which dense_attn does not need.
- * The size includes room that only speeds some calls up (score rows of long decode steps, records
- * of a prefill whose chunk lists are cut into parts); a call that has the rest of it but not that
- * room runs without, so a workspace made for the largest call serves the smaller ones. */
+ * A workspace made for the largest call serves the smaller ones: a decode step whose size includes
+ * score rows that the workspace has no room for runs without them. */
 int dash_attn_workspace_bytes(const dash_params* p, size_t* out_bytes);
 
 /* Stage 0 (Eq. 3 at zero summary query = uniform mean; Alg. 1).

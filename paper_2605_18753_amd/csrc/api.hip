@@ -100,14 +100,16 @@ int make_layout(const dash_params* p, Layout* L, bool routing) {
   if (decode_mfma) off += align256((size_t)pairs * part_slots * g * (p->head_dim + 2) * 4);
   L->off_flags = off;
   if (splits > 1) off += align256((size_t)pairs * splits * 8);   // a single split writes no flag
+  // room for the parts' records of a prefill: the same for every call, so that a workspace made for a
+  // larger call holds a smaller one that is cut into more parts
+  L->s2_parts = s2_parts(*p, *L);
+  L->off_s2_part = off;
+  if (L->use_mfma) off += align256(s2_part_room(*p));
   L->total_min = off > 0 ? off : 256;
   if (decode_mfma && splits == 1) off += align256(512 * 8);       // see part_slots
   L->off_dec_scores = off;
   L->dec_scores = decode_scores_apart(*p, *L);
   if (L->dec_scores) off += align256((size_t)p->batch * p->h_q * decode_scores_ld(*L) * 4);
-  L->s2_parts = s2_parts(*p, *L);
-  L->off_s2_part = off;
-  if (L->s2_parts > 1) off += align256(s2_part_bytes(*p, *L));
   L->total = off > 0 ? off : 256;
   if (p->dtype == DASH_BF16) {
     // the bf16 kernels address one (batch, kv-head) slice of every tensor with 32-bit byte
@@ -151,14 +153,14 @@ static int run_stage1(const dash_params* p, const Layout& L, const void* q, cons
 
 static int run_stage2(const dash_params* p, const Layout& L, const void* q, const void* k,
                       const void* v, void* o, const uint32_t* mask, const float* bias, char* ws,
-                      size_t ws_bytes, bool dense, hipStream_t st) {
+                      bool dense, hipStream_t st) {
   const uint32_t* m = mask ? mask : reinterpret_cast<const uint32_t*>(ws + L.off_mask);
   const float* bb = bias ? bias : reinterpret_cast<const float*>(ws + L.off_bias);
   hipError_t e;
   if (p->dtype == DASH_F32) e = launch_s2_f32(*p, L, q, k, v, o, m, bb, dense, st);
   else if (p->n_q == 1)
     e = launch_decode_s2(*p, L, q, k, v, o, m, bb, ws, dense, st);
-  else e = launch_s2_mfma(*p, L, q, k, v, o, m, bb, ws_bytes >= L.total ? ws + L.off_s2_part : nullptr, dense, st);
+  else e = launch_s2_mfma(*p, L, q, k, v, o, m, bb, ws + L.off_s2_part, dense, st);
   return e == hipSuccess ? DASH_OK : DASH_ELAUNCH;
 }
 
@@ -236,7 +238,7 @@ int dash_stage2_attend(const dash_params* p, const void* q, const void* k, const
   if (rc != DASH_OK) return rc;
   if (!q || !k || !v || !o) return DASH_EINVAL;
   if ((rc = check_ws(L.total_min, workspace, workspace_bytes)) != DASH_OK) return rc;
-  return run_stage2(p, L, q, k, v, o, mask, blk_bias, (char*)workspace, workspace_bytes, false, (hipStream_t)stream);
+  return run_stage2(p, L, q, k, v, o, mask, blk_bias, (char*)workspace, false, (hipStream_t)stream);
 }
 
 int dash_attn_prefill(const dash_params* p, const void* q, const void* k, const void* v, void* o,
@@ -254,7 +256,7 @@ int dash_attn_prefill(const dash_params* p, const void* q, const void* k, const 
   if (launch_kbar_compress(*p, L, k, kbar, 0, L.t_c, st, ksplit) != hipSuccess) return DASH_ELAUNCH;
   rc = run_stage1(p, L, q, kbar, mask, blk_cnt, blk_idx, blk_bias, tau, (char*)workspace, st, nullptr, nullptr, ksplit != nullptr);
   if (rc != DASH_OK) return rc;
-  return run_stage2(p, L, q, k, v, o, mask, blk_bias, (char*)workspace, workspace_bytes, false, st);
+  return run_stage2(p, L, q, k, v, o, mask, blk_bias, (char*)workspace, false, st);
 }
 
 static int decode_impl(const dash_params* p, const void* q, const void* k_cache, const void* v_cache,
@@ -284,7 +286,7 @@ static int decode_impl(const dash_params* p, const void* q, const void* k_cache,
   rc = run_stage1(p, L, q, kbar_cache, mask, blk_cnt, blk_idx, blk_bias, tau, (char*)workspace, st,
                   update_cache ? k_cache : nullptr, update_cache ? kbar_cache : nullptr);
   if (rc != DASH_OK) return rc;
-  return run_stage2(p, L, q, k_cache, v_cache, o, mask, blk_bias, (char*)workspace, workspace_bytes, false, st);
+  return run_stage2(p, L, q, k_cache, v_cache, o, mask, blk_bias, (char*)workspace, false, st);
 }
 
 int dash_attn_decode(const dash_params* p, const void* q, const void* k_cache, const void* v_cache,
@@ -325,7 +327,7 @@ int dense_attn(const dash_params* p, const void* q, const void* k, const void* v
   if (rc != DASH_OK) return rc;
   if (!q || !k || !v || !o) return DASH_EINVAL;
   if ((rc = check_ws(L.total_min, workspace, workspace_bytes)) != DASH_OK) return rc;
-  return run_stage2(p, L, q, k, v, o, nullptr, nullptr, (char*)workspace, workspace_bytes, true, (hipStream_t)stream);
+  return run_stage2(p, L, q, k, v, o, nullptr, nullptr, (char*)workspace, true, (hipStream_t)stream);
 }
 
 static int backward_layout(const dash_params* p, Layout* L) {

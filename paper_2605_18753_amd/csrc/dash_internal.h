@@ -27,7 +27,7 @@ struct Layout {
   size_t off_ksplit, off_mask, off_bias, off_scores, off_part, off_flags, off_dec_scores, off_s2_part, total;
   bool dec_scores;     // decode: the workspace has room for score rows of a launch of their own
   int s2_parts;        // bf16 prefill: most parts of a 128-row tile's chunk list (1: not cut); records at off_s2_part
-  size_t total_min;    // without the room for those score rows / records: calls work, some slower
+  size_t total_min;    // decode: without the room for those score rows (total otherwise); what a call has to have
 };
 
 // Validates p and fills L.  Returns a dash_status.  routing = false skips the
@@ -74,9 +74,9 @@ hipError_t launch_s1_decode(const dash_params& p, const Layout& L, const void* q
                             const S1Out& out, const void* k_upd, float* kbar_upd, hipStream_t st);
 hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, const void* k,
                           const void* v, void* o, const uint32_t* mask, const float* bias,
-                          char* part_ws, bool dense, hipStream_t st);   // part_ws: room for the records, or null
+                          char* part_ws, bool dense, hipStream_t st);   // part_ws: s2_part_room() bytes
 int s2_parts(const dash_params& p, const Layout& L);
-size_t s2_part_bytes(const dash_params& p, const Layout& L);
+size_t s2_part_room(const dash_params& p);
 hipError_t launch_s2_f32(const dash_params& p, const Layout& L, const void* q, const void* k,
                          const void* v, void* o, const uint32_t* mask, const float* bias,
                          bool dense, hipStream_t st);

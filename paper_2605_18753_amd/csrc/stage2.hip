@@ -74,6 +74,7 @@ template <int D> __device__ __forceinline__ int v_swz(int row) {
 }
 
 constexpr int kMinPartTiles = 8;   // 64-key tiles a part has at least
+constexpr int kMaxParts = 1536;    // records of a launch
 
 template <int D, bool DENSE>
 __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
@@ -550,7 +551,7 @@ int s2_parts(const dash_params& p, const Layout& L) {
   const float tiles = (float)(L.t_all * (p.block_size >> 6));
   int best = 1;
   float best_cost = INFINITY;
-  for (int n = 1; n * wgs <= 1536 && (n == 1 || n * kMinPartTiles <= tiles); n++) {
+  for (int n = 1; n * wgs <= kMaxParts && (n == 1 || n * kMinPartTiles <= tiles); n++) {
     const int64_t w = n * wgs, rest = w % 512;
     const float rounds = (float)(w / 512) + (rest == 0 ? 0.f : rest <= 256 ? 0.7f : 1.f);
     const float cost = rounds * tiles / n + (n == 1 ? 0.f : 3.f + 6.f * w / 512);
@@ -563,9 +564,8 @@ static size_t s2_cnt_bytes(const dash_params& p, const Layout& L) {
   return ((size_t)s2_tiles(p, L) * p.h_kv * p.batch * 4 + 255) & ~(size_t)255;
 }
 
-size_t s2_part_bytes(const dash_params& p, const Layout& L) {
-  return s2_cnt_bytes(p, L) + (size_t)s2_tiles(p, L) * p.h_kv * p.batch * L.s2_parts * 128 * (p.head_dim + 2) * 4;
-}
+// the most s2_parts allows: 1536 records of tiles that number fewer than 1024
+size_t s2_part_room(const dash_params& p) { return 1024 * 4 + (size_t)kMaxParts * 128 * (p.head_dim + 2) * 4; }
 
 hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, const void* k,
                           const void* v, void* o, const uint32_t* mask, const float* bias,
@@ -573,7 +573,7 @@ hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, 
   S2Args a;
   fill_s2_args(a, p, L, q, k, v, o, mask, bias);
   a.n_tiles = s2_tiles(p, L);
-  if (part_ws && L.s2_parts > 1) {
+  if (L.s2_parts > 1) {
     a.max_parts = L.s2_parts;
     a.part_cnt = reinterpret_cast<int32_t*>(part_ws);
     a.part_ml = reinterpret_cast<float*>(part_ws + s2_cnt_bytes(p, L));

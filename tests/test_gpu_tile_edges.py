@@ -139,14 +139,8 @@ def test_prefill_cut_chunk_lists(name, h_q, h_kv, n_q, n_kv, d, block, extra):
     run = U.run_prefill(w, q, k, v)
     rows = None if n_q * n_kv < 1 << 20 else U.sample_rows(w, 60)
     U.check_against_oracle(w, q, k, v, run, rows=rows)
-    # without room for the parts' records: uncut, the same up to the rounding of the results
     o = torch.full_like(q, float("nan"))
     ws = B.alloc_workspace(run.params, DEV)
-    whole = B.workspace_bytes(run.params)
-    B.dash_stage1_route(run.params, q, run.kbar, run.lists, ws)
-    B.dash_stage2_attend(run.params, q, k, v, o, run.lists, ws[:whole - 256])
-    torch.cuda.synchronize()
-    assert (o.float() - run.o.float()).abs().max() <= 2e-2 * run.o.float().abs().max()
     # the dense reference is cut the same way
     B.dense_attn(run.params, q, k, v, o, ws)
     torch.cuda.synchronize()
