@@ -131,8 +131,9 @@ __global__ __launch_bounds__(512) void s2_f32_kernel(S2FArgs a) {
   ListWalk it(tl.uni, DENSE ? 64 : a.words, wave, NWV);
   for (int c = it.next(); c >= 0; c = it.next()) {
     const bool diag = a.causal && c == cw;
+    const bool mine = DENSE || tl.has(t_n, c);
     float bias = 0.f;
-    if (!DENSE && !diag) bias = tl.has(t_n, c) ? a.bias[(base + t_n) * a.t_all + tl.rank(t_n, c)] : -INFINITY;
+    if (!DENSE && !diag && mine) bias = a.bias[(base + t_n) * a.t_all + tl.rank(t_n, c)];
     // SUB sub-tiles of 16 keys per step: all K loads of a step are in flight together, and its V loads
     // are issued before the softmax that they wait behind
     constexpr int SUB = D == 64 ? 4 : 2;
@@ -149,8 +150,8 @@ __global__ __launch_bounds__(512) void s2_f32_kernel(S2FArgs a) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int st = 0; st < SUB; st++) s[st] = mma_dot<D>(kf[st], qf);
-      // dead keys: after the row's position, past the end of the sequence
-      const int lim = min(diag ? pos : 0x7fffffff, a.n_kv - 1) - kpos0 - 4 * hq;
+      // dead keys: after the row's position, past the end of the sequence, of a chunk the row did not keep
+      const int lim = mine ? min(diag ? pos : 0x7fffffff, a.n_kv - 1) - kpos0 - 4 * hq : -1;
       float mx = -INFINITY;
 #pragma unroll
       for (int st = 0; st < SUB; st++)
@@ -170,10 +171,10 @@ __global__ __launch_bounds__(512) void s2_f32_kernel(S2FArgs a) {
       for (int st = 0; st < SUB; st++)
 #pragma unroll
         for (int t = 0; t < 4; t++) {
-          const float p = exp_diff(s[st][t], m_use);
-          l_run += p;
-          mma_outer<D>(vr[st][t], p, o);
+          s[st][t] = exp_diff(s[st][t], m_use);
+          l_run += s[st][t];
         }
+      mma_outer_keys<D, SUB>(vr, s, lim, ntok, a.g_q, lane, o);
     }
   }
   // ---- add up the waves: rows weighted by e^(m_wave - M) --------------------------------------
@@ -242,7 +243,7 @@ struct RowF32 {
 };
 
 template <int D, bool GRAD>
-__global__ __launch_bounds__(256) void bwd_f32_row_kernel(BwdArgs a, RowF32 x) {
+__global__ __launch_bounds__(256, 2) void bwd_f32_row_kernel(BwdArgs a, RowF32 x) {
   using C = F32Cfg<D>;
   constexpr int NWV = 4;
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -312,20 +313,20 @@ __global__ __launch_bounds__(256) void bwd_f32_row_kernel(BwdArgs a, RowF32 x) {
   for (int c = it.next(); c >= 0; c = it.next()) {
     const bool diag = a.causal && c == cw, mine = tl.has(t_n, c);
     float bias = 0.f, db = 0.f;
-    if (!diag) bias = mine ? a.bias[(base + t_n) * a.t_all + tl.rank(t_n, c)] : -INFINITY;
+    if (!diag && mine) bias = a.bias[(base + t_n) * a.t_all + tl.rank(t_n, c)];
     for (int st = 0; st < nsub; st++) {
       const int kpos0 = c * a.block + st * 16;
       if (kpos0 >= a.n_kv || (diag && kpos0 > tok0 + ntok - 1)) break;
-      f32x4 kf[C::NS], vf[C::NS], kr[GRAD ? 4 : 1][C::NV];     // one round trip per sub-tile
+      f32x4 kf[C::NS], vf[C::NS], kr[1][4][C::NV];             // one round trip per sub-tile
       load_row<D>(kb + (int64_t)min(kpos0 + n, a.n_kv - 1) * a.ks_t, hq, kf);
       load_row<D>(vb + (int64_t)min(kpos0 + n, a.n_kv - 1) * a.vs_t, hq, vf);
       if constexpr (GRAD) {
 #pragma unroll
-        for (int t = 0; t < 4; t++) load_row2<D>(kb + (int64_t)min(kpos0 + 4 * hq + t, a.n_kv - 1) * a.ks_t, n, kr[t]);
+        for (int t = 0; t < 4; t++) load_row2<D>(kb + (int64_t)min(kpos0 + 4 * hq + t, a.n_kv - 1) * a.ks_t, n, kr[0][t]);
       }
       __builtin_amdgcn_sched_barrier(0);
       f32x4 s = mma_dot<D>(kf, qf), dp = mma_dot<D>(vf, of);
-      const int lim = min(diag ? tok : 0x7fffffff, a.n_kv - 1) - kpos0 - 4 * hq;
+      const int lim = mine ? min(diag ? tok : 0x7fffffff, a.n_kv - 1) - kpos0 - 4 * hq : -1;   // as in the forward
       if constexpr (!GRAD) {
         float mx = m_run;
 #pragma unroll
@@ -342,16 +343,16 @@ __global__ __launch_bounds__(256) void bwd_f32_row_kernel(BwdArgs a, RowF32 x) {
         for (int v = 0; v < 4; v++) {
           const float p = exp_diff(s[v], m_use);
           l_run += p;
-          dn_run = fmaf(p, dp[v], dn_run);
+          dn_run = fmaf(p, v > lim ? 0.f : dp[v], dn_run);
         }
       } else {
 #pragma unroll
         for (int t = 0; t < 4; t++) {
-          const float p = t > lim ? 0.f : exp_diff(fmaf(s[t], a.scale, bias), lse);
-          const float dz = p * (dp[t] - dsum);
-          db += dz;
-          mma_outer<D>(kr[t], dz, dq);
+          s[t] = t > lim ? 0.f : exp_diff(fmaf(s[t], a.scale, bias), lse) * (dp[t] - dsum);
+          db += s[t];
         }
+        const f32x4 dz[1] = {s};
+        mma_outer_keys<D, 1>(kr, dz, lim, ntok, a.g_q, lane, dq);
       }
     }
     if constexpr (GRAD) {
@@ -450,15 +451,15 @@ __global__ __launch_bounds__(256) void bwd_f32_key_kernel(BwdArgs a, int parts) 
     if (tb == 0u) continue;                   // bits of tokens past the end are 0
     // all loads of the row tile in flight together
     const int64_t ra = min(tok0 + n / a.g_q, a.n_q - 1);
-    f32x4 qa[C::NS], oa[C::NS], qw[4][C::NV], ow[4][C::NV];
+    f32x4 qa[C::NS], oa[C::NS], qw[1][4][C::NV], ow[1][4][C::NV];
     load_row<D>(qb + (n % a.g_q) * a.qs_h + ra * a.qs_t, hq, qa);
     load_row<D>(ob + (n % a.g_q) * a.os_h + ra * a.os_t, hq, oa);
 #pragma unroll
     for (int t = 0; t < 4; t++) {
       const int row = 4 * hq + t;
       const int64_t rt = min(tok0 + row / a.g_q, a.n_q - 1);
-      load_row2<D>(ob + (row % a.g_q) * a.os_h + rt * a.os_t, n, ow[t]);
-      load_row2<D>(qb + (row % a.g_q) * a.qs_h + rt * a.qs_t, n, qw[t]);
+      load_row2<D>(ob + (row % a.g_q) * a.os_h + rt * a.os_t, n, ow[0][t]);
+      load_row2<D>(qb + (row % a.g_q) * a.qs_h + rt * a.qs_t, n, qw[0][t]);
     }
     // per-row values: lane (m, kq) fetches one of the four of row m, then every lane takes its rows'
     const int cdiag = tok0 / a.block;
@@ -482,20 +483,26 @@ __global__ __launch_bounds__(256) void bwd_f32_key_kernel(BwdArgs a, int parts) 
       bs[v] = __shfl(val, 32 + row);
       ds[v] = __shfl(val, 16 + row);
       dx[v] = __shfl(val, 48 + row);
-      if (!((tb >> (row / a.g_q)) & 1u)) bs[v] = -INFINITY;
     }
     const f32x4 s = mma_dot<D>(qa, kf), dp = mma_dot<D>(oa, vf);
+    // tokens of the tile that do not attend this lane's key: the chunk not kept, or the key after them
+    uint32_t dead = ~tb & ((1u << tokt) - 1u);
+    if (a.causal && kpos0 + n > tok0) dead |= (1u << min(kpos0 + n - tok0, tokt)) - 1u;
+    f32x4 p, dz;
 #pragma unroll
     for (int t = 0; t < 4; t++) {
-      const int row = 4 * hq + t, tk = tok0 + row / a.g_q;
-      const bool dead = a.causal && kpos0 + n > tk;
-      const float p = dead ? 0.f : exp_diff(fmaf(s[t], a.scale, bs[t]), ls[t]);
-      const float dz = p * (dp[t] - ds[t]);
-      mma_outer<D>(ow[t], p, dv);
-      mma_outer<D>(qw[t], dz, dk);
-#pragma unroll
-      for (int nv = 0; nv < C::NV; nv++) kbar[nv] += qw[t][nv] * dx[t];
+      const bool off = (dead >> ((4 * hq + t) / a.g_q)) & 1u;
+      p[t] = off ? 0.f : exp_diff(fmaf(s[t], a.scale, bs[t]), ls[t]);
+      dz[t] = off ? 0.f : p[t] * (dp[t] - ds[t]);
     }
+    mma_outer_rows<D>(ow, p, dead, a.g_q, lane, dv);
+    mma_outer_rows<D>(qw, dz, dead, a.g_q, lane, dk);
+#pragma unroll
+    for (int t = 0; t < 4; t++)
+#pragma unroll
+      for (int nv = 0; nv < C::NV; nv++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) kbar[nv][e] = dx[t] == 0.f ? kbar[nv][e] : fmaf(qw[0][t][nv][e], dx[t], kbar[nv][e]);
   }
   // ---- add up the waves ------------------------------------------------------------------------
 #pragma unroll

@@ -51,6 +51,75 @@ template <int D> __device__ __forceinline__ void load_row2(const float* row, int
 #pragma unroll
   for (int nv = 0; nv < D / 64; nv++) v[nv] = *reinterpret_cast<const f32x4*>(row + 64 * nv + 4 * m);
 }
+// Whether a lane of the wave holds a NaN or an infinity among these rows.
+template <int D, int SUB> __device__ __forceinline__ bool any_nonfinite(const f32x4 (&rows)[SUB][4][D / 64]) {
+  float z = 0.f;
+#pragma unroll
+  for (int st = 0; st < SUB; st++)
+#pragma unroll
+    for (int t = 0; t < 4; t++)
+#pragma unroll
+      for (int nv = 0; nv < D / 64; nv++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) z = fmaf(rows[st][t][nv][e], 0.f, z);   // 0, or NaN
+  return __any(z != z);
+}
+// Second kind, contraction over SUB x 16 keys that the tokens of the tile do not all attend: lane (n, hq)
+// attends its row 16 st + t iff it is <= lim (lim already less 4 hq), w is 0 elsewhere.  0 times a NaN or an
+// infinity is NaN, so where the rows hold one the tokens of the tile are summed one after the
+// other over the keys that the token attends.  (One FMA per loaded value finds out: 1 in 50 of the time of the
+// MFMAs that follow; tiles whose keys are all attended skip it.)
+template <int D, int SUB> __device__ __forceinline__ void mma_outer_keys(const f32x4 (&rows)[SUB][4][D / 64], const f32x4 (&w)[SUB], int lim,
+                                                                       int ntok, int g_q, int lane, f32x4 (&acc)[D / 16]) {
+  if (__any(lim < 16 * SUB - 13) && any_nonfinite<D, SUB>(rows)) {
+    for (int tok = 0; tok < ntok; tok++) {
+      const int lt = __shfl(lim, (lane & 48) + tok * g_q);
+      const bool mine = min((lane & 15) / g_q, ntok - 1) == tok;
+#pragma unroll
+      for (int nv = 0; nv < D / 64; nv++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) {         // one result register group at a time: no second set of accumulators
+          f32x4 sum = acc[4 * nv + e];
+#pragma unroll
+          for (int st = 0; st < SUB; st++)
+#pragma unroll
+            for (int t = 0; t < 4; t++)
+              sum = __builtin_amdgcn_mfma_f32_16x16x4f32(16 * st + t <= lt ? rows[st][t][nv][e] : 0.f, w[st][t], sum, 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < 4; v++) acc[4 * nv + e][v] = mine ? sum[v] : acc[4 * nv + e][v];
+        }
+    }
+    return;
+  }
+#pragma unroll
+  for (int st = 0; st < SUB; st++)
+#pragma unroll
+    for (int t = 0; t < 4; t++) mma_outer<D>(rows[st][t], w[st][t], acc);
+}
+// The same with the roles exchanged: contraction over the 16 (token, head) rows of a tile, lane n is a key,
+// `dead` says per lane and token of the tile (a bit each) whether the key is not attended by it.
+template <int D> __device__ __forceinline__ void mma_outer_rows(const f32x4 (&rows)[1][4][D / 64], const f32x4& w, uint32_t dead, int g_q, int lane,
+                                                                f32x4 (&acc)[D / 16]) {
+  if (__any(dead != 0u) && any_nonfinite<D, 1>(rows)) {
+    for (int tok = 0; tok < 16 / g_q; tok++) {
+      const bool mine = !((dead >> tok) & 1u);
+#pragma unroll
+      for (int nv = 0; nv < D / 64; nv++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          f32x4 sum = acc[4 * nv + e];
+#pragma unroll
+          for (int t = 0; t < 4; t++)
+            sum = __builtin_amdgcn_mfma_f32_16x16x4f32((4 * (lane >> 4) + t) / g_q == tok ? rows[0][t][nv][e] : 0.f, w[t], sum, 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < 4; v++) acc[4 * nv + e][v] = mine ? sum[v] : acc[4 * nv + e][v];
+        }
+    }
+    return;
+  }
+#pragma unroll
+  for (int t = 0; t < 4; t++) mma_outer<D>(rows[0][t], w[t], acc);
+}
 // a second-kind result into LDS row n of a [16][LD] tile
 template <int D> __device__ __forceinline__ void put_tile(float* tile, int n, int hq, const f32x4 (&acc)[D / 16], float w) {
 #pragma unroll
