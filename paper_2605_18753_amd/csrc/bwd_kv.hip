@@ -34,7 +34,11 @@ namespace dash {
 // number of parts of a key tile whose rows are nT 32-row tiles
 __host__ __device__ inline int kv_parts(int nT, int steps_per_part) { return nT <= steps_per_part ? 1 : (nT + steps_per_part - 1) / steps_per_part; }
 
-template <int D>
+// TAIL: several heads and a last row tile that is not full.  The rows behind its last token are then copied as
+// zeros: the buffer resources reach over what lies between the heads (the padding of a larger buffer, another
+// head's rows), and 0 times what it holds could be a NaN.  In every launch the selection costs 0.5 % at d = 128
+// (three registers spilled; 8.04 against 8.00 ms, forward and backward of the shape above), nothing at d = 64.
+template <int D, bool TAIL>
 __global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
   using C = BCfg<D>;
   constexpr int RB = C::ROW_BYTES, HALF = 32 * RB, STAGE = 2 * HALF;   // a stage: 32 Q rows, 32 dO rows
@@ -90,14 +94,20 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
   const uint32_t o_off = (uint32_t)(((c_row / a.g_q) * (int)a.os_t + (c_row % a.g_q) * (int)a.os_h) * 2) + c_chunk;
   const uint32_t q_step = (uint32_t)((4 * RPI / a.g_q) * (int)a.qs_t * 2), o_step = (uint32_t)((4 * RPI / a.g_q) * (int)a.os_t * 2);
   uint32_t cp_q = 0, cp_o = 0, cp_dst = 0;          // scalar offsets and LDS address of the step being copied
+  int cp_left = 0;                                  // TAIL: its tokens before the end of the sequence
   auto copy_begin = [&](int T, int slot) {
     cp_q = (uint32_t)(T * tokw) * (uint32_t)a.qs_t * 2u;
     cp_o = (uint32_t)(T * tokw) * (uint32_t)a.os_t * 2u;
     cp_dst = lds0 + 128 * RB + slot * STAGE + wave * 1024;
+    if constexpr (TAIL) cp_left = a.n_q - T * tokw;
   };
+  const int c_tok = c_row / a.g_q, t_step = 4 * RPI / a.g_q;   // tokens of a copy instruction, TAIL
   auto copy_one = [&](int i) {                      // i < CP: Q rows, then dO rows
-    if (i < CP) copy16_to_lds(q_rs, cp_dst + i * 4096, q_off, cp_q + i * q_step);
-    else copy16_to_lds(o_rs, cp_dst + HALF + (i - CP) * 4096, o_off, cp_o + (i - CP) * o_step);
+    const int j = i < CP ? i : i - CP;
+    uint32_t off = i < CP ? q_off : o_off;
+    if constexpr (TAIL) off = c_tok + j * t_step < cp_left ? off : 0x80000000u;   // past the end of any buffer (less than 2^31): zeros
+    if (i < CP) copy16_to_lds(q_rs, cp_dst + j * 4096, off, cp_q + j * q_step);
+    else copy16_to_lds(o_rs, cp_dst + HALF + j * 4096, off, cp_o + j * o_step);
   };
 
   // ---- operand read offsets -------------------------------------------------------------------
@@ -392,6 +402,15 @@ __global__ void bwd_kbar_sum_kernel(const float* parts, float* out, int n_parts,
   out[i] = v;
 }
 
+template <int D, bool TAIL> static hipError_t launch_kv(const BwdArgs& a, hipStream_t st) {
+  constexpr size_t lds = (size_t)128 * BCfg<D>::ROW_BYTES + 2 * 64 * BCfg<D>::ROW_BYTES + 4 * 64 * 4;
+  auto kern = bwd_kv_kernel<D, TAIL>;
+  static LdsOptIn opt_in;
+  if (hipError_t e = allow_dyn_lds((const void*)kern, lds, opt_in); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((a.n_kv + 127) / 128 * a.hb), (unsigned)a.kv_max_parts), dim3(256), lds, st, a);
+  return hipGetLastError();
+}
+
 template <int D> static hipError_t launch_t(const BwdArgs& a, hipStream_t st) {
   hipError_t e;
   if (a.t_c > 0) {
@@ -404,14 +423,10 @@ template <int D> static hipError_t launch_t(const BwdArgs& a, hipStream_t st) {
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
   }
-  const int ktiles = (a.n_kv + 127) / 128;
-  constexpr size_t lds = (size_t)128 * BCfg<D>::ROW_BYTES + 2 * 64 * BCfg<D>::ROW_BYTES + 4 * 64 * 4;
-  auto kern = bwd_kv_kernel<D>;
-  static LdsOptIn opt_in;
-  if ((e = allow_dyn_lds((const void*)kern, lds, opt_in)) != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(ktiles * a.hb), (unsigned)a.kv_max_parts), dim3(256), lds, st, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const bool tail = a.g_q > 1 && a.n_q % (32 / a.g_q) != 0;
+  if ((e = tail ? launch_kv<D, true>(a, st) : launch_kv<D, false>(a, st)) != hipSuccess) return e;
   if (a.kv_max_parts > 1) {
+    const int ktiles = (a.n_kv + 127) / 128;
     hipLaunchKernelGGL(bwd_kv_reduce_kernel<D>, dim3((unsigned)(ktiles * a.hb * (128 * (D / 4) / 256))), dim3(256), 0, st, a);
     e = hipGetLastError();
   }

@@ -102,3 +102,35 @@ def test_backward_of_what_does_not_meet_the_token_is_untouched(shape, which):
         # and it does reach what meets it
         reached = not bool(torch.isfinite(got[0][0, 0, rows]).any())
         assert reached
+
+
+@pytest.mark.parametrize("dtype,g,n,d,block", [("bf16", 4, 333, 128, 64), ("bf16", 2, 129, 64, 64), ("bf16", 16, 195, 128, 128),
+                                               ("bf16", 1, 1000, 64, 64), ("fp32", 4, 333, 128, 64)])
+def test_rows_behind_the_end_of_a_padded_buffer_are_not_used(dtype, g, n, d, block):
+    w = Workload("padded", 2, 2 * g, 2, n, n, d, block, dtype=dtype, offset_sigma=0.8, gamma=2.0, seed=53)
+    q, k, v = (t.to(DEV) for t in make_inputs(w, "cpu"))
+    d_o = torch.randn(q.shape, generator=torch.Generator().manual_seed(54)).to(q.dtype).to(DEV)
+
+    def step(q, k, v, d_o):
+        # o and d_o share their strides
+        o = torch.empty(d_o.untyped_storage().nbytes() // d_o.element_size(), dtype=q.dtype, device=DEV).as_strided(d_o.shape, d_o.stride())
+        p = B.make_params(q, k, v, o, block, w.alpha, w.gamma, w.sigma, True)
+        kbar = torch.empty(B.kbar_shape(p), dtype=torch.float32, device=DEV)
+        lists = B.Lists.allocate(p, DEV)
+        B.dash_attn_prefill(p, q, k, v, o, kbar, lists, B.alloc_workspace(p, DEV))
+        out = [torch.empty_strided(t.size(), t.stride(), dtype=t.dtype, device=DEV) for t in (q, k, v)]
+        B.dash_attn_backward(p, q, k, v, d_o, kbar, lists, *out, B.alloc_backward_workspace(p, DEV))
+        torch.cuda.synchronize()
+        return [o] + out
+
+    def padded(t):
+        big = torch.full((t.shape[0], t.shape[1], n + 40, d), float("nan"), dtype=t.dtype, device=DEV)
+        big[:, :, :n] = t
+        return big[:, :, :n]
+
+    for name, a, b in zip(("o", "dq", "dk", "dv"), step(*(padded(t) for t in (q, k, v, d_o))), step(q, k, v, d_o)):
+        bad = int((~torch.isfinite(a.float())).sum())
+        assert bad == 0, name
+        # fp32: parts of a list are added in no fixed order
+        same = torch.equal(a, b) if dtype == "bf16" else bool((a - b).abs().max() <= 1e-6 * b.abs().max())
+        assert same, name
