@@ -274,8 +274,10 @@ static int decode_impl(const dash_params* p, const void* q, const void* k_cache,
   L.seq_lens = seq_lens;
   hipStream_t st = (hipStream_t)stream;
   if (decode_route_applicable(*p, L, workspace_bytes)) {
-    S1Out out;
-    out.mask = mask; out.cnt = blk_cnt; out.idx = blk_idx; out.bias = blk_bias; out.tau = tau;
+    S1Out out;   // mask and biases stay in the workspace if not asked for: dash_stage2_attend finds them there
+    out.mask = mask ? mask : reinterpret_cast<uint32_t*>((char*)workspace + L.off_mask);
+    out.bias = blk_bias ? blk_bias : reinterpret_cast<float*>((char*)workspace + L.off_bias);
+    out.cnt = blk_cnt; out.idx = blk_idx; out.tau = tau;
     return launch_decode_route(*p, L, q, k_cache, v_cache, o, kbar_cache, update_cache, out, (char*)workspace,
                                workspace_bytes, st) == hipSuccess ? DASH_OK : DASH_ELAUNCH;
   }

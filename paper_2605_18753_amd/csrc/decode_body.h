@@ -52,7 +52,7 @@ struct DecArgs {
   // Stage 1 (DEC_ROUTE)
   const float* kbar;
   const float* scores; int ld_scores;   // score rows [pair][g_q][ld_scores] of a scoring launch, or null: scored here
-  uint32_t* mask_out; int32_t* cnt; int32_t* idx; float* bias_out; float* tau;   // optional outputs
+  uint32_t* mask_out; float* bias_out; int32_t* cnt; int32_t* idx; float* tau;   // the lists; the last three may be null
   int t_c, window, rows_cap, share_cap;     // LDS sizes: floats of the score area, entries of a split's share
   float xscale, pexp, alpha, inv_sigma;
   float* kbar_upd;           // summary cache to update, or null
@@ -361,22 +361,23 @@ __global__ __launch_bounds__(256, 2) void s2_decode_kernel(DecArgs a) {
     const int nt_all = (total - 1) * nsub + ((pos - cw * s.block) >> 5) + 1;
     const int per = (nt_all + ns - 1) / ns;
     const int e0 = split * per / nsub, e1 = min((min(split * per + per, nt_all) + nsub - 1) / nsub, total);
-    // biases of this split's entries; the whole list, if asked for, by split 0.  The slots are dealt
-    // to the waves.
-    int32_t* oidx = split == 0 && a.idx ? a.idx + (int64_t)pair * s.t_all : nullptr;
-    float* obias = split == 0 && a.bias_out ? a.bias_out + (int64_t)pair * s.t_all : nullptr;
-    const bool emit = oidx || obias;
+    // ids and biases of this split's entries, into the lists too.  The slots are dealt to the waves; an entry cut
+    // between two splits is written by both, with the same values.
+    int32_t* oidx = a.idx ? a.idx + (int64_t)pair * s.t_all : nullptr;
+    float* obias = a.bias_out + (int64_t)pair * s.t_all;
     int start = 0;
     for (int j = 0; j < nslot; j++) {
       const uint32_t lo = __builtin_amdgcn_readlane(word, 2 * j), hi = __builtin_amdgcn_readlane(word, 2 * j + 1);
       const uint64_t bal = (uint64_t)lo | ((uint64_t)hi << 32);
       const int cnt = __popcll(bal);
-      if ((j & 3) == wave && (emit || (start < e1 && start + cnt > e0)) && ((bal >> lane) & 1u)) {
+      if ((j & 3) == wave && start < e1 && start + cnt > e0 && ((bal >> lane) & 1u)) {
         const int p = start + __popcll(bal & ((1ull << lane) - 1ull));
-        const float d = (ln(weight(lane + 64 * j)) - mu) * a.inv_sigma;
-        if (p >= e0 && p < e1) sbias[p - e0] = d * kLog2e;
-        if (oidx) oidx[p] = lane + 64 * j;
-        if (obias) obias[p] = d;
+        if (p >= e0 && p < e1) {
+          const float d = (ln(weight(lane + 64 * j)) - mu) * a.inv_sigma;
+          sbias[p - e0] = d * kLog2e;
+          obias[p] = d;
+          if (oidx) oidx[p] = lane + 64 * j;
+        }
       }
       start += cnt;
     }
@@ -384,12 +385,14 @@ __global__ __launch_bounds__(256, 2) void s2_decode_kernel(DecArgs a) {
       if (lane == (c >> 5)) word |= 1u << (c & 31);
     if (tid <= cw - c0) {
       const int p = routed + tid;
-      if (p >= e0 && p < e1) sbias[p - e0] = 0.f;
-      if (oidx) oidx[p] = c0 + tid;
-      if (obias) obias[p] = 0.f;
+      if (p >= e0 && p < e1) {
+        sbias[p - e0] = 0.f;
+        obias[p] = 0.f;
+        if (oidx) oidx[p] = c0 + tid;
+      }
     }
     if (split == 0 && a.cnt && tid == 0) a.cnt[pair] = total;
-    if (split == 0 && a.mask_out && tid < s.words) a.mask_out[(int64_t)pair * s.words + tid] = word;
+    if (split == 0 && tid < s.words) a.mask_out[(int64_t)pair * s.words + tid] = word;
     __syncthreads();                          // the score rows give way to the K / V ring
   }
 

@@ -152,3 +152,23 @@ def test_prefill_cut_chunk_lists(name, h_q, h_kv, n_q, n_kv, d, block, extra):
             z.masked_fill_(torch.arange(n_kv)[None, :] > pos[:, None], float("-inf"))
         ref = torch.softmax(z, -1) @ vf[0, h // g]
         assert (o[0, h].double().cpu() - ref).abs().max() <= 2e-2 * ref.abs().max()
+
+
+@pytest.mark.parametrize("batch,h_q,h_kv,n_kv,extra", [
+    (1, 8, 2, 1000, {}), (2, 16, 1, 400 * 64 + 7, {"gamma": 2.0}), (1, 4, 1, 700 * 64, {"gamma": 1.5, "window": 2}), (300, 2, 2, 300, {})])
+def test_decode_keeps_its_lists_in_the_workspace(batch, h_q, h_kv, n_kv, extra):
+    """Lists that are not asked for stay in the workspace for dash_stage2_attend, as those of
+    dash_stage1_route do.  The workspace first holds the lists of other queries."""
+    w = Workload("edge_ws_lists", batch, h_q, h_kv, 1, n_kv, 64, 64, offset_sigma=1.0, seed=47, **extra)
+    q, k, v = make_inputs(w, DEV)
+    o, again = torch.empty_like(q), torch.empty_like(q)
+    p = B.make_params(q, k, v, o, w.block, w.alpha, w.gamma, 1e6, True, window=w.window)
+    kbar = torch.empty(B.kbar_shape(p), dtype=torch.float32, device=DEV)
+    B.dash_kbar_compress(p, k, kbar)
+    ws = B.alloc_workspace(p, DEV)
+    B.dash_stage1_route(p, -q, kbar, B.Lists(), ws)
+    B.dash_attn_decode(p, q, k, v, kbar, o, B.Lists(), ws)
+    B.dash_stage2_attend(p, q, k, v, again, B.Lists(), ws)
+    torch.cuda.synchronize()
+    # the same kernel on the same splits
+    assert torch.equal(o, again)
