@@ -75,17 +75,31 @@ int make_layout(const dash_params* p, Layout* L, bool routing) {
   const bool decode_mfma = p->dtype == DASH_BF16 && p->n_q == 1;
   const int pairs = p->batch * p->h_kv;
   int splits = 1;
+  int slots = p->batch;
   int part_slots = 1;   // room for records per pair: rounded up, so that a workspace made for more pairs holds fewer
   if (decode_mfma) {
-    const int target = 512;   // workgroups per launch: two per CU, all resident at once
+    // Workgroups per launch: two per CU, all resident at once.  Rounded down: a second round of a few workgroups
+    // costs more than places left empty (pairs of one head, 30000 keys, rounded down / up: 200 pairs 66 / 77 us, 257 86 /
+    // 83, 300 97 / 105, 511 132 / 151; groups of 4, 2000 keys: 171 pairs 40 / 44, 257 54 / 60; the other way at 171 pairs
+    // of one head and 8000 keys, 40 / 36)
+    const int target = 512;
     splits = target / pairs;
     part_slots = (target + pairs - 1) / pairs;
     const int cap = L->t_all < 64 ? L->t_all : 64;
     if (splits > cap) splits = cap;
     if (part_slots > cap) part_slots = cap;
     if (splits < 1) splits = 1;
+    // per-sequence lengths: all the places a kv head has, also where they are no multiple of the batch (24
+    // sequences of up to 60000 tokens x 8 kv-heads in 2 splits each leave a quarter of them empty: 143 us against
+    // 122 in all 64).  Where half of the places are taken by one split each it stays at that: 40 sequences of up to
+    // 20000 tokens x 8: 197 us, with the longer ones in two 203.
+    if (splits > 1) {
+      slots = target / p->h_kv;
+      if (slots > (int64_t)p->batch * cap) slots = p->batch * cap;
+    }
   }
   L->splits = splits;
+  L->slots = slots;
   const size_t rows = (size_t)p->batch * p->h_kv * p->n_q;
   size_t off = 0;
   L->off_ksplit = off;
@@ -99,14 +113,15 @@ int make_layout(const dash_params* p, Layout* L, bool routing) {
   L->off_part = off;
   if (decode_mfma) off += align256((size_t)pairs * part_slots * g * (p->head_dim + 2) * 4);
   L->off_flags = off;
-  if (splits > 1) off += align256((size_t)pairs * splits * 8);   // a single split writes no flag
+  const size_t flag_bytes = 512 * 8;                             // no call has more workgroups that write one
+  if (splits > 1) off += flag_bytes;                             // a single split writes none
   // room for the parts' records of a prefill: the same for every call, so that a workspace made for a
   // larger call holds a smaller one that is cut into more parts
   L->s2_parts = s2_parts(*p, *L);
   L->off_s2_part = off;
   if (L->use_mfma) off += align256(s2_part_room(*p));
   L->total_min = off > 0 ? off : 256;
-  if (decode_mfma && splits == 1) off += align256(512 * 8);       // see part_slots
+  if (decode_mfma && splits == 1) off += flag_bytes;              // see part_slots
   L->off_dec_scores = off;
   L->dec_scores = decode_scores_apart(*p, *L);
   if (L->dec_scores) off += align256((size_t)p->batch * p->h_q * decode_scores_ld(*L) * 4);

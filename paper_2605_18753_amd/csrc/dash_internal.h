@@ -18,6 +18,7 @@ struct Layout {
   int words;        // mask words per query
   int pos0;         // sequence position of query 0: n_kv - n_q
   int splits;       // decode: KV splits per (batch, kv head)
+  int slots;        // decode with per-sequence lengths: KV splits of a kv head over the whole batch, dealt in the kernel
   float scale;      // logit scale
   float xscale;     // gamma * (alpha-1) * scale: Stage-1 score factor
   float pexp;       // 1/(alpha-1)

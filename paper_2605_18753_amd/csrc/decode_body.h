@@ -46,7 +46,8 @@ enum { DEC_ROUTE = 0, DEC_LISTS = 1, DEC_DENSE = 2 };
 
 struct DecArgs {
   S2Args s;                  // tensors, sizes, part (split partials), seq_lens; mask / bias: the lists to read (DEC_LISTS)
-  int splits;                // splits per pair (uniform lengths); average over the batch (per-sequence lengths)
+  int splits;                // splits per pair (uniform lengths)
+  int slots;                 // splits of a kv-head over the whole batch (per-sequence lengths)
   int batch, n_main;         // n_main: workgroups of the attention; the ones behind update the summary cache
   uint64_t nonce; uint64_t* flags;   // [n_main]
   // Stage 1 (DEC_ROUTE)
@@ -223,50 +224,99 @@ __global__ __launch_bounds__(256, 2) void s2_decode_kernel(DecArgs a) {
     r = pair % s.h_kv; b = pair / s.h_kv;
     split = blockIdx.x / pairs; ns = a.splits; rec0 = pair * ns; len = s.n_kv;
   } else {
-    // per-sequence lengths: half of the splits * batch slots of a kv-head are dealt evenly (the kept
-    // chunks grow more slowly than the length), the others by length: sequence i gets
-    // half + floor(extra N_{i+1} / N) - floor(extra N_i / N), N_i = the chunks of the sequences before it (at most
-    // 64, the flags one wave reads), so that no slot is left over
-    const int slots = a.splits * a.batch, half = max(a.splits >> 1, 1), extra = slots - half * a.batch;
+    // per-sequence lengths: the slots of a kv-head are dealt to the sequences, at most 64 each (the flags one wave
+    // reads)
+    const int slots = a.slots;
     r = blockIdx.x % s.h_kv;
     const int slot = blockIdx.x / s.h_kv;
-    int tot = 0;
-    for (int i0 = 0; i0 < a.batch; i0 += 64) {
-      const int i = i0 + lane;
-      int t = i < a.batch ? (min(max(s.seq_lens[i], 1), s.n_kv) - 1) / s.block + 1 : 0;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) t += __shfl_xor(t, o);
-      tot += t;
-    }
     b = -1; split = 0; ns = 1;
-    int first = 0, base = 0, n_before = 0;
-    for (int i0 = 0; i0 < a.batch && b < 0; i0 += 64) {
-      const int i = i0 + lane;
-      const int nc = i < a.batch ? (min(max(s.seq_lens[i], 1), s.n_kv) - 1) / s.block + 1 : 0;
-      int upto = nc;
+    int first = 0;
+    auto chunks_of = [&](int i) { return i < a.batch ? (min(max(s.seq_lens[i], 1), s.n_kv) - 1) / s.block + 1 : 0; };
+    // the sequence that `slot` belongs to, from its sequences' shares; share(i) is asked for i = i0 + lane
+    auto find = [&](auto&& share) {
+      int base = 0;
+      for (int i0 = 0; i0 < a.batch && b < 0; i0 += 64) {
+        const int cnt = share(i0 + lane);
+        int incl = cnt;
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(upto, o);
-        if (lane >= o) upto += t;
+        for (int o = 1; o < 64; o <<= 1) {
+          const int t = __shfl_up(incl, o);
+          if (lane >= o) incl += t;
+        }
+        const uint64_t hit = __ballot(base + incl > slot);
+        if (hit) {
+          const int l = __builtin_ctzll(hit);
+          b = i0 + l;
+          ns = __builtin_amdgcn_readlane(cnt, l);
+          first = base + __builtin_amdgcn_readlane(incl, l) - ns;
+        }
+        base += __builtin_amdgcn_readlane(incl, 63);
       }
-      upto += n_before;
-      n_before = __builtin_amdgcn_readlane(upto, 63);
-      const int share = half + (int)((int64_t)extra * upto / tot) - (int)((int64_t)extra * (upto - nc) / tot);
-      const int cnt = i < a.batch ? min(min(share, 64), nc) : 0;
-      int incl = cnt;
+    };
+    if constexpr (KIND == DEC_LISTS) {
+      // The lists are there, so the slots are dealt by what they say: ceil(sub-tiles / T) each with the smallest
+      // T, of 64 that a lane each tries, whose shares fit the slots.  N / (slots - batch) always does.
+      // 16 sequences of up to 128k tokens x 8 kv-heads, 9 % of the chunks kept: 139.5 us per step, evenly 146, by
+      // length as below 148; a quarter kept: 357, 388, 376; 24 of up to 60000 tokens: 107, 120, 122.
+      if (slots == a.batch) {
+        b = first = slot;
+      } else {
+        int* work = reinterpret_cast<int*>(lds);                     // [batch], fewer than 512
+        for (int i0 = wave; i0 < a.batch; i0 += 16) {
+          uint32_t m[4];
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
+          for (int k = 0; k < 4; k++)
+            m[k] = i0 + 4 * k < a.batch && lane < s.words ? s.mask[((int64_t)(i0 + 4 * k) * s.h_kv + r) * s.words + lane] : 0u;
+#pragma unroll
+          for (int k = 0; k < 4; k++) {
+            const int i = i0 + 4 * k, kept = (int)wave_sum((float)__popc(m[k]));
+            if (i < a.batch && lane == 0) {
+              const int end = min(max(s.seq_lens[i], 1), s.n_kv) - 1;
+              work[i] = max((kept - 1) * (s.block >> 5) + ((end % s.block) >> 5) + 1, 1);
+            }
+          }
+        }
+        __syncthreads();
+        float total = 0.f;
+        for (int i = lane; i < a.batch; i += 64) total += (float)work[i];
+        total = wave_sum(total);
+        auto share_at = [&](int i, float inv_t) { return min(max((int)ceilf((float)work[i] * inv_t), 1), 64); };
+        const float lo = total / (float)slots, hi = total / (float)(slots - a.batch) + 1.f;
+        float inv_t = 1.f / fmaxf(lo + (hi - lo) * (float)lane * (1.f / 63.f), 1.f);
+        int sum = 0;
+        for (int i = 0; i < a.batch; i++) sum += share_at(i, inv_t);
+        const uint64_t fits = __ballot(sum <= slots);
+        // (no lane: one split each)
+        inv_t = fits ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv_t), __builtin_ctzll(fits))) : 0.f;
+        find([&](int i) { return i < a.batch ? share_at(i, inv_t) : 0; });
+        __syncthreads();                                               // the ring takes the place of `work`
       }
-      const uint64_t hit = __ballot(base + incl > slot);
-      if (hit) {
-        const int l = __builtin_ctzll(hit);
-        b = i0 + l;
-        ns = __builtin_amdgcn_readlane(cnt, l);
-        first = base + __builtin_amdgcn_readlane(incl, l) - ns;
+    } else {
+      // Half of the slots are dealt evenly (the kept chunks grow more slowly than the length), the others by
+      // length: sequence i gets half + floor(extra N_{i+1} / N) - floor(extra N_i / N), N_i = the chunks of the sequences
+      // before it, so that no slot is left over
+      const int half = max(slots / (2 * a.batch), 1), extra = slots - half * a.batch;
+      int tot = 0;
+      for (int i0 = 0; i0 < a.batch; i0 += 64) {
+        int t = chunks_of(i0 + lane);
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) t += __shfl_xor(t, o);
+        tot += t;
       }
-      base += __builtin_amdgcn_readlane(incl, 63);
+      int n_before = 0;
+      find([&](int i) {
+        const int nc = chunks_of(i);
+        int upto = nc;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int t = __shfl_up(upto, o);
+          if (lane >= o) upto += t;
+        }
+        upto += n_before;
+        n_before = __builtin_amdgcn_readlane(upto, 63);
+        const int share = half + (int)((int64_t)extra * upto / tot) - (int)((int64_t)extra * (upto - nc) / tot);
+        return i < a.batch ? min(min(share, 64), nc) : 0;
+      });
     }
     if (b < 0) return;                        // more slots than splits
     b = __builtin_amdgcn_readfirstlane(b);

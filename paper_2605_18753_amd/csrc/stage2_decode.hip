@@ -55,13 +55,15 @@ static hipError_t launch_attend_t(const DecArgs& a, size_t lds, hipStream_t st) 
 
 // entries a split's share can hold (host bound of the kernel's split rule)
 static int share_cap(const dash_params& p, const Layout& L) {
-  if (L.splits <= 1) return L.t_all;
-  int cap;
+  int cap = L.t_all;
   if (!L.seq_lens) {
-    cap = (L.t_all + L.splits - 1) / L.splits + 2;      // a share may start and end inside a chunk
+    if (L.splits > 1) cap = (L.t_all + L.splits - 1) / L.splits + 2;      // a share may start and end inside a chunk
   } else {
-    const int64_t extra = (int64_t)(L.splits - (L.splits >> 1)) * p.batch;   // splits > 1
-    cap = (int)(((int64_t)p.batch * L.t_all + extra - 1) / extra) + 3;
+    const int64_t extra = L.slots - (int64_t)(L.slots / (2 * p.batch) > 1 ? L.slots / (2 * p.batch) : 1) * p.batch;
+    if (extra > 0) {
+      const int64_t c = ((int64_t)p.batch * L.t_all + extra - 1) / extra + 4;
+      cap = c < L.t_all ? (int)c : L.t_all;
+    }
     if (cap < (L.t_all + 63) / 64 + 2) cap = (L.t_all + 63) / 64 + 2;
   }
   return cap < L.t_all ? cap : L.t_all;
@@ -73,7 +75,8 @@ static DecArgs make_dec_args(const dash_params& p, const Layout& L, const void* 
   fill_s2_args(a.s, p, L, q, k, v, o, mask, bias);
   a.s.part = reinterpret_cast<float*>(ws + L.off_part);
   a.flags = reinterpret_cast<uint64_t*>(ws + L.off_flags);
-  a.splits = L.splits; a.batch = p.batch; a.n_main = p.batch * p.h_kv * L.splits;
+  a.splits = L.splits; a.slots = L.slots; a.batch = p.batch;
+  a.n_main = L.seq_lens ? p.h_kv * L.slots : p.batch * p.h_kv * L.splits;
   a.nonce = next_nonce();
   a.share_cap = (share_cap(p, L) + 3) & ~3;
   const size_t ring = p.head_dim == 128 ? DecCfg<128>::RING_BYTES : DecCfg<64>::RING_BYTES;

@@ -1,11 +1,13 @@
 """GPU parity at the sizes where the tilings change: the ranges of the decode step's kernels, the
 128-key tiles and the cut row ranges of the backward pass, the 16-row tiles of the fp32 kernels.
 Oracle and tolerances are those of parity_util and test_gpu_backward."""
+import numpy as np
 import pytest
 import torch
 
 import parity_util as U
 import test_gpu_backward as TB
+from oracle import dash_oracle as orc
 from paper_2605_18753_amd import binding as B
 from paper_2605_18753_amd.inputs import Workload, make_inputs
 
@@ -172,3 +174,47 @@ def test_decode_keeps_its_lists_in_the_workspace(batch, h_q, h_kv, n_kv, extra):
     torch.cuda.synchronize()
     # the same kernel on the same splits
     assert torch.equal(o, again)
+
+
+# Per-sequence lengths: the splits of a kv-head are dealt to the sequences 64 at a time, by length or,
+# over lists in memory, by what the lists hold.
+@pytest.mark.parametrize("name,batch,h_q,h_kv,n_kv,d,block,cut,extra", [
+    ("more_than_two_rounds", 130, 2, 1, 1500, 64, 64, 0, {}),
+    ("one_split_left_over", 65, 4, 4, 900, 128, 64, 0, {"window": 1}),
+    ("some_have_two", 40, 16, 8, 700, 64, 64, 0, {}),
+    ("no_slot_to_spare", 520, 1, 1, 300, 64, 64, 0, {}),
+    ("lists", 70, 8, 1, 400 * 64 + 9, 64, 64, "scores", {"gamma": 2.0}),
+    ("lists_few_sequences", 3, 16, 1, 350 * 128 + 77, 128, 128, "scores", {"gamma": 2.0, "window": 2}),
+    ("lists_200_pairs", 100, 16, 2, 321 * 64 + 1, 64, 64, "scores", {"gamma": 3.0}),
+    # more summaries than score rows are kept for
+    ("lists_one_split_each", 257, 16, 1, 1060 * 64, 64, 64, 0, {"gamma": 4.0})])
+def test_ragged_decode_deals_its_splits(name, batch, h_q, h_kv, n_kv, d, block, cut, extra):
+    w = Workload("edge_ragged_" + name, batch, h_q, h_kv, 1, n_kv, d, block, offset_sigma=0.7, seed=48, **extra)
+    q, k, v = make_inputs(w, DEV)
+    o = torch.full_like(q, float("nan"))
+    p = B.make_params(q, k, v, o, block, w.alpha, w.gamma, w.sigma, True, window=w.window)
+    kbar = torch.empty(B.kbar_shape(p), dtype=torch.float32, device=DEV)
+    B.dash_kbar_compress(p, k, kbar)
+    rng = np.random.default_rng(49)
+    lens = np.where(rng.random(batch) < 0.5, rng.integers(1, n_kv + 1, batch), rng.integers(1, min(n_kv, 200) + 1, batch))
+    lens[[0, -1]] = 1, n_kv
+    lists, ws = B.Lists.allocate(p, DEV), B.alloc_workspace(p, DEV)
+    if cut == "scores":                           # a workspace without its score rows: routing in a launch of its own
+        cut = (batch * h_q * ((n_kv // block + 15) // 16 * 16) * 4 + 255) // 256 * 256
+    ws = ws[:ws.numel() - cut]
+    B.dash_attn_decode_ragged(p, q, k, v, kbar, torch.tensor(lens, dtype=torch.int32, device=DEV), o, lists, ws, update_cache=False)
+    torch.cuda.synchronize()
+    prm, g, rep = U.oracle_params(w), h_q // h_kv, U.SupportReport()
+    longest = int(np.argsort(lens)[-2])
+    for b in sorted({i for i in (0, 1, 62, 63, 64, 65, 127, 128, 129, batch // 2, longest, batch - 2, batch - 1) if i < batch}):
+        n = int(lens[b])
+        for r in {0, h_kv - 1}:
+            kn, vn = U.to_np(k[b, r, :n]), U.to_np(v[b, r, :n])
+            rr = orc.dash_row_at(U.to_np(q[b, r * g:(r + 1) * g, 0]), kn, vn, orc.block_mean_summaries(kn, block), prm, n - 1, (b, r, 0))
+            U.compare_row(rr, w, lists.mask[b, r, 0].cpu().numpy(), int(lists.cnt[b, r, 0]), lists.idx[b, r, 0].cpu().numpy(),
+                          lists.bias[b, r, 0].cpu().numpy(), lists.tau[b, r * g:(r + 1) * g, 0].cpu().numpy(), rep, B.list_stride(p))
+            got = U.to_np(o[b, r * g:(r + 1) * g, 0]).astype(np.float64)
+            assert np.abs(got - rr.o).max() <= 2e-2 * np.abs(rr.o).max(), (b, r)
+    assert rep.mismatched == 0 and rep.exempt <= 1
+    # every sequence was written
+    assert not bool(torch.isnan(o.float()).any())
