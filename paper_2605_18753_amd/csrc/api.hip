@@ -115,11 +115,11 @@ int make_layout(const dash_params* p, Layout* L, bool routing) {
   L->off_flags = off;
   const size_t flag_bytes = 512 * 8;                             // no call has more workgroups that write one
   if (splits > 1) off += flag_bytes;                             // a single split writes none
-  // room for the parts' records of a prefill: the same for every call, so that a workspace made for a
-  // larger call holds a smaller one that is cut into more parts
+  // room for the parts' records of a prefill, and of smaller ones that are cut into more parts
+  L->total_route = off > 0 ? off : 256;
   L->s2_parts = s2_parts(*p, *L);
   L->off_s2_part = off;
-  if (L->use_mfma) off += align256(s2_part_room(*p));
+  if (L->use_mfma) off += align256(s2_part_room(*p, *L));
   L->total_min = off > 0 ? off : 256;
   if (decode_mfma && splits == 1) off += flag_bytes;              // see part_slots
   L->off_dec_scores = off;
@@ -240,7 +240,7 @@ int dash_stage1_route(const dash_params* p, const void* q, const float* kbar, ui
   int rc = make_layout(p, &L);
   if (rc != DASH_OK) return rc;
   if (!q || (!kbar && L.t_c > 0)) return DASH_EINVAL;
-  if ((rc = check_ws(L.total_min, workspace, workspace_bytes)) != DASH_OK) return rc;
+  if ((rc = check_ws(L.total_route, workspace, workspace_bytes)) != DASH_OK) return rc;
   return run_stage1(p, L, q, kbar, mask, blk_cnt, blk_idx, blk_bias, tau, (char*)workspace,
                     (hipStream_t)stream);
 }

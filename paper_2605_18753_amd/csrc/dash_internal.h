@@ -29,6 +29,7 @@ struct Layout {
   bool dec_scores;     // decode: the workspace has room for score rows of a launch of their own
   int s2_parts;        // bf16 prefill: most parts of a 128-row tile's chunk list (1: not cut); records at off_s2_part
   size_t total_min;    // decode: without the room for those score rows (total otherwise); what a call has to have
+  size_t total_route;  // ... of dash_stage1_route: a prefill's without the parts' records
 };
 
 // Validates p and fills L.  Returns a dash_status.  routing = false skips the
@@ -77,7 +78,7 @@ hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, 
                           const void* v, void* o, const uint32_t* mask, const float* bias,
                           char* part_ws, bool dense, hipStream_t st);   // part_ws: s2_part_room() bytes
 int s2_parts(const dash_params& p, const Layout& L);
-size_t s2_part_room(const dash_params& p);
+size_t s2_part_room(const dash_params& p, const Layout& L);
 hipError_t launch_s2_f32(const dash_params& p, const Layout& L, const void* q, const void* k,
                          const void* v, void* o, const uint32_t* mask, const float* bias,
                          bool dense, hipStream_t st);

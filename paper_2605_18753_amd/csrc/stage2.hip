@@ -533,6 +533,7 @@ static hipError_t launch_s2_t(const S2Args& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+static int64_t s2_most_records(const dash_params& p, const Layout& L);
 static int s2_tiles(const dash_params& p, const Layout& L) { return (p.n_q + 128 / L.g_q - 1) / (128 / L.g_q); }
 
 // Parts a tile's chunk list is cut into at most.  512 workgroups are resident at once, two per CU
@@ -549,9 +550,10 @@ int s2_parts(const dash_params& p, const Layout& L) {
   const int64_t wgs = (int64_t)s2_tiles(p, L) * p.h_kv * p.batch;
   if (wgs >= (L.pos0 >= p.n_q ? 1024 : 512)) return 1;
   const float tiles = (float)(L.t_all * (p.block_size >> 6));
+  const int64_t most = s2_most_records(p, L);
   int best = 1;
   float best_cost = INFINITY;
-  for (int n = 1; n * wgs <= kMaxParts && (n == 1 || n * kMinPartTiles <= tiles); n++) {
+  for (int n = 1; n * wgs <= (n == 1 ? wgs : most) && (n == 1 || n * kMinPartTiles <= tiles); n++) {
     const int64_t w = n * wgs, rest = w % 512;
     const float rounds = (float)(w / 512) + (rest == 0 ? 0.f : rest <= 256 ? 0.7f : 1.f);
     const float cost = rounds * tiles / n + (n == 1 ? 0.f : 3.f + 6.f * w / 512);
@@ -564,8 +566,22 @@ static size_t s2_cnt_bytes(const dash_params& p, const Layout& L) {
   return ((size_t)s2_tiles(p, L) * p.h_kv * p.batch * 4 + 255) & ~(size_t)255;
 }
 
-// the most s2_parts allows: 1536 records of tiles that number fewer than 1024
-size_t s2_part_room(const dash_params& p) { return 1024 * 4 + (size_t)kMaxParts * 128 * (p.head_dim + 2) * 4; }
+// Records that s2_parts may ask for in a call of these parameters or in one with fewer queries, keys or
+// sequences, so that a workspace made for the larger call serves the smaller one: parts of kMinPartTiles tiles
+// each; and, from the costs above over all numbers of workgroups, no more than 256 below 24 tiles, 512 below 37 and 1024
+// below 43 (a 1000-token prompt of 8 kv-heads, which is not cut itself: 17 MB at head dimension 128; one of up to
+// 960 tokens: none).
+static int64_t s2_most_records(const dash_params& p, const Layout& L) {
+  const int tiles = L.t_all * (p.block_size >> 6);
+  if (tiles < 2 * kMinPartTiles) return 0;
+  const int64_t wgs = (int64_t)s2_tiles(p, L) * p.h_kv * p.batch, by_parts = wgs * (tiles / kMinPartTiles);
+  const int by_cost = tiles < 24 ? 256 : tiles < 37 ? 512 : tiles < 43 ? 1024 : kMaxParts;
+  return by_parts < by_cost ? by_parts : by_cost;
+}
+size_t s2_part_room(const dash_params& p, const Layout& L) {
+  const int64_t n = s2_most_records(p, L);
+  return n == 0 ? 0 : 1024 * 4 + (size_t)n * 128 * (p.head_dim + 2) * 4;     // counts of fewer than 1024 tiles
+}
 
 hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, const void* k,
                           const void* v, void* o, const uint32_t* mask, const float* bias,

@@ -218,3 +218,17 @@ def test_ragged_decode_deals_its_splits(name, batch, h_q, h_kv, n_kv, d, block, 
     assert rep.mismatched == 0 and rep.exempt <= 1
     # every sequence was written
     assert not bool(torch.isnan(o.float()).any())
+
+
+def test_routing_needs_no_room_for_records():
+    """dash_stage1_route writes none of the records of cut chunk lists."""
+    w = Workload("edge_route_ws", 1, 8, 2, 1024, 1024, 128, 64, offset_sigma=0.7, seed=50)
+    q, k, v = make_inputs(w, DEV)
+    run = U.run_prefill(w, q, k, v)
+    lists, ws = B.Lists.allocate(run.params, DEV), B.alloc_workspace(run.params, DEV)
+    pieces, mask, bias = 2 * 16 * 3 * 128 * 2, 2 * 1024 * 4, 2 * 1024 * 16 * 4       # all multiples of 256
+    assert pieces + mask + bias + 256 < ws.numel()
+    B.dash_stage1_route(run.params, q, run.kbar, lists, ws[:pieces + mask + bias + 256])
+    torch.cuda.synchronize()
+    for name in ("mask", "cnt", "idx", "tau"):
+        assert torch.equal(getattr(lists, name), getattr(run.lists, name)), name

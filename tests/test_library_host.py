@@ -54,6 +54,33 @@ def test_workspace_and_list_sizes():
     assert 16 * 8 * 2048 * 4 < B.workspace_bytes(pd) < 16 * 32 * 2047 * 4
 
 
+def test_prefill_workspace_follows_the_shape():
+    """A prefill needs room for the records of cut chunk lists only as far as it, or a smaller call in the same
+    workspace, can be cut: nothing below 16 tiles of 64 keys, at most 1536 records of 128 rows."""
+    size = lambda n, **kw: B.workspace_bytes(params(**{**dict(h_q=32, h_kv=8, n_q=n, n_kv=n), **kw}))
+    lists = lambda n, h_kv=8: h_kv * (n // 64) * 3 * 128 * 2 + h_kv * n * ((n + 63) // 64 + (n + 2047) // 2048) * 4 + 4 * 256
+    record = 128 * 130 * 4
+    for n in (2, 100, 700, 960):
+        assert size(n) <= lists(n), n
+    assert size(1000) <= lists(1000) + 4096 + 256 * record
+    assert size(2000) <= lists(2000) + 4096 + 512 * record
+    assert size(1024, h_q=1, h_kv=1) <= lists(1024, 1) + 4096 + 16 * record        # 8 row tiles in two parts
+    assert size(32768) <= lists(32768) + 4096 + 1536 * record
+    # a workspace made for a larger call serves the smaller ones
+    for h_q, h_kv in ((32, 8), (2, 2), (16, 1), (128, 64)):
+        for d in (64, 128):
+            for blk in (64, 128):
+                get = lambda b, n_q, n_kv: B.workspace_bytes(params(batch=b, h_q=h_q, h_kv=h_kv, n_q=n_q, n_kv=n_kv, head_dim=d, block_size=blk))
+                last = 0
+                for n in list(range(64, 4096, 64)) + [8192, 30000, 131072]:
+                    now = get(1, n, n)
+                    assert now >= last, (h_q, h_kv, d, blk, n)
+                    last = now
+                    for n_q in (2, 64, 65, 600, 2000, 4096):
+                        if n_q < n and (n - n_q) % 64 == 0:
+                            assert get(1, n_q, n) <= now and now <= get(2, n, n)
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(h_q=7), -1), (dict(alpha=1.0), -1), (dict(alpha=0.5), -1), (dict(sigma=0.0), -1),
     (dict(gamma=-1.0), -1), (dict(batch=0), -1), (dict(n_q=2048), -1), (dict(causal=2), -1),
