@@ -9,8 +9,10 @@
 // Scratch for dash_attn_decode_static, the entry point for callers that cannot allocate: one
 // array per GPU the library's code is loaded on, held until the process ends.  In host code the
 // name stands for the symbol, not for a device address: the address is asked for once per device
-// (static_scratch below) and only that pointer is handed to kernels.
-constexpr size_t kStaticScratchBytes = (size_t)8 << 20;
+// (static_scratch below) and only that pointer is handed to kernels.  8 MiB for lists and partial results, and the
+// split flags.
+constexpr size_t kFlagBytes = 512 * 8;     // no call has more workgroups that write a split flag
+constexpr size_t kStaticScratchBytes = ((size_t)8 << 20) + kFlagBytes;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace dash {
@@ -113,15 +115,14 @@ int make_layout(const dash_params* p, Layout* L, bool routing) {
   L->off_part = off;
   if (decode_mfma) off += align256((size_t)pairs * part_slots * g * (p->head_dim + 2) * 4);
   L->off_flags = off;
-  const size_t flag_bytes = 512 * 8;                             // no call has more workgroups that write one
-  if (splits > 1) off += flag_bytes;                             // a single split writes none
+  if (splits > 1) off += kFlagBytes;                             // a single split writes none
   // room for the parts' records of a prefill, and of smaller ones that are cut into more parts
   L->total_route = off > 0 ? off : 256;
   L->s2_parts = s2_parts(*p, *L);
   L->off_s2_part = off;
   if (L->use_mfma) off += align256(s2_part_room(*p, *L));
   L->total_min = off > 0 ? off : 256;
-  if (decode_mfma && splits == 1) off += flag_bytes;              // see part_slots
+  if (decode_mfma && splits == 1) off += kFlagBytes;              // see part_slots
   L->off_dec_scores = off;
   L->dec_scores = decode_scores_apart(*p, *L);
   if (L->dec_scores) off += align256((size_t)p->batch * p->h_q * decode_scores_ld(*L) * 4);
