@@ -270,25 +270,29 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
       const float m_use = m_new == -INFINITY ? 0.f : m_new;
       const float corr = __builtin_amdgcn_exp2f(m_run - m_use), off = bias_row - m_use;
       m_run = m_new;
-      l_run *= corr;
-      dn_run *= corr;
+      // The tile's sums first, then the running ones: D enters every dz of the row, and what it is off by
+      // comes back, times 1 / w, where a chunk is next to its threshold.  (All keys in one chain: the bias
+      // gradients of a row of 1152 keys, which cancel, add up to 1e-6 instead of 6e-8.)
+      float l_tile = 0.f, dn_tile = 0.f;
       auto e_quad = [&](int kt, int q4) {
         if (q4 < 0) return;
 #pragma unroll
         for (int j = 4 * q4; j < 4 * q4 + 4; j++) {
           s[kt][j] = __builtin_amdgcn_exp2f(fmaf(s[kt][j], a.c1, off));
-          l_run += s[kt][j];
+          l_tile += s[kt][j];
         }
       };
       auto n_quad = [&](int kt, int q4) {
         if (q4 < 0) return;
 #pragma unroll
-        for (int j = 4 * q4; j < 4 * q4 + 4; j++) dn_run = fmaf(s[kt][j], dp[kt][j], dn_run);
+        for (int j = 4 * q4; j < 4 * q4 + 4; j++) dn_tile = fmaf(s[kt][j], dp[kt][j], dn_tile);
       };
       dp[0] = product(vb, dof, 0, [&](int i) { e_quad(0, quad_at(i)); });
       dp[1] = product(vb, dof, 1, [&](int i) { e_quad(1, quad_at(i)); n_quad(0, quad_at(i)); });
 #pragma unroll
       for (int q4 = 0; q4 < 4; q4++) n_quad(1, q4);
+      l_run = fmaf(l_run, corr, l_tile);
+      dn_run = fmaf(dn_run, corr, dn_tile);
     } else {
       const float off = bias_row - lse2;
       u32x4 pb[4];

@@ -97,8 +97,9 @@ BACKWARD = [
     ("b_257_mha", 2, 2, 2, 257, 64, 64, {"offset_sigma": 0.8}),
     ("b_193_b128", 1, 8, 1, 193, 128, 128, {"offset_sigma": 0.8}),
     ("b_parts_g16_d64", 1, 16, 1, 1037, 64, 64, {"offset_sigma": 0.8, "gamma": 2.0}),
-    # 1280 tokens: among the 4608 rows of 1152 tokens one has a routed chunk so close to its threshold that its
-    # gradient is not determined to 2e-2: du / u with du = 6e-8 (the rounding of tau) and 1/w = 1/u^2
+    # among the 4608 rows of 1152 tokens one keeps a chunk 3e-6 above its threshold: 1/w = 1e11 there, and the chunk's
+    # own bias gradient is 0 less the mean of all, so that its row shows what the mean is off by
+    ("b_parts_noncausal_b128_near", 1, 4, 1, 1152, 128, 128, {"offset_sigma": 0.8, "causal": False}),
     ("b_parts_noncausal_b128", 1, 4, 1, 1280, 128, 128, {"offset_sigma": 0.8, "causal": False}),
     ("b_window3_alpha125_g2", 1, 2, 1, 831, 64, 64, {"offset_sigma": 0.8, "alpha": 1.25, "window": 3}),
     ("f_17", 1, 2, 1, 17, 64, 64, {"dtype": "fp32"}),
