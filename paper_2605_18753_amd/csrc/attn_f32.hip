@@ -178,12 +178,11 @@ __global__ __launch_bounds__(512) void s2_f32_kernel(S2FArgs a) {
 #pragma unroll
       for (int i = 0; i < C::NS; i++) o[i] *= corr;
 #pragma unroll
-      for (int st = 0; st < SUB; st++)
+      for (int st = 0; st < SUB; st++) {
 #pragma unroll
-        for (int t = 0; t < 4; t++) {
-          s[st][t] = exp_diff(s[st][t], m_use);
-          l_run += s[st][t];
-        }
+        for (int t = 0; t < 4; t++) s[st][t] = exp_diff(s[st][t], m_use);
+        l_run += (s[st][0] + s[st][1]) + (s[st][2] + s[st][3]);
+      }
       mma_outer_keys<D, SUB>(vr, s, lim, ntok, a.g_q, lane, o);
     }
   }
@@ -347,14 +346,14 @@ __global__ __launch_bounds__(256, 2) void bwd_f32_row_kernel(BwdArgs a, RowF32 x
         const float m_use = mx == -INFINITY ? 0.f : mx;
         const float corr = exp_diff(m_run, m_use);
         m_run = mx;
-        l_run *= corr;
-        dn_run *= corr;
+        float dn = 0.f;
 #pragma unroll
         for (int v = 0; v < 4; v++) {
-          const float p = exp_diff(s[v], m_use);
-          l_run += p;
-          dn_run = fmaf(p, v > lim ? 0.f : dp[v], dn_run);
+          s[v] = exp_diff(s[v], m_use);
+          dn = fmaf(s[v], v > lim ? 0.f : dp[v], dn);
         }
+        l_run = fmaf(l_run, corr, (s[0] + s[1]) + (s[2] + s[3]));
+        dn_run = fmaf(dn_run, corr, dn);
       } else {
 #pragma unroll
         for (int t = 0; t < 4; t++) {

@@ -335,13 +335,14 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
       const int g = i / NDT, t = i % NDT;
       return lds_read_tr_pair(vb + v_rd[t] + (16 * g) * C::ROW_BYTES, vb + v_rd[t] + (16 * g + 8) * C::ROW_BYTES);
     };
+    float l_tile = 0.f;   // summed by the tile: one chain over all keys of a long row loses digits
     // exponential pair k of tile i - 1: P^T slots 2 (k % 4), + 1 of contraction step g = k / 4
     auto e_pair = [&](int k) {
       const int g = k >> 2, kt = g >> 1, j = 8 * (g & 1) + 2 * (k & 3);
       const float p0 = __builtin_amdgcn_exp2f(fmaf(so[kt][j], a.c1, off));
       const float p1 = __builtin_amdgcn_exp2f(fmaf(so[kt][j + 1], a.c1, off));
-      l_run += p0 + p1;
-      asm volatile("" : "+v"(l_run));   // keeps the row-sum update in its slot
+      l_tile += p0 + p1;
+      asm volatile("" : "+v"(l_tile));   // keeps the row-sum update in its slot
       const bf16x2 w = {(__bf16)p0, (__bf16)p1};
       pb[g][k & 3] = __builtin_bit_cast(uint32_t, w);
     };
@@ -428,6 +429,7 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
 #pragma unroll
       for (int q = 0; q < 8; q++) max_quad(q);
     }
+    l_run += l_tile;
     // this lane half's max of the base-2 logits s c1 + bias (c1 > 0)
     tmax_old = fmaf(mloc, a.c1, bias_row);
     bias_old = bias_row;
