@@ -233,3 +233,46 @@ def test_routing_needs_no_room_for_records():
     torch.cuda.synchronize()
     for name in ("mask", "cnt", "idx", "tau"):
         assert torch.equal(getattr(lists, name), getattr(run.lists, name)), name
+
+
+# Tensors in other layouts: tokens before heads, and heads of a larger padded buffer.  The kernels read and write
+# the same values in the same order, so the results are those of contiguous tensors, bit for bit.
+@pytest.mark.parametrize("layout", ["token_major", "padded"])
+@pytest.mark.parametrize("name,h_q,h_kv,n_q,n_kv,d,block,extra", [
+    ("cut_lists_g4", 8, 2, 65, 64 * 150 + 65, 128, 64, {}), ("cut_lists_g1_d64", 2, 2, 130, 64 * 70 + 130, 64, 64, {"window": 2}),
+    ("cut_lists_g16_b128", 16, 1, 9, 128 * 40 + 64 + 9, 128, 128, {"gamma": 2.0}),
+    ("decode_in_place", 8, 2, 1, 1000, 128, 64, {}), ("decode_scores_apart", 4, 1, 1, 641 * 64 + 5, 64, 64, {"gamma": 1.5}),
+    ("decode_scores_apart_g16", 16, 1, 1, 400 * 128 + 3, 128, 128, {"gamma": 2.0}), ("decode_one_split", 4, 1, 1, 300, 64, 64, {})])
+def test_other_layouts(layout, name, h_q, h_kv, n_q, n_kv, d, block, extra):
+    batch = 260 if name == "decode_one_split" else 2
+    w = Workload("edge_layout_" + name, batch, h_q, h_kv, n_q, n_kv, d, block, offset_sigma=0.7, seed=55, **extra)
+    q, k, v = make_inputs(w, DEV)
+
+    def relaid(t):
+        b, h, n, _ = t.shape
+        if layout == "token_major":
+            out = torch.empty(b, n, h, d, dtype=t.dtype, device=DEV).transpose(1, 2)
+        else:
+            out = torch.full((b + 1, h + 1, n + 24, d), float("nan"), dtype=t.dtype, device=DEV)[1:, 1:, 16:16 + n]
+        return out.copy_(t)
+
+    def results(q, k, v):
+        o, dense = relaid(torch.zeros_like(q)), relaid(torch.zeros_like(q))
+        if q.is_contiguous():
+            o, dense = torch.empty_like(q), torch.empty_like(q)
+        p = B.make_params(q, k, v, o, block, w.alpha, w.gamma, w.sigma, True, window=w.window)
+        kbar = torch.empty(B.kbar_shape(p), dtype=torch.float32, device=DEV)
+        lists, ws = B.Lists.allocate(p, DEV), B.alloc_workspace(p, DEV)
+        if n_q == 1:
+            B.dash_kbar_compress(p, k, kbar)
+            B.dash_attn_decode(p, q, k, v, kbar, o, lists, ws)
+        else:
+            B.dash_attn_prefill(p, q, k, v, o, kbar, lists, ws)
+        B.dense_attn(p, q, k, v, dense, ws)
+        torch.cuda.synchronize()
+        return dict(o=o, dense=dense, kbar=kbar, mask=lists.mask, cnt=lists.cnt, tau=lists.tau)
+
+    want, got = results(q, k, v), results(relaid(q), relaid(k), relaid(v))
+    for key in want:
+        assert torch.equal(got[key], want[key]), key
+    assert bool(torch.isfinite(want["o"].float()).all())
