@@ -17,9 +17,10 @@
  *     allocates no device memory, never synchronises, reads no environment
  *     variable, and enqueues all work on `stream` (a hipStream_t passed as void*;
  *     NULL = the default stream).  Nothing a call computes depends on an earlier
- *     call: the only thing the library remembers is, per device, that a kernel's
- *     one-time opt-in to a large dynamic LDS size has been made (thread-safe), and the
- *     address of the scratch array of dash_attn_decode_static.
+ *     call: what the library remembers is, per device, that a kernel's
+ *     one-time opt-in to a large dynamic LDS size has been made (thread-safe) and the
+ *     address of the scratch array of dash_attn_decode_static, and, per process, a counter
+ *     that gives the split flags of every decode step a number of their own.
  *     Entry points may be called from several threads.
  *   - Tensors are [batch, head, token, head_dim] with head_dim contiguous; the
  *     other three strides are given in ELEMENTS in dash_params.  Rows must be
@@ -40,6 +41,11 @@
  *     chunk is a candidate, there is no diagonal branch, and n_kv must be a
  *     multiple of block_size (dense_attn and the size queries accept any n_kv).
  *   - kbar pointers may be NULL when n_kv < block_size (no complete chunk).
+ *   - NaN and infinities: with fp32 tensors one in a token reaches what attends that token (and,
+ *     through a chunk's summary, what routes over the chunk) and nothing else.  The bf16 kernels
+ *     multiply the keys and values of a chunk by a weight of 0 for the tokens of a row tile that did
+ *     not keep it, so one in k, v, q or d_o can reach the other tokens of its tile.  Rows outside
+ *     the n_q / n_kv of a call are never multiplied, whatever the buffer holds between the heads.
  *   - Limits of this build (DASH_EUNSUPPORTED beyond them): at most 2048 chunks per
  *     sequence, ceil(n_kv / block_size) <= 2048 (131072 tokens at chunks of 64, 262144 at
  *     128); a call with several queries (n_q > 1) that continues a longer cache must start
@@ -103,8 +109,9 @@ int32_t dash_mask_words(const dash_params* p);
  * call, dense_attn included, so it accepts what any of them accepts: a non-causal n_kv
  * that is not a multiple of block_size gets a size here and DASH_EINVAL from the
  * routing calls (a tail chunk has no summary), which dense_attn does not need.
- * A workspace made for the largest call serves the smaller ones: a decode step whose size includes
- * score rows that the workspace has no room for runs without them. */
+ * A workspace made for the largest call serves the smaller ones (the size of a bf16 prefill rises with
+ * its queries, keys and sequences, and has room for the partial results of every smaller one): a decode step
+ * whose size includes score rows that the workspace has no room for runs without them. */
 int dash_attn_workspace_bytes(const dash_params* p, size_t* out_bytes);
 
 /* Stage 0 (Eq. 3 at zero summary query = uniform mean; Alg. 1).
@@ -181,7 +188,8 @@ int dash_attn_prefill(const dash_params* p, const void* q, const void* k,
  * results (Sec. 3.5).  kbar_cache is in/out: if the current token completes a
  * chunk (n_kv % block_size == 0) that chunk's summary is written by the same
  * launch that routes (it is the query's own chunk, not a candidate of this
- * step); the other entries are read only.  List outputs optional as above. */
+ * step); the other entries are read only.  List outputs optional as above (mask and
+ * biases that are not asked for stay in the workspace for dash_stage2_attend). */
 int dash_attn_decode(const dash_params* p, const void* q, const void* k_cache,
                      const void* v_cache, float* kbar_cache, void* o,
                      uint32_t* mask, int32_t* blk_cnt, int32_t* blk_idx,
@@ -192,7 +200,7 @@ int dash_attn_decode(const dash_params* p, const void* q, const void* k_cache,
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same step with the same kernels and the same results, except that the scratch
  * (attended-chunk lists when not asked for, split-KV partial results)
- * lives in an 8 MiB array inside the library, one per GPU, held until the process ends.
+ * lives in an array of 8 MiB (and 4 KiB of split flags) inside the library, one per GPU, held until the process ends.
  * The call allocates nothing.  DASH_EWORKSPACE if lists and partial results exceed
  * 8 MiB (the 128k-token decode step of 16 sequences x 8 kv-heads needs 2.1 MiB).
  * Every call on a GPU uses that GPU's one array: calls that overlap on one GPU (different
@@ -258,10 +266,10 @@ int dense_attn(const dash_params* p, const void* q, const void* k, const void* v
  * For alpha > 2 the entmax slope is unbounded at the edge of the support, so rows
  * with a chunk close to its threshold have gradients only as accurate as the fp32
  * scores allow; alpha <= 3 only (checked against the oracle up to there;
- * DASH_EUNSUPPORTED above).  n_q == n_kv only (DASH_EUNSUPPORTED otherwise).  bf16 tensors take the matrix-core
- * kernels; fp32 tensors take plain fp32 kernels that accumulate dk and dv with
- * atomics (a correctness vehicle like the fp32 forward, sums in no fixed order);
- * DASH_EINVAL for a NULL pointer. */
+ * DASH_EUNSUPPORTED above).  n_q == n_kv only (DASH_EUNSUPPORTED otherwise).  bf16 tensors: bf16
+ * matrix products with fp32 sums, added in a fixed order; fp32 tensors: products and sums in fp32
+ * (fp32 matrix cores), where the parts that a small problem is cut into are added with atomics, in no
+ * fixed order.  DASH_EINVAL for a NULL pointer. */
 int dash_attn_backward_workspace_bytes(const dash_params* p, size_t* out_bytes);
 int dash_attn_backward(const dash_params* p, const void* q, const void* k, const void* v,
                        const void* d_o, const float* kbar,

@@ -14,8 +14,8 @@
 // partial sums), whatever the tiling; about one tile in twenty has one.
 //
 // What bounds it: L2 reads of the summaries (16 KB per 16 rows and 16 chunks at d = 128), and the
-// fp32 matrix rate.  Training-shaped workload (4 x 16 heads x 8192 tokens): 1.33 ms with one wave
-// per token and fp32 FMAs on 8 lanes per summary row -> 0.58 ms.
+// fp32 matrix rate (its pipe 12 % busy per wave).  Training-shaped workload (4 x 16 heads x 8192 tokens): 1.33 ms with one wave
+// per token and fp32 FMAs on 8 lanes per summary row -> 0.62-0.65 ms.
 #include <math.h>
 
 #include "backward_args.h"
