@@ -34,6 +34,17 @@ namespace dash {
 // number of parts of a key tile whose rows are nT 32-row tiles
 __host__ __device__ inline int kv_parts(int nT, int steps_per_part) { return nT <= steps_per_part ? 1 : (nT + steps_per_part - 1) / steps_per_part; }
 
+// The parts of a summary's gradient at p0, added in order; all loads in flight together.
+constexpr int kMaxKbarParts = 16;
+template <typename V> __device__ __forceinline__ V kbar_sum(const BwdArgs& a, const float* p0) {
+  V x[kMaxKbarParts], sum = V{};
+#pragma unroll
+  for (int p = 0; p < kMaxKbarParts; p++) x[p] = p < a.kb_parts ? *reinterpret_cast<const V*>(p0 + p * a.kb_stride) : V{};
+#pragma unroll
+  for (int p = 0; p < kMaxKbarParts; p++) sum += x[p];
+  return sum;
+}
+
 // TAIL: several heads and a last row tile that is not full.  The rows behind its last token are then copied as
 // zeros: the buffer resources reach over what lies between the heads (the padding of a larger buffer, another
 // head's rows), and 0 times what it holds could be a NaN.  In every launch the selection costs 0.5 % at d = 128
@@ -280,11 +291,19 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
       }
     return;
   }
+  // block-mean summaries: every key of a complete chunk receives 1/B of the chunk's dkbar, whose parts are added
+  // up once per workgroup (key by key, one load after the other, it took 30 us at 16 parts)
+  float* kbs = reinterpret_cast<float*>(lds);       // [2 chunks][D]
+  if (!a.dkbar_out) {
+    __syncthreads();                                // nobody reads the tiles any more
+    for (int i = tid; i < 2 * D; i += 256) {
+      const int cc = i < D ? c0 : c1;
+      kbs[i] = cc < a.t_c ? kbar_sum<float>(a, a.dkbar + ((int64_t)hbi * a.t_c + cc) * D + i % D) / (float)a.block : 0.f;
+    }
+    __syncthreads();
+  }
   if (my_key >= a.n_kv) return;
-  // block-mean summaries: every key of a complete chunk receives 1/B of the chunk's dkbar
   const bool fold = c < a.t_c && !a.dkbar_out;
-  const float kscale = 1.f / (float)a.block;
-  const float* kbp = a.dkbar + ((int64_t)hbi * a.t_c + c) * D;
   uint16_t* dkp = a.dk + b * a.ks_b + r * a.ks_h + (int64_t)my_key * a.ks_t;
   uint16_t* dvp = a.dv + b * a.vs_b + r * a.vs_h + (int64_t)my_key * a.vs_t;
 #pragma unroll
@@ -293,10 +312,7 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
     for (int q4 = 0; q4 < 4; q4++) {
       const int d0 = t * 32 + q4 * 8 + h * 4;
       f32x4 kg = {0.f, 0.f, 0.f, 0.f};
-      if (fold) {
-        for (int p = 0; p < a.kb_parts; p++) kg += *reinterpret_cast<const f32x4*>(kbp + p * a.kb_stride + d0);
-        kg *= kscale;
-      }
+      if (fold) kg = *reinterpret_cast<const f32x4*>(kbs + (wave < 2 ? 0 : D) + d0);
       float kv[4];
 #pragma unroll
       for (int i = 0; i < 4; i++) kv[i] = fmaf(dkacc[t][q4 * 4 + i], a.scale, kg[i]);
@@ -322,14 +338,13 @@ __global__ __launch_bounds__(256) void bwd_kv_reduce_kernel(BwdArgs a) {
   if (parts == 1 || key >= a.n_kv) return;
   const float* pk = a.kv_part + ((int64_t)ktile * a.hb + hbi) * a.kv_max_parts * (2 * 128 * D) + kl * D + d0;
   f32x4 dk = {0.f, 0.f, 0.f, 0.f}, dv = dk, kgr = dk;
+#pragma unroll 4
   for (int p = 0; p < parts; p++) {
     dk += *reinterpret_cast<const f32x4*>(pk + (int64_t)p * (2 * 128 * D));
     dv += *reinterpret_cast<const f32x4*>(pk + (int64_t)p * (2 * 128 * D) + 128 * D);
   }
-  if (c < a.t_c && !a.dkbar_out) {
-    for (int p = 0; p < a.kb_parts; p++) kgr += *reinterpret_cast<const f32x4*>(a.dkbar + p * a.kb_stride + ((int64_t)hbi * a.t_c + c) * D + d0);
-    kgr *= 1.f / (float)a.block;
-  }
+  if (c < a.t_c && !a.dkbar_out)
+    kgr = kbar_sum<f32x4>(a, a.dkbar + ((int64_t)hbi * a.t_c + c) * D + d0) * (1.f / (float)a.block);
   float kv[4];
 #pragma unroll
   for (int i = 0; i < 4; i++) kv[i] = fmaf(dk[i], a.scale, kgr[i]);
@@ -453,7 +468,7 @@ void bwd_kv_plan(BwdArgs& a) {
   }
   const int64_t groups = (int64_t)((a.t_c + 15) / 16) * a.hb;
   const int64_t p = groups > 0 ? 1024 / groups : 1;
-  a.kb_parts = p < 1 ? 1 : (p > 16 ? 16 : (int)p);
+  a.kb_parts = p < 1 ? 1 : (p > kMaxKbarParts ? kMaxKbarParts : (int)p);
   a.kb_stride = (int64_t)a.hb * a.t_c;      // x head_dim, set by the caller
 }
 
