@@ -45,11 +45,6 @@
 
 namespace dash {
 
-__global__ void bwd_fill_zero_kernel(uint32_t* p, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    p[i] = 0u;
-}
-
 // ---------------------------------------------------------------------------
 // Row-owner kernel.
 // ---------------------------------------------------------------------------
@@ -78,6 +73,12 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
   const int tokw = 32 / a.g_q;
   const int tok_w0 = tile * 4 * tokw + wave * tokw;
   const int nsub = a.block >> 6;
+
+  // the column masks that the second walk sets bits of: cleared by the first (a launch of its own took 4-5 us)
+  if constexpr (!GRAD) {
+    const int64_t words = (int64_t)a.hb * a.t_all * a.cwords;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < words; i += (int64_t)gridDim.x * 256) a.colmask[i] = 0u;
+  }
 
   const int my_tok = tok_w0 + n / a.g_q;
   const int my_head = r * a.g_q + n % a.g_q;
@@ -441,12 +442,6 @@ template <int D> static hipError_t launch_bwd_t(const BwdArgs& a, hipStream_t st
   using C = BCfg<D>;
   static LdsOptIn done_lse, done_grad;
   hipError_t e;
-  {
-    const size_t nwords = (size_t)a.hb * a.t_all * a.cwords;
-    hipLaunchKernelGGL(bwd_fill_zero_kernel, dim3((unsigned)((nwords + 255) / 256 < 1024 ? (nwords + 255) / 256 : 1024)),
-                       dim3(256), 0, st, a.colmask, nwords);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
   {
     const size_t lds = 4 * C::TILE_BYTES + 5 * 64 * 4;
     auto kern = bwd_q_kernel<D, false>;
