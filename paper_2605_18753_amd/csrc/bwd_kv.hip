@@ -15,7 +15,7 @@
 // the matrix pipe, two workgroups (two waves per SIMD) per CU.  Measured on the training-shaped
 // workload (4 x 16 heads x 8192 tokens): 3.85 ms with 64 keys per workgroup, both operands of S and dP
 // in LDS, one tile buffer and dkbar in the same kernel -> 2.43 ms + 0.17 ms for dkbar; 2 x 16 / 4 heads x
-// 3001 tokens, d 64 (192 key tiles, cut into parts): 375 -> 180 + 20 + 12 us.
+// 3001 tokens, d 64 (192 key tiles, cut into parts): 375 -> 189 + 17 + 11 us.
 //
 // A launch with few key tiles cuts the row tiles of each into parts: fp32 partial sums go to the
 // workspace and bwd_kv_reduce_kernel adds them in a fixed order.
