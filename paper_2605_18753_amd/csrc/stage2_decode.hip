@@ -105,14 +105,25 @@ constexpr size_t kMaxScoreBytes = 66 * 1024;   // two workgroups per CU with the
 // summaries each at 64 B/clk) for groups of up to 4 heads, 32 n_cand for larger ones (their
 // v_mfma_f32_16x16x4 rate).  A launch of its own costs about 4 us = 10^4 clocks and pays beyond
 // that.
-static bool score_in_place(const Layout& L) {
-  return score_floats(L, L.g_q) * 4 <= kMaxScoreBytes && (L.splits == 1 || L.t_c <= (L.g_q > 4 ? 320 : 640));
+// The thresholds are solved in those workgroups too.  That is cheap except for alpha > 2, a bisection of some 25 evaluations
+// with a logarithm and an exponential per chunk: there only up to 64 row slots of 64 chunks per CU, beyond
+// which one workgroup of 16 waves per pair (dash_stage1_route's kernel, then the attention over its lists) is faster.
+// alpha 3, us per step, solved here / in a launch: 16 x 8 pairs of 30000 tokens, group of 4 (64 slots) 47 / 85; 4 x 4 of
+// 40000 (128) 60 / 40; 24 x 2 of 20000, group of 16 (256) 97 / 64; 4 x 2 of 65000, group of 8, scores in a launch of their own (256) 84 / 71.
+static bool solve_in_place(const dash_params& p, const Layout& L) {
+  if (L.pexp >= 1.f) return true;
+  int nj = 1;                                  // slots of 64 chunks a wave's registers are laid out for
+  while (nj * 64 < L.t_c) nj *= 2;
+  return L.g_q * nj * ((int64_t)p.batch * p.h_kv * L.splits > 256 ? 2 : 1) <= 64;
+}
+static bool score_in_place(const dash_params& p, const Layout& L) {
+  return solve_in_place(p, L) && score_floats(L, L.g_q) * 4 <= kMaxScoreBytes && (L.splits == 1 || L.t_c <= (L.g_q > 4 ? 320 : 640));
 }
 // Score rows of a launch of their own are kept in the workspace, for up to 48 MB of summaries;
 // beyond that streaming the summaries takes the time of a routing launch anyway (9 us), and
 // dash_stage1_route's kernel followed by the attention over its lists is as fast without the rows.
 bool decode_scores_apart(const dash_params& p, const Layout& L) {
-  if (p.dtype != DASH_BF16 || p.n_q != 1 || !p.causal || L.t_c <= 0 || score_in_place(L)) return false;
+  if (p.dtype != DASH_BF16 || p.n_q != 1 || !p.causal || L.t_c <= 0 || !solve_in_place(p, L) || score_in_place(p, L)) return false;
   return (size_t)p.batch * p.h_kv * L.t_c * p.head_dim * 4 < ((size_t)48 << 20);
 }
 
@@ -121,7 +132,7 @@ int decode_scores_ld(const Layout& L) { return ((L.t_c + 15) / 16) * 16; }
 // Whether the step fits the one-launch kernel with the workspace the caller has (ws_bytes).
 bool decode_route_applicable(const dash_params& p, const Layout& L, size_t ws_bytes) {
   if (p.dtype != DASH_BF16) return false;
-  return score_in_place(L) || (L.dec_scores && ws_bytes >= L.total);
+  return score_in_place(p, L) || (L.dec_scores && ws_bytes >= L.total);
 }
 
 hipError_t launch_decode_route(const dash_params& p, const Layout& L, const void* q, const void* k, const void* v, void* o,

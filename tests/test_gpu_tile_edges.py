@@ -30,6 +30,11 @@ DECODE = [
     ("g8_321_chunks_apart", 1, 8, 1, 321 * 64 + 1, 128, 64, {"gamma": 2.0}),
     ("g16_apart_d64_b128_alpha3", 1, 16, 1, 400 * 128, 64, 128, {"alpha": 3.0}),
     ("2047_candidates_g2_alpha2", 1, 2, 1, 131072, 64, 64, {"alpha": 2.0, "gamma": 1.5}),
+    # alpha > 2: up to 64 row slots per CU are solved in the attention's workgroups, more in a launch
+    ("alpha3_512_chunks_one_per_cu", 1, 8, 1, 512 * 64 + 1, 64, 64, {"alpha": 3.0}),
+    ("alpha3_513_chunks_in_a_launch", 1, 8, 1, 513 * 64 + 1, 64, 64, {"alpha": 3.0}),
+    ("alpha25_g4_512_chunks_two_per_cu", 8, 4, 1, 512 * 64 + 63, 64, 64, {"alpha": 2.5, "window": 1}),
+    ("alpha25_g8_257_chunks_in_a_launch", 8, 8, 1, 258 * 64, 64, 64, {"alpha": 2.5}),
     ("257_pairs_one_split", 257, 1, 1, 700, 64, 64, {}),
     ("171_pairs_alpha125", 57, 12, 3, 1500, 64, 64, {"alpha": 1.25, "window": 1}),
     ("alpha17_window8", 1, 4, 2, 3000, 128, 128, {"alpha": 1.7, "window": 8}),
