@@ -112,10 +112,6 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
                          (int64_t)(row_ok ? my_tok : a.n_q - 1) * a.qs_t + h * 8;
 #pragma unroll
     for (int ks = 0; ks < D / 16; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
-    // the loads must be complete (and known to be) before the tile loop: a wait for
-    // them inside the loop would also wait for the tile copies in flight
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) asm volatile("" : "+v"(qf[ks]));
   }
 
   // ---- chunk bitmaps -------------------------------------------------------
@@ -123,9 +119,10 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
   // bias list, and the next bias value (prefetched).
   const int trk_tok = tok_w0 + lane;
   const bool trk_ok = lane < tokw && trk_tok < a.n_q;
-  const int64_t trk_base = ((int64_t)b * a.h_kv + r) * a.n_q + (trk_ok ? trk_tok : 0);
+  const int64_t trk_base = ((int64_t)b * a.h_kv + r) * a.n_q + min(tok_w0, a.n_q - 1);   // uniform; a lane's row by offset
   const uint32_t* trk_mask = DENSE ? nullptr : a.mask + trk_base * a.words;
   const float* trk_bias = DENSE ? nullptr : a.bias + trk_base * a.t_all;
+  const uint32_t trk_m0 = trk_ok ? (uint32_t)(lane * a.words) : 0u, trk_b0 = trk_ok ? (uint32_t)(lane * a.t_all) : 0u;
   int trk_rank = 0, trk_wi = -1;
   uint32_t trk_word = 0;
   float trk_next = 0.f;
@@ -171,12 +168,12 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
       }
       for (; skip > 0; skip--) it_bits &= it_bits - 1u;
       if (!DENSE && trk_ok) {                   // the tracked token's entries before the part's first chunk
-        for (int wi = 0; wi < it_wi; wi++) trk_rank += __popc(trk_mask[wi]);
-        trk_rank += __popc(trk_mask[it_wi] & ((1u << __builtin_ctz(it_bits)) - 1u));
+        for (int wi = 0; wi < it_wi; wi++) trk_rank += __popc(trk_mask[trk_m0 + wi]);
+        trk_rank += __popc(trk_mask[trk_m0 + it_wi] & ((1u << __builtin_ctz(it_bits)) - 1u));
       }
     }
   }
-  if (!DENSE) trk_next = trk_bias[min(trk_rank, a.t_all - 1)];
+  if (!DENSE) trk_next = trk_bias[trk_b0 + min(trk_rank, a.t_all - 1)];
 
   // ---- tile iterator (workgroup-uniform) ---------------------------------
   int it_sub = nsub - 1, it_u = -1;
@@ -250,21 +247,22 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
   float bias_row = 0.f;   // bias * log2e of this lane's row for the current chunk
   bool wave_on = false, diag = false;
 
+  auto wave_has = [&](int u) -> bool {
+    return wave_ok && ((__builtin_amdgcn_readfirstlane(wvmask[wave * 64 + (u >> 5)]) >> (u & 31)) & 1u);
+  };
   auto begin_chunk = [&](int u) {
-    // decides participation and fetches the per-token bias of chunk u
-    wave_on = wave_ok && ((__builtin_amdgcn_readfirstlane(wvmask[wave * 64 + (u >> 5)]) >> (u & 31)) & 1u);
+    // fetches the per-token bias of chunk u, which one of the wave's tokens kept
     diag = a.causal && u == cw;
-    if (!wave_on) return;
     float bt = 0.f;
     if (!DENSE && !diag) {
-      if ((u >> 5) != trk_wi) { trk_wi = u >> 5; trk_word = trk_mask[trk_wi]; }
+      if ((u >> 5) != trk_wi) { trk_wi = u >> 5; trk_word = trk_mask[trk_m0 + trk_wi]; }
       const bool bit = trk_ok && ((trk_word >> (u & 31)) & 1u);
       bt = bit ? trk_next * kLog2e : -INFINITY;
       trk_rank += bit ? 1 : 0;
       // By every lane, whether its token kept the chunk or not: where only some load, the others' values are merged
       // right behind the load, and the wave waits for memory here instead of at the next chunk (32k prefill 8.64 ->
       // 8.24 ms, 2000 tokens against a 32k cache 735 -> 674 us, 16k with a group of 16 1.62 -> 1.54 ms).
-      trk_next = trk_bias[min(trk_rank, a.t_all - 1)];
+      trk_next = trk_bias[trk_b0 + min(trk_rank, a.t_all - 1)];
     }
     bias_row = __shfl(bt, n / a.g_q);
   };
@@ -283,6 +281,10 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
   // issued one at a time between the MFMAs: a burst right after the barrier would queue all waves
   // behind the 64 B/clk global -> LDS path.
   bool have = advance();
+  // the loads of Q, issued before those of the masks, must be complete (and known to be) before the tile
+  // loop: a wait for them inside the loop would also wait for the tile copies in flight
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++) asm volatile("" : "+v"(qf[ks]));
   if (have) {
     copy_begin(it_u, it_sub);
 #pragma unroll
@@ -298,12 +300,24 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
     const bool cur = have;
     const int cu = it_u, csub = it_sub;
     const bool more = cur && advance();
+    if (cur && csub == 0) wave_on = wave_has(cu);
+    const bool on = cur && wave_on;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    bool on = false;
-    if (cur) {
+    const char* kb = lds + P * C::TILE_BYTES;
+    const char* vb = lds + (2 + (P ^ 1)) * C::TILE_BYTES;
+    auto k_read = [&](int i) -> bf16x8 {   // slot i: d slice i / 2, key half i % 2
+      return *reinterpret_cast<const bf16x8*>(kb + k_rd[i >> 1] + (i & 1) * 32 * C::ROW_BYTES);
+    };
+    constexpr int KAHEAD = 4, VAHEAD = 2;
+    bf16x8 kf[NS];
+    // The first K operands are on their way while the tile is set up, and whether it is the wave's is asked before the
+    // barrier: the two LDS round trips behind it were 3 % of a tile (with the copies' branches and the order of Q and masks
+    // in the prologue: 32k prefill 8.24 -> 7.79 ms, 128k 95.6 -> 90.4, 1000 tokens 31.9 -> 29.8 us).
+    if (on) {
+#pragma unroll
+      for (int i = 0; i < KAHEAD; i++) kf[i] = k_read(i);
       if (csub == 0) begin_chunk(cu);
-      on = wave_on;
     }
     cp_v = cp_k_v;                                             // V of tile i
     if (more) copy_begin(it_u, it_sub);                        // K of tile i + 1
@@ -325,11 +339,6 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
       }
       off = bias_old - (m_run == -INFINITY ? 0.f : m_run);
     }
-    const char* kb = lds + P * C::TILE_BYTES;
-    const char* vb = lds + (2 + (P ^ 1)) * C::TILE_BYTES;
-    auto k_read = [&](int i) -> bf16x8 {   // slot i: d slice i / 2, key half i % 2
-      return *reinterpret_cast<const bf16x8*>(kb + k_rd[i >> 1] + (i & 1) * 32 * C::ROW_BYTES);
-    };
     auto v_read = [&](int i) -> bf16x8 {   // slot i: contraction step g = i / NDT, d-tile t = i % NDT
       const int g = i / NDT, t = i % NDT;
       return lds_read_tr_pair(vb + v_rd[t] + (16 * g) * C::ROW_BYTES, vb + v_rd[t] + (16 * g + 8) * C::ROW_BYTES);
@@ -347,16 +356,12 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
     };
     // copy instruction c of the iteration: K of tile i + 1, then V of tile i
     auto copies = [&](int c) {
-      if (c < C::COPIES) { if (more) copy_k(c, P ^ 1); }
-      else if (c < 2 * C::COPIES) { if (cur) copy_v(c - C::COPIES, P); }
+      if (c < C::COPIES) copy_k(c, P ^ 1);                     // behind the last tile: that tile again, into a slot nobody reads
+      else if (c < 2 * C::COPIES) copy_v(c - C::COPIES, P);
     };
-    constexpr int KAHEAD = 4, VAHEAD = 2;
     constexpr int EQ = 12;                                     // exponential pairs behind the first product
     auto first_product = [&](auto e_tag) {
       constexpr bool EXPS = decltype(e_tag)::value;
-      bf16x8 kf[NS];
-#pragma unroll
-      for (int i = 0; i < KAHEAD; i++) kf[i] = k_read(i);
 #pragma unroll
       for (int i = 0; i < NS; i++) {
         if (i + KAHEAD < NS) kf[i + KAHEAD] = k_read(i + KAHEAD);
@@ -395,8 +400,10 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
           }
       }
     } else {
+      if (cur) {
 #pragma unroll
-      for (int c = 0; c < 2 * C::COPIES; c++) copies(c);
+        for (int c = 0; c < 2 * C::COPIES; c++) copies(c);
+      }
       if (pend) {
 #pragma unroll
         for (int k = 0; k < EQ; k++) e_pair(k);
