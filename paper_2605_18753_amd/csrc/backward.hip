@@ -97,16 +97,15 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
     for (int ks = 0; ks < KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) dof[ks] = *reinterpret_cast<const bf16x8*>(dop + ks * 16);
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) asm volatile("" : "+v"(qf[ks]), "+v"(dof[ks]));
   }
 
   // ---- chunk bitmaps ---------------------------------------------------------
   const int trk_tok = tok_w0 + lane;
   const bool trk_ok = lane < tokw && trk_tok < a.n_q;
-  const int64_t trk_base = ((int64_t)b * a.h_kv + r) * a.n_q + (trk_ok ? trk_tok : 0);
+  const int64_t trk_base = ((int64_t)b * a.h_kv + r) * a.n_q + min(tok_w0, a.n_q - 1);   // uniform; a lane's row by offset
   const uint32_t* trk_mask = a.mask + trk_base * a.words;
   const float* trk_bias = a.bias + trk_base * a.t_all;
+  const uint32_t trk_m0 = trk_ok ? (uint32_t)(lane * a.words) : 0u, trk_b0 = trk_ok ? (uint32_t)(lane * a.t_all) : 0u;
   int trk_rank = 0, trk_wi = -1;
   uint32_t trk_word = 0;
   bool trk_has = false;
@@ -190,27 +189,25 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
     dsum = a.dsum[row];
     asm volatile("" : "+v"(lse2), "+v"(dsum));
   }
-  float trk_next = trk_ok ? trk_bias[0] : 0.f;
+  float trk_next = trk_bias[trk_b0];
+  float* biasd = a.biasd + trk_base * a.t_all;
+  float* dbd = a.dbd + trk_base * a.t_all;
   float bias_row = 0.f;
   bool wave_on = false, diag = false;
+  auto wave_has = [&](int u) -> bool {
+    return wave_ok && ((__builtin_amdgcn_readfirstlane(wvmask[wave * 64 + (u >> 5)]) >> (u & 31)) & 1u);
+  };
   auto begin_chunk = [&](int u) {
-    wave_on = wave_ok && ((__builtin_amdgcn_readfirstlane(wvmask[wave * 64 + (u >> 5)]) >> (u & 31)) & 1u);
     diag = a.causal && u == cw;
-    if (!wave_on) return;
     float bt = 0.f;
     trk_has = false;
     if (!diag) {
-      bt = -INFINITY;
-      if (trk_ok) {
-        if ((u >> 5) != trk_wi) { trk_wi = u >> 5; trk_word = trk_mask[trk_wi]; }
-        if ((trk_word >> (u & 31)) & 1u) {
-          trk_has = true;
-          bt = trk_next * kLog2e;
-          if (GRAD) a.biasd[trk_base * a.t_all + u] = trk_next;
-          trk_rank++;
-          if (trk_rank < a.t_all) trk_next = trk_bias[trk_rank];
-        }
-      }
+      if ((u >> 5) != trk_wi) { trk_wi = u >> 5; trk_word = trk_mask[trk_m0 + trk_wi]; }
+      trk_has = trk_ok && ((trk_word >> (u & 31)) & 1u);
+      bt = trk_has ? trk_next * kLog2e : -INFINITY;
+      if (GRAD) { if (trk_has) biasd[trk_b0 + u] = trk_next; }
+      trk_rank += trk_has ? 1 : 0;
+      trk_next = trk_bias[trk_b0 + min(trk_rank, a.t_all - 1)];   // by every lane: see s2_attend_kernel
     }
     bias_row = __shfl(bt, n / a.g_q);
   };
@@ -333,18 +330,33 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
 
   // ---- main loop: as in the forward kernel ------------------------------------------------
   bool have = advance();
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) asm volatile("" : "+v"(qf[ks]), "+v"(dof[ks]));   // landed before the copies are in flight
   if (have) {
     copy_begin(it_u, it_sub);
 #pragma unroll
     for (int c = 0; c < 2 * C::COPIES; c++) copy_one(c, 0);
   }
+  // the bias gradient of a chunk is stored behind the next barrier: before it, the wait for the copies would be one for the store
+  float db_out = 0.f;
+  int db_u = -1;
+  auto put_db = [&]() {
+    if constexpr (GRAD) {
+      if (db_u >= 0) dbd[trk_b0 + db_u] = db_out;
+      db_u = -1;
+    }
+  };
   auto iteration = [&](auto p_tag) {
     constexpr int P = decltype(p_tag)::value;
     const int cu = it_u, csub = it_sub;
     const bool more = advance();
+    if (csub == 0) wave_on = wave_has(cu);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's copies of the tile have landed
+    // the loads of the chunk before are known to have arrived, or a wait for them below would be one for the store
+    asm volatile("" : "+v"(trk_next), "+v"(trk_word));
     __syncthreads();
-    if (csub == 0) begin_chunk(cu);
+    put_db();
+    if (wave_on && csub == 0) begin_chunk(cu);
     if (more) copy_begin(it_u, it_sub);
     if (wave_on) {
       const int kpos0 = cu * a.block + csub * 64;
@@ -355,7 +367,8 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
         float tot = db_acc + __shfl_xor(db_acc, 32);
         for (int o = 1; o < a.g_q; o <<= 1) tot += __shfl_xor(tot, o);
         const float mine = __shfl(tot, (lane * a.g_q) & 31);
-        if (!diag && trk_ok && trk_has) a.dbd[trk_base * a.t_all + cu] = mine;
+        db_out = mine;
+        db_u = !diag && trk_has ? cu : -1;
         db_acc = 0.f;
       }
     } else if (more) {
@@ -369,6 +382,7 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
     if (!have) break;
     iteration(std::integral_constant<int, 1>{});
   }
+  put_db();
 
   // ---- outputs -----------------------------------------------------------------
   const float l_tot = l_run + __shfl_xor(l_run, 32);
