@@ -15,7 +15,9 @@
 // the matrix pipe, two workgroups (two waves per SIMD) per CU.  Measured on the training-shaped
 // workload (4 x 16 heads x 8192 tokens): 3.85 ms with 64 keys per workgroup, both operands of S and dP
 // in LDS, one tile buffer and dkbar in the same kernel -> 2.43 ms + 0.17 ms for dkbar; 2 x 16 / 4 heads x
-// 3001 tokens, d 64 (192 key tiles, cut into parts): 375 -> 189 + 17 + 11 us.
+// 3001 tokens, d 64 (192 key tiles, cut into parts): 375 -> 189 + 17 + 11 us.  Then, bwd_kv_kernel alone, both builds in
+turn: 2403 -> 2251 and 186 -> 168 us with the column masks' words loaded 32 row tiles ahead (two loads behind the barrier were
+waited for), the rows' scalars at 32-bit offsets, and no division per step.
 //
 // A launch with few key tiles cuts the row tiles of each into parts: fp32 partial sums go to the
 // workspace and bwd_kv_reduce_kernel adds them in a fixed order.
@@ -137,11 +139,15 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
   int it_wi = (T_beg >> 5) - 1;
   uint32_t it_bits = 0u, it_own = 0u;               // it_own: the bits of this wave's chunk
   bool it_on = false;
+  const int it_last = a.cwords - 1;
+  uint32_t it_n0 = cm0[min(it_wi + 1, it_last)], it_n1 = cm1[min(it_wi + 1, it_last)];   // the words of the next 32 row tiles
   auto next_step = [&]() -> int {
     while (it_bits == 0u) {
       it_wi++;
       if (it_wi * 32 >= T_end) return -1;
-      const uint32_t w0 = __builtin_amdgcn_readfirstlane(cm0[it_wi]), w1 = __builtin_amdgcn_readfirstlane(cm1[it_wi]);
+      const uint32_t w0 = __builtin_amdgcn_readfirstlane(it_n0), w1 = __builtin_amdgcn_readfirstlane(it_n1);
+      it_n0 = cm0[min(it_wi + 1, it_last)];
+      it_n1 = cm1[min(it_wi + 1, it_last)];
       it_own = wave < 2 ? w0 : w1;
       it_bits = w0 | w1;
       if (it_wi * 32 < T_beg) it_bits &= ~0u << (T_beg & 31);
@@ -156,15 +162,19 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
   uint32_t f_mask = 0u;
   float f_bias = 0.f, f_lse = 0.f, f_dsum = 0.f;
   int f_tok = 0;
+  const uint32_t* s_mask = a.mask + (int64_t)hbi * a.n_q * a.words + (c >> 5);
+  const float* s_bias = a.biasd + (int64_t)hbi * a.n_q * a.t_all + c;
+  const float* s_lse = a.lse + ((int64_t)b * a.h_q + r * a.g_q) * a.n_q;
+  const float* s_dsum = a.dsum + ((int64_t)b * a.h_q + r * a.g_q) * a.n_q;
+  const uint32_t s_head = (uint32_t)((n % a.g_q) * a.n_q);
+  const int tok_off = n / a.g_q, own0 = c * a.block;      // first token whose own chunk is c
   auto fetch = [&](int T) {
-    f_tok = T * tokw + n / a.g_q;
-    const int tk = min(f_tok, a.n_q - 1);
-    const int64_t trow = (int64_t)hbi * a.n_q + tk;
-    const int64_t hrow = ((int64_t)b * a.h_q + r * a.g_q + n % a.g_q) * a.n_q + tk;
-    f_mask = a.mask[trow * a.words + (c >> 5)];
-    f_bias = a.biasd[trow * a.t_all + c];           // meaningful only where the mask bit is set
-    f_lse = a.lse[hrow];
-    f_dsum = a.dsum[hrow];
+    f_tok = T * tokw + tok_off;
+    const uint32_t tk = (uint32_t)min(f_tok, a.n_q - 1);         // < 2^18: at most 2^11 chunks of 2^7 keys, 2^6 words
+    f_mask = s_mask[__umul24(tk, a.words)];
+    f_bias = s_bias[__umul24(tk, a.t_all)];         // meaningful only where the mask bit is set
+    f_lse = s_lse[s_head + tk];
+    f_dsum = s_dsum[s_head + tk];
   };
   float* sc = scal + wave * 64;                     // this wave's [bias - log-sum-exp][32], [D][32]
 
@@ -179,9 +189,10 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
   int slot = 0;
   while (T >= 0) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wave's copies of the step have landed
+    asm volatile("" : "+v"(it_n0), "+v"(it_n1), "+v"(f_mask), "+v"(f_bias), "+v"(f_lse), "+v"(f_dsum));   // and its loads
     if (lane < 32) {
       const bool bit = f_tok < a.n_q && ((f_mask >> (c & 31)) & 1u);
-      const bool isdiag = a.causal && c == f_tok / a.block;
+      const bool isdiag = a.causal && (uint32_t)(f_tok - own0) < (uint32_t)a.block;
       // bias - log-sum-exp in base-2 units (-inf: the row does not attend the chunk)
       sc[n] = bit ? (isdiag ? 0.f : f_bias * kLog2e) - f_lse : -INFINITY;
       sc[32 + n] = f_dsum;
@@ -222,7 +233,7 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
     // the key mask matters only where the rows' own chunk is this one, or at the end of the sequence
-    if ((a.causal && (tok0 + tokw - 1) / a.block >= c && tok0 / a.block <= c) || kpos0 + 128 > a.n_kv) {
+    if ((a.causal && tok0 + tokw > own0 && tok0 < own0 + a.block) || kpos0 + 128 > a.n_kv) {
 #pragma unroll
       for (int j = 0; j < 16; j++) {
         const int row = (j >> 2) * 8 + 4 * h + (j & 3);
