@@ -56,8 +56,8 @@ namespace dash {
 // What bounds it: the matrix and LDS pipes about equally (48 KB of operand reads per 48 MFMAs and
 // wave in the second walk).  Training-shaped workload (4 x 16 heads x 8192 tokens): 1.35 + 2.43 ms
 // with a single tile buffer (copy, wait, compute) and dO as an LDS operand -> 1.30 + 2.07 ms; then, both builds in turn,
-1266 -> 1184 and 2096 -> 2017 us (2 x 16 heads x 3001 tokens, d 64: 69 -> 64 and 107 -> 103) without the waits for the bias
-just asked for and for the bias gradient just stored.
+// 1266 -> 1184 and 2096 -> 2017 us (2 x 16 heads x 3001 tokens, d 64: 69 -> 64 and 107 -> 103) without the waits for the bias
+// just asked for and for the bias gradient just stored.
 template <int D, bool GRAD>
 __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
   using C = BCfg<D>;

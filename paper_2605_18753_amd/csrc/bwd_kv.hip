@@ -16,8 +16,8 @@
 // workload (4 x 16 heads x 8192 tokens): 3.85 ms with 64 keys per workgroup, both operands of S and dP
 // in LDS, one tile buffer and dkbar in the same kernel -> 2.43 ms + 0.17 ms for dkbar; 2 x 16 / 4 heads x
 // 3001 tokens, d 64 (192 key tiles, cut into parts): 375 -> 189 + 17 + 11 us.  Then, bwd_kv_kernel alone, both builds in
-turn: 2403 -> 2251 and 186 -> 168 us with the column masks' words loaded 32 row tiles ahead (two loads behind the barrier were
-waited for), the rows' scalars at 32-bit offsets, and no division per step.
+// turn: 2403 -> 2251 and 186 -> 168 us with the column masks' words loaded 32 row tiles ahead (two loads behind the barrier were
+// waited for), the rows' scalars at 32-bit offsets, and no division per step.
 //
 // A launch with few key tiles cuts the row tiles of each into parts: fp32 partial sums go to the
 // workspace and bwd_kv_reduce_kernel adds them in a fixed order.
