@@ -15,7 +15,9 @@
 //
 // What bounds it: L2 reads of the summaries (16 KB per 16 rows and 16 chunks at d = 128), and the
 // fp32 matrix rate (its pipe 12 % busy per wave).  Training-shaped workload (4 x 16 heads x 8192 tokens): 1.33 ms with one wave
-// per token and fp32 FMAs on 8 lanes per summary row -> 0.62-0.65 ms.
+// per token and fp32 FMAs on 8 lanes per summary row -> 616 us -> 502 with the registers bounded and mask, bias gradient, q and
+// tau asked for a tile or a walk ahead (both builds in turn); 24000 tokens, 8 / 2 heads, d 128 and 64: 673 -> 522, 371 -> 259 us;
+// 2 x 16 / 4 heads x 3001 tokens of d 64 (at most three tiles a row): 33 us both.
 #include <math.h>
 
 #include "backward_args.h"
@@ -294,10 +296,18 @@ template <int D> __device__ __forceinline__ float near_margin(const uint16_t* q,
   return fmaf(x, xscale, -tau);
 }
 
+typedef f32x4 f32x4u __attribute__((aligned(4)));
+
 constexpr int kKeepTiles = 16;   // margin tiles kept in LDS: 1 KB each and wave
 
+// Waves per SIMD that the registers have to leave room for.  Without a bound the accumulators of both products
+// are kept twice (109 + 64 registers at d = 128: two waves): KEEP takes 126 then, without a spill; rows of more
+// than 256 chunks 168 with four spilled, which is still better than 178 and two waves (20001 tokens, 4 heads,
+// d 128: 280 us without a bound and the loads ahead, 217 with two waves, 192 with three).
+constexpr int kRouteWaves = 4, kRouteWavesLong = 3;
+
 template <int D, int G, bool KEEP>
-__global__ __launch_bounds__(256) void bwd_route_kernel(BwdArgs a, int n_tiles, int keep_tiles) {
+__global__ __launch_bounds__(256, KEEP ? kRouteWaves : kRouteWavesLong) void bwd_route_kernel(BwdArgs a, int n_tiles, int keep_tiles) {
   using C = F32Cfg<D>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -319,26 +329,38 @@ __global__ __launch_bounds__(256) void bwd_route_kernel(BwdArgs a, int n_tiles, 
   const float* dbrow = a.dbd + trow * a.t_all;
   float* dxrow = a.dxd + hrow * a.t_all;
   const float* kb = a.kbar + ((int64_t)b * a.h_kv + r) * a.t_c * D;
-  const bool vec = (a.t_all & 3) == 0;        // 16-byte aligned chunk-indexed rows
+  const bool wide = a.t_all >= 4;             // a row has four chunks to read at once, at whatever alignment of 4 bytes
 
   f32x4 dq[C::NS];
 #pragma unroll
   for (int i = 0; i < C::NS; i++) dq[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // this lane's four chunks of tile ct: mask bits, and the bias gradient where they are set
-  auto bits_of = [&](int ct) -> uint32_t {
-    const uint32_t f = (mrow[ct >> 1] >> (16 * (ct & 1) + 4 * hq)) & 15u;
+  // this lane's four chunks of a tile: mask bits, and the bias gradient where they are set.  Every lane loads, from
+  // inside its row whatever the tile, and one tile ahead: a load under a condition is waited for where it is merged.
+  struct Raw { uint32_t word; f32x4 db; };
+  auto raw_of = [&](int ct) -> Raw {
+    Raw x;
+    x.word = mrow[ct >> 1];
+    const int c = ct * 16 + 4 * hq;
+    if (wide) {
+      x.db = *reinterpret_cast<const f32x4u*>(dbrow + min(c, a.t_all - 4));
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; i++) x.db[i] = dbrow[min(c + i, a.t_all - 1)];
+    }
+    return x;
+  };
+  auto bits_in = [&](int ct, const Raw& x) -> uint32_t {
+    const uint32_t f = (x.word >> (16 * (ct & 1) + 4 * hq)) & 15u;
     const int left = n_cand - (ct * 16 + 4 * hq);
     return left >= 4 ? f : (left <= 0 ? 0u : f & ((1u << left) - 1u));
   };
-  auto db_of = [&](int ct, uint32_t bits) -> f32x4 {
-    const float* p = dbrow + ct * 16 + 4 * hq;
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (vec && bits) v = *reinterpret_cast<const f32x4*>(p);
+  auto db_in = [&](int ct, const Raw& x, uint32_t bits) -> f32x4 {
+    f32x4 v = x.db;
+    const int ahead = wide ? ct * 16 + 4 * hq - (a.t_all - 4) : 0;           // > 0: read from that many chunks before
+    if (ahead & 1 && ahead > 0) v = f32x4{v[1], v[2], v[3], 0.f};
+    if (ahead & 2 && ahead > 0) v = f32x4{v[2], v[3], 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      if (!vec && ((bits >> i) & 1u)) v[i] = p[i];
-      if (!((bits >> i) & 1u)) v[i] = 0.f;
-    }
+    for (int i = 0; i < 4; i++) v[i] = ((bits >> i) & 1u) ? v[i] : 0.f;      // not written where the bit is not set
     return v;
   };
   // dx of all candidates, zero where not routed (the summary gradient reads them all)
@@ -346,18 +368,30 @@ __global__ __launch_bounds__(256) void bwd_route_kernel(BwdArgs a, int n_tiles, 
     if (!row_ok) return;
     float* p = dxrow + ct * 16 + 4 * hq;
     const int left = n_cand - (ct * 16 + 4 * hq);
-    if (vec && left >= 4) {
-      *reinterpret_cast<f32x4*>(p) = dx;
+    if (left >= 4) {
+      *reinterpret_cast<f32x4u*>(p) = dx;
     } else {
 #pragma unroll
       for (int i = 0; i < 4; i++)
         if (i < left) p[i] = dx[i];
     }
   };
+  // what the second walk starts with arrives during the first
+  const uint16_t* qrow = a.q + b * a.qs_b + (int64_t)r * G * a.qs_h;
+  uint2 qw[C::NS];
+  {
+    const uint16_t* qp = qrow + (n % G) * a.qs_h + (int64_t)tok * a.qs_t + 4 * hq;
+#pragma unroll
+    for (int s = 0; s < C::NS; s++) qw[s] = *reinterpret_cast<const uint2*>(qp + 16 * s);
+  }
+  const float tau = a.tau[hrow];
   float dsum = 0.f, cnt = 0.f;
+  Raw nx = raw_of(0);
   for (int ct = 0; ct < nct; ct++) {
-    const uint32_t bits = bits_of(ct);
-    const f32x4 db = db_of(ct, bits);
+    const Raw x = nx;
+    nx = raw_of(ct + 1 < nct ? ct + 1 : 0);
+    const uint32_t bits = bits_in(ct, x);
+    const f32x4 db = db_in(ct, x, bits);
     dsum += (db[0] + db[1]) + (db[2] + db[3]);
     cnt += (float)__popc(bits);
   }
@@ -367,16 +401,8 @@ __global__ __launch_bounds__(256) void bwd_route_kernel(BwdArgs a, int n_tiles, 
 
   if (__any(cnt > 0.f)) {
     f32x4 qf[C::NS];
-    const uint16_t* qrow = a.q + b * a.qs_b + (int64_t)r * G * a.qs_h;
-    {
-      const uint16_t* qp = qrow + (n % G) * a.qs_h + (int64_t)tok * a.qs_t + 4 * hq;
 #pragma unroll
-      for (int s = 0; s < C::NS; s++) {
-        const uint2 w = *reinterpret_cast<const uint2*>(qp + 16 * s);
-        qf[s] = f32x4{bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y)};
-      }
-    }
-    const float tau = a.tau[hrow];
+    for (int s = 0; s < C::NS; s++) qf[s] = f32x4{bf16_lo(qw[s].x), bf16_hi(qw[s].x), bf16_lo(qw[s].y), bf16_hi(qw[s].y)};
     auto margins = [&](int ct, uint32_t bits) -> f32x4 {
       f32x4 kf[C::NS];
       load_row<D>(kb + (int64_t)min(ct * 16 + n, n_cand - 1) * D, hq, kf);
@@ -410,9 +436,11 @@ __global__ __launch_bounds__(256) void bwd_route_kernel(BwdArgs a, int n_tiles, 
     };
     float s0 = 0.f, s1 = 0.f;
     for (int ct = 0; ct < nct; ct++) {
-      const uint32_t bits = bits_of(ct);
+      const Raw x = nx;
+      nx = raw_of(ct + 1 < nct ? ct + 1 : 0);
+      const uint32_t bits = bits_in(ct, x);
       if (!__any(bits != 0u)) continue;
-      const f32x4 db = db_of(ct, bits), u = margins(ct, bits);
+      const f32x4 db = db_in(ct, x, bits), u = margins(ct, bits);
       if constexpr (KEEP) kept[ct * 64] = u;
       f32x4 g, dwh;
       terms(u, db, bits, g, dwh);
@@ -423,12 +451,14 @@ __global__ __launch_bounds__(256) void bwd_route_kernel(BwdArgs a, int n_tiles, 
     s1 = quad_rows_sum(s1);
     const float ratio = s0 > 0.f ? s1 / s0 : 0.f;
     for (int ct = 0; ct < nct; ct++) {
-      const uint32_t bits = bits_of(ct);
+      const Raw x = nx;
+      nx = raw_of(ct + 1 < nct ? ct + 1 : 0);
+      const uint32_t bits = bits_in(ct, x);
       if (!__any(bits != 0u)) { put_dx(ct, f32x4{0.f, 0.f, 0.f, 0.f}); continue; }
       f32x4 kr[4][C::NV];
 #pragma unroll
       for (int t = 0; t < 4; t++) load_row2<D>(kb + (int64_t)min(ct * 16 + 4 * hq + t, n_cand - 1) * D, n, kr[t]);
-      const f32x4 db = db_of(ct, bits);
+      const f32x4 db = db_in(ct, x, bits);
       f32x4 u, g, dwh, dx;
       if constexpr (KEEP) u = kept[ct * 64]; else u = margins(ct, bits);
       terms(u, db, bits, g, dwh);

@@ -118,6 +118,17 @@ def test_backward(case):
     TB.test_backward_matches_the_oracle(case)
 
 
+# rows of fewer than four chunks, and rows whose last four chunks do not begin at a multiple of four: the routing
+# kernel reads them from up to three chunks before.  (Two and three chunks are not causal: a row with one candidate has no
+# routing gradient, its bias gradient less the mean over that one being exactly 0, so that causal rows of two chunks have none
+# and those of three 0.049 of the whole, by the oracle; the comparison asks for 0.05.)
+@pytest.mark.parametrize("h_q,h_kv,chunks,d,extra", [
+    (2, 1, 2, 64, {"causal": False}), (4, 1, 3, 128, {"causal": False}), (2, 2, 4, 64, {}), (1, 1, 5, 128, {"causal": False}), (4, 2, 6, 64, {"causal": False}),
+    (1, 1, 7, 64, {"causal": False}), (2, 1, 17, 64, {"causal": False}), (1, 1, 18, 128, {}), (1, 1, 19, 64, {"causal": False})])
+def test_backward_of_rows_of_any_number_of_chunks(h_q, h_kv, chunks, d, extra):
+    TB.test_backward_matches_the_oracle((f"b_{chunks}_chunks", 1, h_q, h_kv, chunks * 64, d, 64, {"offset_sigma": 0.8, **extra}))
+
+
 # one, two and three 64-key tiles, waves without rows, a group of 16 whose waves skip chunks
 @pytest.mark.parametrize("h_q,h_kv,n,d,block,extra", [
     (4, 1, 65, 128, 64, {}), (16, 1, 129, 64, 64, {"gamma": 3.0}), (16, 1, 577, 128, 64, {"gamma": 4.0, "offset_sigma": 1.0}),
