@@ -414,8 +414,12 @@ __global__ __launch_bounds__(256, 2) void bwd_f32_row_kernel(BwdArgs a, RowF32 x
 
 // Key kernel, one workgroup of 4 waves per (16-key tile, part of the rows that attend its chunk):
 // dK, dV and the chunk's summary gradient.  Several parts add to cleared outputs.
+// At d = 64 the bound keeps two waves per SIMD: without it 196 + 64 registers, four more than allow that, and the 512
+// workgroups of a small launch ran in two rounds.  With it 218, and the per-row values asked for before the rows: one
+// head, 1024 tokens 23 -> 15 us; backward pass of 16 heads x 2048 tokens 765 -> 577 us, of 8 / 4 heads x 3000 in chunks
+// of 128 839 -> 626.  At d = 128 (one wave) 4 heads over one, 1500 tokens: 343 -> 312.
 template <int D>
-__global__ __launch_bounds__(256) void bwd_f32_key_kernel(BwdArgs a, int parts) {
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_f32_key_kernel(BwdArgs a, int parts) {
   using C = F32Cfg<D>;
   constexpr int NWV = 4;
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -458,6 +462,20 @@ __global__ __launch_bounds__(256) void bwd_f32_key_kernel(BwdArgs a, int parts) 
     const int lt = tok0 - gb * 64;
     const uint32_t tb = (__builtin_amdgcn_readfirstlane(bits[lt >> 5]) >> (lt & 31)) & (tokt == 32 ? ~0u : (1u << tokt) - 1u);
     if (tb == 0u) continue;                   // bits of tokens past the end are 0
+    // per-row values: lane (m, kq) fetches one of the four of row m, then every lane takes its rows'
+    const int cdiag = tok0 / a.block;
+    const bool isdiag = a.causal && c == cdiag;
+    const int n_cand = a.causal ? max(cdiag - a.window, 0) : a.t_c;
+    float val;
+    bool val_ok = true;                       // else not written
+    {
+      const int tk = min(tok0 + n / a.g_q, a.n_q - 1);
+      const int64_t hrow = ((int64_t)b * a.h_q + r * a.g_q + n % a.g_q) * a.n_q + tk;
+      const bool bit = (tb >> (n / a.g_q)) & 1u;
+      if (hq >= 2) val_ok = bit && (hq == 2 ? !isdiag : c < n_cand);
+      const float* vp = hq == 0 ? a.lse + hrow : hq == 1 ? a.dsum + hrow : hq == 2 ? a.biasd + (mrow + tk) * a.t_all + c : a.dxd + hrow * a.t_all + c;
+      val = *vp;
+    }
     // all loads of the row tile in flight together
     const int64_t ra = min(tok0 + n / a.g_q, a.n_q - 1);
     f32x4 qa[C::NS], oa[C::NS], qw[1][4][C::NV], ow[1][4][C::NV];
@@ -470,20 +488,7 @@ __global__ __launch_bounds__(256) void bwd_f32_key_kernel(BwdArgs a, int parts) 
       load_row2<D>(ob + (row % a.g_q) * a.os_h + rt * a.os_t, n, ow[0][t]);
       load_row2<D>(qb + (row % a.g_q) * a.qs_h + rt * a.qs_t, n, qw[0][t]);
     }
-    // per-row values: lane (m, kq) fetches one of the four of row m, then every lane takes its rows'
-    const int cdiag = tok0 / a.block;
-    const bool isdiag = a.causal && c == cdiag;
-    const int n_cand = a.causal ? max(cdiag - a.window, 0) : a.t_c;
-    float val = 0.f;
-    {
-      const int tk = min(tok0 + n / a.g_q, a.n_q - 1);
-      const int64_t hrow = ((int64_t)b * a.h_q + r * a.g_q + n % a.g_q) * a.n_q + tk;
-      const bool bit = (tb >> (n / a.g_q)) & 1u;
-      if (hq == 0) val = a.lse[hrow];
-      else if (hq == 1) val = a.dsum[hrow];
-      else if (hq == 2) { if (bit && !isdiag) val = a.biasd[(mrow + tk) * a.t_all + c]; }
-      else if (bit && c < n_cand) val = a.dxd[hrow * a.t_all + c];
-    }
+    val = val_ok ? val : 0.f;
     float bs[4], ls[4], ds[4], dx[4];
 #pragma unroll
     for (int v = 0; v < 4; v++) {
