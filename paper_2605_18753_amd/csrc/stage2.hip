@@ -76,15 +76,21 @@ template <int D> __device__ __forceinline__ int v_swz(int row) {
 constexpr int kMinPartTiles = 8;   // 64-key tiles a part has at least
 constexpr int kMaxParts = 1536;    // records of a launch
 
-template <int D, bool DENSE>
-__global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
+// PAIR: eight waves, two groups of four with a ring each, on the same 128 rows: the first walks the first half of the chunk list, the
+// second the other, and they add up through LDS.  For launches that leave every CU at most one workgroup (see s2_paired): a
+// lone wave per SIMD takes three times a tile's matrix time, so the longest list is what such a launch takes.
+template <int D, bool DENSE, bool PAIR>
+__global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a) {
   using C = S2Cfg<D>;
-  extern __shared__ __attribute__((aligned(1024))) char lds[];
-  uint32_t* wgmask = reinterpret_cast<uint32_t*>(lds + C::MASK_OFF);   // [64]
+  extern __shared__ __attribute__((aligned(1024))) char lds_all[];
+  // PAIR: waves 4 .. 7 are a second group with a ring of its own
+  const int grp = PAIR ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
+  char* lds = lds_all + grp * C::MASK_OFF;
+  uint32_t* wgmask = reinterpret_cast<uint32_t*>(lds_all + (PAIR ? 2 : 1) * C::MASK_OFF);   // [64]
   uint32_t* wvmask = wgmask + 64;                                      // [4][64]
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
   const int n = lane & 31, h = lane >> 5;
   // workgroup id -> (tile, kv-head, batch): consecutive ids walk the (head, batch)
   // pairs so that the 8 XCDs (round-robin dispatch) each see few distinct KV streams
@@ -132,7 +138,7 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
   if (DENSE) {
     // every chunk up to the wave's own (causal) / every chunk (non-causal)
     const int last = a.causal ? cw : a.t_all - 1;
-    if (wave_ok)
+    if (wave_ok && grp == 0)
       for (int wi = lane; wi < a.words; wi += 64) {
         const int lo = wi * 32;
         uint32_t m = 0u;
@@ -141,7 +147,7 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
         if (m) atomicOr(&wgmask[wi], m);
       }
   } else {
-    if (wave_ok)
+    if (wave_ok && grp == 0)
       or_mask_rows(a.mask + (((int64_t)b * a.h_kv + r) * a.n_q + tok_w0) * a.words, min(tokw, a.n_q - tok_w0) * a.words,
                    a.words, wvmask + wave * 64, wgmask, lane);
   }
@@ -150,15 +156,24 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
   // ---- this workgroup's part of the chunk list ----------------------------
   int it_wi = -1, it_left = 0x7fffffff, n_parts = 1;
   uint32_t it_bits = 0u;
-  if (a.max_parts > 1) {
+  int iters = 0;                                // PAIR: iterations of either group, those of the longer half
+  if (PAIR || a.max_parts > 1) {
     int n_chunks = 0;
     for (int wi = 0; wi < a.words; wi++) n_chunks += __popc(__builtin_amdgcn_readfirstlane(wgmask[wi]));
-    const int per = max((n_chunks + a.max_parts - 1) / a.max_parts, kMinPartTiles / nsub);
-    n_parts = max((n_chunks + per - 1) / per, 1);
-    if (part >= n_parts) return;
-    if (part == 0 && tid == 0) a.part_cnt[blockIdx.x] = n_parts;
-    it_left = per;
-    int skip = part * per;                      // entries of the parts before this one (< n_chunks)
+    int skip;                                   // entries of the parts before this one (< n_chunks)
+    if constexpr (PAIR) {
+      const int per = (n_chunks + 1) >> 1;
+      iters = per > 0 ? per * nsub + 1 : 0;
+      it_left = grp == 0 ? per : n_chunks - per;
+      skip = it_left > 0 ? grp * per : 0;
+    } else {
+      const int per = max((n_chunks + a.max_parts - 1) / a.max_parts, kMinPartTiles / nsub);
+      n_parts = max((n_chunks + per - 1) / per, 1);
+      if (part >= n_parts) return;
+      if (part == 0 && tid == 0) a.part_cnt[blockIdx.x] = n_parts;
+      it_left = per;
+      skip = part * per;
+    }
     if (skip > 0) {
       for (;;) {
         it_bits = __builtin_amdgcn_readfirstlane(wgmask[++it_wi]);
@@ -444,12 +459,22 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
   };
   {
     f32x16 sa[2], sb[2];
-    while (drain) {
-      drain = have;
-      iteration(std::integral_constant<int, 0>{}, sa, sb);
-      if (!drain) break;
-      drain = have;
-      iteration(std::integral_constant<int, 1>{}, sb, sa);
+    if constexpr (PAIR) {
+      // as many iterations in either group: one without a tile is its barrier
+      while (iters > 0) {
+        iteration(std::integral_constant<int, 0>{}, sa, sb);
+        if (--iters == 0) break;
+        iteration(std::integral_constant<int, 1>{}, sb, sa);
+        iters--;
+      }
+    } else {
+      while (drain) {
+        drain = have;
+        iteration(std::integral_constant<int, 0>{}, sa, sb);
+        if (!drain) break;
+        drain = have;
+        iteration(std::integral_constant<int, 1>{}, sb, sa);
+      }
     }
   }
 
@@ -468,11 +493,11 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
     if (h == 0) reinterpret_cast<float2*>(a.part_ml)[rec * 128 + row] = make_float2(m_run, l_tot);
     return;
   }
-  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  if (row_ok) {
+  auto put_tiles = [&](int t0, int t1, float inv) {
+    if (!row_ok) return;
     uint16_t* op = a.o + b * a.os_b + my_head * a.os_h + (int64_t)my_tok * a.os_t;
 #pragma unroll
-    for (int t = 0; t < NDT; t++)
+    for (int t = t0; t < t1; t++)
 #pragma unroll
       for (int q4 = 0; q4 < 4; q4++) {
         // accumulator t, registers 4 q4 .. + 3: O^T rows 8 q4 + 4 h + i of d-tile t
@@ -482,7 +507,44 @@ __global__ __launch_bounds__(256, 2) void s2_attend_kernel(S2Args a) {
         w.y = pack_bf16x2(oacc[t][q4 * 4 + 2] * inv, oacc[t][q4 * 4 + 3] * inv);
         *reinterpret_cast<uint2*>(op + t * 32 + m0) = w;
       }
+  };
+  if constexpr (PAIR) {
+    // The groups add up through LDS: each hands the other half of its d-tiles, as [d / 4][row][4], and its rows' maxima
+    // and sums, where its ring was, and writes the other half.
+    constexpr int H = NDT / 2;
+    const int row = wave * 32 + n;
+    __syncthreads();                                           // nobody reads the tiles any more
+    auto exchange = [&](auto g_tag) {
+      constexpr int G = decltype(g_tag)::value, MINE = G * H, GIVE = (G ^ 1) * H;
+      f32x4* xo = reinterpret_cast<f32x4*>(lds) + row;
+#pragma unroll
+      for (int t = 0; t < H; t++)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; q4++)
+          xo[(t * 8 + q4 * 2 + h) * 128] = f32x4{oacc[GIVE + t][q4 * 4], oacc[GIVE + t][q4 * 4 + 1], oacc[GIVE + t][q4 * 4 + 2], oacc[GIVE + t][q4 * 4 + 3]};
+      if (h == 0) reinterpret_cast<float2*>(lds + 3 * C::TILE_BYTES)[row] = make_float2(m_run, l_tot);
+      __syncthreads();
+      const char* other = lds_all + (G ^ 1) * C::MASK_OFF;
+      const float2 ml = reinterpret_cast<const float2*>(other + 3 * C::TILE_BYTES)[row];
+      const float M = fmaxf(m_run, ml.x), m_use = M == -INFINITY ? 0.f : M;
+      const float w0 = __builtin_amdgcn_exp2f(m_run - m_use), w1 = __builtin_amdgcn_exp2f(ml.x - m_use);
+      const float den = fmaf(w0, l_tot, w1 * ml.y);
+      const f32x4* xi = reinterpret_cast<const f32x4*>(other) + row;
+#pragma unroll
+      for (int t = 0; t < H; t++)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; q4++) {
+          const f32x4 x = xi[(t * 8 + q4 * 2 + h) * 128];
+#pragma unroll
+          for (int e = 0; e < 4; e++) oacc[MINE + t][q4 * 4 + e] = fmaf(w0, oacc[MINE + t][q4 * 4 + e], w1 * x[e]);
+        }
+      put_tiles(MINE, MINE + H, den > 0.f ? 1.f / den : 0.f);
+    };
+    if (grp == 0) exchange(std::integral_constant<int, 0>{});
+    else exchange(std::integral_constant<int, 1>{});
+    return;
   }
+  put_tiles(0, NDT, l_tot > 0.f ? 1.f / l_tot : 0.f);
 }
 
 // Adds the parts of the tiles that have several: o = sum_p 2^(m_p - M) O_p / sum_p 2^(m_p - M) l_p.
@@ -529,9 +591,17 @@ __global__ __launch_bounds__(256) void s2_merge_kernel(S2Args a) {
 }
 
 template <int D, bool DENSE>
-static hipError_t launch_s2_t(const S2Args& a, hipStream_t st) {
+static hipError_t launch_s2_t(const S2Args& a, bool pair, hipStream_t st) {
   using C = S2Cfg<D>;
-  auto kern = s2_attend_kernel<D, DENSE>;
+  if (pair) {
+    auto kern = s2_attend_kernel<D, DENSE, true>;
+    static LdsOptIn opt_in;
+    constexpr size_t lds = C::LDS_BYTES + C::MASK_OFF;
+    if (hipError_t e = allow_dyn_lds((const void*)kern, lds, opt_in); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb), dim3(512), lds, st, a);
+    return hipGetLastError();
+  }
+  auto kern = s2_attend_kernel<D, DENSE, false>;
   static LdsOptIn opt_in;
   if (hipError_t e = allow_dyn_lds((const void*)kern, C::LDS_BYTES, opt_in); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb, a.max_parts), dim3(256), C::LDS_BYTES, st, a);
@@ -552,7 +622,16 @@ static int s2_tiles(const dash_params& p, const Layout& L) { return (p.n_q + 128
 // where the tiles make two uneven rounds.  Measured, 8 kv-heads, group of 4, against a 32k cache, uncut -> cut:
 // 65 tokens 707 -> 74 us, 300 709 -> 189, 700 718 -> 396, 1000 724 -> 500, 1500 850 -> 713, 2500 1449 -> 1190;
 // whole prompts: 1 kv-head, 8000 tokens 195 -> 138, 2 kv-heads of one head, 12000 tokens 285 -> 152.
-// Where the rule does not cut: 8 x 1000 tokens 33.2 -> 34.3 in two parts, 8 x 600 23.2 -> 26.7.
+// Where the rule does not cut: 8 x 1000 tokens 33.2 -> 34.3 in two parts, 8 x 600 23.2 -> 26.7; two groups of waves (s2_paired)
+// need no records and no second launch and do gain there.  Their estimate is half the tiles and 8: near 256 workgroups it is the least
+// (whole forward, cut -> paired: 8 / 2 heads x 4096 tokens 89.9 -> 80.2 us, 4 heads over one x 8192 147 -> 138), with fewer
+// cutting stays better (2 heads x 8000 96 us cut, 139 paired; 4 heads over one x 3000 51, 64).
+// Whether a launch that is not cut walks each list with two groups of waves.  It takes as long as the longest half, and a CU has room
+// for one such workgroup: no more than 256 of them.  Of up to four tiles the halves gain what the exchange costs (whole forward,
+// one group -> two, 32 / 8 heads: 128 tokens 20.7 -> 21.2 us, 192 25.0 -> 25.8, 256 28.2 -> 28.3; 257 29.4 -> 28.5, 500 37.1 -> 33.8,
+// 1000 45.9 -> 41.7; 16 heads over one x 2048 66.1 -> 55.4).
+static bool s2_paired(int64_t wgs, float tiles) { return wgs <= 256 && tiles > 4.f; }
+
 int s2_parts(const dash_params& p, const Layout& L) {
   if (!L.use_mfma) return 1;
   const int64_t wgs = (int64_t)s2_tiles(p, L) * p.h_kv * p.batch;
@@ -564,7 +643,8 @@ int s2_parts(const dash_params& p, const Layout& L) {
   for (int n = 1; n * wgs <= (n == 1 ? wgs : most) && (n == 1 || n * kMinPartTiles <= tiles); n++) {
     const int64_t w = n * wgs, rest = w % 512;
     const float rounds = (float)(w / 512) + (rest == 0 ? 0.f : rest <= 256 ? 0.7f : 1.f);
-    const float cost = rounds * tiles / n + (n == 1 ? 0.f : 3.f + 6.f * w / 512);
+    float cost = rounds * tiles / n + (n == 1 ? 0.f : 3.f + 6.f * w / 512);
+    if (n == 1 && s2_paired(wgs, tiles)) cost = fminf(cost, 0.5f * tiles + 8.f);
     if (cost < best_cost) { best_cost = cost; best = n; }
   }
   return best;
@@ -603,8 +683,9 @@ hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, 
     a.part_ml = reinterpret_cast<float*>(part_ws + s2_cnt_bytes(p, L));
     a.part_o = a.part_ml + (size_t)a.n_tiles * a.hb * a.max_parts * 128 * 2;
   }
-  if (p.head_dim == 128) return dense ? launch_s2_t<128, true>(a, st) : launch_s2_t<128, false>(a, st);
-  return dense ? launch_s2_t<64, true>(a, st) : launch_s2_t<64, false>(a, st);
+  const bool pair = a.max_parts == 1 && s2_paired((int64_t)a.n_tiles * a.hb, (float)(L.t_all * (p.block_size >> 6)));
+  if (p.head_dim == 128) return dense ? launch_s2_t<128, true>(a, pair, st) : launch_s2_t<128, false>(a, pair, st);
+  return dense ? launch_s2_t<64, true>(a, pair, st) : launch_s2_t<64, false>(a, pair, st);
 }
 
 }  // namespace dash

@@ -173,6 +173,33 @@ def test_prefill_cut_chunk_lists(name, h_q, h_kv, n_q, n_kv, d, block, extra):
         assert (o[0, h].double().cpu() - ref).abs().max() <= 2e-2 * ref.abs().max()
 
 
+# Two groups of waves walk the halves of a tile's chunk list where at most 256 tiles are not cut and have more than four tiles of 64
+# keys: an even and an odd number of chunks, chunks of two tiles, tiles with fewer chunks than groups, waves without rows, the last launch
+# of 256 tiles and the first of more, sparse rows whose second half is the own chunk alone.
+@pytest.mark.parametrize("name,batch,h_q,h_kv,n,d,block,extra", [
+    ("four_tiles", 1, 4, 2, 256, 128, 64, {}), ("five_tiles", 1, 4, 2, 257, 128, 64, {}), ("six_tiles_b128", 2, 2, 1, 321, 64, 128, {}),
+    ("ragged_g16", 1, 16, 1, 577, 64, 64, {"gamma": 2.0}), ("window", 1, 8, 8, 390, 128, 64, {"window": 2}),
+    ("256_tiles", 32, 1, 1, 1024, 64, 64, {"gamma": 2.0}),
+    ("264_tiles", 33, 1, 1, 1024, 64, 64, {"gamma": 2.0}), ("sparse_g1", 1, 2, 2, 999, 128, 64, {"gamma": 4.0, "offset_sigma": 1.0}),
+    ("noncausal", 1, 8, 8, 832, 128, 64, {"causal": False})])
+def test_prefill_in_two_groups(name, batch, h_q, h_kv, n, d, block, extra):
+    w = Workload("edge_pair_" + name, batch, h_q, h_kv, n, n, d, block, seed=49, **{"offset_sigma": 0.7, **extra})
+    q, k, v = make_inputs(w, DEV)
+    run = U.run_prefill(w, q, k, v)
+    U.check_against_oracle(w, q, k, v, run, rows=U.sample_rows(w, 80) if batch > 2 else None)
+    o = torch.full_like(q, float("nan"))
+    B.dense_attn(run.params, q, k, v, o, B.alloc_workspace(run.params, DEV))
+    torch.cuda.synchronize()
+    g, pos = h_q // h_kv, torch.arange(n)
+    for b in (0, batch - 1):
+        for h in range(h_q):
+            z = q[b, h].double().cpu() @ k[b, h // g].double().cpu().T / d ** 0.5
+            if w.causal:
+                z.masked_fill_(pos[None, :] > pos[:, None], float("-inf"))
+            ref = torch.softmax(z, -1) @ v[b, h // g].double().cpu()
+            assert (o[b, h].double().cpu() - ref).abs().max() <= 2e-2 * ref.abs().max()   # the bar of the cut lists' test
+
+
 @pytest.mark.parametrize("batch,h_q,h_kv,n_kv,extra", [
     (1, 8, 2, 1000, {}), (2, 16, 1, 400 * 64 + 7, {"gamma": 2.0}), (1, 4, 1, 700 * 64, {"gamma": 1.5, "window": 2}), (300, 2, 2, 300, {})])
 def test_decode_keeps_its_lists_in_the_workspace(batch, h_q, h_kv, n_kv, extra):
