@@ -89,6 +89,21 @@ struct PairX {
     buf ^= 1;
     return false;
   }
+  // the same for values of which lane m of a DPP row holds score row m % 4's
+  template <int K>
+  __device__ __forceinline__ void swap_rows(const float (&mine)[K], float (&other)[K]) {
+    static_assert(K <= 2, "at most 8 values per exchange");
+    float* slot = area + ((buf * 8 + wave) * 4 + kq) * 12 + (m & 3);
+    if (m < 4) {
+#pragma unroll
+      for (int k = 0; k < K; k++) slot[4 * k] = mine[k];
+    }
+    __syncthreads();
+    const float* o = area + ((buf * 8 + (wave ^ 4)) * 4 + kq) * 12 + (m & 3);
+#pragma unroll
+    for (int k = 0; k < K; k++) other[k] = o[4 * k];
+    buf ^= 1;
+  }
   // whether any wave of the workgroup raises its flag
   __device__ __forceinline__ bool any_flag(bool flag) {
     float* slot = area + ((buf * 8 + wave) * 4) * 12 + 8;
@@ -107,119 +122,143 @@ struct PairX {
 // x = -inf (an absent chunk) and -inf - -inf give 0.
 __device__ __forceinline__ float excess(float x, float tau) { return __builtin_amdgcn_fmed3f(x - tau, 0.f, 1.f); }
 
+// Reductions of four score rows at once that leave score row m % 4 in lane m of a DPP row (a
+// quarter of the lanes each, all with the same bits): the order of the additions is that of
+// row16_reduce.
+__device__ __forceinline__ float add_quads(float x) {      // + the same score row's sums of the other three quads
+  x += dpp_f<0x141>(dpp_f<0x1B>(x));                       // quad reversed, half row mirrored: lane m ^ 4
+  return x + dpp_f<0x128>(x);                              // row_ror 8
+}
+__device__ __forceinline__ float pick4(const float (&a)[4], int m) {
+  const float x = m & 1 ? a[1] : a[0], y = m & 1 ? a[3] : a[2];
+  return m & 2 ? y : x;
+}
+__device__ __forceinline__ float sum4_scatter(const float (&a)[4], int m) {
+  const float x = (m & 1 ? a[1] : a[0]) + dpp_f<0xB1>(m & 1 ? a[0] : a[1]);
+  const float y = (m & 1 ? a[3] : a[2]) + dpp_f<0xB1>(m & 1 ? a[2] : a[3]);
+  return add_quads((m & 2 ? y : x) + dpp_f<0x4E>(m & 2 ? x : y));
+}
+// lane m's four values of score rows 0..3 -> the four lanes' of its quad of score row m % 4
+__device__ __forceinline__ void quad_transpose(const float (&a)[4], float (&t)[4], int m) {
+  const float g0 = dpp_f<0xB1>(m & 1 ? a[0] : a[1]), g1 = dpp_f<0xB1>(m & 1 ? a[2] : a[3]);
+  const float b0 = m & 1 ? g0 : a[0], b1 = m & 1 ? a[1] : g0, c0 = m & 1 ? g1 : a[2], c1 = m & 1 ? a[3] : g1;
+  const float h0 = dpp_f<0x4E>(m & 2 ? b0 : c0), h1 = dpp_f<0x4E>(m & 2 ? b1 : c1);
+  t[0] = m & 2 ? h0 : b0; t[1] = m & 2 ? h1 : b1; t[2] = m & 2 ? c0 : h0; t[3] = m & 2 ? c1 : h1;
+}
+
 // One bracketed Newton step of row state (tau, lo, hi, done) from the sums F = sum u^p,
-// G = sum u^(p-1) at tau: the update of stage1.hip's 16-lane solver.
+// G = sum u^(p-1) at tau: the update of stage1.hip's 16-lane solver, without branches.
 template <int MODE>
 __device__ __forceinline__ void newton_step(float F, float G, float p, int n_cand, float& tau, float& lo, float& hi,
                                             bool& done) {
-  if (done) return;
   const float f = F - 1.f;
-  if (f == 0.f) { done = true; return; }
-  if (f > 0.f) lo = tau; else hi = tau;
-  const float mid = 0.5f * (lo + hi);
+  const float l = f > 0.f ? tau : lo, h = f > 0.f ? hi : tau, mid = 0.5f * (l + h);
   float cand = (MODE == MODE_BISECT || !(G > 0.f)) ? mid : tau + f / (p * G);
-  if (MODE != MODE_BISECT && cand == tau) { done = true; return; }   // Newton step below the fp32 spacing of tau
-  if (!(cand > lo && cand < hi)) cand = mid;
-  if (!(cand > lo && cand < hi)) { done = true; tau = lo; return; }  // bracket closed
+  // the root, or a Newton step below the fp32 spacing of tau
+  const bool stay = f == 0.f || (MODE != MODE_BISECT && cand == tau);
+  if (!(cand > l && cand < h)) cand = mid;
+  const bool closed = !(cand > l && cand < h);               // bracket closed
   // alpha = 1.5: a Newton step s from the left leaves an error of about (n / 2G) s^2;
   // once that is below 2e-8 the step is final
-  if (MODE == MODE_P2 && f > 0.f && cand != mid) {
-    const float st = cand - tau;
-    if ((float)n_cand * st * st < 4e-8f * G) done = true;
-  }
-  tau = cand;
+  const float st = cand - tau;
+  const bool last = MODE == MODE_P2 && f > 0.f && cand != mid && (float)n_cand * st * st < 4e-8f * G;
+  const float next = closed ? l : cand;
+  tau = done || stay ? tau : next;
+  lo = l;
+  hi = h;
+  done = done || stay || closed || last;
 }
 
 // Threshold of four score rows per lane at once (rows j = 0..3; row j of DPP row kq is
 // spread over the row's 16 lanes, NT values per lane; with SPLIT = 2 over the 16 lanes
 // of this wave and of its partner): the iteration of stage1.hip's 16-lane solver, row by
-// row the same operations in the same order.
+// row the same operations in the same order.  Once the sums over a lane's values are formed, each
+// lane goes on with one of the four rows only: the row sums take three quarters of the
+// instructions and the warm start and the Newton step (with its division) a quarter
+// of what they take where every lane carries all four (same bits; whole prefill of 1000 tokens 41.2 ->
+// 36.5 us, 32k 9.06 -> 8.72 ms, 128k 101.5 -> 99.9 ms).
+// tau: the thresholds of rows 0..3; returns that of row m % 4.
 template <int NT, int MODE, int SPLIT>
-__device__ __forceinline__ void solve4(const f32x4 (&v)[NT], int n_cand, float alpha, float p, float (&tau)[4],
-                                       PairX& px, int half) {
-  float mloc[4], lo[4], hi[4], mx[4];
-  bool done[4];
+__device__ __forceinline__ float solve4(const f32x4 (&v)[NT], int n_cand, float alpha, float p, float (&tau)[4],
+                                        PairX& px, int half) {
+  const int m = px.m;
+  float mloc[4], mx4[4];
 #pragma unroll
   for (int j = 0; j < 4; j++) {
-    float m = -INFINITY;
+    float x = -INFINITY;
 #pragma unroll
-    for (int t = 0; t < NT; t++) m = fmaxf(m, v[t][j]);
-    mloc[j] = m;
-    mx[j] = row16_reduce(m, OpMax());
+    for (int t = 0; t < NT; t++) x = fmaxf(x, v[t][j]);
+    mloc[j] = x;
+    mx4[j] = row16_reduce(x, OpMax());
   }
+  float mx[1] = {pick4(mx4, m)};
   if constexpr (SPLIT == 2) {
-    float other[4];
-    px.swap(mx, other);
-#pragma unroll
-    for (int j = 0; j < 4; j++) mx[j] = fmaxf(mx[j], other[j]);
+    float other[1];
+    px.swap_rows(mx, other);
+    mx[0] = fmaxf(mx[0], other[0]);
   }
-#pragma unroll
-  for (int j = 0; j < 4; j++) {
-    lo[j] = mx[j] - 1.f;
-    hi[j] = mx[j] - exp2f(-(alpha - 1.f) * log2f((float)n_cand));
-    tau[j] = lo[j];
-    done[j] = false;
-  }
+  float lo = mx[0] - 1.f, hi = mx[0] - exp2f(-(alpha - 1.f) * log2f((float)n_cand));
+  float th[1] = {lo};
+  bool done = false;
   if constexpr (MODE != MODE_BISECT) {
     // warm start on the 16 lane maxima (a subset: its root and every Newton iterate from
-    // the left on it are lower bounds of tau)
+    // the left on it are lower bounds of tau); a lane takes those of its quad
+    float w[4];
+    quad_transpose(mloc, w, m);
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
+    for (int it = 0; it < 5; it++) {
+      float f[4], g[4];
 #pragma unroll
-      for (int it = 0; it < 5; it++) {
-        float f, g;
-        pow_terms<MODE>(excess(mloc[j], tau[j]), p, f, g);
-        asm volatile("" : "+v"(f), "+v"(g));
-        const float F = row16_reduce(f, OpAdd()), G = row16_reduce(g, OpAdd());
-        if (F > 1.f && G > 0.f) tau[j] += (F - 1.f) / (p * G);
+      for (int k = 0; k < 4; k++) {
+        pow_terms<MODE>(excess(w[k], th[0]), p, f[k], g[k]);
+        asm volatile("" : "+v"(f[k]), "+v"(g[k]));
       }
+      const float F = add_quads((f[0] + f[1]) + (f[2] + f[3])), G = add_quads((g[0] + g[1]) + (g[2] + g[3]));
+      const float st = (F - 1.f) / (p * G);
+      th[0] += F > 1.f && G > 0.f ? st : 0.f;
     }
     if constexpr (SPLIT == 2) {   // each wave started on its own half: the larger lower bound serves both
-      float other[4];
-      px.swap(tau, other);
-#pragma unroll
-      for (int j = 0; j < 4; j++) tau[j] = fmaxf(tau[j], other[j]);
+      float other[1];
+      px.swap_rows(th, other);
+      th[0] = fmaxf(th[0], other[0]);
     }
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      tau[j] = fmaxf(tau[j], lo[j]);
-      if (!(tau[j] < hi[j])) tau[j] = lo[j];
-    }
+    th[0] = fmaxf(th[0], lo);
+    if (!(th[0] < hi)) th[0] = lo;
   }
+  auto spread = [&]() {
+    tau[0] = dpp_f<0x00>(th[0]); tau[1] = dpp_f<0x55>(th[0]); tau[2] = dpp_f<0xAA>(th[0]); tau[3] = dpp_f<0xFF>(th[0]);
+  };
+  spread();
   for (int it = 0; it < 64; it++) {
-    float FG[8];
+    float F[4], G[4];
 #pragma unroll
     for (int j = 0; j < 4; j++) {
-      float F = 0.f, G = 0.f;
+      F[j] = 0.f; G[j] = 0.f;
 #pragma unroll
       for (int t = 0; t < NT; t++) {
         float f, g;
         pow_terms<MODE>(excess(v[t][j], tau[j]), p, f, g);
-        F += f; G += g;
+        F[j] += f; G[j] += g;
       }
       // keep the partial sums as rounded values: a multiply contracted into the first
       // cross-lane add would make the lanes of a row disagree by an ulp
-      asm volatile("" : "+v"(F), "+v"(G));
-      FG[j] = row16_reduce(F, OpAdd());
-      FG[4 + j] = row16_reduce(G, OpAdd());
+      asm volatile("" : "+v"(F[j]), "+v"(G[j]));
     }
+    float FG[2] = {sum4_scatter(F, m), sum4_scatter(G, m)};
     if constexpr (SPLIT == 2) {
       // both waves add first half + second half in that order, so they take the same step
-      float other[8];
-      px.swap(FG, other);
+      float other[2];
+      px.swap_rows(FG, other);
 #pragma unroll
-      for (int k = 0; k < 8; k++) FG[k] = half == 0 ? FG[k] + other[k] : other[k] + FG[k];
+      for (int k = 0; k < 2; k++) FG[k] = half == 0 ? FG[k] + other[k] : other[k] + FG[k];
     }
-    bool all_done = true;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      newton_step<MODE>(FG[j], FG[4 + j], p, n_cand, tau[j], lo[j], hi[j], done[j]);
-      all_done = all_done && done[j];
-    }
-    bool busy = __any(!all_done);
+    newton_step<MODE>(FG[0], FG[1], p, n_cand, th[0], lo, hi, done);
+    spread();
+    bool busy = __any(!done);
     if constexpr (SPLIT == 2) busy = px.any_flag(busy);   // the loop ends for the whole workgroup at once
     if (!busy) break;
   }
+  return th[0];
 }
 
 // One workgroup's rows with NT chunk tiles of 16 per wave.  SPLIT = 1: every wave holds
@@ -247,7 +286,7 @@ __device__ __forceinline__ void regs_tile(const S1Args& a, char* lds, int b, int
   f32x4 v[NT];   // scores, then probabilities: v[t][j] = row 4 kq + j at chunk 16 (half NT + t) + m
 #pragma unroll
   for (int t = 0; t < NT; t++) v[t] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  float tau[4] = {0.f, 0.f, 0.f, 0.f};
+  float tau[4] = {0.f, 0.f, 0.f, 0.f}, tau_row = 0.f;       // of rows 4 kq .. 4 kq + 3; of row 4 kq + m % 4
 
   if (ntile > 0) {
     // ---- Q fragments (operand A): row m of the wave, d 32 ks + 8 kq .. + 7 ----------
@@ -333,19 +372,16 @@ __device__ __forceinline__ void regs_tile(const S1Args& a, char* lds, int b, int
   // serves its partner and keeps the barrier count).
   if (SPLIT == 2 || n_cand > 0) {
     // ---- thresholds, then probabilities in place ---------------------------------------
-    solve4<NT, MODE, SPLIT>(v, max(n_cand, 1), a.alpha, a.pexp, tau, px, half);
+    tau_row = solve4<NT, MODE, SPLIT>(v, max(n_cand, 1), a.alpha, a.pexp, tau, px, half);
 #pragma unroll
     for (int t = 0; t < NT; t++)
 #pragma unroll
       for (int j = 0; j < 4; j++) v[t][j] = pow_p<MODE>(excess(v[t][j], tau[j]), a.pexp);
   }
-  if (a.tau && m == 0 && half == 0) {
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int row = 4 * kq + j;
-      const int tok = tok_w0 + row / G, head = r * G + row % G;
-      if (tok < a.tok_end) a.tau[((int64_t)b * a.h_q + head) * a.n_q + tok] = n_cand > 0 ? tau[j] : 0.f;
-    }
+  if (a.tau && m < 4 && half == 0) {
+    const int row = 4 * kq + m;
+    const int tok = tok_w0 + row / G, head = r * G + row % G;
+    if (tok < a.tok_end) a.tau[((int64_t)b * a.h_q + head) * a.n_q + tok] = n_cand > 0 ? tau_row : 0.f;
   }
 
   // ---- group weights, bias, lists: one token per DPP row (or per KQT rows) at a time ------
