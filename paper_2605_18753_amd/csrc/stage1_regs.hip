@@ -512,9 +512,14 @@ __global__ __launch_bounds__(512, RegsVar<VAR>::MIN_WG) void s1_regs_kernel(S1Ar
     else if (ntile <= 8) regs_tile<D, G, MODE, 1, 8, ST>(a, lds, b, r, tok0, ntile);
     else regs_tile<D, G, MODE, 1, 16, ST>(a, lds, b, r, tok0, ntile);
   } else if constexpr (VAR == 1) {
-    regs_tile<D, G, MODE, 1, 32, ST>(a, lds, b, r, tok0, ntile);
+    // A row costs its register slots, filled or not: with 24 of them for up to 384 chunks besides 32 (and, on wave pairs,
+    // 24 for up to 768) 32k tokens take 418 us instead of 444, 2000 tokens against a 32k cache 61 for 64, 128k in
+    // chunks of 128 4.53 ms on pairs for 4.67.  12 besides 16 gave 2 % and is left out.
+    if (ntile <= 24) regs_tile<D, G, MODE, 1, 24, ST>(a, lds, b, r, tok0, ntile);
+    else regs_tile<D, G, MODE, 1, 32, ST>(a, lds, b, r, tok0, ntile);
   } else {
-    if (ntile <= 64) regs_tile<D, G, MODE, 2, 32, ST>(a, lds, b, r, tok0, ntile);
+    if (ntile <= 48) regs_tile<D, G, MODE, 2, 24, ST>(a, lds, b, r, tok0, ntile);
+    else if (ntile <= 64) regs_tile<D, G, MODE, 2, 32, ST>(a, lds, b, r, tok0, ntile);
     else regs_tile<D, G, MODE, 2, 48, ST>(a, lds, b, r, tok0, ntile);
   }
 }

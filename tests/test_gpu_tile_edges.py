@@ -319,3 +319,20 @@ def test_other_layouts(layout, name, h_q, h_kv, n_q, n_kv, d, block, extra):
     for key in want:
         assert torch.equal(got[key], want[key]), key
     assert bool(torch.isfinite(want["o"].float()).all())
+
+
+@pytest.mark.parametrize("h_q,h_kv,n_q,chunks,d,extra", [
+    (4, 1, 300, 384, 128, {}),                      # the last rows whose scores fill 24 register slots, then 32
+    (16, 1, 200, 384, 64, {"gamma": 2.0}),
+    (1, 1, 400, 384, 128, {"alpha": 3.0}),
+    (4, 2, 300, 768, 128, {"window": 1}),           # the same on wave pairs
+    (8, 1, 200, 768, 128, {"alpha": 1.25}),
+])
+def test_routing_row_length_steps(h_q, h_kv, n_q, chunks, d, extra):
+    """Rows with `chunks` candidates and with one more, whose kernels hold another number of scores per lane."""
+    first = (chunks + extra.get("window", 0) + 1) * 64 - 128
+    w = Workload(f"edge_row_{chunks}_{h_q}_{d}", 1, h_q, h_kv, n_q, first + n_q, d, 64, offset_sigma=0.7, seed=67, **extra)
+    q, k, v = make_inputs(w, DEV)
+    run = U.run_prefill(w, q, k, v)
+    toks = [0, 127, 128, n_q - 1]                   # token 128 is the first with one candidate more
+    U.check_against_oracle(w, q, k, v, run, rows=[(0, r, i) for r in range(h_kv) for i in toks])
