@@ -122,53 +122,6 @@ struct PairX {
 // x = -inf (an absent chunk) and -inf - -inf give 0.
 __device__ __forceinline__ float excess(float x, float tau) { return __builtin_amdgcn_fmed3f(x - tau, 0.f, 1.f); }
 
-// Reductions of four score rows at once that leave score row m % 4 in lane m of a DPP row (a
-// quarter of the lanes each, all with the same bits): the order of the additions is that of
-// row16_reduce.
-__device__ __forceinline__ float add_quads(float x) {      // + the same score row's sums of the other three quads
-  x += dpp_f<0x141>(dpp_f<0x1B>(x));                       // quad reversed, half row mirrored: lane m ^ 4
-  return x + dpp_f<0x128>(x);                              // row_ror 8
-}
-__device__ __forceinline__ float pick4(const float (&a)[4], int m) {
-  const float x = m & 1 ? a[1] : a[0], y = m & 1 ? a[3] : a[2];
-  return m & 2 ? y : x;
-}
-__device__ __forceinline__ float sum4_scatter(const float (&a)[4], int m) {
-  const float x = (m & 1 ? a[1] : a[0]) + dpp_f<0xB1>(m & 1 ? a[0] : a[1]);
-  const float y = (m & 1 ? a[3] : a[2]) + dpp_f<0xB1>(m & 1 ? a[2] : a[3]);
-  return add_quads((m & 2 ? y : x) + dpp_f<0x4E>(m & 2 ? x : y));
-}
-// lane m's four values of score rows 0..3 -> the four lanes' of its quad of score row m % 4
-__device__ __forceinline__ void quad_transpose(const float (&a)[4], float (&t)[4], int m) {
-  const float g0 = dpp_f<0xB1>(m & 1 ? a[0] : a[1]), g1 = dpp_f<0xB1>(m & 1 ? a[2] : a[3]);
-  const float b0 = m & 1 ? g0 : a[0], b1 = m & 1 ? a[1] : g0, c0 = m & 1 ? g1 : a[2], c1 = m & 1 ? a[3] : g1;
-  const float h0 = dpp_f<0x4E>(m & 2 ? b0 : c0), h1 = dpp_f<0x4E>(m & 2 ? b1 : c1);
-  t[0] = m & 2 ? h0 : b0; t[1] = m & 2 ? h1 : b1; t[2] = m & 2 ? c0 : h0; t[3] = m & 2 ? c1 : h1;
-}
-
-// One bracketed Newton step of row state (tau, lo, hi, done) from the sums F = sum u^p,
-// G = sum u^(p-1) at tau: the update of stage1.hip's 16-lane solver, without branches.
-template <int MODE>
-__device__ __forceinline__ void newton_step(float F, float G, float p, int n_cand, float& tau, float& lo, float& hi,
-                                            bool& done) {
-  const float f = F - 1.f;
-  const float l = f > 0.f ? tau : lo, h = f > 0.f ? hi : tau, mid = 0.5f * (l + h);
-  float cand = (MODE == MODE_BISECT || !(G > 0.f)) ? mid : tau + f / (p * G);
-  // the root, or a Newton step below the fp32 spacing of tau
-  const bool stay = f == 0.f || (MODE != MODE_BISECT && cand == tau);
-  if (!(cand > l && cand < h)) cand = mid;
-  const bool closed = !(cand > l && cand < h);               // bracket closed
-  // alpha = 1.5: a Newton step s from the left leaves an error of about (n / 2G) s^2;
-  // once that is below 2e-8 the step is final
-  const float st = cand - tau;
-  const bool last = MODE == MODE_P2 && f > 0.f && cand != mid && (float)n_cand * st * st < 4e-8f * G;
-  const float next = closed ? l : cand;
-  tau = done || stay ? tau : next;
-  lo = l;
-  hi = h;
-  done = done || stay || closed || last;
-}
-
 // Threshold of four score rows per lane at once (rows j = 0..3; row j of DPP row kq is
 // spread over the row's 16 lanes, NT values per lane; with SPLIT = 2 over the 16 lanes
 // of this wave and of its partner): the iteration of stage1.hip's 16-lane solver, row by
