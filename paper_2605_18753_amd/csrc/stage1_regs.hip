@@ -242,6 +242,17 @@ __device__ __forceinline__ void regs_tile(const S1Args& a, char* lds, int b, int
   float tau[4] = {0.f, 0.f, 0.f, 0.f}, tau_row = 0.f;       // of rows 4 kq .. 4 kq + 3; of row 4 kq + m % 4
 
   if (ntile > 0) {
+    // ---- Q fragments (operand A): row m of the wave, d 32 ks + 8 kq .. + 7 ----------
+    bf16x8 qf[C::KS];
+    {
+      const int tok = tok_w0 + m / G, head = r * G + m % G;
+      const uint16_t* qp = (const uint16_t*)a.q + b * a.qs_b + head * a.qs_h +
+                           (int64_t)(tok < a.n_q ? tok : a.n_q - 1) * a.qs_t + kq * 8;
+#pragma unroll
+      for (int ks = 0; ks < C::KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 32);
+#pragma unroll
+      for (int ks = 0; ks < C::KS; ks++) asm volatile("" : "+v"(qf[ks]));   // landed before the counted waits
+    }
     // ---- tiles of split summaries: global -> LDS --------------------------------------
     // A tile is 16 chunks x 3 pieces x d bf16, contiguous in memory.  Copy instruction i
     // of the workgroup fills LDS slots 64 i .. 64 i + 63 (16 bytes each); slot s holds, of
@@ -269,19 +280,6 @@ __device__ __forceinline__ void regs_tile(const S1Args& a, char* lds, int b, int
 #pragma unroll
     for (int gt = 0; gt < C::STAGES - 1; gt++)
       if (gt < ntile) issue_tile(gt);
-    // ---- Q fragments (operand A): row m of the wave, d 32 ks + 8 kq .. + 7 ----------
-    // Asked for behind the first tiles' copies, so that both are one round trip to memory (the kernel, with solve4's
-    // share: 1000 tokens, 32 / 8 heads 14.7 -> 9.5 us; 32k 770 -> 585 us; 16k with a group of 16 197 -> 140 us).
-    bf16x8 qf[C::KS];
-    {
-      const int tok = tok_w0 + m / G, head = r * G + m % G;
-      const uint16_t* qp = (const uint16_t*)a.q + b * a.qs_b + head * a.qs_h +
-                           (int64_t)(tok < a.n_q ? tok : a.n_q - 1) * a.qs_t + kq * 8;
-#pragma unroll
-      for (int ks = 0; ks < C::KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 32);
-#pragma unroll
-      for (int ks = 0; ks < C::KS; ks++) asm volatile("" : "+v"(qf[ks]));   // landed before the counted waits
-    }
     // all waves take part in the copy of, and the barrier for, every tile; a wave runs the
     // matrix cores on the tiles of its own half only
 #pragma nounroll
