@@ -632,10 +632,10 @@ def main():
         "config": {"workload": w.name, "batch": w.batch, "h_q": w.h_q, "h_kv": w.h_kv, "n": w.n_q,
                    "head_dim": w.head_dim, "block": w.block, "alpha": w.alpha, "gamma": w.gamma,
                    "sigma": w.sigma, "causal": True, "offset_sigma": w.offset_sigma, "seed": w.seed},
-        "roofline": {"bound": "mfma", "kernel": "s2_attend_kernel<128,false>",
+        "roofline": {"bound": "mfma", "kernel": "s2_attend_kernel<128,false,false>",
                      "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / MFMA_BF16_PEAK_TFLOPS,
-                     "traffic": None if a.small else traffic_from_profile("s2_attend_kernel<128,false>", "C2 gamma=1"),
+                     "traffic": None if a.small else traffic_from_profile("s2_attend_kernel<128,false,false>", "C2 gamma=1"),
                      "traffic_source": os.path.relpath(TRAFFIC_PROFILE, ROOT)},
         "cpu_baseline": cpu,
         "extras": {
