@@ -57,8 +57,14 @@ __device__ __forceinline__ float add_quads(float x) {      // + the same score r
   x += dpp_f<0x141>(dpp_f<0x1B>(x));                       // quad reversed, half row mirrored: lane m ^ 4
   return x + dpp_f<0x128>(x);                              // row_ror 8
 }
+// The values go through empty assembly: of plain selects over four copies of an array the compiler makes an indexed
+// load, and puts the array into scratch memory for it (32 bytes a lane; a store and a dependent load between the row maxima
+// and the first step of every solve: routing 8 heads x 300 tokens 12.6 us with, 12.1 without, 2 x 16 / 4 heads x 3001 tokens of
+// d 64 19.8 -> 19.1; a decode step of 24 sequences of 32768 tokens, 32 / 2 heads, lists not asked for, 48.8 -> 48.3; same bits).
 __device__ __forceinline__ float pick4(const float (&a)[4], int m) {
-  const float x = m & 1 ? a[1] : a[0], y = m & 1 ? a[3] : a[2];
+  float a0 = a[0], a1 = a[1], a2 = a[2], a3 = a[3];
+  asm("" : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3));
+  const float x = m & 1 ? a1 : a0, y = m & 1 ? a3 : a2;
   return m & 2 ? y : x;
 }
 __device__ __forceinline__ float sum4_scatter(const float (&a)[4], int m) {

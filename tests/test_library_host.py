@@ -3,6 +3,7 @@ declares, sizes its workspace, and rejects bad arguments before touching a GPU."
 import ctypes
 import os
 import re
+import struct
 
 import pytest
 
@@ -255,3 +256,43 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def kernel_scratch(path):
+    """Scratch bytes per lane of every kernel of the library's gfx950 code objects: the second word of the
+    kernel's descriptor, which the symbol `<kernel>.kd` points at."""
+    blob, magic, found = open(path, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", {}
+    for at in (m.start() for m in re.finditer(magic, blob)):
+        count, entry = struct.unpack_from("<Q", blob, at + 24)[0], at + 32
+        for _ in range(count):
+            off, size, name_len = struct.unpack_from("<QQQ", blob, entry)
+            target = blob[entry + 24:entry + 24 + name_len]
+            entry += 24 + name_len
+            if b"gfx950" not in target:
+                continue
+            elf = blob[at + off:at + off + size]
+            sh_off, sh_num = struct.unpack_from("<Q", elf, 40)[0], struct.unpack_from("<H", elf, 60)[0]
+            # per section: type, address, file offset, size, linked section
+            sections = [struct.unpack_from("<4xI8xQQQI", elf, sh_off + 64 * i) for i in range(sh_num)]
+            for kind, _, sym_off, sym_size, link in sections:
+                if kind != 11:                                    # dynamic symbols
+                    continue
+                names = sections[link][2]
+                for at_sym in range(sym_off, sym_off + sym_size, 24):
+                    name, index, value = struct.unpack_from("<I2xHQ", elf, at_sym)
+                    text = elf[names + name:elf.index(b"\0", names + name)].decode()
+                    if text.endswith(".kd"):
+                        _, address, file_off, _, _ = sections[index]
+                        found[text[:-3]] = struct.unpack_from("<I", elf, file_off + value - address + 4)[0]
+    return found
+
+
+def test_threshold_solvers_use_no_scratch_memory():
+    """The solver that holds four score rows per lane selects one of them by lane; as an indexed load from an array
+    that was 32 bytes of scratch in each of these kernels.  Not the builds for rows of more than 512 chunks, whose scores do not
+    all fit the registers, nor decode at alpha outside {1.25, 1.5, 2}, where room is set aside that no instruction uses."""
+    scratch = kernel_scratch(B.LIB_PATH)
+    routing = {n: b for n, b in scratch.items() if re.search(r"14s1_regs_kernelILi\d+ELi\d+ELi\dELi[01]E", n)}
+    decode = {n: b for n, b in scratch.items() if re.search(r"16s2_decode_kernelILi\d+ELi0ELi[012]ELb[01]E", n)}
+    assert len(routing) == 2 * 5 * 5 * 2 and len(decode) == 2 * 3 * 2
+    assert not {n: b for n, b in {**routing, **decode}.items() if b}
