@@ -339,15 +339,24 @@ __device__ __forceinline__ void regs_tile(const S1Args& a, char* lds, int b, int
 
   // ---- group weights, bias, lists: one token per DPP row (or per KQT rows) at a time ------
   const float inv_g = 1.f / (float)G;
+  const int first = half * NT * 16;           // this wave's first chunk
 #pragma unroll
   for (int tt = 0; tt < TPL; tt++) {
     const int tok = tok_w0 + (KQT > 1 ? kq / KQT : kq * TPL + tt);
     const bool tok_ok = tok < a.tok_end && (kq % KQT) == 0;   // of the rows sharing a token the first one writes
+    // A lane's place, hidden from the compiler where a lane has several tokens, and chunks and mask words counted from the
+    // wave's own first ones: the comparisons of all tiles are the same for every token, and were kept in scalar registers from
+    // the first token to the last (775 of them spilled at a group of 1 and 48 tiles, 144 now).  Spills of that number are not
+    // only slow (2048 tokens against a 96k cache, 4 heads: 102 us -> 80): the compiler places some ahead of
+    // the instruction that turns the lanes of a branch on again, and a register copy behind them, so that the copy
+    // reaches some lanes only.  Builds of rows of 1025 to 1536 chunks at a group of 1 gave wrong lists that way.
+    int mt = m;
+    if constexpr (TPL > 1) asm volatile("" : "+v"(mt));
     float slog = 0.f, nsup = 0.f;
 #pragma unroll
     for (int t = 0; t < NT; t++) {
       float s = 0.f;
-      if ((half * NT + t) * 16 + m < n_cand) {
+      if (t * 16 + mt < n_cand - first) {
 #pragma unroll
         for (int h = 0; h < HPL; h++) s += v[t][tt * HPL + h];
       }
@@ -376,30 +385,26 @@ __device__ __forceinline__ void regs_tile(const S1Args& a, char* lds, int b, int
     const int64_t base = ((int64_t)b * a.h_kv + r) * a.n_q + (tok_ok ? tok : 0);
     int32_t* oidx = a.idx ? a.idx + base * a.t_all : nullptr;
     float* obias = a.bias + base * a.t_all;
-    // mask word w of the token is kept by lane w % 16 of its DPP row, in slot w / 16
-    uint32_t word[4] = {0u, 0u, 0u, 0u};
+    // words [w_lo, w_hi) are this wave's to write: those of its tiles, and for the last
+    // half every word behind them (local chunks, zeros)
+    const int w_lo = half * (NT / 2);
+    const int w_hi = half == SPLIT - 1 ? a.words : (half + 1) * (NT / 2);
+    // mask word w_lo + w of the token is kept by lane w % 16 of its DPP row, in slot w / 16
+    uint32_t word[4] = {0u, 0u, 0u, 0u}, even = 0u;
 #pragma unroll
     for (int t = 0; t < NT; t++) {
       const bool member = v[t][tt * HPL] != INFINITY;
       const uint64_t bal = __ballot(member);
       const uint32_t field = (uint32_t)(bal >> (16 * kq)) & 0xffffu;
-      const int gt = half * NT + t;   // NT is even: a mask word lies in one half
-      if (m == ((gt >> 1) & 15)) {
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-          if ((gt >> 5) == i) word[i] |= field << (16 * (t & 1));
-      }
+      if (t & 1) { if (mt == ((t >> 1) & 15)) word[t >> 5] = even | field << 16; }   // NT is even: a mask word lies in one half
+      else even = field;
       if (member && tok_ok) {
         const int pos = running + __popc(field & ((1u << m) - 1u));
-        if (oidx) oidx[pos] = gt * 16 + m;
+        if (oidx) oidx[pos] = first + t * 16 + mt;
         obias[pos] = (v[t][tt * HPL] - mu) * a.inv_sigma;
       }
       running += __popc(field);
     }
-    // words [w_lo, w_hi) are this wave's to write: those of its tiles, and for the last
-    // half every word behind them (local chunks, zeros)
-    const int w_lo = half * (NT / 2);
-    const int w_hi = half == SPLIT - 1 ? a.words : (half + 1) * (NT / 2);
     if (a.causal) {
       // the always-attended local set, bias 0: the chunks of the window, then the query's own
       const int cd = (a.pos0 + min(tok, a.n_q - 1)) / a.block;
@@ -409,10 +414,11 @@ __device__ __forceinline__ void regs_tile(const S1Args& a, char* lds, int b, int
           if (oidx) oidx[total + c - c0] = c;
           obias[total + c - c0] = 0.f;
         }
-        if (((c >> 5) & 15) == m) {
+        const int w = (c >> 5) - w_lo;            // below 0: a word of the other half
+        if ((w & 15) == m) {
 #pragma unroll
           for (int i = 0; i < 4; i++)
-            if ((c >> 9) == i) word[i] |= 1u << (c & 31);
+            if ((w >> 4) == i) word[i] |= 1u << (c & 31);
         }
       }
       if (tok_ok && half == 0 && a.cnt && m == 0) a.cnt[base] = total + cd - c0 + 1;
@@ -423,8 +429,8 @@ __device__ __forceinline__ void regs_tile(const S1Args& a, char* lds, int b, int
       uint32_t* om = a.mask + base * a.words;
 #pragma unroll
       for (int i = 0; i < 4; i++) {   // at most 2048 chunks: 64 words
-        const int w = 16 * i + m;
-        if (w >= w_lo && w < w_hi) om[w] = word[i];
+        const int w = w_lo + 16 * i + m;
+        if (w < w_hi) om[w] = word[i];
       }
     }
   }

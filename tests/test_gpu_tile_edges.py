@@ -336,3 +336,14 @@ def test_routing_row_length_steps(h_q, h_kv, n_q, chunks, d, extra):
     run = U.run_prefill(w, q, k, v)
     toks = [0, 127, 128, n_q - 1]                   # token 128 is the first with one candidate more
     U.check_against_oracle(w, q, k, v, run, rows=[(0, r, i) for r in range(h_kv) for i in toks])
+
+
+@pytest.mark.parametrize("h_q,h_kv,chunks,alpha", [(1, 1, 1024, 1.5), (2, 2, 1500, 1.5), (1, 1, 1100, 1.25), (1, 1, 1100, 2.0),
+                                                   (2, 1, 1024, 1.5), (4, 1, 1400, 1.5), (16, 1, 1024, 1.5)])
+def test_routing_of_rows_of_more_than_1024_chunks(h_q, h_kv, chunks, alpha):
+    """Every group size and exponent; rows in every quarter of a wave's lanes, in both of a workgroup's chunks."""
+    w = Workload(f"edge_long_{chunks}_{h_q}_{alpha}", 1, h_q, h_kv, 200, (chunks - 1) * 64 + 200, 128, 64, offset_sigma=0.7, seed=68,
+                 alpha=alpha, gamma=1.5)
+    q, k, v = make_inputs(w, DEV)
+    run = U.run_prefill(w, q, k, v)
+    U.check_against_oracle(w, q, k, v, run, rows=[(0, r, i) for r in range(h_kv) for i in (0, 5, 74, 127, 128, 133, 139, 143, 199)])

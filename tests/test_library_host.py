@@ -4,6 +4,8 @@ import ctypes
 import os
 import re
 import struct
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
@@ -258,32 +260,37 @@ def test_bench_refuses_more_than_one_gpu():
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
 
 
-def kernel_scratch(path):
-    """Scratch bytes per lane of every kernel of the library's gfx950 code objects: the second word of the
-    kernel's descriptor, which the symbol `<kernel>.kd` points at."""
-    blob, magic, found = open(path, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", {}
-    for at in (m.start() for m in re.finditer(magic, blob)):
+def code_objects(path):
+    """The library's gfx950 code objects, as ELF images."""
+    blob = open(path, "rb").read()
+    for at in (m.start() for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", blob)):
         count, entry = struct.unpack_from("<Q", blob, at + 24)[0], at + 32
         for _ in range(count):
             off, size, name_len = struct.unpack_from("<QQQ", blob, entry)
             target = blob[entry + 24:entry + 24 + name_len]
             entry += 24 + name_len
-            if b"gfx950" not in target:
+            if b"gfx950" in target:
+                yield blob[at + off:at + off + size]
+
+
+def kernel_scratch(path):
+    """Scratch bytes per lane of every kernel: the second word of the kernel's descriptor, which the symbol
+    `<kernel>.kd` points at."""
+    found = {}
+    for elf in code_objects(path):
+        sh_off, sh_num = struct.unpack_from("<Q", elf, 40)[0], struct.unpack_from("<H", elf, 60)[0]
+        # per section: type, address, file offset, size, linked section
+        sections = [struct.unpack_from("<4xI8xQQQI", elf, sh_off + 64 * i) for i in range(sh_num)]
+        for kind, _, sym_off, sym_size, link in sections:
+            if kind != 11:                                        # dynamic symbols
                 continue
-            elf = blob[at + off:at + off + size]
-            sh_off, sh_num = struct.unpack_from("<Q", elf, 40)[0], struct.unpack_from("<H", elf, 60)[0]
-            # per section: type, address, file offset, size, linked section
-            sections = [struct.unpack_from("<4xI8xQQQI", elf, sh_off + 64 * i) for i in range(sh_num)]
-            for kind, _, sym_off, sym_size, link in sections:
-                if kind != 11:                                    # dynamic symbols
-                    continue
-                names = sections[link][2]
-                for at_sym in range(sym_off, sym_off + sym_size, 24):
-                    name, index, value = struct.unpack_from("<I2xHQ", elf, at_sym)
-                    text = elf[names + name:elf.index(b"\0", names + name)].decode()
-                    if text.endswith(".kd"):
-                        _, address, file_off, _, _ = sections[index]
-                        found[text[:-3]] = struct.unpack_from("<I", elf, file_off + value - address + 4)[0]
+            names = sections[link][2]
+            for at_sym in range(sym_off, sym_off + sym_size, 24):
+                name, index, value = struct.unpack_from("<I2xHQ", elf, at_sym)
+                text = elf[names + name:elf.index(b"\0", names + name)].decode()
+                if text.endswith(".kd"):
+                    _, address, file_off, _, _ = sections[index]
+                    found[text[:-3]] = struct.unpack_from("<I", elf, file_off + value - address + 4)[0]
     return found
 
 
@@ -296,3 +303,62 @@ def test_threshold_solvers_use_no_scratch_memory():
     decode = {n: b for n, b in scratch.items() if re.search(r"16s2_decode_kernelILi\d+ELi0ELi[012]ELb[01]E", n)}
     assert len(routing) == 2 * 5 * 5 * 2 and len(decode) == 2 * 3 * 2
     assert not {n: b for n, b in {**routing, **decode}.items() if b}
+
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+WRITES_VECTOR_REGISTERS = re.compile(r"v_(?!writelane|readlane|readfirstlane|cmp)|scratch_|global_|buffer_|flat_|ds_")
+
+
+def copies_ahead_of_their_lanes(elf_path):
+    """Places where a branch that is taken with no lane left lands, and vector registers are written there before the
+    lanes of the code around it are turned on again."""
+    dump = subprocess.Popen([OBJDUMP, "-d", "--no-show-raw-insn", elf_path], stdout=subprocess.PIPE, text=True)
+    kernel, start, code, found = None, 0, {}, []
+
+    def check():
+        at = sorted(code)
+        index = {a: i for i, a in enumerate(at)}
+        lands = lambda branch: {start + int(m.group(1), 16) for t in code.values() if t.startswith(branch)
+                                for m in [re.search(r"\+0x([0-9a-f]+)>", t)] if m}
+        blocks = lands(("s_branch", "s_cbranch"))
+        for target in lands("s_cbranch_execz") & index.keys():
+            written = None
+            for a in at[index[target]:]:
+                text = code[a]
+                if a != target and a in blocks:
+                    break
+                if text.startswith("s_or_b64 exec, exec,"):
+                    if written:
+                        found.append((kernel, hex(a - start), written))
+                    break
+                if "exec" in text or text.startswith(("s_branch", "s_endpgm", "s_setpc")):
+                    break
+                if WRITES_VECTOR_REGISTERS.match(text):
+                    written = written or text.split("//")[0].strip()
+
+    for line in dump.stdout:
+        if line.endswith(">:\n"):
+            if code:
+                check()
+            address, kernel = line.split(" ", 1)
+            start, code = int(address, 16), {}
+        elif "//" in line:
+            code[int(line.split("//")[1].split(":")[0], 16)] = line.strip()
+    if code:
+        check()
+    assert dump.wait() == 0
+    return found
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
+def test_no_vector_register_is_written_ahead_of_its_lanes(tmp_path):
+    """Where many scalar registers are spilled, the compiler can place a copy of a vector register between the spills and the
+    instruction that turns the lanes of a branch on again: the copy then reaches the lanes of the branch only.  The
+    routing kernel for rows of 1025 to 1536 chunks at a group of 1 was built that way, and gave wrong lists."""
+    paths = []
+    for i, elf in enumerate(code_objects(B.LIB_PATH)):
+        paths.append(str(tmp_path / f"{i}.elf"))
+        open(paths[-1], "wb").write(elf)
+    assert paths
+    with ThreadPoolExecutor(4) as pool:
+        assert [x for found in pool.map(copies_ahead_of_their_lanes, paths) for x in found] == []
