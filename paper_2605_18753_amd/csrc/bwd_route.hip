@@ -301,9 +301,12 @@ typedef f32x4 f32x4u __attribute__((aligned(4)));
 constexpr int kKeepTiles = 16;   // margin tiles kept in LDS: 1 KB each and wave
 
 // Waves per SIMD that the registers have to leave room for.  Without a bound the accumulators of both products
-// are kept twice (109 + 64 registers at d = 128: two waves): KEEP takes 126 then, without a spill; rows of more
-// than 256 chunks 168 with four spilled, which is still better than 178 and two waves (20001 tokens, 4 heads,
-// d 128: 280 us without a bound and the loads ahead, 217 with two waves, 192 with three).
+// are kept twice (109 + 64 registers at d = 128: two waves).  With it, at d = 128: KEEP 126 registers at a group of 1, 122 at
+// 16, and 128 with two spilled at 2, 4 and 8 (12 bytes of scratch; with three waves, and none spilled, the whole backward pass takes
+// 0.3 % less to 0.4 % more at seven shapes of these groups, and 305 us for 300 at 2 x 16 / 4 heads x 2000 tokens); rows of more
+// than 256 chunks 168 with four spilled at a group of 1, six at 2, 4 and 8, none at 16, which is still better than 178 and two
+// waves (20001 tokens, 4 heads: 280 us without a bound and the loads ahead, 217 with two waves, 192 with three).  None is spilled
+// at d = 64.
 constexpr int kRouteWaves = 4, kRouteWavesLong = 3;
 
 template <int D, int G, bool KEEP>

@@ -68,28 +68,22 @@ template <int D, int STAGES_> struct RegsCfg {
 };
 
 // Exchange between the two waves that share 16 rows (waves w and w ^ 4): DPP row kq of a
-// wave hands up to 8 floats to DPP row kq of its partner (swap), or every wave a flag to
-// the whole workgroup (any_flag).  One barrier per call, two alternating buffers: every
+// wave hands two floats (swap), or two of each of its four score rows (swap_rows), to DPP row kq of its partner, or
+// every wave a flag to the whole workgroup (any_flag).  One barrier per call, two alternating buffers: every
 // wave of the workgroup makes the same sequence of calls.
 struct PairX {
   float* area;   // LDS: [2 buffers][8 waves][4 DPP rows][12]: 8 values, 1 flag, 3 unused
   int wave, kq, m, buf;
-  template <int K>
-  __device__ __forceinline__ bool swap(const float (&mine)[K], float (&other)[K]) {
-    static_assert(K <= 8, "at most 8 values per exchange");
+  __device__ __forceinline__ void swap(const float (&mine)[2], float (&other)[2]) {
     float* slot = area + ((buf * 8 + wave) * 4 + kq) * 12;
-    if (m == 0) {
-#pragma unroll
-      for (int k = 0; k < K; k++) slot[k] = mine[k];
-    }
+    if (m == 0) { slot[0] = mine[0]; slot[1] = mine[1]; }
     __syncthreads();
     const float* o = area + ((buf * 8 + (wave ^ 4)) * 4 + kq) * 12;
-#pragma unroll
-    for (int k = 0; k < K; k++) other[k] = o[k];
+    other[0] = o[0];
+    other[1] = o[1];
     buf ^= 1;
-    return false;
   }
-  // the same for values of which lane m of a DPP row holds score row m % 4's
+  // values of which lane m of a DPP row holds score row m % 4's
   template <int K>
   __device__ __forceinline__ void swap_rows(const float (&mine)[K], float (&other)[K]) {
     static_assert(K <= 2, "at most 8 values per exchange");
@@ -471,7 +465,9 @@ __global__ __launch_bounds__(512, RegsVar<VAR>::MIN_WG) void s1_regs_kernel(S1Ar
   } else if constexpr (VAR == 1) {
     // A row costs its register slots, filled or not: with 24 of them for up to 384 chunks besides 32 (and, on wave pairs,
     // 24 for up to 768) 32k tokens take 418 us instead of 444, 2000 tokens against a 32k cache 61 for 64, 128k in
-    // chunks of 128 4.53 ms on pairs for 4.67.  12 besides 16 gave 2 % and is left out.
+    // chunks of 128 4.53 ms on pairs for 4.67.  12 besides 16 gave 2 % and is left out.  On pairs rows of 513 to 768 chunks are
+    // cut at chunk 384, longer ones at 512 or 768: their sums are added in another order than in one wave, which moves
+    // a threshold in its last place.
     if (ntile <= 24) regs_tile<D, G, MODE, 1, 24, ST>(a, lds, b, r, tok0, ntile);
     else regs_tile<D, G, MODE, 1, 32, ST>(a, lds, b, r, tok0, ntile);
   } else {

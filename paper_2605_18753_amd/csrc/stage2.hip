@@ -13,11 +13,12 @@
 // the MFMA work of a chunk none of its tokens kept; rows of a wave that did not keep a chunk
 // get bias -inf for it, which keeps the per-token result exact.
 //
-// What bounds it.  Timing copies of this kernel without one part at a time (32k causal, group
-// of 4, dense): no direct copies -12 %, no LDS operand reads -11 %, no exponentials -8 %, no
+// What bounds it.  Timing copies of an earlier state of this kernel without one part at a time (32k causal,
+// group of 4, dense): no direct copies -12 %, no LDS operand reads -11 %, no exponentials -8 %, no
 // barriers -2 %, none of them -29 % (1.5 PFLOP/s, near the rate of a register-fed MFMA loop at the
-// clock this load runs at): copies, operand feed and vector work share the time about evenly and the
-// order of the instructions no longer matters (exponential and operand-read distances: +-1 %).
+// clock this load runs at): copies, operand feed and vector work share the time about evenly.  The distances
+// of exponentials and operand reads from their use are worth +-1 %; where a tile's first operands, its bias and its place in
+// the list are asked for was worth 10 % since (see begin_chunk and the iteration).
 // Without the pipeline across tiles (softmax of a tile between its own two products): 8.84 ->
 // 8.43 ms at the 32k prefill, 110 -> 104 ms at 128k tokens, 820 -> 735 us for 2000 tokens against a
 // 32k cache.
@@ -614,6 +615,16 @@ static hipError_t launch_s2_t(const S2Args& a, bool pair, hipStream_t st) {
 static int64_t s2_most_records(const dash_params& p, const Layout& L);
 static int s2_tiles(const dash_params& p, const Layout& L) { return (p.n_q + 128 / L.g_q - 1) / (128 / L.g_q); }
 
+// Whether a launch that is not cut walks each list with two groups of waves.  It takes as long as the longest half, and a CU has room
+// for one such workgroup: no more than 256 of them.  Of up to four tiles the halves gain what the exchange costs (whole forward,
+// one group -> two, 32 / 8 heads: 128 tokens 20.7 -> 21.2 us, 192 25.0 -> 25.8, 256 28.2 -> 28.3; 257 29.4 -> 28.5, 500 37.1 -> 33.8,
+// 1000 45.9 -> 41.7; 16 heads over one x 2048 66.1 -> 55.4).  What the lists hold is not known here: where routing leaves a tile of
+// 128 rows no more than four chunks of 64 keys in all, the second group is a loss (1000 tokens, 32 / 8 heads, this launch alone, one
+// group -> two: 1 chunk 9.6 -> 11.1 us, 2 10.8 -> 11.9, 3 11.9 -> 12.8, 4 13.2 -> 13.7; 5 14.5 -> 14.6, 6 15.7 -> 15.4, 9 19.3 -> 17.8, all
+// 27.7 -> 23.3), most of it the larger workgroup's start: leaving such a list to the first group, without the exchange, gives
+// 0.5 us back at 1 chunk, nothing at 2 and 3, and loses at 4.
+static bool s2_paired(int64_t wgs, float tiles) { return wgs <= 256 && tiles > 4.f; }
+
 // Parts a tile's chunk list is cut into at most.  512 workgroups are resident at once, two per CU
 // (a single one on a CU runs 1.4 times as fast); fewer tiles than that leave the chip idle for as long
 // as the longest list takes.  The number of parts is the one with the least estimated time, in units of
@@ -622,16 +633,12 @@ static int s2_tiles(const dash_params& p, const Layout& L) { return (p.n_q + 128
 // where the tiles make two uneven rounds.  Measured, 8 kv-heads, group of 4, against a 32k cache, uncut -> cut:
 // 65 tokens 707 -> 74 us, 300 709 -> 189, 700 718 -> 396, 1000 724 -> 500, 1500 850 -> 713, 2500 1449 -> 1190;
 // whole prompts: 1 kv-head, 8000 tokens 195 -> 138, 2 kv-heads of one head, 12000 tokens 285 -> 152.
-// Where the rule does not cut: 8 x 1000 tokens 33.2 -> 34.3 in two parts, 8 x 600 23.2 -> 26.7; two groups of waves (s2_paired)
-// need no records and no second launch and do gain there.  Their estimate is half the tiles and 8: near 256 workgroups it is the least
-// (whole forward, cut -> paired: 8 / 2 heads x 4096 tokens 89.9 -> 80.2 us, 4 heads over one x 8192 147 -> 138), with fewer
-// cutting stays better (2 heads x 8000 96 us cut, 139 paired; 4 heads over one x 3000 51, 64).
-// Whether a launch that is not cut walks each list with two groups of waves.  It takes as long as the longest half, and a CU has room
-// for one such workgroup: no more than 256 of them.  Of up to four tiles the halves gain what the exchange costs (whole forward,
-// one group -> two, 32 / 8 heads: 128 tokens 20.7 -> 21.2 us, 192 25.0 -> 25.8, 256 28.2 -> 28.3; 257 29.4 -> 28.5, 500 37.1 -> 33.8,
-// 1000 45.9 -> 41.7; 16 heads over one x 2048 66.1 -> 55.4).
-static bool s2_paired(int64_t wgs, float tiles) { return wgs <= 256 && tiles > 4.f; }
-
+// Where the rule does not cut: 8 x 1000 tokens 33.2 -> 34.3 in two parts, 8 x 600 23.2 -> 26.7.  Two groups of waves (s2_paired)
+// need no records and no second launch.  Their estimate, half the tiles and 8, says where they beat the cut, not what they gain over one
+// group: near 256 workgroups (this launch alone, the best cut / two groups: 16 heads x 1024 tokens 25.9 / 24.2 us, x 1600
+// 36.1 / 31.7, x 2048 47.1 / 39.6, 8 / 2 heads x 4096 66.0 / 63.5), while with fewer the cut is as fast or faster (16 tiles:
+// 16 workgroups 22.3 / 23.4, 64 22.6 / 23.1 and 23.9 / 23.8; 21 tiles: 44 24.3 / 27.2, 88 26.3 / 27.5; 25 tiles: 104 27.8 / 31.1;
+// 32 tiles: 64 26.6 / 37.5, 128 34.0 / 36.3; 40 tiles: 80 31.8 / 45.0, 160 37.9 / 43.4).
 int s2_parts(const dash_params& p, const Layout& L) {
   if (!L.use_mfma) return 1;
   const int64_t wgs = (int64_t)s2_tiles(p, L) * p.h_kv * p.batch;

@@ -180,24 +180,45 @@ def test_prefill_cut_chunk_lists(name, h_q, h_kv, n_q, n_kv, d, block, extra):
     ("four_tiles", 1, 4, 2, 256, 128, 64, {}), ("five_tiles", 1, 4, 2, 257, 128, 64, {}), ("six_tiles_b128", 2, 2, 1, 321, 64, 128, {}),
     ("ragged_g16", 1, 16, 1, 577, 64, 64, {"gamma": 2.0}), ("window", 1, 8, 8, 390, 128, 64, {"window": 2}),
     ("256_tiles", 32, 1, 1, 1024, 64, 64, {"gamma": 2.0}),
-    ("264_tiles", 33, 1, 1, 1024, 64, 64, {"gamma": 2.0}), ("sparse_g1", 1, 2, 2, 999, 128, 64, {"gamma": 4.0, "offset_sigma": 1.0}),
+    ("264_tiles", 33, 1, 1, 1024, 64, 64, {"gamma": 2.0}), ("sparse_g1", 1, 2, 2, 950, 128, 64, {"gamma": 4.0, "offset_sigma": 1.0}),
     ("noncausal", 1, 8, 8, 832, 128, 64, {"causal": False})])
 def test_prefill_in_two_groups(name, batch, h_q, h_kv, n, d, block, extra):
     w = Workload("edge_pair_" + name, batch, h_q, h_kv, n, n, d, block, seed=49, **{"offset_sigma": 0.7, **extra})
     q, k, v = make_inputs(w, DEV)
     run = U.run_prefill(w, q, k, v)
     U.check_against_oracle(w, q, k, v, run, rows=U.sample_rows(w, 80) if batch > 2 else None)
-    o = torch.full_like(q, float("nan"))
-    B.dense_attn(run.params, q, k, v, o, B.alloc_workspace(run.params, DEV))
+    check_dense_uncut(w, run.params, q, k, v)
+
+
+def check_dense_uncut(w, p, q, k, v):
+    """dense_attn against fp64, in a launch that is not cut into parts: the records of parts are all that it
+    writes into the workspace."""
+    o, ws = torch.full_like(q, float("nan")), B.alloc_workspace(p, DEV).fill_(0xA5)
+    B.dense_attn(p, q, k, v, o, ws)
     torch.cuda.synchronize()
-    g, pos = h_q // h_kv, torch.arange(n)
-    for b in (0, batch - 1):
-        for h in range(h_q):
-            z = q[b, h].double().cpu() @ k[b, h // g].double().cpu().T / d ** 0.5
+    assert bool((ws == 0xA5).all()), "cut into parts: not the kernels this is about"
+    g, pos = w.h_q // w.h_kv, torch.arange(w.n_q)
+    for b in {0, w.batch - 1}:
+        for h in range(w.h_q):
+            z = q[b, h].double().cpu() @ k[b, h // g].double().cpu().T / w.head_dim ** 0.5
             if w.causal:
                 z.masked_fill_(pos[None, :] > pos[:, None], float("-inf"))
             ref = torch.softmax(z, -1) @ v[b, h // g].double().cpu()
             assert (o[b, h].double().cpu() - ref).abs().max() <= 2e-2 * ref.abs().max()   # the bar of the cut lists' test
+
+
+# logits that rise or fall by a factor of four along the keys: a late raise of the running maximum, and two groups of waves
+# whose maxima lie far apart, either way round
+@pytest.mark.parametrize("first,last", [(1.0, 4.0), (4.0, 1.0)])
+@pytest.mark.parametrize("name,batch,h_q,h_kv,n,d", [("two_groups", 1, 8, 8, 832, 128), ("two_groups_d64", 1, 16, 2, 832, 64), ("one_group", 33, 1, 1, 1000, 128)])
+def test_prefill_of_rising_and_falling_logits(name, batch, h_q, h_kv, n, d, first, last):
+    w = Workload("edge_ramp_" + name, batch, h_q, h_kv, n, n, d, 64, seed=50, offset_sigma=0.3)
+    q, k, v = make_inputs(w, DEV)
+    k = (k.float() * torch.linspace(first, last, n, device=DEV).view(1, 1, n, 1)).to(k.dtype)
+    q = (q.float() * 3.0).to(q.dtype)
+    run = U.run_prefill(w, q, k, v)
+    U.check_against_oracle(w, q, k, v, run, rows=U.sample_rows(w, 96))
+    check_dense_uncut(w, run.params, q, k, v)
 
 
 @pytest.mark.parametrize("batch,h_q,h_kv,n_kv,extra", [
