@@ -147,32 +147,7 @@ __device__ __forceinline__ void solve_rows16(float* S, int ld, int row0, int n_c
     asm volatile("" : "+v"(F), "+v"(G));
     F = row16_reduce(F, OpAdd());
     G = row16_reduce(G, OpAdd());
-    if (!done) {
-      const float f = F - 1.f;
-      if (f == 0.f) {
-        done = true;
-      } else {
-        if (f > 0.f) lo = tau; else hi = tau;
-        const float mid = 0.5f * (lo + hi);
-        float cand = (MODE == MODE_BISECT || !(G > 0.f)) ? mid : tau + f / (p * G);
-        if (MODE != MODE_BISECT && cand == tau) {
-          done = true;
-        } else {
-          if (!(cand > lo && cand < hi)) cand = mid;
-          if (!(cand > lo && cand < hi)) { done = true; tau = lo; }
-          else {
-            // alpha = 1.5: a Newton step s from the left leaves an error of about
-            // (k / 2G) s^2 <= (n / 2G) s^2 (f'' = 2k, f' = -2G); once that is below
-            // 2e-8 the step is final and the confirming evaluation is skipped
-            if (MODE == MODE_P2 && f > 0.f && cand != mid) {
-              const float st = cand - tau;
-              if ((float)n_cand * st * st < 4e-8f * G) done = true;
-            }
-            tau = cand;
-          }
-        }
-      }
-    }
+    newton_step<MODE>(F, G, p, n_cand, tau, lo, hi, done);
     if (!__any(!done)) break;
   }
 #pragma unroll

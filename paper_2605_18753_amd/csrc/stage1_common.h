@@ -81,7 +81,8 @@ __device__ __forceinline__ void quad_transpose(const float (&a)[4], float (&t)[4
 }
 
 // One bracketed Newton step of row state (tau, lo, hi, done) from the sums F = sum u^p,
-// G = sum u^(p-1) at tau: without branches.
+// G = sum u^(p-1) at tau: without branches, each lane for the row it has (fp32 routing, one head of 1024 tokens, against
+// branches: 15.4 -> 14.6 us, 8 / 2 heads x 4096 46.6 -> 45.0, at alpha 3 70.4 -> 68.5; same bits).
 template <int MODE>
 __device__ __forceinline__ void newton_step(float F, float G, float p, int n_cand, float& tau, float& lo, float& hi,
                                             bool& done) {
@@ -92,8 +93,9 @@ __device__ __forceinline__ void newton_step(float F, float G, float p, int n_can
   const bool stay = f == 0.f || (MODE != MODE_BISECT && cand == tau);
   if (!(cand > l && cand < h)) cand = mid;
   const bool closed = !(cand > l && cand < h);               // bracket closed
-  // alpha = 1.5: a Newton step s from the left leaves an error of about (n / 2G) s^2;
-  // once that is below 2e-8 the step is final
+  // alpha = 1.5: a Newton step s from the left leaves an error of about (k / 2G) s^2 <= (n / 2G) s^2
+  // for k chunks in the support (f'' = 2k, f' = -2G); once that is below 2e-8 the step is final and the confirming
+  // evaluation is skipped
   const float st = cand - tau;
   const bool last = MODE == MODE_P2 && f > 0.f && cand != mid && (float)n_cand * st * st < 4e-8f * G;
   const float next = closed ? l : cand;

@@ -86,92 +86,95 @@ __device__ __forceinline__ void solve_rows_regs(float (&v)[RB][NJ], int n_cand, 
       tau_out[rb] = tau[rb];
     }
   } else {
-  float mx[RB], lo[RB], hi[RB], tau[RB];
-  bool done[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; rb++) {
-    float m = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < NJ; j++) m = fmaxf(m, v[rb][j]);
-    mx[rb] = wave_max(m);
-    lo[rb] = mx[rb] - 1.f;
-    hi[rb] = mx[rb] - exp2f(-(alpha - 1.f) * log2f((float)n_cand));
-    tau[rb] = lo[rb];
-    done[rb] = false;
-  }
-  if constexpr (MODE != MODE_BISECT) {
-    // warm start on the 64 lane maxima (a subset: its root and every Newton
-    // iterate from the left on it are lower bounds of tau)
-    float ml[RB];
+    float mx[RB], lo[RB], hi[RB], tau[RB];
+    bool done[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; rb++) {
-      ml[rb] = -INFINITY;
+      float m = -INFINITY;
 #pragma unroll
-      for (int j = 0; j < NJ; j++) ml[rb] = fmaxf(ml[rb], v[rb][j]);
+      for (int j = 0; j < NJ; j++) m = fmaxf(m, v[rb][j]);
+      mx[rb] = wave_max(m);
+      lo[rb] = mx[rb] - 1.f;
+      hi[rb] = mx[rb] - exp2f(-(alpha - 1.f) * log2f((float)n_cand));
+      tau[rb] = lo[rb];
+      done[rb] = false;
     }
-    for (int it = 0; it < 5; it++) {
+    if constexpr (MODE != MODE_BISECT) {
+      // warm start on the 64 lane maxima (a subset: its root and every Newton
+      // iterate from the left on it are lower bounds of tau)
+      float ml[RB];
 #pragma unroll
       for (int rb = 0; rb < RB; rb++) {
-        float f, g;
-        pow_terms<MODE>(fmaxf(ml[rb] - tau[rb], 0.f), p, f, g);
-        const float F = wave_sum(f), G = wave_sum(g);
-        if (F > 1.f && G > 0.f) tau[rb] += (F - 1.f) / (p * G);
+        ml[rb] = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < NJ; j++) ml[rb] = fmaxf(ml[rb], v[rb][j]);
+      }
+      for (int it = 0; it < 5; it++) {
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++) {
+          float f, g;
+          pow_terms<MODE>(fmaxf(ml[rb] - tau[rb], 0.f), p, f, g);
+          const float F = wave_sum(f), G = wave_sum(g);
+          if (F > 1.f && G > 0.f) tau[rb] += (F - 1.f) / (p * G);
+        }
+      }
+#pragma unroll
+      for (int rb = 0; rb < RB; rb++) {
+        tau[rb] = fmaxf(tau[rb], lo[rb]);
+        if (!(tau[rb] < hi[rb])) tau[rb] = lo[rb];
       }
     }
+    for (int it = 0; it < 64; it++) {
+      bool all_done = true;
 #pragma unroll
-    for (int rb = 0; rb < RB; rb++) {
-      tau[rb] = fmaxf(tau[rb], lo[rb]);
-      if (!(tau[rb] < hi[rb])) tau[rb] = lo[rb];
-    }
-  }
-  for (int it = 0; it < 64; it++) {
-    bool all_done = true;
+      for (int rb = 0; rb < RB; rb++) {
+        float F = 0.f, G = 0.f;
 #pragma unroll
-    for (int rb = 0; rb < RB; rb++) {
-      float F = 0.f, G = 0.f;
-#pragma unroll
-      for (int j = 0; j < NJ; j++) {
-        float f, g;
-        pow_terms<MODE>(fmaxf(v[rb][j] - tau[rb], 0.f), p, f, g);
-        F += f; G += g;
-      }
-      F = wave_sum(F);
-      G = wave_sum(G);
-      if (!done[rb]) {
-        const float f = F - 1.f;
-        if (f == 0.f) {
-          done[rb] = true;
-        } else {
-          if (f > 0.f) lo[rb] = tau[rb]; else hi[rb] = tau[rb];
-          const float mid = 0.5f * (lo[rb] + hi[rb]);
-          float cand = (MODE == MODE_BISECT || !(G > 0.f)) ? mid : tau[rb] + f / (p * G);
-          if (MODE != MODE_BISECT && cand == tau[rb]) {
-            done[rb] = true;                       // Newton step below the fp32 spacing of tau
+        for (int j = 0; j < NJ; j++) {
+          float f, g;
+          pow_terms<MODE>(fmaxf(v[rb][j] - tau[rb], 0.f), p, f, g);
+          F += f; G += g;
+        }
+        F = wave_sum(F);
+        G = wave_sum(G);
+        // newton_step with its branches: a wave holds whole rows, so all its lanes take the same one.  With newton_step's selects
+        // a decode step at alpha 2.5, 25 steps a row, takes 1 to 4 % longer (1000 tokens, 32 / 8 heads 15.8 -> 16.4 us); at alpha 1.25 to
+        // 1.7 no difference.  Same bits.
+        if (!done[rb]) {
+          const float f = F - 1.f;
+          if (f == 0.f) {
+            done[rb] = true;
           } else {
-            if (!(cand > lo[rb] && cand < hi[rb])) cand = mid;
-            if (!(cand > lo[rb] && cand < hi[rb])) {
-              done[rb] = true;                     // bracket closed: adjacent floats
-              tau[rb] = lo[rb];
+            if (f > 0.f) lo[rb] = tau[rb]; else hi[rb] = tau[rb];
+            const float mid = 0.5f * (lo[rb] + hi[rb]);
+            float cand = (MODE == MODE_BISECT || !(G > 0.f)) ? mid : tau[rb] + f / (p * G);
+            if (MODE != MODE_BISECT && cand == tau[rb]) {
+              done[rb] = true;                       // Newton step below the fp32 spacing of tau
             } else {
-              if (MODE == MODE_P2 && f > 0.f && cand != mid) {   // see solve_rows16 in stage1.hip
-                const float st = cand - tau[rb];
-                if ((float)n_cand * st * st < 4e-8f * G) done[rb] = true;
+              if (!(cand > lo[rb] && cand < hi[rb])) cand = mid;
+              if (!(cand > lo[rb] && cand < hi[rb])) {
+                done[rb] = true;                     // bracket closed: adjacent floats
+                tau[rb] = lo[rb];
+              } else {
+                if (MODE == MODE_P2 && f > 0.f && cand != mid) {   // see newton_step
+                  const float st = cand - tau[rb];
+                  if ((float)n_cand * st * st < 4e-8f * G) done[rb] = true;
+                }
+                tau[rb] = cand;
               }
-              tau[rb] = cand;
             }
           }
         }
+        all_done = all_done && done[rb];
       }
-      all_done = all_done && done[rb];
+      if (all_done) break;
     }
-    if (all_done) break;
-  }
 #pragma unroll
-  for (int rb = 0; rb < RB; rb++) {
+    for (int rb = 0; rb < RB; rb++) {
 #pragma unroll
-    for (int j = 0; j < NJ; j++) v[rb][j] = pow_p<MODE>(fmaxf(v[rb][j] - tau[rb], 0.f), p);
-    tau_out[rb] = tau[rb];
-  }
+      for (int j = 0; j < NJ; j++) v[rb][j] = pow_p<MODE>(fmaxf(v[rb][j] - tau[rb], 0.f), p);
+      tau_out[rb] = tau[rb];
+    }
   }
 }
 
