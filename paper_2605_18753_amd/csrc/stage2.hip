@@ -122,17 +122,20 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
   }
 
   // ---- chunk bitmaps -------------------------------------------------------
-  // lane t < tokw tracks token tok_w0 + t: its mask row, its rank in the compact
-  // bias list, and the next bias value (prefetched).
+  // lane t < tokw tracks token tok_w0 + t: its mask row, where in the compact bias
+  // list its next bias lies, and that value (prefetched).
   const int trk_tok = tok_w0 + lane;
   const bool trk_ok = lane < tokw && trk_tok < a.n_q;
   const int64_t trk_base = ((int64_t)b * a.h_kv + r) * a.n_q + min(tok_w0, a.n_q - 1);   // uniform; a lane's row by offset
   const uint32_t* trk_mask = DENSE ? nullptr : a.mask + trk_base * a.words;
-  const float* trk_bias = DENSE ? nullptr : a.bias + trk_base * a.t_all;
-  const uint32_t trk_m0 = trk_ok ? (uint32_t)(lane * a.words) : 0u, trk_b0 = trk_ok ? (uint32_t)(lane * a.t_all) : 0u;
-  int trk_rank = 0, trk_wi = -1;
+  const __amdgpu_buffer_rsrc_t trk_bias = __builtin_amdgcn_make_buffer_rsrc(
+      DENSE ? nullptr : const_cast<float*>(a.bias) + trk_base * a.t_all, 0, DENSE ? 0 : max(min(tokw, a.n_q - tok_w0), 0) * a.t_all * 4, 0x00020000);
+  auto ask_bias = [&](uint32_t at) -> float { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(trk_bias, at, 0, 0)); };
+  const uint32_t trk_m0 = trk_ok ? (uint32_t)(lane * a.words) : 0u;
+  uint32_t trk_at = trk_ok ? (uint32_t)(lane * a.t_all) * 4u : ~3u;   // of the next bias, in bytes; past the end for lanes without a token
+  int trk_wi = -1;
   uint32_t trk_word = 0;
-  float trk_next = 0.f;
+  float trk_old = 0.f, trk_next = 0.f;
 
   for (int i = tid; i < 5 * 64; i += 256) wgmask[i] = 0u;
   __syncthreads();
@@ -184,12 +187,12 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
       }
       for (; skip > 0; skip--) it_bits &= it_bits - 1u;
       if (!DENSE && trk_ok) {                   // the tracked token's entries before the part's first chunk
-        for (int wi = 0; wi < it_wi; wi++) trk_rank += __popc(trk_mask[trk_m0 + wi]);
-        trk_rank += __popc(trk_mask[trk_m0 + it_wi] & ((1u << __builtin_ctz(it_bits)) - 1u));
+        for (int wi = 0; wi < it_wi; wi++) trk_at += 4 * __popc(trk_mask[trk_m0 + wi]);
+        trk_at += 4 * __popc(trk_mask[trk_m0 + it_wi] & ((1u << __builtin_ctz(it_bits)) - 1u));
       }
     }
   }
-  if (!DENSE) trk_next = trk_bias[trk_b0 + min(trk_rank, a.t_all - 1)];
+  if (!DENSE) trk_next = ask_bias(trk_at);
 
   // ---- tile iterator (workgroup-uniform) ---------------------------------
   int it_sub = nsub - 1, it_u = -1;
@@ -273,12 +276,17 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
     if (!DENSE && !diag) {
       if ((u >> 5) != trk_wi) { trk_wi = u >> 5; trk_word = trk_mask[trk_m0 + trk_wi]; }
       const bool bit = trk_ok && ((trk_word >> (u & 31)) & 1u);
-      bt = bit ? trk_next * kLog2e : -INFINITY;
-      trk_rank += bit ? 1 : 0;
-      // By every lane, whether its token kept the chunk or not: where only some load, the others' values are merged
-      // right behind the load, and the wave waits for memory here instead of at the next chunk (32k prefill 8.64 ->
-      // 8.24 ms, 2000 tokens against a 32k cache 735 -> 674 us, 16k with a group of 16 1.62 -> 1.54 ms).
-      trk_next = trk_bias[trk_b0 + min(trk_rank, a.t_all - 1)];
+      const float next = trk_old + trk_next;   // one of them is 0
+      bt = bit ? next * kLog2e : -INFINITY;
+      trk_old = bit ? 0.f : next;
+      trk_at += bit ? 4u : 0u;
+      // One load for every lane, and none that merges values behind it: where only some lanes load, the others' values are
+      // merged right behind the load, and the wave waits for memory here instead of at the next chunk (32k prefill 8.64 ->
+      // 8.24 ms, 2000 tokens against a 32k cache 735 -> 674 us, 16k with a group of 16 1.62 -> 1.54 ms).  Lanes whose token did not
+      // keep the chunk read past the end of the resource, which touches no memory, and keep their value: reading it again took
+      // a cache line of every token for each chunk (128k tokens at alpha 2, chunks of 64, 32 / 8 heads: 55 -> 43 to 50 ms, 8 / 2
+      // heads 13.3 -> 12.5; chunks of 128 82 -> 79; 32k and 64k tokens the same to 5 % less).
+      trk_next = ask_bias(bit ? trk_at : ~3u);
     }
     bias_row = __shfl(bt, n / a.g_q);
   };

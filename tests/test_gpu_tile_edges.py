@@ -181,7 +181,9 @@ def test_prefill_cut_chunk_lists(name, h_q, h_kv, n_q, n_kv, d, block, extra):
     ("ragged_g16", 1, 16, 1, 577, 64, 64, {"gamma": 2.0}), ("window", 1, 8, 8, 390, 128, 64, {"window": 2}),
     ("256_tiles", 32, 1, 1, 1024, 64, 64, {"gamma": 2.0}),
     ("264_tiles", 33, 1, 1, 1024, 64, 64, {"gamma": 2.0}), ("sparse_g1", 1, 2, 2, 950, 128, 64, {"gamma": 4.0, "offset_sigma": 1.0}),
-    ("noncausal", 1, 8, 8, 832, 128, 64, {"causal": False})])
+    ("noncausal", 1, 8, 8, 832, 128, 64, {"causal": False}),
+    # every chunk kept: behind the last bias of the last token the array ends
+    ("noncausal_all", 1, 2, 1, 640, 128, 64, {"causal": False, "gamma": 0.01})])
 def test_prefill_in_two_groups(name, batch, h_q, h_kv, n, d, block, extra):
     w = Workload("edge_pair_" + name, batch, h_q, h_kv, n, n, d, block, seed=49, **{"offset_sigma": 0.7, **extra})
     q, k, v = make_inputs(w, DEV)
