@@ -20,8 +20,8 @@
 // pair, their thresholds and the list are computed redundantly, which costs a few
 // microseconds of otherwise idle vector and matrix units but no launch, no list in memory and
 // no dependent round trip.  Measured (us per step, separate routing and merge launches -> this
-// kernel): one sequence of 1000 tokens, 8 kv-heads, 27.6 -> 14.3; 24 of 32k, 2 kv-heads, group of 16 (with a scoring
-// launch, see score_in_place in stage2_decode.hip) 76 -> 68; 12 of up to 20000, 8 kv-heads, 83 -> 64.
+// kernel): one sequence of 1000 tokens, 8 kv-heads, 27.6 -> 13.5; 24 of 32k, 2 kv-heads, group of 16 (with a scoring
+// launch, see score_in_place in stage2_decode.hip) 76 -> 64; 12 of up to 20000, 8 kv-heads, 83 -> 64.
 //
 // Merge.  A workgroup writes its partial record and then a flag, both past the caches
 // (agent-scope stores), and reads the flags of its pair's splits: whoever sees all of them set

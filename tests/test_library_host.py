@@ -310,8 +310,8 @@ WRITES_VECTOR_REGISTERS = re.compile(r"v_(?!writelane|readlane|readfirstlane|cmp
 
 
 def copies_ahead_of_their_lanes(elf_path):
-    """Places where a branch that is taken with no lane left lands, and vector registers are written there before the
-    lanes of the code around it are turned on again."""
+    """Places where a branch that is taken with no lane left lands, or where a loop ends with none left, and vector
+    registers are written there before the lanes of the code around it are turned on again."""
     dump = subprocess.Popen([OBJDUMP, "-d", "--no-show-raw-insn", elf_path], stdout=subprocess.PIPE, text=True)
     kernel, start, code, found = None, 0, {}, []
 
@@ -321,7 +321,8 @@ def copies_ahead_of_their_lanes(elf_path):
         lands = lambda branch: {start + int(m.group(1), 16) for t in code.values() if t.startswith(branch)
                                 for m in [re.search(r"\+0x([0-9a-f]+)>", t)] if m}
         blocks = lands(("s_branch", "s_cbranch"))
-        for target in lands("s_cbranch_execz") & index.keys():
+        ends = {b for a, b in zip(at, at[1:]) if code[a].startswith("s_cbranch_execnz")}
+        for target in (lands("s_cbranch_execz") | ends) & index.keys():
             written = None
             for a in at[index[target]:]:
                 text = code[a]
