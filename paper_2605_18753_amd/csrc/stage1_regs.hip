@@ -340,7 +340,7 @@ __device__ __forceinline__ void regs_tile(const S1Args& a, char* lds, int b, int
     const bool tok_ok = tok < a.tok_end && (kq % KQT) == 0;   // of the rows sharing a token the first one writes
     // A lane's place, hidden from the compiler where a lane has several tokens, and chunks and mask words counted from the
     // wave's own first ones: the comparisons of all tiles are the same for every token, and were kept in scalar registers from
-    // the first token to the last (775 of them spilled at a group of 1 and 48 tiles, 144 now).  Spills of that number are not
+    // the first token to the last (up to 786 of them spilled at a group of 1 and 48 tiles, at most 146 now).  Spills of that number are not
     // only slow (2048 tokens against a 96k cache, 4 heads: 102 us -> 80): the compiler places some ahead of
     // the instruction that turns the lanes of a branch on again, and a register copy behind them, so that the copy
     // reaches some lanes only.  Builds of rows of 1025 to 1536 chunks at a group of 1 gave wrong lists that way.
