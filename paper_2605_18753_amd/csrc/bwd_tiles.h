@@ -44,12 +44,6 @@ template <int D> __device__ __forceinline__ bf16x8 read_t(const char* tile, uint
                           tile + (hi ^ (uint32_t)(t << 6)) + (16 * g) * BCfg<D>::ROW_BYTES);
 }
 
-// two fp32 -> packed bf16 (round to nearest even) with the hardware conversion
-__device__ __forceinline__ uint32_t cvt_bf16x2(float lo, float hi) {
-  const bf16x2 w = {(__bf16)lo, (__bf16)hi};
-  return __builtin_bit_cast(uint32_t, w);
-}
-
 __device__ __forceinline__ f32x16 zero16() {
   const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   return z;

@@ -37,6 +37,11 @@ __device__ __forceinline__ uint32_t lds_addr_of(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
 }
 
+// 16 bytes of LDS at a byte address
+__device__ __forceinline__ bf16x8 lds_read_b128(uint32_t addr) {
+  return *reinterpret_cast<__attribute__((address_space(3))) const bf16x8*>(addr);
+}
+
 // Transposing LDS read (ds_read_b64_tr_b16): within each group of 16 lanes, lane
 // s points at four consecutive 16-bit elements; lane i of the group receives
 // element i % 4 of the four source lanes i / 4, i / 4 + 4, i / 4 + 8, i / 4 + 12.
@@ -45,6 +50,18 @@ __device__ __forceinline__ bf16x8 lds_read_tr_pair(const char* lo_addr, const ch
   const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(lo_addr));
   const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(hi_addr));
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+__device__ __forceinline__ bf16x8 lds_read_tr_pair(uint32_t lo_addr, uint32_t hi_addr) {
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) s16x4*>(lo_addr));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) s16x4*>(hi_addr));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// two fp32 -> packed bf16 (round to nearest even) with the hardware conversion
+__device__ __forceinline__ uint32_t cvt_bf16x2(float lo, float hi) {
+  const bf16x2 w = {(__bf16)lo, (__bf16)hi};
+  return __builtin_bit_cast(uint32_t, w);
 }
 
 }  // namespace dash

@@ -5,7 +5,8 @@
 //
 // Tiling.  A workgroup (4 waves) owns 128 (token, head) rows of one kv-head:
 // wave w owns 32 rows = all g_q heads of 32/g_q consecutive tokens.  The
-// workgroup walks the union of its tokens' chunk masks in ascending order.
+// workgroup walks the union of its tokens' chunk masks in ascending order, written out
+// as a list of 64-key tiles first.
 // Every 64-key tile of K and V is copied once from global memory straight into
 // LDS (buffer_load_dwordx4 ... lds, no staging registers), two stages deep.  A wave
 // pipelines its tiles: the first product of tile i runs together with the exponentials of
@@ -13,12 +14,13 @@
 // the MFMA work of a chunk none of its tokens kept; rows of a wave that did not keep a chunk
 // get bias -inf for it, which keeps the per-token result exact.
 //
-// What bounds it.  Timing copies of an earlier state of this kernel without one part at a time (32k causal,
-// group of 4, dense): no direct copies -12 %, no LDS operand reads -11 %, no exponentials -8 %, no
-// barriers -2 %, none of them -29 % (1.5 PFLOP/s, near the rate of a register-fed MFMA loop at the
-// clock this load runs at): copies, operand feed and vector work share the time about evenly.  The distances
-// of exponentials and operand reads from their use are worth +-1 %; where a tile's first operands, its bias and its place in
-// the list are asked for was worth 10 % since (see begin_chunk and the iteration).
+// What bounds it.  Dense rows and random data: power.  16k causal tokens, group of 4, take 1.92 ms, 1.15 PFLOP/s, the rate of the
+// library's 8192^3 product; the same launch on zeros takes a quarter less, at a clock of 2.1 GHz for 1.65.  Timing copies without
+// one part: no direct copies -6.5 %, half of them -2.6, no LDS operand reads -9, no exponentials -6, no row maximum -1, neither copies nor operand
+// reads -17.5.  Rows that skip tiles, and launches of one workgroup per CU: the time one wave takes for a tile, 2300
+// clocks for 1024 of matrix work (2750 while the list was walked in scalar branches and the chunk was set up behind the barrier:
+// 32k prefill 8.36 -> 8.01 ms, 2000 tokens against a 32k cache 695 -> 631 us, 16k with a group of 16 1622 -> 1551, 1000 tokens 37.1 -> 36.2).
+// The distances of exponentials and operand reads from their use are worth +-1 %.
 // Without the pipeline across tiles (softmax of a tile between its own two products): 8.84 ->
 // 8.43 ms at the 32k prefill, 110 -> 104 ms at 128k tokens, 820 -> 735 us for 2000 tokens against a
 // 32k cache.
@@ -52,14 +54,16 @@
 namespace dash {
 
 
+constexpr int kMaxTiles = 4096;    // 64-key tiles of a sequence: at most 2048 chunks of 64 or 128
+
 template <int D> struct S2Cfg {
   static constexpr int NCH = D / 8;                       // 16-byte chunks per row
   static constexpr int ROW_BYTES = D * 2;
   static constexpr int TILE_BYTES = 64 * ROW_BYTES;       // one K or V tile
   static constexpr int COPIES = TILE_BYTES / 16 / 256;    // copy instructions per thread, tile and tensor
   static constexpr int ROWS_PER_COPY = 256 / NCH;         // rows one copy instruction of the workgroup covers
-  static constexpr int MASK_OFF = 4 * TILE_BYTES;            // after the K ring [2] and the V ring [2]
-  static constexpr size_t LDS_BYTES = (size_t)MASK_OFF + 5 * 64 * 4;
+  static constexpr int RING_BYTES = 4 * TILE_BYTES;          // the K ring [2] and the V ring [2]
+  static constexpr size_t LDS_BYTES = (size_t)RING_BYTES + 5 * 64 * 4 + kMaxTiles * 2;   // ring, chunk bitmaps, list of tiles
 };
 
 // Chunk permutations (position of logical 16-byte chunk c of tile row `row`).
@@ -86,9 +90,10 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
   // PAIR: waves 4 .. 7 are a second group with a ring of its own
   const int grp = PAIR ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
-  char* lds = lds_all + grp * C::MASK_OFF;
-  uint32_t* wgmask = reinterpret_cast<uint32_t*>(lds_all + (PAIR ? 2 : 1) * C::MASK_OFF);   // [64]
+  char* lds = lds_all + grp * C::RING_BYTES;
+  uint32_t* wgmask = reinterpret_cast<uint32_t*>(lds_all + (PAIR ? 2 : 1) * C::RING_BYTES);   // [64]
   uint32_t* wvmask = wgmask + 64;                                      // [4][64]
+  uint16_t* list = reinterpret_cast<uint16_t*>(wgmask + 5 * 64);       // [kMaxTiles]
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
@@ -101,7 +106,7 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
   const int r = hbi % a.h_kv, b = hbi / a.h_kv;
   const int tokw = 32 / a.g_q;                          // tokens per wave
   const int tok_w0 = tile * 4 * tokw + wave * tokw;     // first token of this wave
-  const int nsub = a.block >> 6;
+  const int sub_log = a.block >> 7;                     // log2 of the 64-key tiles of a chunk
 
   // ---- per-row constants ---------------------------------------------------
   const int my_tok = tok_w0 + n / a.g_q;
@@ -122,18 +127,15 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
   }
 
   // ---- chunk bitmaps -------------------------------------------------------
-  // lane t < tokw tracks token tok_w0 + t: its mask row, where in the compact bias
-  // list its next bias lies, and that value (prefetched).
-  const int trk_tok = tok_w0 + lane;
-  const bool trk_ok = lane < tokw && trk_tok < a.n_q;
+  // Every lane tracks the token of its row: the mask word of the present 32 chunks, where in the compact bias list
+  // the token's next bias lies, and that value (prefetched).  The lanes of a token ask for the same address.
   const int64_t trk_base = ((int64_t)b * a.h_kv + r) * a.n_q + min(tok_w0, a.n_q - 1);   // uniform; a lane's row by offset
   const uint32_t* trk_mask = DENSE ? nullptr : a.mask + trk_base * a.words;
   const __amdgpu_buffer_rsrc_t trk_bias = __builtin_amdgcn_make_buffer_rsrc(
       DENSE ? nullptr : const_cast<float*>(a.bias) + trk_base * a.t_all, 0, DENSE ? 0 : max(min(tokw, a.n_q - tok_w0), 0) * a.t_all * 4, 0x00020000);
   auto ask_bias = [&](uint32_t at) -> float { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(trk_bias, at, 0, 0)); };
-  const uint32_t trk_m0 = trk_ok ? (uint32_t)(lane * a.words) : 0u;
-  uint32_t trk_at = trk_ok ? (uint32_t)(lane * a.t_all) * 4u : ~3u;   // of the next bias, in bytes; past the end for lanes without a token
-  int trk_wi = -1;
+  const uint32_t trk_m0 = row_ok ? (uint32_t)(n / a.g_q * a.words) : 0u;
+  uint32_t trk_at = row_ok ? (uint32_t)(n / a.g_q * a.t_all) * 4u : ~3u;   // of the next bias, in bytes; past the end for lanes without a token
   uint32_t trk_word = 0;
   float trk_old = 0.f, trk_next = 0.f;
 
@@ -157,57 +159,67 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
   }
   __syncthreads();
 
-  // ---- this workgroup's part of the chunk list ----------------------------
-  int it_wi = -1, it_left = 0x7fffffff, n_parts = 1;
-  uint32_t it_bits = 0u;
-  int iters = 0;                                // PAIR: iterations of either group, those of the longer half
-  if (PAIR || a.max_parts > 1) {
-    int n_chunks = 0;
-    for (int wi = 0; wi < a.words; wi++) n_chunks += __popc(__builtin_amdgcn_readfirstlane(wgmask[wi]));
-    int skip;                                   // entries of the parts before this one (< n_chunks)
-    if constexpr (PAIR) {
-      const int per = (n_chunks + 1) >> 1;
-      iters = per > 0 ? per * nsub + 1 : 0;
-      it_left = grp == 0 ? per : n_chunks - per;
-      skip = it_left > 0 ? grp * per : 0;
-    } else {
-      const int per = max((n_chunks + a.max_parts - 1) / a.max_parts, kMinPartTiles / nsub);
-      n_parts = max((n_chunks + per - 1) / per, 1);
-      if (part >= n_parts) return;
-      if (part == 0 && tid == 0) a.part_cnt[blockIdx.x] = n_parts;
-      it_left = per;
-      skip = part * per;
+  // ---- the workgroup's list of 64-key tiles ----------------------------------
+  // Entry: tile number (< 4096), bits 12 + w: wave w takes part.  Written once: a walk over the mask words between the tiles is a
+  // chain of scalar branches, some 400 clocks of the 2750 that one wave per SIMD took for a tile.
+  int n_chunks;
+  {
+    constexpr int LPW = PAIR ? 8 : 4, BPL = 32 / LPW;          // lanes per mask word, bits per lane
+    const int own = __popc(wgmask[lane]);
+    int incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl, o);
+      incl += lane >= o ? up : 0;
     }
-    if (skip > 0) {
-      for (;;) {
-        it_bits = __builtin_amdgcn_readfirstlane(wgmask[++it_wi]);
-        const int c = __popc(it_bits);
-        if (skip < c) break;
-        skip -= c;
+    n_chunks = __builtin_amdgcn_readlane(incl, 63);
+    const int wi = tid / LPW, b0 = (tid % LPW) * BPL;
+    const uint32_t m = wgmask[wi];
+    int at = __shfl(incl - own, wi) + __popc(m & ((1u << b0) - 1u));
+    const uint32_t w0 = wvmask[wi] >> b0, w1 = wvmask[64 + wi] >> b0, w2 = wvmask[128 + wi] >> b0, w3 = wvmask[192 + wi] >> b0;
+#pragma unroll
+    for (int j = 0; j < BPL; j++)
+      if ((m >> (b0 + j)) & 1u) {
+        const uint32_t on = ((w0 >> j) & 1u) | ((w1 >> j) & 1u) << 1 | ((w2 >> j) & 1u) << 2 | ((w3 >> j) & 1u) << 3;
+        const uint32_t e = (uint32_t)((wi * 32 + b0 + j) << sub_log) | on << 12;
+        list[at << sub_log] = (uint16_t)e;
+        if (sub_log) list[at * 2 + 1] = (uint16_t)(e + 1);
+        at++;
       }
-      for (; skip > 0; skip--) it_bits &= it_bits - 1u;
-      if (!DENSE && trk_ok) {                   // the tracked token's entries before the part's first chunk
-        for (int wi = 0; wi < it_wi; wi++) trk_at += 4 * __popc(trk_mask[trk_m0 + wi]);
-        trk_at += 4 * __popc(trk_mask[trk_m0 + it_wi] & ((1u << __builtin_ctz(it_bits)) - 1u));
-      }
-    }
   }
-  if (!DENSE) trk_next = ask_bias(trk_at);
+  __syncthreads();
 
-  // ---- tile iterator (workgroup-uniform) ---------------------------------
-  int it_sub = nsub - 1, it_u = -1;
-  auto advance = [&]() -> bool {   // moves (it_u, it_sub) to the next 64-key tile
-    if (it_u >= 0 && it_sub + 1 < nsub) { it_sub++; return true; }
-    if (--it_left < 0) return false;
-    while (it_bits == 0u) {
-      if (++it_wi >= a.words) return false;
-      it_bits = __builtin_amdgcn_readfirstlane(wgmask[it_wi]);
+  // ---- this workgroup's part of it --------------------------------------------
+  int n_parts = 1, first = 0, mine = n_chunks;   // chunks before the part, chunks of the part
+  int last_it = n_chunks << sub_log;             // iterations 0 .. last_it: one more than tiles; PAIR: those of the longer half
+  if constexpr (PAIR) {
+    const int per = (n_chunks + 1) >> 1;
+    first = grp * per;
+    mine = grp == 0 ? per : n_chunks - per;
+    last_it = per << sub_log;
+  } else if (a.max_parts > 1) {
+    const int per = max((n_chunks + a.max_parts - 1) / a.max_parts, kMinPartTiles >> sub_log);
+    n_parts = max((n_chunks + per - 1) / per, 1);
+    if (part >= n_parts) return;
+    if (part == 0 && tid == 0) a.part_cnt[blockIdx.x] = n_parts;
+    first = part * per;
+    mine = min(per, n_chunks - first);
+    last_it = mine << sub_log;
+  }
+  const int n_it = mine << sub_log;              // the part's tiles
+  list += first << sub_log;
+  auto entry = [&](int i) -> int { return list[max(min(i, n_it - 1), 0)]; };   // behind the last tile: that one again
+  int e_cur = __builtin_amdgcn_readfirstlane(entry(0)), e_next = __builtin_amdgcn_readfirstlane(entry(1)), e_ahead = 0;
+  if (n_it == 0) e_cur = e_next = 0;             // no list: whatever lies there
+  if (!DENSE) {
+    const int u0 = (e_cur & 0xfff) >> sub_log;
+    if (first > 0 && n_it > 0 && row_ok) {       // the token's entries before the part's first chunk
+      for (int wi = 0; wi < u0 >> 5; wi++) trk_at += 4 * __popc(trk_mask[trk_m0 + wi]);
+      trk_at += 4 * __popc(trk_mask[trk_m0 + (u0 >> 5)] & ((1u << (u0 & 31)) - 1u));
     }
-    it_u = it_wi * 32 + __builtin_ctz(it_bits);
-    it_bits &= it_bits - 1u;
-    it_sub = 0;
-    return true;
-  };
+    trk_word = trk_mask[trk_m0 + (u0 >> 5)];
+    trk_next = ask_bias(trk_at);
+  }
 
   // ---- global -> LDS tile copies -------------------------------------------
   // Copy instruction i of wave w fills the 1 KB LDS segment (4i + w): slot
@@ -225,11 +237,8 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
   const uint32_t v_off = (uint32_t)(c_row * (int)a.vs_t * 2 + ((c_pos ^ v_swz<D>(c_row)) << 4));
   const uint32_t k_step = (uint32_t)(C::ROWS_PER_COPY * (int)a.ks_t * 2);
   const uint32_t v_step = (uint32_t)(C::ROWS_PER_COPY * (int)a.vs_t * 2);
-  uint32_t cp_k = 0, cp_k_v = 0, cp_v = 0;   // scalar byte offsets: K of the tile being copied, V of the same, V being copied
-  auto copy_begin = [&](int u, int sub) {
-    cp_k = (uint32_t)(u * a.block + sub * 64) * (uint32_t)a.ks_t * 2u;
-    cp_k_v = (uint32_t)(u * a.block + sub * 64) * (uint32_t)a.vs_t * 2u;
-  };
+  const uint32_t k_tile = (uint32_t)a.ks_t * 128u, v_tile = (uint32_t)a.vs_t * 128u;   // bytes from tile to tile
+  uint32_t cp_k = 0, cp_v = 0;   // scalar byte offsets of the K and V tiles being copied
   auto copy_k = [&](int c, int slot) {
     copy16_to_lds(k_rs, lds0 + slot * C::TILE_BYTES + wave * 1024 + c * 4096, k_off, cp_k + c * k_step);
   };
@@ -237,12 +246,12 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
     copy16_to_lds(v_rs, lds0 + (2 + slot) * C::TILE_BYTES + wave * 1024 + c * 4096, v_off, cp_v + c * v_step);
   };
 
-  // ---- operand read addresses (bytes inside a stage) -------------------------
+  // ---- operand read addresses (in LDS, of slot 0) ------------------------------
   // K, A operand of S^T: lane (n, h) reads logical chunk 2 ks + h of rows n, 32 + n
   uint32_t k_rd[D / 16];
 #pragma unroll
   for (int ks = 0; ks < D / 16; ks++)
-    k_rd[ks] = (uint32_t)(n * C::ROW_BYTES + (((2 * ks + h) ^ k_swz<D>(n)) << 4));
+    k_rd[ks] = lds0 + (uint32_t)(n * C::ROW_BYTES + (((2 * ks + h) ^ k_swz<D>(n)) << 4));
   // V, A operand of O^T (transposing read): lanes 16 g .. 16 g + 15 serve d
   // columns 16 (g & 1) .. + 15 of a d-tile and contraction half h = g >> 1; lane
   // s of the group points at key row 4 h + s / 4, d offset 16 (g & 1) + 4 (s % 4)
@@ -251,8 +260,8 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
   uint32_t v_rd[D / 32];
 #pragma unroll
   for (int t = 0; t < D / 32; t++)
-    v_rd[t] = (uint32_t)((4 * h + (s16 >> 2)) * C::ROW_BYTES +
-                         ((((4 * t) ^ v_swz<D>(s16 >> 2)) + 2 * a16 + ((s16 & 3) >> 1)) << 4) + ((s16 & 1) << 3));
+    v_rd[t] = lds0 + (uint32_t)((4 * h + (s16 >> 2)) * C::ROW_BYTES +
+                                ((((4 * t) ^ v_swz<D>(s16 >> 2)) + 2 * a16 + ((s16 & 3) >> 1)) << 4) + ((s16 & 1) << 3));
 
   // ---- online-softmax state (base-2 logits) -------------------------------
   float m_run = -INFINITY, l_run = 0.f;
@@ -264,31 +273,21 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
     for (int j = 0; j < 16; j++) oacc[dt][j] = 0.f;
 
   float bias_row = 0.f;   // bias * log2e of this lane's row for the current chunk
-  bool wave_on = false, diag = false;
-
-  auto wave_has = [&](int u) -> bool {
-    return wave_ok && ((__builtin_amdgcn_readfirstlane(wvmask[wave * 64 + (u >> 5)]) >> (u & 31)) & 1u);
-  };
   auto begin_chunk = [&](int u) {
-    // fetches the per-token bias of chunk u, which one of the wave's tokens kept
-    diag = a.causal && u == cw;
-    float bt = 0.f;
-    if (!DENSE && !diag) {
-      if ((u >> 5) != trk_wi) { trk_wi = u >> 5; trk_word = trk_mask[trk_m0 + trk_wi]; }
-      const bool bit = trk_ok && ((trk_word >> (u & 31)) & 1u);
-      const float next = trk_old + trk_next;   // one of them is 0
-      bt = bit ? next * kLog2e : -INFINITY;
-      trk_old = bit ? 0.f : next;
-      trk_at += bit ? 4u : 0u;
-      // One load for every lane, and none that merges values behind it: where only some lanes load, the others' values are
-      // merged right behind the load, and the wave waits for memory here instead of at the next chunk (32k prefill 8.64 ->
-      // 8.24 ms, 2000 tokens against a 32k cache 735 -> 674 us, 16k with a group of 16 1.62 -> 1.54 ms).  Lanes whose token did not
-      // keep the chunk read past the end of the resource, which touches no memory, and keep their value: reading it again took
-      // a cache line of every token for each chunk (128k tokens at alpha 2, chunks of 64, 32 / 8 heads: 55 -> 43 to 50 ms, 8 / 2
-      // heads 13.3 -> 12.5; chunks of 128 82 -> 79; 32k and 64k tokens the same to 5 % less).
-      trk_next = ask_bias(bit ? trk_at : ~3u);
-    }
-    bias_row = __shfl(bt, n / a.g_q);
+    // the bias of chunk u, which one of the wave's tokens kept, for this lane's row
+    if (DENSE || (a.causal && u == cw)) { bias_row = 0.f; return; }
+    const bool bit = row_ok && ((trk_word >> (u & 31)) & 1u);
+    const float next = trk_old + trk_next;   // one of them is 0
+    bias_row = bit ? next * kLog2e : -INFINITY;
+    trk_old = bit ? 0.f : next;
+    trk_at += bit ? 4u : 0u;
+    // One load for every lane, and none that merges values behind it: where only some lanes load, the others' values are
+    // merged right behind the load, and the wave waits for memory here instead of at the next chunk (32k prefill 8.64 ->
+    // 8.24 ms, 2000 tokens against a 32k cache 735 -> 674 us, 16k with a group of 16 1.62 -> 1.54 ms).  Lanes whose token did not
+    // keep the chunk read past the end of the resource, which touches no memory, and keep their value: reading it again took
+    // a cache line of every token for each chunk (128k tokens at alpha 2, chunks of 64, 32 / 8 heads: 55 -> 43 to 50 ms, 8 / 2
+    // heads 13.3 -> 12.5; chunks of 128 82 -> 79; 32k and 64k tokens the same to 5 % less).
+    trk_next = ask_bias(bit ? trk_at : ~3u);
   };
 
   // ---- the tile pipeline -----------------------------------------------------
@@ -304,69 +303,60 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
   // tile i - 2), whose slots the copies of this iteration (K of tile i + 1, V of tile i) overwrite; those are
   // issued one at a time between the MFMAs: a burst right after the barrier would queue all waves
   // behind the 64 B/clk global -> LDS path.
-  bool have = advance();
+  //
+  // Whatever needs no tile stands before the barrier: the chunk's bias, the reference maximum.
   // the loads of Q, issued before those of the masks, must be complete (and known to be) before the tile
   // loop: a wait for them inside the loop would also wait for the tile copies in flight
 #pragma unroll
   for (int ks = 0; ks < D / 16; ks++) asm volatile("" : "+v"(qf[ks]));
-  if (have) {
-    copy_begin(it_u, it_sub);
+  if (n_it > 0) {
+    cp_k = (uint32_t)(e_cur & 0xfff) * k_tile;
 #pragma unroll
     for (int c = 0; c < C::COPIES; c++) copy_k(c, 0);
   }
-  bool pend = false;                 // a tile whose S^T waits for its softmax and second product
-  bool drain = have;                 // the last iteration of the workgroup has no tile of its own
+  int pend = 0;                      // a tile whose S^T waits for its softmax and second product
   float bias_old = 0.f, tmax_old = 0.f;
-  u32x4 pb[4];
-  auto iteration = [&](auto p_tag, f32x16 (&s)[2], f32x16 (&so)[2]) {
+  auto iteration = [&](auto p_tag, int it, f32x16 (&s)[2], f32x16 (&so)[2]) __attribute__((always_inline)) {
     constexpr int P = decltype(p_tag)::value;
     constexpr int NS = D / 8;                                  // MFMAs per product and tile
-    const bool cur = have;
-    const int cu = it_u, csub = it_sub;
-    const bool more = cur && advance();
-    if (cur && csub == 0) wave_on = wave_has(cu);
-    const bool on = cur && wave_on;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    const char* kb = lds + P * C::TILE_BYTES;
-    const char* vb = lds + (2 + (P ^ 1)) * C::TILE_BYTES;
-    auto k_read = [&](int i) -> bf16x8 {   // slot i: d slice i / 2, key half i % 2
-      return *reinterpret_cast<const bf16x8*>(kb + k_rd[i >> 1] + (i & 1) * 32 * C::ROW_BYTES);
-    };
     constexpr int KAHEAD = 4, VAHEAD = 2;
-    bf16x8 kf[NS];
-    // The first K operands are on their way while the tile is set up, and whether it is the wave's is asked before the
-    // barrier: the two LDS round trips behind it were 3 % of a tile (with the copies' branches and the order of Q and masks
-    // in the prologue: 32k prefill 8.24 -> 7.79 ms, 128k 95.6 -> 90.4, 1000 tokens 31.9 -> 29.8 us).
-    if (on) {
-#pragma unroll
-      for (int i = 0; i < KAHEAD; i++) kf[i] = k_read(i);
-      if (csub == 0) begin_chunk(cu);
+    constexpr int EQ = 12, E0 = 2;                             // exponential pairs before the second product, and before the first MFMA
+    const bool cur = it < n_it;
+    const int t_cur = e_cur & 0xfff, t_next = e_next & 0xfff;
+    const int on = (e_cur >> (12 + wave)) & ((it - n_it) >> 31) & 1;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (!DENSE) {
+      const int u = t_cur >> sub_log, un = t_next >> sub_log;
+      if (on && (t_cur & sub_log) == 0) begin_chunk(u);
+      if ((un ^ u) >> 5) trk_word = trk_mask[trk_m0 + (un >> 5)];   // arrives with the next tile's copies
     }
-    cp_v = cp_k_v;                                             // V of tile i
-    if (more) copy_begin(it_u, it_sub);                        // K of tile i + 1
     // Lazy rescaling: the reference max m_run of a row is only raised when the tile's max
     // exceeds it by more than 2^kLazy; until then p = 2^(t - m_run) may reach 2^kLazy, which fp32 / bf16
     // hold without loss, and the final division by the row sum is unaffected.
-    float off = 0.f;
-    if (pend) {
-      if (__builtin_expect(__any(tmax_old > m_run + kLazy), 0)) {
-        const float m_new = fmaxf(m_run, fmaxf(tmax_old, __shfl_xor(tmax_old, 32)));
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;
-        const float corr = __builtin_amdgcn_exp2f(m_run - m_use);   // m_run = -inf -> 0
-        m_run = m_new;
-        l_run *= corr;
+    if (pend && __builtin_expect(__any(tmax_old > m_run + kLazy), 0)) {
+      const float m_new = fmaxf(m_run, fmaxf(tmax_old, __shfl_xor(tmax_old, 32)));
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;
+      const float corr = __builtin_amdgcn_exp2f(m_run - m_use);   // m_run = -inf -> 0
+      m_run = m_new;
+      l_run *= corr;
 #pragma unroll
-        for (int dt = 0; dt < NDT; dt++)
+      for (int dt = 0; dt < NDT; dt++)
 #pragma unroll
-          for (int j = 0; j < 16; j++) oacc[dt][j] *= corr;
-      }
-      off = bias_old - (m_run == -INFINITY ? 0.f : m_run);
+        for (int j = 0; j < 16; j++) oacc[dt][j] *= corr;
     }
-    auto v_read = [&](int i) -> bf16x8 {   // slot i: contraction step g = i / NDT, d-tile t = i % NDT
-      const int g = i / NDT, t = i % NDT;
-      return lds_read_tr_pair(vb + v_rd[t] + (16 * g) * C::ROW_BYTES, vb + v_rd[t] + (16 * g + 8) * C::ROW_BYTES);
+    const float off = bias_old - (m_run == -INFINITY ? 0.f : m_run);
+    cp_v = (uint32_t)t_cur * v_tile;                           // V of tile i
+    cp_k = (uint32_t)t_next * k_tile;                          // K of tile i + 1
+    asm volatile("s_barrier" ::: "memory");
+    e_ahead = entry(it + 2);
+    auto k_read = [&](int i) -> bf16x8 {   // slot i: d slice i / 2, key half i % 2
+      return lds_read_b128(k_rd[i >> 1] + (uint32_t)(P * C::TILE_BYTES + (i & 1) * 32 * C::ROW_BYTES));
     };
+    auto v_read = [&](int i) -> bf16x8 {   // slot i: contraction step g = i / NDT, d-tile t = i % NDT
+      const uint32_t at = v_rd[i % NDT] + (uint32_t)((2 + (P ^ 1)) * C::TILE_BYTES + 16 * (i / NDT) * C::ROW_BYTES);
+      return lds_read_tr_pair(at, at + 8 * C::ROW_BYTES);
+    };
+    u32x4 pb[4];
     float l_tile = 0.f;   // summed by the tile: one chain over all keys of a long row loses digits
     // exponential pair k of tile i - 1: P^T slots 2 (k % 4), + 1 of contraction step g = k / 4
     auto e_pair = [&](int k) {
@@ -374,18 +364,28 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
       const float p0 = __builtin_amdgcn_exp2f(fmaf(so[kt][j], a.c1, off));
       const float p1 = __builtin_amdgcn_exp2f(fmaf(so[kt][j + 1], a.c1, off));
       l_tile += p0 + p1;
-      asm volatile("" : "+v"(l_tile));   // keeps the row-sum update in its slot
       const bf16x2 w = {(__bf16)p0, (__bf16)p1};
-      pb[g][k & 3] = __builtin_bit_cast(uint32_t, w);
+      uint32_t x = __builtin_bit_cast(uint32_t, w);
+      asm volatile("" : "+v"(l_tile), "+v"(x));   // keeps the row sum and the packing in their slot
+      pb[g][k & 3] = x;
     };
     // copy instruction c of the iteration: K of tile i + 1, then V of tile i
     auto copies = [&](int c) {
       if (c < C::COPIES) copy_k(c, P ^ 1);                     // behind the last tile: that tile again, into a slot nobody reads
       else if (c < 2 * C::COPIES) copy_v(c - C::COPIES, P);
     };
-    constexpr int EQ = 12;                                     // exponential pairs behind the first product
+    bf16x8 vf[NS];
     auto first_product = [&](auto e_tag) {
       constexpr bool EXPS = decltype(e_tag)::value;
+      bf16x8 kf[NS];
+#pragma unroll
+      for (int i = 0; i < KAHEAD; i++) kf[i] = k_read(i);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (EXPS) {
+#pragma unroll
+        for (int k = 0; k < E0; k++) e_pair(k);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int i = 0; i < NS; i++) {
         if (i + KAHEAD < NS) kf[i + KAHEAD] = k_read(i + KAHEAD);
@@ -399,19 +399,19 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
         }
         if constexpr (EXPS) {
 #pragma unroll
-          for (int k = i * EQ / NS; k < (i + 1) * EQ / NS; k++) e_pair(k);
+          for (int k = E0 + i * (EQ - E0) / NS; k < E0 + (i + 1) * (EQ - E0) / NS; k++) e_pair(k);
+          if (i >= NS - VAHEAD) vf[i - (NS - VAHEAD)] = v_read(i - (NS - VAHEAD));
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     };
-    if (on) {
-      if (pend) first_product(std::true_type{});
-      else first_product(std::false_type{});
-      // key kpos0 + 4 h + c (c = the compile-time part of the key index of an accumulator
-      // register) is dead if it lies after the row's position in the diagonal chunk or past the
-      // end of the sequence, i.e. if c > lim
-      const int kpos0 = cu * a.block + csub * 64;
-      if (diag || kpos0 + 64 > a.n_kv) {
+    // key kpos0 + 4 h + c (c = the compile-time part of the key index of an accumulator
+    // register) is dead if it lies after the row's position in the diagonal chunk or past the
+    // end of the sequence, i.e. if c > lim
+    auto mask_keys = [&]() {
+      const int kpos0 = t_cur * 64;
+      const bool diag = a.causal && (t_cur >> sub_log) == cw;
+      if (__builtin_expect(diag || kpos0 + 64 > a.n_kv, 0)) {
         const int k0 = kpos0 + 4 * h;
         int lim = min(diag ? row_pos - k0 : 0x7fffffff, a.n_kv - 1 - k0);
         asm volatile("" : "+v"(lim));   // keep the per-register comparisons against immediates
@@ -423,27 +423,14 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
             s[kt][j] = c > lim ? -INFINITY : s[kt][j];
           }
       }
-    } else {
-      if (cur) {
-#pragma unroll
-        for (int c = 0; c < 2 * C::COPIES; c++) copies(c);
-      }
-      if (pend) {
-#pragma unroll
-        for (int k = 0; k < EQ; k++) e_pair(k);
-      }
-    }
+    };
     float mloc = -INFINITY;
     auto max_quad = [&](int q) {   // four of the tile's 32 scores per lane
       const int kt = q >> 2, j = 4 * (q & 3);
       mloc = fmaxf(fmaxf(mloc, s[kt][j]), s[kt][j + 1]);
       mloc = fmaxf(fmaxf(mloc, s[kt][j + 2]), s[kt][j + 3]);
     };
-    if (pend) {
-      bf16x8 vf[NS];
-#pragma unroll
-      for (int i = 0; i < VAHEAD; i++) vf[i] = v_read(i);
-      __builtin_amdgcn_sched_barrier(0);
+    auto second_product = [&]() {
 #pragma unroll
       for (int i = 0; i < NS; i++) {
         if (i + VAHEAD < NS) vf[i + VAHEAD] = v_read(i + VAHEAD);
@@ -455,35 +442,49 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
         else if (i >= 4) { max_quad(2 * (i - 4)); max_quad(2 * (i - 4) + 1); }
         __builtin_amdgcn_sched_barrier(0);
       }
-    } else if (on) {
+      l_run += l_tile;
+    };
+    if (on) {
+      if (pend) first_product(std::true_type{});
+      else first_product(std::false_type{});
+      mask_keys();
+    } else {
+      asm volatile("" : "=v"(s[0]), "=v"(s[1]));               // nobody reads them
+      if (cur) {
+#pragma unroll
+        for (int c = 0; c < 2 * C::COPIES; c++) copies(c);
+      }
+      if (pend) {
+#pragma unroll
+        for (int i = 0; i < VAHEAD; i++) vf[i] = v_read(i);
+#pragma unroll
+        for (int k = 0; k < EQ; k++) e_pair(k);
+      }
+    }
+    // The branches rejoin around the second product, and two conditions stand for an else: otherwise the compiler keeps two
+    // sets of accumulators and copies one to the other.
+    if (pend) {
+      __builtin_amdgcn_sched_barrier(0);
+      second_product();
+    }
+    if (!pend && on) {
 #pragma unroll
       for (int q = 0; q < 8; q++) max_quad(q);
     }
-    l_run += l_tile;
     // this lane half's max of the base-2 logits s c1 + bias (c1 > 0)
     tmax_old = fmaf(mloc, a.c1, bias_row);
     bias_old = bias_row;
     pend = on;
-    have = more;
+    e_cur = e_next;
+    e_next = __builtin_amdgcn_readfirstlane(e_ahead);
   };
-  {
+  if (last_it > 0) {
     f32x16 sa[2], sb[2];
-    if constexpr (PAIR) {
-      // as many iterations in either group: one without a tile is its barrier
-      while (iters > 0) {
-        iteration(std::integral_constant<int, 0>{}, sa, sb);
-        if (--iters == 0) break;
-        iteration(std::integral_constant<int, 1>{}, sb, sa);
-        iters--;
-      }
-    } else {
-      while (drain) {
-        drain = have;
-        iteration(std::integral_constant<int, 0>{}, sa, sb);
-        if (!drain) break;
-        drain = have;
-        iteration(std::integral_constant<int, 1>{}, sb, sa);
-      }
+    for (int it = 0;;) {
+      iteration(std::integral_constant<int, 0>{}, it, sa, sb);
+      if (++it > last_it) break;
+      iteration(std::integral_constant<int, 1>{}, it, sb, sa);
+      if (++it > last_it) break;
     }
   }
 
@@ -512,8 +513,8 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
         // accumulator t, registers 4 q4 .. + 3: O^T rows 8 q4 + 4 h + i of d-tile t
         const int m0 = q4 * 8 + h * 4;
         uint2 w;
-        w.x = pack_bf16x2(oacc[t][q4 * 4 + 0] * inv, oacc[t][q4 * 4 + 1] * inv);
-        w.y = pack_bf16x2(oacc[t][q4 * 4 + 2] * inv, oacc[t][q4 * 4 + 3] * inv);
+        w.x = cvt_bf16x2(oacc[t][q4 * 4 + 0] * inv, oacc[t][q4 * 4 + 1] * inv);
+        w.y = cvt_bf16x2(oacc[t][q4 * 4 + 2] * inv, oacc[t][q4 * 4 + 3] * inv);
         *reinterpret_cast<uint2*>(op + t * 32 + m0) = w;
       }
   };
@@ -533,7 +534,7 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
           xo[(t * 8 + q4 * 2 + h) * 128] = f32x4{oacc[GIVE + t][q4 * 4], oacc[GIVE + t][q4 * 4 + 1], oacc[GIVE + t][q4 * 4 + 2], oacc[GIVE + t][q4 * 4 + 3]};
       if (h == 0) reinterpret_cast<float2*>(lds + 3 * C::TILE_BYTES)[row] = make_float2(m_run, l_tot);
       __syncthreads();
-      const char* other = lds_all + (G ^ 1) * C::MASK_OFF;
+      const char* other = lds_all + (G ^ 1) * C::RING_BYTES;
       const float2 ml = reinterpret_cast<const float2*>(other + 3 * C::TILE_BYTES)[row];
       const float M = fmaxf(m_run, ml.x), m_use = M == -INFINITY ? 0.f : M;
       const float w0 = __builtin_amdgcn_exp2f(m_run - m_use), w1 = __builtin_amdgcn_exp2f(ml.x - m_use);
@@ -593,8 +594,8 @@ __global__ __launch_bounds__(256) void s2_merge_kernel(S2Args a) {
 #pragma unroll
   for (int i = 0; i < NG; i++) {
     uint2 w;
-    w.x = pack_bf16x2(o[i][0] * inv, o[i][1] * inv);
-    w.y = pack_bf16x2(o[i][2] * inv, o[i][3] * inv);
+    w.x = cvt_bf16x2(o[i][0] * inv, o[i][1] * inv);
+    w.y = cvt_bf16x2(o[i][2] * inv, o[i][3] * inv);
     *reinterpret_cast<uint2*>(op + i * 64) = w;
   }
 }
@@ -605,7 +606,7 @@ static hipError_t launch_s2_t(const S2Args& a, bool pair, hipStream_t st) {
   if (pair) {
     auto kern = s2_attend_kernel<D, DENSE, true>;
     static LdsOptIn opt_in;
-    constexpr size_t lds = C::LDS_BYTES + C::MASK_OFF;
+    constexpr size_t lds = C::LDS_BYTES + C::RING_BYTES;
     if (hipError_t e = allow_dyn_lds((const void*)kern, lds, opt_in); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb), dim3(512), lds, st, a);
     return hipGetLastError();

@@ -211,6 +211,42 @@ def check_dense_uncut(w, p, q, k, v):
 
 # logits that rise or fall by a factor of four along the keys: a late raise of the running maximum, and two groups of waves
 # whose maxima lie far apart, either way round
+@pytest.mark.parametrize("h_q,n_q,chunks,d,block", [(4, 64, 33, 128, 64), (4, 64, 2048, 64, 64), (2, 130, 2048, 64, 128), (16, 40, 64, 64, 64)])
+def test_attention_over_lists_at_word_edges(h_q, n_q, chunks, d, block):
+    """Lists whose chunks lie at the edges of mask bytes and words, up to the longest sequence (4096
+    tiles of 64 keys), other ones for every token; reference in fp32."""
+    n_kv = n_q + (chunks * block - n_q) // 64 * 64
+    w = Workload("edge_lists", 1, h_q, 1, n_q, n_kv, d, block, seed=53)
+    q, k, v = make_inputs(w, DEV)
+    o = torch.empty_like(q)
+    p = B.make_params(q, k, v, o, block)
+    t_all, pos = B.list_stride(p), n_kv - n_q + torch.arange(n_q, device=DEV)
+    edge = [c for c in (0, 1, 7, 8, 31, 32, 33, 62, 63, 64, 1023, 1024, 2015, 2016, 2046) if c < t_all]
+    keep = torch.zeros((n_q, t_all), dtype=torch.bool, device=DEV)
+    for i, c in enumerate(edge):
+        keep[:, c] = (torch.arange(n_q, device=DEV) // 3 + i) % 3 != 0
+    own = pos // block
+    keep &= torch.arange(t_all, device=DEV)[None] < own[:, None]
+    keep[torch.arange(n_q), own] = True
+    words = B.mask_words(p)
+    bits = torch.nn.functional.pad(keep, (0, words * 32 - t_all)).view(n_q, words, 32).to(torch.int64)
+    mask = (bits << torch.arange(32, device=DEV)).sum(-1)
+    mask = torch.where(mask >= 1 << 31, mask - (1 << 32), mask).to(torch.int32).view(1, 1, n_q, words)
+    by_chunk = torch.randn((n_q, t_all), device=DEV)
+    by_chunk[torch.arange(n_q), own] = 0.0
+    bias = torch.zeros((1, 1, n_q, t_all), device=DEV)
+    for t in range(n_q):
+        row = by_chunk[t, keep[t]]
+        bias[0, 0, t, :row.numel()] = row
+    B.dash_stage2_attend(p, q, k, v, o, B.Lists(mask=mask.contiguous(), bias=bias), B.alloc_workspace(p, DEV))
+    add = torch.where(keep, by_chunk, torch.full_like(by_chunk, float("-inf"))).repeat_interleave(block, 1)[:, :n_kv]
+    add = torch.where(torch.arange(n_kv, device=DEV)[None] <= pos[:, None], add, torch.full_like(add, float("-inf")))
+    ref = torch.softmax(q[0].float() @ k[0, 0].float().T / d ** 0.5 + add[None], -1) @ v[0, 0].float()
+    err = ((o[0].float() - ref).abs().amax(-1) / ref.abs().amax()).max().item()
+    print(f"[parity] lists at word edges {chunks} x {block}: {err:.2e}")
+    assert err <= 2e-2, err
+
+
 @pytest.mark.parametrize("first,last", [(1.0, 4.0), (4.0, 1.0)])
 @pytest.mark.parametrize("name,batch,h_q,h_kv,n,d", [("two_groups", 1, 8, 8, 832, 128), ("two_groups_d64", 1, 16, 2, 832, 64), ("one_group", 33, 1, 1, 1000, 128)])
 def test_prefill_of_rising_and_falling_logits(name, batch, h_q, h_kv, n, d, first, last):
