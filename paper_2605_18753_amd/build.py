@@ -12,7 +12,7 @@ LIB = os.path.join(HERE, "libdash_attn.so")
 MICROBENCH_LIB = os.path.join(HERE, "libdash_microbench.so")
 # (source, extra defines, object name); stage1_regs.hip is compiled once per GQA group size
 SOURCES = [(s, [], s.replace(".hip", ".o")) for s in
-           ["api.hip", "compress.hip", "stage1.hip", "stage2.hip", "stage2_decode.hip", "attn_f32.hip", "backward.hip", "bwd_route.hip", "bwd_kv.hip"]]
+           ["api.hip", "compress.hip", "stage1.hip", "stage2.hip", "stage2_gather.hip", "stage2_decode.hip", "attn_f32.hip", "backward.hip", "bwd_route.hip", "bwd_kv.hip"]]
 SOURCES += [("stage1_regs.hip", [f"-DDASH_S1R_G={g}"], f"stage1_regs_g{g}.o") for g in (1, 2, 4, 8, 16)]
 # ... the decode step once per entmax exponent mode
 SOURCES += [("decode_route.hip", [f"-DDASH_DEC_MODE={m}"], f"decode_route_m{m}.o") for m in range(5)]

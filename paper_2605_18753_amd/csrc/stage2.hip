@@ -139,6 +139,10 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
   uint32_t trk_word = 0;
   float trk_old = 0.f, trk_next = 0.f;
 
+  S2Costs costs;
+  if constexpr (!DENSE && !PAIR) {
+    if (a.costs) costs = a.costs[lane];
+  }
   for (int i = tid; i < 5 * 64; i += 256) wgmask[i] = 0u;
   __syncthreads();
   if (DENSE) {
@@ -156,6 +160,9 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
     if (wave_ok && grp == 0)
       or_mask_rows(a.mask + (((int64_t)b * a.h_kv + r) * a.n_q + tok_w0) * a.words, min(tokw, a.n_q - tok_w0) * a.words,
                    a.words, wvmask + wave * 64, wgmask, lane);
+  }
+  if constexpr (!DENSE && !PAIR) {
+    if (a.costs && s2_gathered(costs)) return;   // every wave finds the same
   }
   __syncthreads();
 
@@ -611,11 +618,14 @@ static hipError_t launch_s2_t(const S2Args& a, bool pair, hipStream_t st) {
     hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb), dim3(512), lds, st, a);
     return hipGetLastError();
   }
+  if (!DENSE && a.costs)
+    if (hipError_t e = launch_s2_costs(a, st); e != hipSuccess) return e;
   auto kern = s2_attend_kernel<D, DENSE, false>;
   static LdsOptIn opt_in;
   if (hipError_t e = allow_dyn_lds((const void*)kern, C::LDS_BYTES, opt_in); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb, a.max_parts), dim3(256), C::LDS_BYTES, st, a);
   hipError_t e = hipGetLastError();
+  if (e == hipSuccess && !DENSE && a.costs) e = launch_s2_gather(a, D, st);
   if (e != hipSuccess || a.max_parts == 1) return e;
   hipLaunchKernelGGL(s2_merge_kernel<D>, dim3(a.n_tiles * a.hb * 8), dim3(256), 0, st, a);
   return hipGetLastError();
@@ -689,7 +699,7 @@ size_t s2_part_room(const dash_params& p, const Layout& L) {
 
 hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, const void* k,
                           const void* v, void* o, const uint32_t* mask, const float* bias,
-                          char* part_ws, bool dense, hipStream_t st) {
+                          char* part_ws, void* costs, bool dense, hipStream_t st) {
   S2Args a;
   fill_s2_args(a, p, L, q, k, v, o, mask, bias);
   a.n_tiles = s2_tiles(p, L);
@@ -700,6 +710,7 @@ hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, 
     a.part_o = a.part_ml + (size_t)a.n_tiles * a.hb * a.max_parts * 128 * 2;
   }
   const bool pair = a.max_parts == 1 && s2_paired((int64_t)a.n_tiles * a.hb, (float)(L.t_all * (p.block_size >> 6)));
+  if (!dense && !pair && a.max_parts == 1 && s2_may_gather(a, p.head_dim)) a.costs = reinterpret_cast<S2Costs*>(costs);
   if (p.head_dim == 128) return dense ? launch_s2_t<128, true>(a, pair, st) : launch_s2_t<128, false>(a, pair, st);
   return dense ? launch_s2_t<64, true>(a, pair, st) : launch_s2_t<64, false>(a, pair, st);
 }

@@ -247,6 +247,75 @@ def test_attention_over_lists_at_word_edges(h_q, n_q, chunks, d, block):
     assert err <= 2e-2, err
 
 
+GATHERED = [
+    # name, h_q, h_kv, n_q, n_kv, d, block, causal, sparsity, interleaved: at least 320000 tiles of 128 rows x 64 keys
+    ("g4_odd_tail", 32, 8, 2000, 44240, 128, 64, True, 0.97, False),
+    ("g4_interleaved_b128", 32, 8, 4097, 4097 + 64 * 300, 128, 128, True, 0.95, True),
+    ("g4_d64_dense", 32, 8, 2000, 44240, 64, 64, True, 0.3, False),
+    ("g1_d64", 32, 32, 13001, 13001, 64, 64, True, 0.93, False),
+    ("g1_noncausal", 16, 16, 13056, 13056, 128, 128, False, 0.9, False),
+    ("g2_d64_interleaved", 16, 8, 18432, 18432, 64, 64, True, 0.95, True),
+    ("g2_one_token_over", 32, 16, 12865, 12865, 128, 64, True, 0.9, False),
+    ("g8", 32, 4, 12901, 12901, 128, 64, True, 0.985, False),
+]
+
+
+@pytest.mark.parametrize("name,h_q,h_kv,n_q,n_kv,d,block,causal,sparsity,interleaved", GATHERED, ids=[c[0] for c in GATHERED])
+def test_attention_over_gathered_rows(name, h_q, h_kv, n_q, n_kv, d, block, causal, sparsity, interleaved):
+    """Launches large enough to be left to the kernel that gathers the rows of a chunk; tokens that keep every chunk, and chunks that
+    every token of a stretch keeps, among sparse ones; logits that grow along the keys.  Reference in fp64 on sampled tokens.  The bar is
+    that of the other given lists."""
+    w = Workload("gathered_" + name, 1, h_q, h_kv, n_q, n_kv, d, block, causal=causal, seed=57)
+    q, k, v = make_inputs(w, DEV)
+    k *= torch.linspace(0.5, 3.0, n_kv, device=DEV).view(1, 1, n_kv, 1).to(k.dtype)
+    if interleaved:                              # [batch, token, head, d] in memory
+        q, k, v = (x.transpose(1, 2).contiguous().transpose(1, 2) for x in (q, k, v))
+    o = torch.full_like(q, float("nan"))
+    p = B.make_params(q, k, v, o, block, causal=causal)
+    t_all, words = B.list_stride(p), B.mask_words(p)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(58)
+    c = torch.arange(words * 32, device=DEV)
+    keep = torch.rand((h_kv, n_q, words * 32), generator=gen, device=DEV) >= sparsity
+    keep[:, n_q // 2 + 5] = True                 # a token of every chunk
+    keep[:, n_q // 3: n_q // 3 + 300, 7] = True  # a chunk of every token
+    own = ((n_kv - n_q + torch.arange(n_q, device=DEV)) // block).view(1, n_q, 1)
+    keep = (keep & (c < own)) | (c == own) if causal else keep & (c < t_all)
+    mask = torch.zeros((1, h_kv, n_q, words), dtype=torch.int64, device=DEV)
+    for i in range(32):
+        mask[0] |= keep.view(h_kv, n_q, words, 32)[..., i].to(torch.int64) << i
+    mask = torch.where(mask >= 1 << 31, mask - (1 << 32), mask).to(torch.int32)
+    bias = torch.randn((1, h_kv, n_q, t_all), generator=gen, device=DEV)
+    ws = B.alloc_workspace(p, DEV).fill_(0xA5)
+    B.dash_stage2_attend(p, q, k, v, o, B.Lists(mask=mask, bias=bias), ws)
+    # which kernel it was: the workgroups of the gathering one count themselves
+    blocks = (-(-n_q // (128 // (h_q // h_kv))) + 1) // 2 * h_kv
+    assert int(ws[512:1536].view(torch.int32).sum()) == (0 if sparsity < 0.5 else blocks)
+    again = torch.empty_like(o)
+    B.dash_stage2_attend(p, q, k, v, again, B.Lists(mask=mask, bias=bias), ws)
+    assert torch.equal(o, again)
+    g, worst = h_q // h_kv, 0.0
+    toks = sorted({0, 1, 63, 64, n_q // 3 + 17, n_q // 2 + 4, n_q // 2 + 5, n_q // 2 + 6, n_q - 2, n_q - 1} | {(i * 977) % n_q for i in range(20)})
+    assert bool(torch.isfinite(o[0].float()).all())
+    for r in range(h_kv):
+        for t in toks:
+            pos = n_kv - n_q + t
+            kept = keep[r, t, :t_all]
+            add = torch.full((t_all,), float("-inf"), device=DEV, dtype=torch.float64)
+            add[kept] = bias[0, r, t, :int(kept.sum())].double()
+            if causal:
+                add[pos // block] = 0.0
+            add = add.repeat_interleave(block)[:n_kv]
+            if causal:
+                add[pos + 1:] = float("-inf")
+            j = add > float("-inf")
+            z = q[0, r * g:(r + 1) * g, t].double() @ k[0, r, j].double().T / d ** 0.5 + add[j]
+            ref = torch.softmax(z, -1) @ v[0, r, j].double()
+            worst = max(worst, ((o[0, r * g:(r + 1) * g, t].double() - ref).abs().max() / ref.abs().max()).item())
+    print(f"[parity] gathered rows {name}: {worst:.2e}")
+    assert worst <= 2e-2, worst
+
+
 @pytest.mark.parametrize("first,last", [(1.0, 4.0), (4.0, 1.0)])
 @pytest.mark.parametrize("name,batch,h_q,h_kv,n,d", [("two_groups", 1, 8, 8, 832, 128), ("two_groups_d64", 1, 16, 2, 832, 64), ("one_group", 33, 1, 1, 1000, 128)])
 def test_prefill_of_rising_and_falling_logits(name, batch, h_q, h_kv, n, d, first, last):
