@@ -619,7 +619,7 @@ static hipError_t launch_s2_t(const S2Args& a, bool pair, hipStream_t st) {
     return hipGetLastError();
   }
   if (!DENSE && a.costs)
-    if (hipError_t e = launch_s2_costs(a, st); e != hipSuccess) return e;
+    if (hipError_t e = launch_s2_costs(a, D, st); e != hipSuccess) return e;
   auto kern = s2_attend_kernel<D, DENSE, false>;
   static LdsOptIn opt_in;
   if (hipError_t e = allow_dyn_lds((const void*)kern, C::LDS_BYTES, opt_in); e != hipSuccess) return e;

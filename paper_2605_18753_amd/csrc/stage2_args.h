@@ -43,7 +43,7 @@ inline void fill_s2_args(S2Args& a, const dash_params& p, const Layout& L, const
 
 // the kernel that gathers rows (stage2_gather.hip)
 bool s2_may_gather(const S2Args& a, int d);
-hipError_t launch_s2_costs(const S2Args& a, hipStream_t st);
+hipError_t launch_s2_costs(const S2Args& a, int d, hipStream_t st);
 hipError_t launch_s2_gather(const S2Args& a, int d, hipStream_t st);
 
 // Whether a launch's tiles are left to s2_gather_kernel; lane i brings the costs of tile i of the kCostTiles.

@@ -18,11 +18,13 @@
 //   O^T[d,row] += V^T P^T   A = V^T: lane (m, kq) loads D/16 consecutive d (from D/16 m) of its 8 keys and pairs the keys up with byte
 //   permutes, one per operand register; accumulator e, register r of lane (m, kq) is d = (4 kq + r) D/16 + e of row m.
 // The A and B operands want adjacent lanes on different rows of K and Q, for which the memory pipe takes 64 accesses an instruction, one a
-// clock.  So adjacent lanes load adjacent pieces of a row and exchange them in registers (turn4): 3250 -> 1340 accesses per item.
+// clock: 3250 of them per item instead of 1340.  So four adjacent lanes load 64 bytes of a row, and the LDS crossbar moves them to their lanes (with
+// selects between neighbouring lanes instead the vector pipe has 27 % more to do: 3.20 -> 3.10 ms at 32k tokens, group of 4, 9 % kept).
 //
-// What bounds it: a wave's chain of loads, products and vector work, two waves per SIMD (256 registers).  128k tokens, 32 / 8 heads, chunks of 128,
-// 12 % of them kept: vector pipe 56 % and matrix pipe 20 % busy, 18.8 TB/s out of L2 (43 ms for what the other kernel does in 87).  Copies
-// without one part: no loads but an item's first -18 %, no exchange of lanes -12, no sums in LDS -10, no exponentials -2.
+// What bounds it: a wave's chain of loads, products and vector work, two waves per SIMD (256 registers; head dimension 64: three, 1.97 -> 1.79 ms
+// there).  128k tokens, 32 / 8 heads, chunks of 128, 12 % of them kept: 87 -> 40 ms for Stage 2 alone, vector pipe half and matrix pipe a fifth
+// busy, 19 TB/s out of L2.  Copies without one part: no loads but an item's first -18 %, no sums in LDS -10, no wait for a token's earlier entries -7,
+// no exponentials -2.
 #include <type_traits>
 
 #include "common.h"
@@ -33,39 +35,6 @@
 namespace dash {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-// Registers x0 .. x3 of every four adjacent lanes as a 4 x 4 matrix, transposed: one select per register and step, its other
-// operand read from the neighbour (the compiler takes a move and a select for each).  A DPP operand wants two instructions
-// between its write and the read.
-__device__ __forceinline__ void turn4(uint32_t& x0, uint32_t& x1, uint32_t& x2, uint32_t& x3) {
-  uint32_t t0, t1, t2, t3;
-  asm("s_mov_b64 vcc, %8\n\t"
-      "s_nop 1\n\t"
-      "v_cndmask_b32_dpp %4, %1, %0, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_dpp %6, %3, %2, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "s_not_b64 vcc, vcc\n\t"
-      "v_cndmask_b32_dpp %5, %0, %1, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_dpp %7, %2, %3, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "s_mov_b64 vcc, %9\n\t"
-      "s_nop 0\n\t"
-      "v_cndmask_b32_dpp %0, %6, %4, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_dpp %1, %7, %5, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "s_not_b64 vcc, vcc\n\t"
-      "v_cndmask_b32_dpp %2, %4, %6, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_dpp %3, %5, %7, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
-      : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
-      : "s"(0x5555555555555555ull), "s"(0x3333333333333333ull) : "vcc", "scc");
-}
-__device__ __forceinline__ void turn2(uint32_t& x0, uint32_t& x1) {
-  uint32_t t0;
-  asm("s_mov_b64 vcc, %3\n\t"
-      "s_nop 1\n\t"
-      "v_cndmask_b32_dpp %2, %1, %0, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "s_not_b64 vcc, vcc\n\t"
-      "v_cndmask_b32_dpp %1, %0, %1, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_mov_b32 %0, %2"
-      : "+v"(x0), "+v"(x1), "=&v"(t0) : "s"(0x5555555555555555ull) : "vcc", "scc");
-}
 
 // over the four lanes m + 16 kq of a row
 __device__ __forceinline__ float quarters_max(float v) {
@@ -91,6 +60,7 @@ constexpr int64_t kMinTiles = 320000;
 
 template <int D, int G> struct GatherCfg {
   static constexpr int ROWS = 256, TOK = ROWS / G, TPI = 32 / G;   // rows and tokens of a workgroup, tokens of an item
+  static constexpr int WAVES = D == 64 ? 12 : 8;
   static constexpr int TOKP = TOK + 1;                             // row stride of the mask words: no bank conflicts
   static size_t lds_bytes(int words) {
     return (size_t)ROWS * D * 4 + 2 * ROWS * 4 + (size_t)words * TOKP * 4 + (((size_t)words * TOKP * 2 + 3) & ~(size_t)3) + words * 32 * 2 + 16 + TOK * 4;
@@ -98,13 +68,12 @@ template <int D, int G> struct GatherCfg {
 };
 
 template <int D, int G>
-__global__ __launch_bounds__(512, 2) void s2_gather_kernel(S2Args a) {
+__global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WAVES / 4)) void s2_gather_kernel(S2Args a) {
   using C = GatherCfg<D, G>;
   constexpr int TOK = C::TOK, TPI = C::TPI, TOKP = C::TOKP;
   constexpr int NE = D / 16;            // accumulators of a 16-row tile
   constexpr int NS = D / 32;            // contraction steps of the first product
   constexpr int NW = TOK > 64 ? TOK / 64 : 1;   // 64 tokens per lane step
-  constexpr int NQ = NS > G ? NS / G : 1;       // tokens of NS rows
   constexpr int NB = D / 16;            // 16-byte pieces of a row's sums per lane
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   f32x4* lo = reinterpret_cast<f32x4*>(lds);                              // [NB][4][256]: piece j, quarter kq, row
@@ -133,16 +102,15 @@ __global__ __launch_bounds__(512, 2) void s2_gather_kernel(S2Args a) {
   const int block_log = 31 - __builtin_clz(a.block);
   const int wn = a.words;
 
-  for (int i = tid; i < TOK * wn; i += 512) {
+  for (int i = tid; i < TOK * wn; i += C::WAVES * 64) {
     const int t = i / wn, w = i - t * wn;
     lmask[w * TOKP + t] = t < n_tok ? a.mask[(row0 + t) * a.words + w] : 0u;
   }
-#pragma unroll
-  for (int i = 0; i < C::ROWS * D / 4 / 512; i++) lo[i * 512 + tid] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = tid; i < C::ROWS * D / 4; i += C::WAVES * 64) lo[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (tid < 256) { lm[tid] = -INFINITY; ll[tid] = 0.f; }
   if (tid < 4 + TOK) ctl[tid] = 0;
   __syncthreads();
-  for (int w = wave; w < wn; w += 8) {
+  for (int w = wave; w < wn; w += C::WAVES) {
     uint32_t v[NW];
 #pragma unroll
     for (int k = 0; k < NW; k++) {
@@ -199,20 +167,17 @@ __global__ __launch_bounds__(512, 2) void s2_gather_kernel(S2Args a) {
   const __amdgpu_buffer_rsrc_t v_rs = rsrc(a.v + b * a.vs_b + r * a.vs_h, ((int64_t)(a.n_kv - 1) * a.vs_t + D) * 2);
   const __amdgpu_buffer_rsrc_t b_rs = rsrc(a.bias + row0 * a.t_all, (int64_t)n_tok * a.t_all * 4);
   const uint32_t ks2 = (uint32_t)a.ks_t * 2u, vs2 = (uint32_t)a.vs_t * 2u;
-  // K (and Q) by NS adjacent lanes from NS consecutive 16-byte pieces of a row; reg j of lane (m, kq) is row (m & ~(NS - 1)) + j, piece
-  // NS kq + m % NS, and the exchange among those lanes turns it into row m, piece NS kq + j
-  const uint32_t k_off = (uint32_t)(m & ~(NS - 1)) * ks2 + (uint32_t)(kq * NS + (m & (NS - 1))) * 16u;
+  // K and Q: lane l loads piece l % 4 of the 64 bytes of step s of row l / 4, and the LDS crossbar hands lane (m, kq) what lane 4 m + kq loaded
+  const uint32_t k_off = (uint32_t)(lane >> 2) * ks2 + (uint32_t)(lane & 3) * 16u;
+  const int from = (4 * m + kq) * 4;
   auto turn = [&](bf16x8 (&f)[NS]) __attribute__((always_inline)) {
-    uint32_t x[4][NS];
 #pragma unroll
-    for (int w = 0; w < 4; w++) {
+    for (int s = 0; s < NS; s++) {
+      u32x4 x = __builtin_bit_cast(u32x4, f[s]);
 #pragma unroll
-      for (int s = 0; s < NS; s++) x[w][s] = __builtin_bit_cast(u32x4, f[s])[w];
-      if constexpr (NS == 4) turn4(x[w][0], x[w][1], x[w][2], x[w][3]);
-      else turn2(x[w][0], x[w][1]);
+      for (int w = 0; w < 4; w++) x[w] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)x[w]);
+      f[s] = __builtin_bit_cast(bf16x8, x);
     }
-#pragma unroll
-    for (int s = 0; s < NS; s++) f[s] = __builtin_bit_cast(bf16x8, u32x4{x[0][s], x[1][s], x[2][s], x[3][s]});
   };
   const uint32_t v_off = (uint32_t)(4 * kq) * vs2 + (uint32_t)m * (D / 8u);
   constexpr int VW = D / 32;            // registers of a value load
@@ -232,7 +197,7 @@ __global__ __launch_bounds__(512, 2) void s2_gather_kernel(S2Args a) {
     for (int kt = 0; kt < 2; kt++) {
 #pragma unroll
       for (int s = 0; s < NS; s++)
-        kf[kt][s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(k_rs, k_off, (uint32_t)(key0 + 16 * kt + s) * ks2, 0));
+        kf[kt][s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(k_rs, k_off + s * 64, (uint32_t)(key0 + 16 * kt) * ks2, 0));
     }
   };
   auto load_v = [&](int key0) {
@@ -277,21 +242,15 @@ __global__ __launch_bounds__(512, 2) void s2_gather_kernel(S2Args a) {
     }
     const int n_in = cnt - sub * TPI;            // of the item and those behind it
     two = n_in > TPI / 2;
-    uint32_t qo[2][NQ];
+    uint32_t qo[2];
 #pragma unroll
     for (int j = 0; j < 2; j++) {
-      const int slot = j * (TPI / 2) + m / G;
-      const int x = __builtin_amdgcn_ds_bpermute(slot * 4, tok_of);
+      const int slot = j * (TPI / 2) + m / G, qs = j * (TPI / 2) + (lane >> 2) / G;   // of the lane's row, of the row it loads
+      const int x = __builtin_amdgcn_ds_bpermute(slot * 4, tok_of), xq = __builtin_amdgcn_ds_bpermute(qs * 4, tok_of);
       const bool ok = slot < n_in;
       tag[j] = ok ? x + m % G : -1;
       const int t = ok ? (x & 0xff) / G : 0;
-      // register s of the NS lanes: row (m & ~(NS - 1)) + s of the tile, of NQ tokens
-#pragma unroll
-      for (int i = 0; i < NQ; i++) {
-        const int qs = j * (TPI / 2) + (m & ~(NS - 1)) / G + i;
-        const int tq = NQ == 1 ? t : (__builtin_amdgcn_ds_bpermute(qs * 4, tok_of) & 0xff) / G;
-        qo[j][i] = qs < n_in ? (uint32_t)((NQ == 1 ? m % G & ~(NS - 1) : 0) * (int)a.qs_h + (tok0 + tq) * (int)a.qs_t + (kq * NS + (m & (NS - 1))) * 8) * 2u : 0x80000000u;
-      }
+      qo[j] = qs < n_in ? (uint32_t)((lane >> 2) % G * (int)a.qs_h + (tok0 + (xq & 0xff) / G) * (int)a.qs_t + (lane & 3) * 8) * 2u : 0x80000000u;
       const bool own = a.causal && chunk == (a.pos0 + tok0 + t) >> block_log;
       // read past the end: 0
       bias[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b_rs, ok && !own ? (uint32_t)(t * a.t_all + (x >> 8)) * 4u : ~3u, 0, 0));
@@ -300,7 +259,7 @@ __global__ __launch_bounds__(512, 2) void s2_gather_kernel(S2Args a) {
     for (int j = 0; j < 2; j++)
 #pragma unroll
       for (int s = 0; s < NS; s++)
-        qf[j][s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(q_rs, qo[j][s * NQ / NS], (uint32_t)(s % (NS / NQ) * (int)a.qs_h) * 2u, 0));
+        qf[j][s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(q_rs, qo[j] + s * 64, 0, 0));
     load_k(chunk << block_log);
     load_v(chunk << block_log);
   };
@@ -324,7 +283,6 @@ __global__ __launch_bounds__(512, 2) void s2_gather_kernel(S2Args a) {
       f32x4 s[NT][2];
       turn(kf[0]);
       turn(kf[1]);
-      __builtin_amdgcn_sched_barrier(0);   // what the exchange writes is no operand of a product in flight
 #pragma unroll
       for (int ks = 0; ks < NS; ks++)
 #pragma unroll
@@ -451,16 +409,17 @@ __global__ __launch_bounds__(512, 2) void s2_gather_kernel(S2Args a) {
       }
       asm volatile("" ::: "memory");
       const float ma = lm[tag_a & 0xff], la = ll[tag_a & 0xff], mb = lm[tag_b & 0xff], lb = ll[tag_b & 0xff];
+      __builtin_amdgcn_s_setprio(2);
       add_up(std::integral_constant<int, 0>{}, tag_a, m_ref[0], l[0], ma, la);
       add_up(std::integral_constant<int, 1>{}, tag_b, m_ref[1], l[1], mb, lb);
       asm volatile("" ::: "memory");             // a wave's LDS operations complete in order
       if (tag_a >= 0) __hip_atomic_store(&ldone[at_a], (tag_a >> 8) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       if (tag_b >= 0) __hip_atomic_store(&ldone[at_b], (tag_b >> 8) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __builtin_amdgcn_s_setprio(0);
     }
     if (next >= n_items) break;
     turn(qf[0]);
     turn(qf[1]);
-    __builtin_amdgcn_sched_barrier(0);
     if (two) attend(std::integral_constant<int, 2>{});
     else attend(std::integral_constant<int, 1>{});
     item = next;
@@ -469,7 +428,7 @@ __global__ __launch_bounds__(512, 2) void s2_gather_kernel(S2Args a) {
 
   {
     const int orow = tid & 255, t = orow / G;
-    if (t < n_tok) {
+    if (tid < 512 && t < n_tok) {
       const float lt = ll[orow], inv = lt > 0.f ? 1.f / lt : 0.f;
       uint16_t* op = a.o + b * a.os_b + (int64_t)(r * G + orow % G) * a.os_h + (int64_t)(tok0 + t) * a.os_t;
 #pragma unroll
@@ -490,14 +449,15 @@ __global__ __launch_bounds__(512, 2) void s2_gather_kernel(S2Args a) {
 
 // What kCostTiles tiles, spread over the launch, cost in either kernel; the sums decide for the launch (s2_gathered).  Tile by tile the launch would
 // take both kernels' longest lists one after the other (2000 tokens against a 32k cache 583 -> 817 us).  A workgroup takes one tile, a wave 32 of its
-// rows, as in s2_attend_kernel.  There a chunk that one of the tile's tokens kept costs the workgroup 0.8 us and another 0.2 for each wave
-// that takes part, two workgroups sharing a CU; here an item costs 0.62 us of a CU (of 128 keys 0.97).  An item holds up to 32 / g_q tokens
-// of a chunk, and on average three tenths of the chunks have one that is not full.  Fitted to both kernels' times over 144 launches (8k, 16k, 32k tokens and 2000
-// against a 32k cache, groups of 1 to 16, head dimensions 64 and 128, chunks of 64 and 128, 2 to 100 % of the chunks kept, queries independent and
-// correlated): the choice takes 0.2 % more time than the faster kernel of each, and none of them more than s2_attend_kernel, which alone
-// takes 14 % more.  32k tokens, there -> here: group of 4, 9 % kept 4.55 -> 3.22 ms, 26 % 6.72 -> 6.26, 41 % 7.3 -> 9.0 (not taken); 9 % with
-// correlated queries 2.44 -> 2.84 (not taken); chunks of 128, 16 % 5.84 -> 3.43; group of 1, 3 % 5.42 -> 3.14, 8 % 7.48 -> 4.14, 13 % 7.83 -> 5.36.
-__global__ __launch_bounds__(256) void s2_costs_kernel(S2Args a) {
+// rows, as in s2_attend_kernel.  There, in units of 0.2 us of half a CU, a chunk that one of the tile's tokens kept costs the workgroup 4 and another 1 for
+// each wave that takes part; here an item of 64 keys costs 5.85 of them per workgroup of a whole CU (head dimension 64: 4.8 of its own, shorter unit), and
+// of 128 keys 3.9 (3.8) per 64.  An item holds up to 32 / g_q tokens of a chunk, and on average three tenths of the chunks have one that is
+// not full.  Fitted to both kernels' times over 94 launches (16k and 32k tokens and 2000 against a 32k cache, groups of 1 to 8, both head dimensions and chunk
+// sizes, 2 to 60 % of the chunks kept, queries independent and correlated): the choice takes 0.7 % more time than the faster kernel of each, and
+// none of them more than s2_attend_kernel.  32k tokens, there -> here: group of 4, 9 % kept 4.50 -> 3.07 ms, 26 % 6.72 -> 6.05 (not taken), 41 % 7.3 -> 8.5 (not
+// taken); 9 % with correlated queries 2.44 -> 2.65 (not taken); chunks of 128, 16 % 5.84 -> 3.27; group of 1, 3 % 5.42 -> 2.9, 8 % 7.48 -> 3.77; head
+// dimension 64, 9 % 3.27 -> 1.79.
+__global__ __launch_bounds__(256) void s2_costs_kernel(S2Args a, float per_item) {
   __shared__ uint32_t all[64], own[4][64];
   __shared__ int sums[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -536,11 +496,12 @@ __global__ __launch_bounds__(256) void s2_costs_kernel(S2Args a) {
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) chunks += __shfl_xor(chunks, o);
   const float items = (float)sums[0] * (float)a.g_q * (1.f / 32.f) + 0.3f * (float)chunks;
-  if (lane == 0) a.costs[blockIdx.x] = S2Costs{4.f * (float)chunks + (float)sums[1], (a.block == 64 ? 6.2f : 4.85f) * items};
+  if (lane == 0) a.costs[blockIdx.x] = S2Costs{4.f * (float)chunks + (float)sums[1], per_item * items};
 }
 
-hipError_t launch_s2_costs(const S2Args& a, hipStream_t st) {
-  hipLaunchKernelGGL(s2_costs_kernel, dim3(kCostTiles), dim3(256), 0, st, a);
+hipError_t launch_s2_costs(const S2Args& a, int d, hipStream_t st) {
+  const float per_item = d == 128 ? (a.block == 64 ? 5.85f : 3.9f) : (a.block == 64 ? 4.8f : 3.8f);
+  hipLaunchKernelGGL(s2_costs_kernel, dim3(kCostTiles), dim3(256), 0, st, a, per_item);
   return hipGetLastError();
 }
 
@@ -550,7 +511,7 @@ static hipError_t launch_t(const S2Args& a, hipStream_t st) {
   static LdsOptIn opt_in;
   const size_t lds = GatherCfg<D, G>::lds_bytes(a.words);
   if (hipError_t e = allow_dyn_lds((const void*)kern, lds, opt_in); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((a.n_tiles + 1) / 2 * a.hb), dim3(512), lds, st, a);
+  hipLaunchKernelGGL(kern, dim3((a.n_tiles + 1) / 2 * a.hb), dim3(GatherCfg<D, G>::WAVES * 64), lds, st, a);
   return hipGetLastError();
 }
 
