@@ -131,13 +131,7 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
   if (wave == 0) {
     int base = 0;
     for (int c = lane; c - lane < wn * 32; c += 64) {
-      int incl = c < wn * 32 ? lcum[c] : 0;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(incl, o);
-        incl += lane >= o ? up : 0;
-      }
-      incl += base;
+      const int incl = base + wave_scan(c < wn * 32 ? lcum[c] : 0);
       if (c < wn * 32) lcum[c] = (uint16_t)incl;
       base = __builtin_amdgcn_readlane(incl, 63);
     }
