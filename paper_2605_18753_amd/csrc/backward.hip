@@ -57,7 +57,8 @@ namespace dash {
 // wave in the second walk).  Training-shaped workload (4 x 16 heads x 8192 tokens): 1.35 + 2.43 ms
 // with a single tile buffer (copy, wait, compute) and dO as an LDS operand -> 1.30 + 2.07 ms; then, both builds in turn,
 // 1266 -> 1184 and 2096 -> 2017 us (2 x 16 heads x 3001 tokens, d 64: 69 -> 64 and 107 -> 103) without the waits for the bias
-// just asked for and for the bias gradient just stored.
+// just asked for and for the bias gradient just stored; then 1184 -> 1148 and 2015 -> 1929 (65 -> 59 and 104 -> 96.5) with the tiles
+// listed in front of the walk and a chunk's bias ready before the barrier, in every lane of its token.
 template <int D, bool GRAD>
 __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
   using C = BCfg<D>;
@@ -65,6 +66,7 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   uint32_t* wgmask = reinterpret_cast<uint32_t*>(lds + 4 * C::TILE_BYTES);   // [64], after the K ring [2] and the V ring [2]
   uint32_t* wvmask = wgmask + 64;                                            // [4][64]
+  uint16_t* list = reinterpret_cast<uint16_t*>(wgmask + 5 * 64);             // [4096]: the workgroup's tiles
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -74,7 +76,7 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
   const int r = hbi % a.h_kv, b = hbi / a.h_kv;
   const int tokw = 32 / a.g_q;
   const int tok_w0 = tile * 4 * tokw + wave * tokw;
-  const int nsub = a.block >> 6;
+  const int sub_log = a.block >> 7;                     // log2 of the 64-key tiles of a chunk
 
   // the column masks that the second walk sets bits of: cleared by the first (a launch of its own took 4-5 us)
   if constexpr (!GRAD) {
@@ -102,15 +104,17 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
   }
 
   // ---- chunk bitmaps ---------------------------------------------------------
-  const int trk_tok = tok_w0 + lane;
-  const bool trk_ok = lane < tokw && trk_tok < a.n_q;
+  // Every lane tracks the token of its row, as in s2_attend_kernel; the first of a token's lanes writes what is the token's.
   const int64_t trk_base = ((int64_t)b * a.h_kv + r) * a.n_q + min(tok_w0, a.n_q - 1);   // uniform; a lane's row by offset
   const uint32_t* trk_mask = a.mask + trk_base * a.words;
-  const float* trk_bias = a.bias + trk_base * a.t_all;
-  const uint32_t trk_m0 = trk_ok ? (uint32_t)(lane * a.words) : 0u, trk_b0 = trk_ok ? (uint32_t)(lane * a.t_all) : 0u;
-  int trk_rank = 0, trk_wi = -1;
-  uint32_t trk_word = 0;
+  const __amdgpu_buffer_rsrc_t trk_bias = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(a.bias) + trk_base * a.t_all, 0, max(min(tokw, a.n_q - tok_w0), 0) * a.t_all * 4, 0x00020000);
+  auto ask_bias = [&](uint32_t at) -> float { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(trk_bias, at, 0, 0)); };
+  const uint32_t trk_m0 = row_ok ? (uint32_t)(n / a.g_q * a.words) : 0u, trk_b0 = row_ok ? (uint32_t)(n / a.g_q * a.t_all) : 0u;
+  uint32_t trk_at = row_ok ? trk_b0 * 4u : ~3u, trk_word = 0;
+  const bool trk_lead = h == 0 && n % a.g_q == 0;
   bool trk_has = false;
+  float trk_old = 0.f, trk_next = ask_bias(trk_at);
 
   for (int i = tid; i < 5 * 64; i += 256) wgmask[i] = 0u;
   __syncthreads();
@@ -131,20 +135,12 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
       }
     }
 
-  // ---- tile iterator ---------------------------------------------------------
-  int it_wi = -1, it_sub = nsub - 1, it_u = -1;
-  uint32_t it_bits = 0u;
-  auto advance = [&]() -> bool {
-    if (it_u >= 0 && it_sub + 1 < nsub) { it_sub++; return true; }
-    while (it_bits == 0u) {
-      if (++it_wi >= a.words) return false;
-      it_bits = __builtin_amdgcn_readfirstlane(wgmask[it_wi]);
-    }
-    it_u = it_wi * 32 + __builtin_ctz(it_bits);
-    it_bits &= it_bits - 1u;
-    it_sub = 0;
-    return true;
-  };
+  const int n_it = list_tiles<256>(wgmask, wvmask, list, sub_log, tid) << sub_log;
+  __syncthreads();
+  auto entry = [&](int i) -> int { return list[max(min(i, n_it - 1), 0)]; };   // behind the last tile: that one again
+  int e_cur = __builtin_amdgcn_readfirstlane(entry(0)), e_next = __builtin_amdgcn_readfirstlane(entry(1)), e_ahead = 0;
+  if (n_it == 0) e_cur = e_next = 0;             // no list: whatever lies there
+  trk_word = trk_mask[trk_m0 + ((e_cur & 0xfff) >> sub_log >> 5)];
 
   // ---- tile copies -------------------------------------------------------------
   const u32x4 k_rs = make_rsrc(a.k + b * a.ks_b + r * a.ks_h, (((int64_t)a.n_kv - 1) * a.ks_t + D) * 2);
@@ -156,10 +152,8 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
   const uint32_t k_step = (uint32_t)(C::ROWS_PER_COPY * (int)a.ks_t * 2);
   const uint32_t v_step = (uint32_t)(C::ROWS_PER_COPY * (int)a.vs_t * 2);
   uint32_t cp_k = 0, cp_v = 0;   // scalar byte offsets of the tile being copied
-  auto copy_begin = [&](int u, int sub) {
-    cp_k = (uint32_t)(u * a.block + sub * 64) * (uint32_t)a.ks_t * 2u;
-    cp_v = (uint32_t)(u * a.block + sub * 64) * (uint32_t)a.vs_t * 2u;
-  };
+  const uint32_t k_tile = (uint32_t)a.ks_t * 128u, v_tile = (uint32_t)a.vs_t * 128u;   // bytes from tile to tile
+  auto copy_begin = [&](int t) { cp_k = (uint32_t)t * k_tile; cp_v = (uint32_t)t * v_tile; };
   auto copy_one = [&](int c, int slot) {
     if (c < C::COPIES)
       copy16_to_lds(k_rs, lds0 + slot * C::TILE_BYTES + wave * 1024 + c * 4096, k_off, cp_k + c * k_step);
@@ -191,27 +185,22 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
     dsum = a.dsum[row];
     asm volatile("" : "+v"(lse2), "+v"(dsum));
   }
-  float trk_next = trk_bias[trk_b0];
   float* biasd = a.biasd + trk_base * a.t_all;
   float* dbd = a.dbd + trk_base * a.t_all;
   float bias_row = 0.f;
-  bool wave_on = false, diag = false;
-  auto wave_has = [&](int u) -> bool {
-    return wave_ok && ((__builtin_amdgcn_readfirstlane(wvmask[wave * 64 + (u >> 5)]) >> (u & 31)) & 1u);
-  };
+  bool diag = false;
   auto begin_chunk = [&](int u) {
-    diag = a.causal && u == cw;
-    float bt = 0.f;
     trk_has = false;
-    if (!diag) {
-      if ((u >> 5) != trk_wi) { trk_wi = u >> 5; trk_word = trk_mask[trk_m0 + trk_wi]; }
-      trk_has = trk_ok && ((trk_word >> (u & 31)) & 1u);
-      bt = trk_has ? trk_next * kLog2e : -INFINITY;
-      if (GRAD) { if (trk_has) biasd[trk_b0 + u] = trk_next; }
-      trk_rank += trk_has ? 1 : 0;
-      trk_next = trk_bias[trk_b0 + min(trk_rank, a.t_all - 1)];   // by every lane: see s2_attend_kernel
-    }
-    bias_row = __shfl(bt, n / a.g_q);
+    bias_row = 0.f;
+    if (a.causal && u == cw) return;
+    const bool bit = row_ok && ((trk_word >> (u & 31)) & 1u);
+    const float next = trk_old + trk_next;   // one of them is 0
+    bias_row = bit ? next * kLog2e : -INFINITY;
+    if (GRAD) { if (bit && trk_lead) biasd[trk_b0 + u] = next; }
+    trk_old = bit ? 0.f : next;
+    trk_at += bit ? 4u : 0u;
+    trk_next = ask_bias(bit ? trk_at : ~3u);   // by every lane: see s2_attend_kernel
+    trk_has = bit;
   };
 
   // ---- one 64-key tile, in two 32-key halves -----------------------------------------
@@ -331,15 +320,14 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
   };
 
   // ---- main loop: as in the forward kernel ------------------------------------------------
-  bool have = advance();
 #pragma unroll
   for (int ks = 0; ks < KS; ks++) asm volatile("" : "+v"(qf[ks]), "+v"(dof[ks]));   // landed before the copies are in flight
-  if (have) {
-    copy_begin(it_u, it_sub);
+  if (n_it > 0) {
+    copy_begin(e_cur & 0xfff);
 #pragma unroll
     for (int c = 0; c < 2 * C::COPIES; c++) copy_one(c, 0);
   }
-  // the bias gradient of a chunk is stored behind the next barrier: before it, the wait for the copies would be one for the store
+  // the bias gradient of a chunk is stored behind the next wait for copies, which would be one for the store
   float db_out = 0.f;
   int db_u = -1;
   auto put_db = [&]() {
@@ -348,41 +336,42 @@ __global__ __launch_bounds__(256, 2) void bwd_q_kernel(BwdArgs a) {
       db_u = -1;
     }
   };
-  auto iteration = [&](auto p_tag) {
+  auto iteration = [&](auto p_tag, int it) {
     constexpr int P = decltype(p_tag)::value;
-    const int cu = it_u, csub = it_sub;
-    const bool more = advance();
-    if (csub == 0) wave_on = wave_has(cu);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's copies of the tile have landed
-    // the loads of the chunk before are known to have arrived, or a wait for them below would be one for the store
-    asm volatile("" : "+v"(trk_next), "+v"(trk_word));
-    __syncthreads();
+    const int t_cur = e_cur & 0xfff, t_next = e_next & 0xfff, u = t_cur >> sub_log, un = t_next >> sub_log;
+    const bool on = (e_cur >> (12 + wave)) & 1, more = it + 1 < n_it;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's copies of the tile have landed, and its loads
+    // whatever needs no tile stands before the barrier
     put_db();
-    if (wave_on && csub == 0) begin_chunk(cu);
-    if (more) copy_begin(it_u, it_sub);
-    if (wave_on) {
-      const int kpos0 = cu * a.block + csub * 64;
+    diag = a.causal && u == cw;
+    if (on && (t_cur & sub_log) == 0) begin_chunk(u);
+    if ((un ^ u) >> 5) trk_word = trk_mask[trk_m0 + (un >> 5)];   // arrives with the next tile's copies
+    if (more) copy_begin(t_next);
+    asm volatile("s_barrier" ::: "memory");
+    e_ahead = entry(it + 2);
+    if (on) {
+      const int kpos0 = t_cur * 64;
       tile_math(p_tag, diag || kpos0 + 64 > a.n_kv, kpos0, more);
-      if (GRAD && csub == nsub - 1) {
-        // bias gradient of chunk cu: sum over the keys (both lane halves) and the
-        // token's heads (adjacent lanes), written by the lane that tracks the token
+      if (GRAD && (t_cur & sub_log) == sub_log) {
+        // bias gradient of chunk u: sum over the keys (both lane halves) and the token's heads (adjacent lanes)
         float tot = db_acc + __shfl_xor(db_acc, 32);
         for (int o = 1; o < a.g_q; o <<= 1) tot += __shfl_xor(tot, o);
-        const float mine = __shfl(tot, (lane * a.g_q) & 31);
-        db_out = mine;
-        db_u = !diag && trk_has ? cu : -1;
+        db_out = tot;
+        db_u = trk_has && trk_lead ? u : -1;
         db_acc = 0.f;
       }
     } else if (more) {
 #pragma unroll
       for (int c = 0; c < 2 * C::COPIES; c++) copy_one(c, P ^ 1);
     }
-    have = more;
+    e_cur = e_next;
+    e_next = __builtin_amdgcn_readfirstlane(e_ahead);
   };
-  while (have) {
-    iteration(std::integral_constant<int, 0>{});
-    if (!have) break;
-    iteration(std::integral_constant<int, 1>{});
+  for (int it = 0; it < n_it;) {
+    iteration(std::integral_constant<int, 0>{}, it);
+    if (++it >= n_it) break;
+    iteration(std::integral_constant<int, 1>{}, it);
+    ++it;
   }
   put_db();
 
@@ -459,14 +448,14 @@ template <int D> static hipError_t launch_bwd_t(const BwdArgs& a, hipStream_t st
   static LdsOptIn done_lse, done_grad;
   hipError_t e;
   {
-    const size_t lds = 4 * C::TILE_BYTES + 5 * 64 * 4;
+    const size_t lds = 4 * C::TILE_BYTES + 5 * 64 * 4 + 4096 * 2;
     auto kern = bwd_q_kernel<D, false>;
     if ((e = allow_dyn_lds((const void*)kern, lds, done_lse)) != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb), dim3(256), lds, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   {
-    const size_t lds = 4 * C::TILE_BYTES + 5 * 64 * 4;
+    const size_t lds = 4 * C::TILE_BYTES + 5 * 64 * 4 + 4096 * 2;
     auto kern = bwd_q_kernel<D, true>;
     if ((e = allow_dyn_lds((const void*)kern, lds, done_grad)) != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb), dim3(256), lds, st, a);

@@ -109,4 +109,26 @@ __device__ __forceinline__ void or_mask_rows(const uint32_t* rows, int n, int wo
   }
 }
 
+// A workgroup's list of 64-key tiles from the chunk bitmaps of its rows, all[64] and waves[4][64] (in LDS, complete).  Entry: tile
+// number (< 4096), bits 12 + w: wave w takes part.  Returns the number of chunks; a chunk has 1 << sub_log tiles.
+template <int THREADS> __device__ __forceinline__ int list_tiles(const uint32_t* all, const uint32_t* waves, uint16_t* list, int sub_log, int tid) {
+  constexpr int LPW = THREADS / 64, BPL = 32 / LPW;          // lanes per mask word, bits per lane
+  const int own = __popc(all[tid & 63]);
+  const int incl = wave_scan(own);
+  const int wi = tid / LPW, b0 = (tid % LPW) * BPL;
+  const uint32_t m = all[wi];
+  int at = __shfl(incl - own, wi) + __popc(m & ((1u << b0) - 1u));
+  const uint32_t w0 = waves[wi] >> b0, w1 = waves[64 + wi] >> b0, w2 = waves[128 + wi] >> b0, w3 = waves[192 + wi] >> b0;
+#pragma unroll
+  for (int j = 0; j < BPL; j++)
+    if ((m >> (b0 + j)) & 1u) {
+      const uint32_t on = ((w0 >> j) & 1u) | ((w1 >> j) & 1u) << 1 | ((w2 >> j) & 1u) << 2 | ((w3 >> j) & 1u) << 3;
+      const uint32_t e = (uint32_t)((wi * 32 + b0 + j) << sub_log) | on << 12;
+      list[at << sub_log] = (uint16_t)e;
+      if (sub_log) list[at * 2 + 1] = (uint16_t)(e + 1);
+      at++;
+    }
+  return __builtin_amdgcn_readlane(incl, 63);
+}
+
 }  // namespace dash

@@ -176,26 +176,7 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
   // ---- the workgroup's list of 64-key tiles ----------------------------------
   // Entry: tile number (< 4096), bits 12 + w: wave w takes part.  Written once: a walk over the mask words between the tiles is a
   // chain of scalar branches, some 400 clocks of the 2750 that one wave per SIMD took for a tile.
-  int n_chunks;
-  {
-    constexpr int LPW = PAIR ? 8 : 4, BPL = 32 / LPW;          // lanes per mask word, bits per lane
-    const int own = __popc(wgmask[lane]);
-    const int incl = wave_scan(own);
-    n_chunks = __builtin_amdgcn_readlane(incl, 63);
-    const int wi = tid / LPW, b0 = (tid % LPW) * BPL;
-    const uint32_t m = wgmask[wi];
-    int at = __shfl(incl - own, wi) + __popc(m & ((1u << b0) - 1u));
-    const uint32_t w0 = wvmask[wi] >> b0, w1 = wvmask[64 + wi] >> b0, w2 = wvmask[128 + wi] >> b0, w3 = wvmask[192 + wi] >> b0;
-#pragma unroll
-    for (int j = 0; j < BPL; j++)
-      if ((m >> (b0 + j)) & 1u) {
-        const uint32_t on = ((w0 >> j) & 1u) | ((w1 >> j) & 1u) << 1 | ((w2 >> j) & 1u) << 2 | ((w3 >> j) & 1u) << 3;
-        const uint32_t e = (uint32_t)((wi * 32 + b0 + j) << sub_log) | on << 12;
-        list[at << sub_log] = (uint16_t)e;
-        if (sub_log) list[at * 2 + 1] = (uint16_t)(e + 1);
-        at++;
-      }
-  }
+  const int n_chunks = list_tiles<PAIR ? 512 : 256>(wgmask, wvmask, list, sub_log, tid);
   __syncthreads();
 
   // ---- this workgroup's part of it --------------------------------------------
