@@ -124,7 +124,8 @@ def test_backward(case):
 # and those of three 0.049 of the whole, by the oracle; the comparison asks for 0.05.)
 @pytest.mark.parametrize("h_q,h_kv,chunks,d,extra", [
     (2, 1, 2, 64, {"causal": False}), (4, 1, 3, 128, {"causal": False}), (2, 2, 4, 64, {}), (1, 1, 5, 128, {"causal": False}), (4, 2, 6, 64, {"causal": False}),
-    (1, 1, 7, 64, {"causal": False}), (2, 1, 17, 64, {"causal": False}), (1, 1, 18, 128, {}), (1, 1, 19, 64, {"causal": False})])
+    (1, 1, 7, 64, {"causal": False}), (2, 1, 17, 64, {"causal": False}), (1, 1, 18, 128, {}), (1, 1, 19, 64, {"causal": False}),
+    (1, 1, 34, 64, {"gamma": 4.0})])              # lists across a mask word, waves that skip tiles
 def test_backward_of_rows_of_any_number_of_chunks(h_q, h_kv, chunks, d, extra):
     TB.test_backward_matches_the_oracle((f"b_{chunks}_chunks", 1, h_q, h_kv, chunks * 64, d, 64, {"offset_sigma": 0.8, **extra}))
 
