@@ -43,25 +43,29 @@ struct TileLists {
   static constexpr size_t BYTES = 64 * 4 + 16 * 64 * 4 + 16 * 64 * 2;
   __device__ __forceinline__ TileLists(char* p)
       : uni((uint32_t*)p), word((uint32_t*)(p + 256)), before((uint16_t*)(p + 256 + 4096)) {}
-  // mask: row of token 0 of the tile; ntok valid tokens.  Ends with a barrier.
-  __device__ __forceinline__ void build(const uint32_t* mask, int words, int ntok, int tid, int nthr) {
-    const int wave = tid >> 6, lane = tid & 63, nw = nthr >> 6;
-    for (int t = wave; t < ntok; t += nw) {
-      const uint32_t w = lane < words ? mask[(int64_t)t * words + lane] : 0u;
-      int incl = __popc(w);
-      const int mine = incl;
+  // mask: row of token 0 of the tile; ntok valid tokens.  Ends with a barrier.  All loads in flight together, and the ranks by DPP: one
+  // token after the other, each load waited for, stood in front of every row kernel (one head, 1024 tokens, forward and backward: 83.0 -> 78 us with
+  // the parts' records asked for in front of the lists and not one after the other; 16 heads x 2048 803 -> 784).
+  template <int THREADS> __device__ __forceinline__ void build(const uint32_t* mask, int words, int ntok, int tid) {
+    constexpr int NW = THREADS / 64, PER = 16 / NW;
+    const int wave = tid >> 6, lane = tid & 63;
+    uint32_t w[PER];
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int x = __shfl_up(incl, o);
-        if (lane >= o) incl += x;
-      }
-      word[t * 64 + lane] = w;
-      before[t * 64 + lane] = (uint16_t)(incl - mine);
+    for (int i = 0; i < PER; i++) {
+      const int t = wave + i * NW;
+      w[i] = t < ntok && lane < words ? mask[(int64_t)t * words + lane] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < PER; i++) {                   // rows of no token: empty
+      const int t = wave + i * NW, mine = __popc(w[i]);
+      word[t * 64 + lane] = w[i];
+      before[t * 64 + lane] = (uint16_t)(wave_scan(mine) - mine);
     }
     __syncthreads();
     if (tid < 64) {
       uint32_t u = 0u;
-      for (int t = 0; t < ntok; t++) u |= word[t * 64 + tid];
+#pragma unroll
+      for (int t = 0; t < 16; t++) u |= word[t * 64 + tid];
       uni[tid] = u;
     }
     __syncthreads();
@@ -128,7 +132,7 @@ __global__ __launch_bounds__(512) void s2_f32_kernel(S2FArgs a) {
     }
     __syncthreads();
   } else {
-    tl.build(a.mask + base * a.words, a.words, ntok, tid, 512);
+    tl.build<512>(a.mask + base * a.words, a.words, ntok, tid);
   }
   f32x4 qf[C::NS];
   load_row<D>(a.q + b * a.qs_b + (int64_t)(r * a.g_q + n % a.g_q) * a.qs_h + (int64_t)tok * a.qs_t, hq, qf);
@@ -288,10 +292,20 @@ __global__ __launch_bounds__(256, 2) void bwd_f32_row_kernel(BwdArgs a, RowF32 x
       }
     }
   }
-  tl.build(a.mask + base * a.words, a.words, ntok, tid, 256);
   f32x4 qf[C::NS], of[C::NS];
   load_row<D>(reinterpret_cast<const float*>(a.q) + b * a.qs_b + head * a.qs_h + (int64_t)tok * a.qs_t, hq, qf);
   load_row<D>(reinterpret_cast<const float*>(a.d_o) + b * a.os_b + head * a.os_h + (int64_t)tok * a.os_t, hq, of);
+  // GRAD: the parts' records (max, sum, sum times dP), four at a time; the first four arrive with the lists
+  float rec[4][3];
+  auto ask_parts = [&](int p0) {
+    const float* rp = x.scratch + row_n * 3;
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+      for (int e = 0; e < 3; e++) rec[i][e] = rp[min(p0 + i, x.parts - 1) * x.rows * 3 + e];
+  };
+  if constexpr (GRAD) { if (x.parts > 1) ask_parts(0); }
+  tl.build<256>(a.mask + base * a.words, a.words, ntok, tid);
   const float* kb = reinterpret_cast<const float*>(a.k) + b * a.ks_b + r * a.ks_h;
   const float* vb = reinterpret_cast<const float*>(a.v) + b * a.vs_b + r * a.vs_h;
   float m_run = -INFINITY, l_run = 0.f, dn_run = 0.f;     // of this lane's keys
@@ -304,14 +318,22 @@ __global__ __launch_bounds__(256, 2) void bwd_f32_row_kernel(BwdArgs a, RowF32 x
       lse = a.lse[row_n];
       dsum = a.dsum[row_n];
     } else {
-      const float* rec = x.scratch + row_n * 3;
       float M = -INFINITY, l = 0.f, dn = 0.f;
-      for (int p = 0; p < x.parts; p++) M = fmaxf(M, rec[p * x.rows * 3]);
-      for (int p = 0; p < x.parts; p++) {
-        const float* rp = rec + p * x.rows * 3;
-        const float w = rp[0] == -INFINITY ? 0.f : exp_diff(rp[0], M);
-        l = fmaf(w, rp[1], l);
-        dn = fmaf(w, rp[2], dn);
+      for (int p0 = 0; p0 < x.parts; p0 += 4) {
+        if (p0 > 0) ask_parts(p0);
+        float m_new = M;
+#pragma unroll
+        for (int i = 0; i < 4; i++) m_new = fmaxf(m_new, rec[i][0]);
+        const float f = M == -INFINITY ? 0.f : exp_diff(M, m_new);
+        l *= f;
+        dn *= f;
+        M = m_new;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          const float w = rec[i][0] == -INFINITY || p0 + i >= x.parts ? 0.f : exp_diff(rec[i][0], M);
+          l = fmaf(w, rec[i][1], l);
+          dn = fmaf(w, rec[i][2], dn);
+        }
       }
       lse = M + logf(l);
       dsum = dn / l;
@@ -323,45 +345,60 @@ __global__ __launch_bounds__(256, 2) void bwd_f32_row_kernel(BwdArgs a, RowF32 x
     const bool diag = a.causal && c == cw, mine = tl.has(t_n, c);
     float bias = 0.f, db = 0.f;
     if (!diag && mine) bias = a.bias[(base + t_n) * a.t_all + tl.rank(t_n, c)];
-    for (int st = 0; st < nsub; st++) {
-      const int kpos0 = c * a.block + st * 16;
+    // SUB sub-tiles of 16 keys per round trip; more of them cost waves (at four, 190 registers: 16 heads x 2047 tokens 962 -> 997 us)
+    constexpr int SUB = D == 64 && !GRAD ? 2 : 1;
+    for (int st0 = 0; st0 < nsub; st0 += SUB) {
+      const int kpos0 = c * a.block + st0 * 16;
       if (kpos0 >= a.n_kv || (diag && kpos0 > tok0 + ntok - 1)) break;
-      f32x4 kf[C::NS], vf[C::NS], kr[1][4][C::NV];             // one round trip per sub-tile
-      load_row<D>(kb + (int64_t)min(kpos0 + n, a.n_kv - 1) * a.ks_t, hq, kf);
-      load_row<D>(vb + (int64_t)min(kpos0 + n, a.n_kv - 1) * a.vs_t, hq, vf);
+      f32x4 kf[SUB][C::NS], vf[SUB][C::NS], kr[SUB][4][C::NV], s[SUB], dp[SUB];
+#pragma unroll
+      for (int st = 0; st < SUB; st++) {
+        load_row<D>(kb + (int64_t)min(kpos0 + 16 * st + n, a.n_kv - 1) * a.ks_t, hq, kf[st]);
+        load_row<D>(vb + (int64_t)min(kpos0 + 16 * st + n, a.n_kv - 1) * a.vs_t, hq, vf[st]);
+      }
       if constexpr (GRAD) {
 #pragma unroll
-        for (int t = 0; t < 4; t++) load_row2<D>(kb + (int64_t)min(kpos0 + 4 * hq + t, a.n_kv - 1) * a.ks_t, n, kr[0][t]);
+        for (int st = 0; st < SUB; st++)
+#pragma unroll
+          for (int t = 0; t < 4; t++) load_row2<D>(kb + (int64_t)min(kpos0 + 16 * st + 4 * hq + t, a.n_kv - 1) * a.ks_t, n, kr[st][t]);
       }
       __builtin_amdgcn_sched_barrier(0);
-      f32x4 s = mma_dot<D>(kf, qf), dp = mma_dot<D>(vf, of);
+#pragma unroll
+      for (int st = 0; st < SUB; st++) { s[st] = mma_dot<D>(kf[st], qf); dp[st] = mma_dot<D>(vf[st], of); }
       const int lim = mine ? min(diag ? tok : 0x7fffffff, a.n_kv - 1) - kpos0 - 4 * hq : -1;   // as in the forward
       if constexpr (!GRAD) {
         float mx = m_run;
 #pragma unroll
-        for (int v = 0; v < 4; v++) {
-          s[v] = v > lim ? -INFINITY : fmaf(s[v], a.scale, bias);
-          mx = fmaxf(mx, s[v]);
-        }
+        for (int st = 0; st < SUB; st++)
+#pragma unroll
+          for (int v = 0; v < 4; v++) {
+            s[st][v] = 16 * st + v > lim ? -INFINITY : fmaf(s[st][v], a.scale, bias);
+            mx = fmaxf(mx, s[st][v]);
+          }
         const float m_use = mx == -INFINITY ? 0.f : mx;
         const float corr = exp_diff(m_run, m_use);
         m_run = mx;
-        float dn = 0.f;
+        float dn = 0.f, l = 0.f;
 #pragma unroll
-        for (int v = 0; v < 4; v++) {
-          s[v] = exp_diff(s[v], m_use);
-          dn = fmaf(s[v], v > lim ? 0.f : dp[v], dn);
+        for (int st = 0; st < SUB; st++) {
+#pragma unroll
+          for (int v = 0; v < 4; v++) {
+            s[st][v] = exp_diff(s[st][v], m_use);
+            dn = fmaf(s[st][v], 16 * st + v > lim ? 0.f : dp[st][v], dn);
+          }
+          l += (s[st][0] + s[st][1]) + (s[st][2] + s[st][3]);
         }
-        l_run = fmaf(l_run, corr, (s[0] + s[1]) + (s[2] + s[3]));
+        l_run = fmaf(l_run, corr, l);
         dn_run = fmaf(dn_run, corr, dn);
       } else {
 #pragma unroll
-        for (int t = 0; t < 4; t++) {
-          s[t] = t > lim ? 0.f : exp_diff(fmaf(s[t], a.scale, bias), lse) * (dp[t] - dsum);
-          db += s[t];
-        }
-        const f32x4 dz[1] = {s};
-        mma_outer_keys<D, 1>(kr, dz, lim, ntok, a.g_q, lane, dq);
+        for (int st = 0; st < SUB; st++)
+#pragma unroll
+          for (int t = 0; t < 4; t++) {
+            s[st][t] = 16 * st + t > lim ? 0.f : exp_diff(fmaf(s[st][t], a.scale, bias), lse) * (dp[st][t] - dsum);
+            db += s[st][t];
+          }
+        mma_outer_keys<D, SUB>(kr, s, lim, ntok, a.g_q, lane, dq);
       }
     }
     if constexpr (GRAD) {

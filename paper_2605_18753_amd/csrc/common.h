@@ -75,6 +75,21 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, OpMax()); }
 __device__ __forceinline__ float row16_sum(float v) { return row16_reduce(v, OpAdd()); }
 
+// over the four lanes n, n + 16, n + 32, n + 48
+__device__ __forceinline__ float quad_rows_max(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t w = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float quad_rows_sum(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t w = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
 // inclusive sum over the lanes up to one's own in six DPP additions: the same through the LDS crossbar stands
 // in front of the first tile of every workgroup of s2_attend_kernel (757 tokens, 32 / 8 heads of 64: 29.9 -> 28.6 us for the whole call)
 __device__ __forceinline__ int wave_scan(int v) {

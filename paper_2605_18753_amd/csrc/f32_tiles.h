@@ -130,13 +130,5 @@ template <int D> __device__ __forceinline__ void put_tile(float* tile, int n, in
       *reinterpret_cast<f32x4*>(tile + n * F32Cfg<D>::LD + 64 * nv + 16 * hq + 4 * v) = x;
     }
 }
-__device__ __forceinline__ float quad_rows_max(float x) {   // over the four lanes of a column n
-  x = fmaxf(x, __shfl_xor(x, 16));
-  return fmaxf(x, __shfl_xor(x, 32));
-}
-__device__ __forceinline__ float quad_rows_sum(float x) {
-  x += __shfl_xor(x, 16);
-  return x + __shfl_xor(x, 32);
-}
 
 }  // namespace dash

@@ -36,22 +36,6 @@ namespace dash {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// over the four lanes m + 16 kq of a row
-__device__ __forceinline__ float quarters_max(float v) {
-  const uint32_t u = __float_as_uint(v);
-  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  const uint32_t w = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
-  const auto b = __builtin_amdgcn_permlane16_swap(w, w, false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float quarters_sum(float v) {
-  const uint32_t u = __float_as_uint(v);
-  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  const uint32_t w = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
-  const auto b = __builtin_amdgcn_permlane16_swap(w, w, false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
 // Launches of fewer 128-row tiles times 64-key tiles of a row (half of them for a whole causal prompt) are not looked at: finding out
 // what the lists hold and the launch not used cost 7 us (4096 tokens, 32 / 8 heads, dense 160 -> 167 us; 16k tokens, 1.5 ms, less than
 // one run differs from the next; 8192 tokens of 16 heads, 66k of these, would gain 279 -> 189 us with 5 % of the chunks kept and lose 290 -> 301
@@ -306,13 +290,13 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
         for (int i = 0; i < 8; i += 2) x = fmaxf(fmaxf(x, s[j][i >> 2][i & 3]), s[j][i >> 2][(i & 3) + 1]);
         tmax[j] = fmaf(x, a.c1, bias[j]);
         // an item begins with its own maximum: with the rows' present one the result would depend on which wave was faster
-        if (FIRST) m_ref[j] = quarters_max(tmax[j]);
+        if (FIRST) m_ref[j] = quad_rows_max(tmax[j]);
         else raise |= tmax[j] > m_ref[j] + kLazy;
       }
       if (!FIRST && __builtin_expect(__any(raise), 0)) {
 #pragma unroll
         for (int j = 0; j < NT; j++) {
-          const float m_new = fmaxf(m_ref[j], quarters_max(tmax[j])), m_use = m_new == -INFINITY ? 0.f : m_new;
+          const float m_new = fmaxf(m_ref[j], quad_rows_max(tmax[j])), m_use = m_new == -INFINITY ? 0.f : m_new;
           const float corr = __builtin_amdgcn_exp2f(m_ref[j] - m_use);
           m_ref[j] = m_new;
           l[j] *= corr;
@@ -392,7 +376,7 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
     set_up(min(next, n_items - 1));            // behind the last item: that one again, not used
     if (item >= 0) {
 #pragma unroll
-      for (int j = 0; j < 2; j++) l[j] = quarters_sum(l[j]);
+      for (int j = 0; j < 2; j++) l[j] = quad_rows_sum(l[j]);
       // every token's earlier entries are in
       const int at_a = (tag_a & 0xff) / G, at_b = (tag_b & 0xff) / G;
       for (;;) {
