@@ -12,7 +12,7 @@
 // slot by slot (one MFMA each) with the vector work of the softmax behind the MFMAs of the next
 // product: the P of a step behind dP, its dS behind dV.
 // What bounds it: the LDS pipe (40 KB per 32 MFMAs and wave: 1.25 of what 128 B/clk feeds) and
-// the matrix pipe, two workgroups (two waves per SIMD) per CU.  Measured on the training-shaped
+// the matrix pipe, two workgroups (two waves per SIMD) per CU, three at d = 64.  Measured on the training-shaped
 // workload (4 x 16 heads x 8192 tokens): 3.85 ms with 64 keys per workgroup, both operands of S and dP
 // in LDS, one tile buffer and dkbar in the same kernel -> 2.43 ms + 0.17 ms for dkbar; 2 x 16 / 4 heads x
 // 3001 tokens, d 64 (192 key tiles, cut into parts): 375 -> 189 + 17 + 11 us.  Then, bwd_kv_kernel alone, both builds in
@@ -50,9 +50,11 @@ template <typename V> __device__ __forceinline__ V kbar_sum(const BwdArgs& a, co
 // TAIL: several heads and a last row tile that is not full.  The rows behind its last token are then copied as
 // zeros: the buffer resources reach over what lies between the heads (the padding of a larger buffer, another
 // head's rows), and 0 times what it holds could be a NaN.  In every launch the selection costs 0.5 % at d = 128
-// (three registers spilled; 8.04 against 8.00 ms, forward and backward of the shape above), nothing at d = 64.
+// (8.04 against 8.00 ms, forward and backward of the shape above), nothing at d = 64, where there is no other build.
+// At d = 64 three waves per SIMD (168 registers, operands read one step ahead instead of two; the build without the selection would spill
+// six): 2 x 16 / 4 heads x 3001 tokens 441 -> 408 us, forward and backward, 16 / 4 heads x 8000 1193 -> 1099, 8 heads x 4000 323 -> 309.
 template <int D, bool TAIL>
-__global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_kv_kernel(BwdArgs a) {
   using C = BCfg<D>;
   constexpr int RB = C::ROW_BYTES, HALF = 32 * RB, STAGE = 2 * HALF;   // a stage: 32 Q rows, 32 dO rows
   constexpr int KS = D / 16, NDT = C::NDT, RPI = 64 / C::NCH;         // RPI: rows per copy instruction of a wave
@@ -70,6 +72,7 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
   const int r = hbi % a.h_kv, b = hbi / a.h_kv;
   const int kpos0 = ktile * 128, my_key = kpos0 + wave * 32 + n;
   const int tokw = 32 / a.g_q;                      // tokens per 32-row tile
+  const int g_log = 31 - __builtin_clz(a.g_q);
   const int n_T = (a.n_q + tokw - 1) / tokw;
   const int T_first = a.causal ? kpos0 / tokw : 0;
   const int parts = kv_parts(n_T - T_first, a.kv_steps);
@@ -218,7 +221,7 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
     uint32_t a_b = a_rd, v_b = v_rd, tl = t_lo, th = t_hi;
     // opaque here, so that the per-slice offsets are formed next to their use
     asm volatile("" : "+v"(a_b), "+v"(v_b), "+v"(tl), "+v"(th));
-    constexpr int AH = 2;
+    constexpr int AH = D == 64 ? 1 : 2;
     f32x16 s, dp;
     bf16x8 qa[KS], oa[KS], va[KS];
 #pragma unroll
@@ -234,12 +237,14 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_kernel(BwdArgs a) {
     }
     // the key mask matters only where the rows' own chunk is this one, or at the end of the sequence
     if ((a.causal && tok0 + tokw > own0 && tok0 < own0 + a.block) || kpos0 + 128 > a.n_kv) {
+      int row0 = 4 * h;
+      // the rows' tokens are formed here: kept in 16 registers throughout they had the kernel spill (4 x 16 heads x 8192 tokens
+      // 7260 -> 7150 us, forward and backward)
+      asm volatile("" : "+v"(row0));
+      const int before = a.causal ? my_key - tok0 : -1;
 #pragma unroll
-      for (int j = 0; j < 16; j++) {
-        const int row = (j >> 2) * 8 + 4 * h + (j & 3);
-        const int pos = a.causal ? tok0 + row / a.g_q : 0x7fffffff;
-        s[j] = (my_key > pos || my_key >= a.n_kv) ? -INFINITY : s[j];
-      }
+      for (int j = 0; j < 16; j++)
+        s[j] = (before > (row0 + (j >> 2) * 8 + (j & 3)) >> g_log || my_key >= a.n_kv) ? -INFINITY : s[j];
     }
     u32x4 pp[2], pd[2];
     auto p_quad = [&](int q4) {                     // P of accumulator registers 4 q4 .. + 3, in place
@@ -463,7 +468,9 @@ template <int D> static hipError_t launch_t(const BwdArgs& a, hipStream_t st) {
     }
   }
   const bool tail = a.g_q > 1 && a.n_q % (32 / a.g_q) != 0;
-  if ((e = tail ? launch_kv<D, true>(a, st) : launch_kv<D, false>(a, st)) != hipSuccess) return e;
+  if constexpr (D == 64) e = launch_kv<D, true>(a, st);
+  else e = tail ? launch_kv<D, true>(a, st) : launch_kv<D, false>(a, st);
+  if (e != hipSuccess) return e;
   if (a.kv_max_parts > 1) {
     const int ktiles = (a.n_kv + 127) / 128;
     hipLaunchKernelGGL(bwd_kv_reduce_kernel<D>, dim3((unsigned)(ktiles * a.hb * (128 * (D / 4) / 256))), dim3(256), 0, st, a);
