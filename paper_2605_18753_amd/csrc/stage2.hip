@@ -84,8 +84,10 @@ constexpr int kMaxParts = 1536;    // records of a launch
 // PAIR: eight waves, two groups of four with a ring each, on the same 128 rows: the first walks the first half of the chunk list, the
 // second the other, and they add up through LDS.  For launches that leave every CU at most one workgroup (see s2_paired): a
 // lone wave per SIMD takes three times a tile's matrix time, so the longest list is what such a launch takes.
-template <int D, bool DENSE, bool PAIR>
-__global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a) {
+// WAVES: per SIMD.  At head dimension 64 three fit with operands of the first product read two steps ahead instead of four (168
+// registers; see launch_s2_t).
+template <int D, bool DENSE, bool PAIR, int WAVES = 2>
+__global__ __launch_bounds__(PAIR ? 512 : 256, WAVES) void s2_attend_kernel(S2Args a) {
   using C = S2Cfg<D>;
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
   // PAIR: waves 4 .. 7 are a second group with a ring of its own
@@ -310,7 +312,7 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, 2) void s2_attend_kernel(S2Args a
   auto iteration = [&](auto p_tag, int it, f32x16 (&s)[2], f32x16 (&so)[2]) __attribute__((always_inline)) {
     constexpr int P = decltype(p_tag)::value;
     constexpr int NS = D / 8;                                  // MFMAs per product and tile
-    constexpr int KAHEAD = 4, VAHEAD = 2;
+    constexpr int KAHEAD = WAVES == 3 ? 2 : 4, VAHEAD = 2;
     constexpr int EQ = 12, E0 = 2;                             // exponential pairs before the second product, and before the first MFMA
     const bool cur = it < n_it;
     const int t_cur = e_cur & 0xfff, t_next = e_next & 0xfff;
@@ -605,6 +607,13 @@ static hipError_t launch_s2_t(const S2Args& a, bool pair, hipStream_t st) {
   if (!DENSE && a.costs)
     if (hipError_t e = launch_s2_costs(a, D, st); e != hipSuccess) return e;
   auto kern = s2_attend_kernel<D, DENSE, false>;
+  // Head dimension 64: three workgroups per CU where there are more of them than that holds.  Stage 2 alone, two -> three: 16 / 4 heads x 8000
+  // tokens (1000 workgroups) 199 -> 172 us, 32 / 8 heads x 16k, queries correlated, 1305 -> 1190, x 32k 5004 -> 4707, 32 / 2 x 16k 1078 -> 970; with fewer
+  // the shorter read-ahead is a loss: 512 workgroups 73.5 -> 75.7 us, 528 41.2 -> 42.3, 752 53.7 -> 54.8.
+  if constexpr (D == 64) {
+    static_assert(C::LDS_BYTES <= 48 * 1024, "both kernels would need their own record of the opt-in");
+    if ((int64_t)a.n_tiles * a.hb * a.max_parts > 768) kern = s2_attend_kernel<D, DENSE, false, 3>;
+  }
   static LdsOptIn opt_in;
   if (hipError_t e = allow_dyn_lds((const void*)kern, C::LDS_BYTES, opt_in); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb, a.max_parts), dim3(256), C::LDS_BYTES, st, a);

@@ -428,13 +428,13 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
 // What kCostTiles tiles, spread over the launch, cost in either kernel; the sums decide for the launch (s2_gathered).  Tile by tile the launch would
 // take both kernels' longest lists one after the other (2000 tokens against a 32k cache 583 -> 817 us).  A workgroup takes one tile, a wave 32 of its
 // rows, as in s2_attend_kernel.  There, in units of 0.2 us of half a CU, a chunk that one of the tile's tokens kept costs the workgroup 4 and another 1 for
-// each wave that takes part; here an item of 64 keys costs 5.85 of them per workgroup of a whole CU (head dimension 64: 4.8 of its own, shorter unit), and
-// of 128 keys 3.9 (3.8) per 64.  An item holds up to 32 / g_q tokens of a chunk, and on average three tenths of the chunks have one that is
+// each wave that takes part; here an item of 64 keys costs 5.85 of them per workgroup of a whole CU (head dimension 64: 5.15 of its own, shorter unit), and
+// of 128 keys 3.9 (4.0) per 64.  An item holds up to 32 / g_q tokens of a chunk, and on average three tenths of the chunks have one that is
 // not full.  Fitted to both kernels' times over 94 launches (16k and 32k tokens and 2000 against a 32k cache, groups of 1 to 8, both head dimensions and chunk
 // sizes, 2 to 60 % of the chunks kept, queries independent and correlated): the choice takes 0.7 % more time than the faster kernel of each, and
 // none of them more than s2_attend_kernel.  32k tokens, there -> here: group of 4, 9 % kept 4.50 -> 3.07 ms, 26 % 6.72 -> 6.05 (not taken), 41 % 7.3 -> 8.5 (not
 // taken); 9 % with correlated queries 2.44 -> 2.65 (not taken); chunks of 128, 16 % 5.84 -> 3.27; group of 1, 3 % 5.42 -> 2.9, 8 % 7.48 -> 3.77; head
-// dimension 64, 9 % 3.27 -> 1.79.
+// dimension 64, 9 % 3.06 -> 1.79.
 __global__ __launch_bounds__(256) void s2_costs_kernel(S2Args a, float per_item) {
   __shared__ uint32_t all[64], own[4][64];
   __shared__ int sums[2];
@@ -478,7 +478,7 @@ __global__ __launch_bounds__(256) void s2_costs_kernel(S2Args a, float per_item)
 }
 
 hipError_t launch_s2_costs(const S2Args& a, int d, hipStream_t st) {
-  const float per_item = d == 128 ? (a.block == 64 ? 5.85f : 3.9f) : (a.block == 64 ? 4.8f : 3.8f);
+  const float per_item = d == 128 ? (a.block == 64 ? 5.85f : 3.9f) : (a.block == 64 ? 5.15f : 4.f);
   hipLaunchKernelGGL(s2_costs_kernel, dim3(kCostTiles), dim3(256), 0, st, a, per_item);
   return hipGetLastError();
 }

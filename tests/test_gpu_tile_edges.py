@@ -318,7 +318,8 @@ def test_attention_over_gathered_rows(name, h_q, h_kv, n_q, n_kv, d, block, caus
 
 
 @pytest.mark.parametrize("first,last", [(1.0, 4.0), (4.0, 1.0)])
-@pytest.mark.parametrize("name,batch,h_q,h_kv,n,d", [("two_groups", 1, 8, 8, 832, 128), ("two_groups_d64", 1, 16, 2, 832, 64), ("one_group", 33, 1, 1, 1000, 128)])
+@pytest.mark.parametrize("name,batch,h_q,h_kv,n,d", [("two_groups", 1, 8, 8, 832, 128), ("two_groups_d64", 1, 16, 2, 832, 64), ("one_group", 33, 1, 1, 1000, 128),
+                                                        ("three_per_cu", 103, 1, 1, 1000, 64), ("three_per_cu_g4", 26, 4, 1, 1001, 64)])
 def test_prefill_of_rising_and_falling_logits(name, batch, h_q, h_kv, n, d, first, last):
     w = Workload("edge_ramp_" + name, batch, h_q, h_kv, n, n, d, 64, seed=50, offset_sigma=0.3)
     q, k, v = make_inputs(w, DEV)
