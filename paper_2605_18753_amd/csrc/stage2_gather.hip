@@ -75,7 +75,7 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
   const int hbi = bid % a.hb;
   const int blk = (a.n_tiles + 1) / 2 - 1 - bid / a.hb;                   // longest rows first
   const int r = hbi % a.h_kv, b = hbi / a.h_kv;
-  // Workgroups of one dispatch round (256, one per CU) begin their walks together: the 32 of a die read the same head's chunks at the same
+  // Workgroups dispatched together (256, one per CU) begin their walks together: the 32 of a die read the same head's chunks at the same
   // time, out of its L2 (128k tokens in chunks of 128: L2 misses 62 % of the requests -> 5 %).
   int* arrived = reinterpret_cast<int*>(a.costs + kCostTiles) + (bid & 7) * 32;
   if (!s2_gathered(a.costs[lane])) return;
@@ -130,7 +130,7 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
   __syncthreads();
   const int n_items = lcum[wn * 32 - 1];
   if (tid == 0) {
-    // never more than about a twentieth of the walk's time: the others of the round may not get a CU for as long as this one runs
+    // never more than about a twentieth of the walk's time: the others may not get a CU for as long as this one runs
     const int all = (min((bid | 255) + 1, (int)gridDim.x) - (bid & 7) + 7) >> 3;
     for (int i = 0; i < n_items >> 5 && __hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all; i++)
       __builtin_amdgcn_s_sleep(16);
