@@ -450,14 +450,25 @@ __global__ __launch_bounds__(256) void s1_route_kernel(S1Args a) {
         }
       }
     } else {
-      for (int row = wave; row < ROWS; row += 4) {
-        const int tok = tok0 + row / a.g_q, head = r * a.g_q + row % a.g_q;
-        const float* src = a.scores + (((int64_t)b * a.h_q + head) * a.n_q + (tok < a.n_q ? tok : 0)) * a.t_c;
-        const bool ok = tok < a.tok_end;
+      // a wave's rows together: one after the other, each load waited for, took a round trip to memory per row (one head, 1024
+      // tokens, forward and backward: 77.6 -> 76.8 us)
+      const float* src[ROWS / 4];
+      bool ok[ROWS / 4];
+#pragma unroll
+      for (int i = 0; i < ROWS / 4; i++) {
+        const int row = wave + 4 * i, tok = tok0 + row / a.g_q, head = r * a.g_q + row % a.g_q;
+        ok[i] = tok < a.tok_end;
+        src[i] = a.scores + (((int64_t)b * a.h_q + head) * a.n_q + (tok < a.n_q ? tok : 0)) * a.t_c;
+      }
+      for (int c = lane; c < n_cand; c += 64) {
+        float x[ROWS / 4];
+#pragma unroll
+        for (int i = 0; i < ROWS / 4; i++) x[i] = ok[i] ? src[i][c] : 0.f;
         // padding rows are zero-filled only where the solver reads them (the 16-lane-row
         // solver takes four rows at a time; the wave-per-row solver stops at the first)
-        if (!ok && n_cand > 512) break;
-        for (int c = lane; c < n_cand; c += 64) S[row * a.ld + c] = ok ? src[c] : 0.f;
+#pragma unroll
+        for (int i = 0; i < ROWS / 4; i++)
+          if (ok[i] || n_cand <= 512) S[(wave + 4 * i) * a.ld + c] = x[i];
       }
     }
   }
