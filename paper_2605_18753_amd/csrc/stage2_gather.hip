@@ -23,8 +23,8 @@
 //
 // What bounds it: a wave's chain of loads, products and vector work, two waves per SIMD (256 registers; head dimension 64: three, 1.97 -> 1.79 ms
 // there).  128k tokens, 32 / 8 heads, chunks of 128, 12 % of them kept: 87 -> 40 ms for Stage 2 alone, vector pipe half and matrix pipe a fifth
-// busy, 19 TB/s out of L2.  Copies without one part: no loads but an item's first -18 %, no sums in LDS -10, no wait for a token's earlier entries -7,
-// no exponentials -2.
+// busy, 19 TB/s out of L2.  Copies without one part: no loads but an item's first -18 %, no sums in LDS -10, no wait for a token's earlier entries -7
+// (before tiles were added one by one), no exponentials -2.
 #include <type_traits>
 
 #include "common.h"
@@ -377,23 +377,25 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
     if (item >= 0) {
 #pragma unroll
       for (int j = 0; j < 2; j++) l[j] = quad_rows_sum(l[j]);
-      // every token's earlier entries are in
-      const int at_a = (tag_a & 0xff) / G, at_b = (tag_b & 0xff) / G;
-      for (;;) {
-        const int da = __hip_atomic_load(&ldone[at_a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        const int db = __hip_atomic_load(&ldone[at_b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (!__any((tag_a >= 0 && da != tag_a >> 8) || (tag_b >= 0 && db != tag_b >> 8))) break;
-        __builtin_amdgcn_s_sleep(1);
-      }
-      asm volatile("" ::: "memory");
-      const float ma = lm[tag_a & 0xff], la = ll[tag_a & 0xff], mb = lm[tag_b & 0xff], lb = ll[tag_b & 0xff];
-      __builtin_amdgcn_s_setprio(2);
-      add_up(std::integral_constant<int, 0>{}, tag_a, m_ref[0], l[0], ma, la);
-      add_up(std::integral_constant<int, 1>{}, tag_b, m_ref[1], l[1], mb, lb);
-      asm volatile("" ::: "memory");             // a wave's LDS operations complete in order
-      if (tag_a >= 0) __hip_atomic_store(&ldone[at_a], (tag_a >> 8) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      if (tag_b >= 0) __hip_atomic_store(&ldone[at_b], (tag_b >> 8) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      __builtin_amdgcn_s_setprio(0);
+      // A tile's sums are added once its tokens' earlier entries are in.  Tile by tile: waiting for both tiles' tokens first takes 3.06 against 2.99 ms at
+      // 32k tokens, group of 4, 9 % kept, one head with 8 % 3.77 / 3.66, head dimension 64 1.78 / 1.69; token by token 3.10, 3.77 and 1.76.
+      auto add = [&](auto j_tag, int tag_j) __attribute__((always_inline)) {
+        constexpr int j = decltype(j_tag)::value;
+        const int at = (tag_j & 0xff) / G;
+        for (;;) {
+          const int done = __hip_atomic_load(&ldone[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (!__any(tag_j >= 0 && done != tag_j >> 8)) break;
+          __builtin_amdgcn_s_sleep(1);
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_setprio(2);             // others wait for these sums
+        add_up(j_tag, tag_j, m_ref[j], l[j], lm[tag_j & 0xff], ll[tag_j & 0xff]);
+        asm volatile("" ::: "memory");             // a wave's LDS operations complete in order
+        if (tag_j >= 0) __hip_atomic_store(&ldone[at], (tag_j >> 8) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __builtin_amdgcn_s_setprio(0);
+      };
+      add(std::integral_constant<int, 0>{}, tag_a);
+      add(std::integral_constant<int, 1>{}, tag_b);
     }
     if (next >= n_items) break;
     turn(qf[0]);
@@ -432,9 +434,9 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
 // of 128 keys 3.9 (4.0) per 64.  An item holds up to 32 / g_q tokens of a chunk, and on average three tenths of the chunks have one that is
 // not full.  Fitted to both kernels' times over 94 launches (16k and 32k tokens and 2000 against a 32k cache, groups of 1 to 8, both head dimensions and chunk
 // sizes, 2 to 60 % of the chunks kept, queries independent and correlated): the choice takes 0.7 % more time than the faster kernel of each, and
-// none of them more than s2_attend_kernel.  32k tokens, there -> here: group of 4, 9 % kept 4.50 -> 3.07 ms, 26 % 6.72 -> 6.05 (not taken), 41 % 7.3 -> 8.5 (not
-// taken); 9 % with correlated queries 2.44 -> 2.65 (not taken); chunks of 128, 16 % 5.84 -> 3.27; group of 1, 3 % 5.42 -> 2.9, 8 % 7.48 -> 3.77; head
-// dimension 64, 9 % 3.06 -> 1.79.
+// none of them more than s2_attend_kernel.  32k tokens, there -> here: group of 4, 9 % kept 4.50 -> 3.00 ms, 26 % 6.72 -> 6.05 (not taken), 41 % 7.3 -> 8.5 (not
+// taken); 9 % with correlated queries 2.44 -> 2.65 (not taken); chunks of 128, 16 % 5.84 -> 3.26; group of 1, 3 % 5.42 -> 2.9, 8 % 7.48 -> 3.66; head
+// dimension 64, 9 % 3.06 -> 1.69.
 __global__ __launch_bounds__(256) void s2_costs_kernel(S2Args a, float per_item) {
   __shared__ uint32_t all[64], own[4][64];
   __shared__ int sums[2];
