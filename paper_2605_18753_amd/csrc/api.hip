@@ -177,7 +177,7 @@ static int run_stage2(const dash_params* p, const Layout& L, const void* q, cons
   if (p->dtype == DASH_F32) e = launch_s2_f32(*p, L, q, k, v, o, m, bb, dense, st);
   else if (p->n_q == 1)
     e = launch_decode_s2(*p, L, q, k, v, o, m, bb, ws, dense, st);
-  else e = launch_s2_mfma(*p, L, q, k, v, o, m, bb, ws + L.off_s2_part, ws + L.off_ksplit, dense, st);
+  else e = launch_s2_mfma(*p, L, q, k, v, o, m, bb, ws + L.off_s2_part, dense, st);
   return e == hipSuccess ? DASH_OK : DASH_ELAUNCH;
 }
 

@@ -77,7 +77,7 @@ hipError_t launch_s1_decode(const dash_params& p, const Layout& L, const void* q
                             const S1Out& out, const void* k_upd, float* kbar_upd, hipStream_t st);
 hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, const void* k,
                           const void* v, void* o, const uint32_t* mask, const float* bias,
-                          char* part_ws, void* costs, bool dense, hipStream_t st);   // part_ws: s2_part_room() bytes; costs: 1536
+                          char* part_ws, bool dense, hipStream_t st);   // part_ws: s2_part_room() bytes
 int s2_parts(const dash_params& p, const Layout& L);
 size_t s2_part_room(const dash_params& p, const Layout& L);
 hipError_t launch_s2_f32(const dash_params& p, const Layout& L, const void* q, const void* k,

@@ -692,7 +692,7 @@ size_t s2_part_room(const dash_params& p, const Layout& L) {
 
 hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, const void* k,
                           const void* v, void* o, const uint32_t* mask, const float* bias,
-                          char* part_ws, void* costs, bool dense, hipStream_t st) {
+                          char* part_ws, bool dense, hipStream_t st) {
   S2Args a;
   fill_s2_args(a, p, L, q, k, v, o, mask, bias);
   a.n_tiles = s2_tiles(p, L);
@@ -703,7 +703,9 @@ hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, 
     a.part_o = a.part_ml + (size_t)a.n_tiles * a.hb * a.max_parts * 128 * 2;
   }
   const bool pair = a.max_parts == 1 && s2_paired((int64_t)a.n_tiles * a.hb, (float)(L.t_all * (p.block_size >> 6)));
-  if (!dense && !pair && a.max_parts == 1 && s2_may_gather(a, p.head_dim)) a.costs = reinterpret_cast<S2Costs*>(costs);
+  // The costs lie where a launch that is cut has its parts' records: 4 KB at least from 64 chunks on (s2_part_room), and no other call of
+  // the same workspace has anything there that it reads later.
+  if (!dense && !pair && a.max_parts == 1 && s2_may_gather(a, p.head_dim)) a.costs = reinterpret_cast<S2Costs*>(part_ws);
   if (p.head_dim == 128) return dense ? launch_s2_t<128, true>(a, pair, st) : launch_s2_t<128, false>(a, pair, st);
   return dense ? launch_s2_t<64, true>(a, pair, st) : launch_s2_t<64, false>(a, pair, st);
 }
