@@ -210,8 +210,6 @@ def check_dense_uncut(w, p, q, k, v):
             assert (o[b, h].double().cpu() - ref).abs().max() <= 2e-2 * ref.abs().max()   # the bar of the cut lists' test
 
 
-# logits that rise or fall by a factor of four along the keys: a late raise of the running maximum, and two groups of waves
-# whose maxima lie far apart, either way round
 @pytest.mark.parametrize("h_q,n_q,chunks,d,block", [(4, 64, 33, 128, 64), (4, 64, 2048, 64, 64), (2, 130, 2048, 64, 128), (16, 40, 64, 64, 64)])
 def test_attention_over_lists_at_word_edges(h_q, n_q, chunks, d, block):
     """Lists whose chunks lie at the edges of mask bytes and words, up to the longest sequence (4096
@@ -320,6 +318,8 @@ def test_attention_over_gathered_rows(name, h_q, h_kv, n_q, n_kv, d, block, caus
     assert worst <= 2e-2, worst
 
 
+# logits that rise or fall by a factor of four along the keys: a late raise of the running maximum, and two groups of waves
+# whose maxima lie far apart, either way round; launches of three workgroups per CU
 @pytest.mark.parametrize("first,last", [(1.0, 4.0), (4.0, 1.0)])
 @pytest.mark.parametrize("name,batch,h_q,h_kv,n,d", [("two_groups", 1, 8, 8, 832, 128), ("two_groups_d64", 1, 16, 2, 832, 64), ("one_group", 33, 1, 1, 1000, 128),
                                                         ("three_per_cu", 103, 1, 1, 1000, 64), ("three_per_cu_g4", 26, 4, 1, 1001, 64)])
