@@ -50,6 +50,7 @@
 #include "dash_internal.h"
 #include "lds_copy.h"
 #include "stage2_args.h"
+#include "tile_walk.h"
 
 namespace dash {
 
@@ -185,10 +186,10 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, WAVES) void s2_attend_kernel(S2Ar
   int n_parts = 1, first = 0, mine = n_chunks;   // chunks before the part, chunks of the part
   int last_it = n_chunks << sub_log;             // iterations 0 .. last_it: one more than tiles; PAIR: those of the longer half
   if constexpr (PAIR) {
-    const int per = (n_chunks + 1) >> 1;
-    first = grp * per;
-    mine = grp == 0 ? per : n_chunks - per;
-    last_it = per << sub_log;
+    const ListPart half = list_half(n_chunks, grp, sub_log);
+    first = half.first;
+    mine = half.chunks;
+    last_it = half.last_it;
   } else if (a.max_parts > 1) {
     const int per = max((n_chunks + a.max_parts - 1) / a.max_parts, kMinPartTiles >> sub_log);
     n_parts = max((n_chunks + per - 1) / per, 1);
@@ -200,9 +201,12 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, WAVES) void s2_attend_kernel(S2Ar
   }
   const int n_it = mine << sub_log;              // the part's tiles
   list += first << sub_log;
-  auto entry = [&](int i) -> int { return list[max(min(i, n_it - 1), 0)]; };   // behind the last tile: that one again
+  auto entry = [&](int i) -> int {               // 0 where there is none
+    const int at = walk_index(i, n_it);
+    const int e = list[max(at, 0)];
+    return at < 0 ? 0 : e;
+  };
   int e_cur = __builtin_amdgcn_readfirstlane(entry(0)), e_next = __builtin_amdgcn_readfirstlane(entry(1)), e_ahead = 0;
-  if (n_it == 0) e_cur = e_next = 0;             // no list: whatever lies there
   if (!DENSE) {
     const int u0 = (e_cur & 0xfff) >> sub_log;
     if (first > 0 && n_it > 0 && row_ok) {       // the token's entries before the part's first chunk

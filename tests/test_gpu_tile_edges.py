@@ -318,6 +318,27 @@ def test_attention_over_gathered_rows(name, h_q, h_kv, n_q, n_kv, d, block, caus
     assert worst <= 2e-2, worst
 
 
+@pytest.mark.parametrize("h,n,d,block", [(8, 832, 128, 64), (2, 512, 64, 64), (4, 896, 64, 128)])
+def test_attention_of_tiles_that_keep_one_chunk(h, n, d, block):
+    """Two groups of waves over lists of a single chunk: the second group's half is empty.  Reference in fp32."""
+    w = Workload("edge_one_chunk", 1, h, h, n, n, d, block, causal=False, seed=55)
+    q, k, v = make_inputs(w, DEV)
+    o = torch.full_like(q, float("nan"))
+    p = B.make_params(q, k, v, o, block, causal=False)
+    chunk = (torch.arange(n, device=DEV) // 128 * 5 + 3) % (n // block)          # one of every 128 rows
+    words = B.mask_words(p)
+    mask = torch.zeros((1, h, n, words), dtype=torch.int64, device=DEV)
+    mask[:, :, torch.arange(n, device=DEV), chunk // 32] = 1 << (chunk % 32)
+    bias = torch.randn((1, h, n, B.list_stride(p)), device=DEV)
+    B.dash_stage2_attend(p, q, k, v, o, B.Lists(mask=mask.to(torch.int32), bias=bias), B.alloc_workspace(p, DEV))
+    key = chunk[:, None] * block + torch.arange(block, device=DEV)
+    z = (q[0].float()[:, :, None] * k[0].float()[:, key]).sum(-1) / d ** 0.5
+    ref = (torch.softmax(z, -1)[..., None] * v[0].float()[:, key]).sum(2)
+    err = ((o[0].float() - ref).abs().amax(-1) / ref.abs().amax()).max().item()
+    print(f"[parity] tiles of one chunk {h} x {n}: {err:.2e}")
+    assert err <= 2e-2, err
+
+
 # logits that rise or fall by a factor of four along the keys: a late raise of the running maximum, and two groups of waves
 # whose maxima lie far apart, either way round; launches of three workgroups per CU
 @pytest.mark.parametrize("first,last", [(1.0, 4.0), (4.0, 1.0)])

@@ -3,6 +3,7 @@ declares, sizes its workspace, and rejects bad arguments before touching a GPU."
 import ctypes
 import os
 import re
+import shutil
 import struct
 import subprocess
 from concurrent.futures import ThreadPoolExecutor
@@ -258,6 +259,53 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+WALK = r"""
+#include <cstdio>
+#include <vector>
+#include "tile_walk.h"
+using namespace dash;
+// As s2_attend_kernel with two groups of waves: a list of n chunks behind which lies whatever was there, and the mask words
+// that the iterations of either group ask for.
+int main() {
+  int bad = 0;
+  for (int n = 0; n <= 40; n++)
+    for (int sub_log = 0; sub_log < 2; sub_log++)
+      for (int grp = 0; grp < 2; grp++) {
+        std::vector<int> list(4096, 0xffff);
+        for (int i = 0; i < n << sub_log; i++) list[i] = i;               // the first n chunks, in (n + 31) / 32 mask words
+        const ListPart part = list_half(n, grp, sub_log);
+        const int n_it = part.chunks << sub_log, words = n > 32 ? 2 : 1;
+        auto entry = [&](int i) {
+          const int at = walk_index(i, n_it);
+          return at < 0 ? 0 : list[(part.first << sub_log) + at];
+        };
+        int cur = entry(0), next = entry(1), tiles = 0;
+        if (part.last_it > 0)
+          for (int it = 0; it <= part.last_it; it++) {
+            const int u = (cur & 0xfff) >> sub_log, un = (next & 0xfff) >> sub_log;
+            if (u >> 5 >= words || un >> 5 >= words) { bad++; std::printf("n %d grp %d it %d: word %d\n", n, grp, it, un >> 5); }
+            if (it < n_it && (cur & 0xfff) == (part.first << sub_log) + it) tiles++;
+            cur = next;
+            next = entry(it + 2);
+          }
+        if (tiles != n_it) { bad++; std::printf("n %d grp %d: %d tiles of %d\n", n, grp, tiles, n_it); }
+      }
+  return bad != 0;
+}
+"""
+
+
+@pytest.mark.skipif(not shutil.which("g++"), reason="no host compiler")
+def test_two_groups_read_mask_words_of_their_rows_only(tmp_path):
+    """A list of one chunk leaves the second group none; its iterations must not take what lies behind the list for an entry:
+    the mask word of such an entry was read up to 127 words past a row."""
+    (tmp_path / "walk.cpp").write_text(WALK)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_18753_amd", "csrc"), str(tmp_path / "walk.cpp"), "-o",
+                    str(tmp_path / "walk")], check=True, timeout=120)
+    r = subprocess.run([str(tmp_path / "walk")], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout
 
 
 def code_objects(path):
