@@ -19,9 +19,12 @@
  *     NULL = the default stream).  Nothing a call computes depends on an earlier
  *     call: what the library remembers is, per device, that a kernel's
  *     one-time opt-in to a large dynamic LDS size has been made (thread-safe) and the
- *     address of the scratch array of dash_attn_decode_static, and, per process, a counter
- *     that gives the split flags of every decode step a number of their own.
- *     Entry points may be called from several threads.
+ *     addresses of two arrays of its own (the scratch of dash_attn_decode_static; the records, 96 KB, in
+ *     which large bf16 prefills choose between two Stage-2 kernels on the device, any number of them at once),
+ *     and, per process, two counters that give the split flags of a decode step and such a choice numbers of their own.
+ *     Entry points may be called from several threads.  A workspace belongs to one call at a time: calls that are in
+ *     flight together (several streams) need one each, or must not use it.  dash_stage2_attend of a bf16 prefill uses
+ *     it for lists that are not given, and for parts where few rows meet a long cache.
  *   - Tensors are [batch, head, token, head_dim] with head_dim contiguous; the
  *     other three strides are given in ELEMENTS in dash_params.  Rows must be
  *     16-byte aligned (base pointers 16-byte aligned, strides multiples of 8

@@ -40,8 +40,9 @@ int make_layout(const dash_params* p, Layout* L, bool routing = true);
 // it is launched with.  The opt-in is a property of the loaded kernel on that device, not a
 // stream operation, so it is made when a launch first needs that much there and the size
 // granted is recorded (per device ordinal; two threads that race both make the call, and
-// the larger size wins).  Besides it, the address of the static scratch (api.hip) and the counter of the
-// split flags' numbers (stage2_decode.hip), nothing in the library outlives a call.
+// the larger size wins).  Besides it, the address of the static scratch (api.hip), the counter of the
+// split flags' numbers (stage2_decode.hip) and the records in which large prefills choose a kernel (stage2_gather.hip), nothing in the
+// library outlives a call.
 struct LdsOptIn { std::atomic<uint32_t> granted[64] = {}; };
 inline hipError_t allow_dyn_lds(const void* kern, size_t bytes, LdsOptIn& rec) {
   if (bytes <= 48 * 1024) return hipSuccess;

@@ -149,12 +149,14 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, WAVES) void s2_attend_kernel(S2Ar
     trk_next = ask_bias(row_ok ? trk_at + ahead : ~3u);
   }
 
-  S2Costs costs;
-  if constexpr (!DENSE && !PAIR) {
-    if (a.costs) costs = a.costs[lane];
-  }
   for (int i = tid; i < 5 * 64; i += 256) wgmask[i] = 0u;
+  if constexpr (!DENSE && !PAIR) {
+    if (a.choice && wave == 0) list[0] = s2_choice(a, lane) > 0;   // one wave asks: what the record says may change between two looks
+  }
   __syncthreads();
+  if constexpr (!DENSE && !PAIR) {
+    if (a.choice && __builtin_amdgcn_readfirstlane((int)list[0])) return;   // left to s2_gather_kernel
+  }
   if (DENSE) {
     // every chunk up to the wave's own (causal) / every chunk (non-causal)
     const int last = a.causal ? cw : a.t_all - 1;
@@ -170,9 +172,6 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, WAVES) void s2_attend_kernel(S2Ar
     if (wave_ok && grp == 0)
       or_mask_rows(a.mask + (((int64_t)b * a.h_kv + r) * a.n_q + tok_w0) * a.words, min(tokw, a.n_q - tok_w0) * a.words,
                    a.words, wvmask + wave * 64, wgmask, lane);
-  }
-  if constexpr (!DENSE && !PAIR) {
-    if (a.costs && s2_gathered(costs)) return;   // every wave finds the same
   }
   __syncthreads();
 
@@ -608,7 +607,7 @@ static hipError_t launch_s2_t(const S2Args& a, bool pair, hipStream_t st) {
     hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb), dim3(512), lds, st, a);
     return hipGetLastError();
   }
-  if (!DENSE && a.costs)
+  if (!DENSE && a.choice)
     if (hipError_t e = launch_s2_costs(a, D, st); e != hipSuccess) return e;
   auto kern = s2_attend_kernel<D, DENSE, false>;
   // Head dimension 64: three workgroups per CU where there are more of them than that holds.  Stage 2 alone, two -> three: 16 / 4 heads x 8000
@@ -622,7 +621,7 @@ static hipError_t launch_s2_t(const S2Args& a, bool pair, hipStream_t st) {
   if (hipError_t e = allow_dyn_lds((const void*)kern, C::LDS_BYTES, opt_in); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(a.n_tiles * a.hb, a.max_parts), dim3(256), C::LDS_BYTES, st, a);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess && !DENSE && a.costs) e = launch_s2_gather(a, D, st);
+  if (e == hipSuccess && !DENSE && a.choice) e = launch_s2_gather(a, D, st);
   if (e != hipSuccess || a.max_parts == 1) return e;
   hipLaunchKernelGGL(s2_merge_kernel<D>, dim3(a.n_tiles * a.hb * 8), dim3(256), 0, st, a);
   return hipGetLastError();
@@ -707,9 +706,7 @@ hipError_t launch_s2_mfma(const dash_params& p, const Layout& L, const void* q, 
     a.part_o = a.part_ml + (size_t)a.n_tiles * a.hb * a.max_parts * 128 * 2;
   }
   const bool pair = a.max_parts == 1 && s2_paired((int64_t)a.n_tiles * a.hb, (float)(L.t_all * (p.block_size >> 6)));
-  // The costs lie where a launch that is cut has its parts' records: 4 KB at least from 64 chunks on (s2_part_room), and no other call of
-  // the same workspace has anything there that it reads later.
-  if (!dense && !pair && a.max_parts == 1 && s2_may_gather(a, p.head_dim)) a.costs = reinterpret_cast<S2Costs*>(part_ws);
+  if (!dense && !pair && a.max_parts == 1 && s2_may_gather(a, p.head_dim)) s2_take_choice(a);
   if (p.head_dim == 128) return dense ? launch_s2_t<128, true>(a, pair, st) : launch_s2_t<128, false>(a, pair, st);
   return dense ? launch_s2_t<64, true>(a, pair, st) : launch_s2_t<64, false>(a, pair, st);
 }

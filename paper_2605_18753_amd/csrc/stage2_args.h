@@ -6,9 +6,16 @@
 
 namespace dash {
 
-// Estimated costs of a tile of 128 rows: of its chunks in s2_attend_kernel, of its items in s2_gather_kernel
-struct S2Costs { float attend, gather; };
+// What a launch that s2_attend_kernel or s2_gather_kernel may take knows of its lists.  The records lie in the library, not in the caller's
+// workspace, into which such a launch writes nothing, and are dealt out in turn (kChoices of them).  Of kCostTiles tiles: the number of the
+// call (high word) and what the tile is estimated to cost in s2_gather_kernel beyond s2_attend_kernel (fp32, low word), in one store.  A record
+// that also serves another call in flight shows that call's number sooner or later, and never this call's again: then either kernel attends,
+// the second over the first.  They leave tiles out only where the whole record is their own, and then both find the same sum.
 constexpr int kCostTiles = 64;
+struct S2Choice {
+  uint64_t costs[kCostTiles];
+  int arrived[8 * 32];        // workgroups of s2_gather_kernel that began, by die
+};
 
 struct S2Args {
   const uint16_t* q; const uint16_t* k; const uint16_t* v; uint16_t* o;
@@ -19,7 +26,7 @@ struct S2Args {
   float* part;   // decode partials
   // prefill: parts of a workgroup's chunk list (1: not cut), their records and how many each tile has
   int max_parts; float* part_o; float* part_ml; int32_t* part_cnt;
-  S2Costs* costs;   // prefill: both kernels' estimated costs of kCostTiles tiles, and the counters behind them; null: s2_attend_kernel
+  S2Choice* choice; uint32_t call;   // prefill: the launch's record and the call's number in it; null: s2_attend_kernel
   const int32_t* seq_lens;   // decode: per-sequence cache lengths (device, [batch]) or null
 };
 
@@ -28,7 +35,7 @@ constexpr float kLazy = 8.f;   // lazy-rescale slack, in base-2 logit units
 inline void fill_s2_args(S2Args& a, const dash_params& p, const Layout& L, const void* q, const void* k,
                          const void* v, void* o, const uint32_t* mask, const float* bias) {
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.o = (uint16_t*)o;
-  a.mask = mask; a.bias = bias; a.part = nullptr; a.max_parts = 1; a.part_o = a.part_ml = nullptr; a.part_cnt = nullptr; a.costs = nullptr; a.seq_lens = L.seq_lens;
+  a.mask = mask; a.bias = bias; a.part = nullptr; a.max_parts = 1; a.part_o = a.part_ml = nullptr; a.part_cnt = nullptr; a.choice = nullptr; a.call = 0; a.seq_lens = L.seq_lens;
   a.h_q = p.h_q; a.h_kv = p.h_kv; a.g_q = L.g_q; a.n_q = p.n_q; a.n_kv = p.n_kv;
   a.block = p.block_size; a.t_all = L.t_all; a.words = L.words; a.pos0 = L.pos0;
   a.causal = p.causal;
@@ -43,14 +50,16 @@ inline void fill_s2_args(S2Args& a, const dash_params& p, const Layout& L, const
 
 // the kernel that gathers rows (stage2_gather.hip)
 bool s2_may_gather(const S2Args& a, int d);
+void s2_take_choice(S2Args& a);
 hipError_t launch_s2_costs(const S2Args& a, int d, hipStream_t st);
 hipError_t launch_s2_gather(const S2Args& a, int d, hipStream_t st);
 
-// Whether a launch's tiles are left to s2_gather_kernel; lane i brings the costs of tile i of the kCostTiles.
-__device__ __forceinline__ bool s2_gathered(S2Costs c) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) { c.attend += __shfl_xor(c.attend, o); c.gather += __shfl_xor(c.gather, o); }
-  return __builtin_amdgcn_readfirstlane(c.gather < c.attend);
+// One wave: what the record says, s2_attend_kernel (< 0), s2_gather_kernel (> 0), or nothing to this call (0).
+__device__ __forceinline__ int s2_choice(const S2Args& a, int lane) {
+  const uint64_t x = __hip_atomic_load(&a.choice->costs[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const bool own = __all((uint32_t)(x >> 32) == a.call);
+  const float more = wave_sum(__uint_as_float((uint32_t)x));
+  return __builtin_amdgcn_readfirstlane(!own ? 0 : more < 0.f ? 1 : -1);
 }
 
 }  // namespace dash

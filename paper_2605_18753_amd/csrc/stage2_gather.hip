@@ -66,7 +66,7 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
   uint32_t* lmask = reinterpret_cast<uint32_t*>(ll + C::ROWS);            // [words][TOKP] mask words
   uint16_t* lpre = reinterpret_cast<uint16_t*>(lmask + a.words * TOKP);   // [words][TOKP] list entries before the word
   uint16_t* lcum = reinterpret_cast<uint16_t*>(lmask + a.words * TOKP + (a.words * TOKP + 1) / 2);   // [words * 32] items up to and with the chunk
-  int* ctl = reinterpret_cast<int*>(lcum + a.words * 32);                 // next item
+  int* ctl = reinterpret_cast<int*>(lcum + a.words * 32);                 // next item, choice
   int* ldone = ctl + 4;                                                   // [TOK] list entries of a token that are in
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -77,8 +77,13 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
   const int r = hbi % a.h_kv, b = hbi / a.h_kv;
   // Workgroups dispatched together (256, one per CU) begin their walks together: the 32 of a die read the same head's chunks at the same
   // time, out of its L2 (128k tokens in chunks of 128: L2 misses 62 % of the requests -> 5 %).
-  int* arrived = reinterpret_cast<int*>(a.costs + kCostTiles) + (bid & 7) * 32;
-  if (!s2_gathered(a.costs[lane])) return;
+  int* arrived = a.choice->arrived + (bid & 7) * 32;
+  if (wave == 0) {                                                        // one wave asks: what the record says may change between two looks
+    const int c = s2_choice(a, lane);
+    if (lane == 0) ctl[1] = c;
+  }
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(ctl[1]) < 0) return;                 // s2_attend_kernel has attended
   if (tid == 0) __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int tok0 = blk * TOK;
   const int n_tok = min(TOK, a.n_q - tok0);
@@ -92,7 +97,8 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
   }
   for (int i = tid; i < C::ROWS * D / 4; i += C::WAVES * 64) lo[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (tid < 256) { lm[tid] = -INFINITY; ll[tid] = 0.f; }
-  if (tid < 4 + TOK) ctl[tid] = 0;
+  if (tid == 0) ctl[0] = 0;
+  if (tid < TOK) ldone[tid] = 0;
   __syncthreads();
   for (int w = wave; w < wn; w += C::WAVES) {
     uint32_t v[NW];
@@ -427,7 +433,7 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
   }
 }
 
-// What kCostTiles tiles, spread over the launch, cost in either kernel; the sums decide for the launch (s2_gathered).  Tile by tile the launch would
+// What kCostTiles tiles, spread over the launch, cost in either kernel; the sum decides for the launch (s2_choice).  Tile by tile the launch would
 // take both kernels' longest lists one after the other (2000 tokens against a 32k cache 583 -> 817 us).  A workgroup takes one tile, a wave 32 of its
 // rows, as in s2_attend_kernel.  There, in units of 0.2 us of half a CU, a chunk that one of the tile's tokens kept costs the workgroup 4 and another 1 for
 // each wave that takes part; here an item of 64 keys costs 5.85 of them per workgroup of a whole CU (head dimension 64: 5.15 of its own, shorter unit), and
@@ -448,7 +454,7 @@ __global__ __launch_bounds__(256) void s2_costs_kernel(S2Args a, float per_item)
   for (int i = tid; i < 256; i += 256) own[i >> 6][i & 63] = 0u;
   if (tid < 64) all[tid] = 0u;
   if (tid < 2) sums[tid] = 0;
-  if (blockIdx.x == 0) reinterpret_cast<int*>(a.costs + kCostTiles)[tid] = 0;   // where s2_gather_kernel counts arrivals
+  if (blockIdx.x == 0) a.choice->arrived[tid] = 0;
   __syncthreads();
   const int words = min(tokw, a.n_q - tok0) * a.words;
   const uint32_t* rows = a.mask + (pair * a.n_q + tok0) * a.words;
@@ -476,7 +482,30 @@ __global__ __launch_bounds__(256) void s2_costs_kernel(S2Args a, float per_item)
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) chunks += __shfl_xor(chunks, o);
   const float items = (float)sums[0] * (float)a.g_q * (1.f / 32.f) + 0.3f * (float)chunks;
-  if (lane == 0) a.costs[blockIdx.x] = S2Costs{4.f * (float)chunks + (float)sums[1], per_item * items};
+  const float more = per_item * items - (4.f * (float)chunks + (float)sums[1]);
+  if (lane == 0)
+    __hip_atomic_store(&a.choice->costs[blockIdx.x], (uint64_t)a.call << 32 | __float_as_uint(more), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// 64 records: that many calls in flight on a GPU have one each.
+constexpr int kChoices = 64;
+static __device__ S2Choice choices[kChoices];
+static std::atomic<void*> g_choices[64];          // their address, per device ordinal; nullptr = not asked for yet
+static std::atomic<uint32_t> g_calls;
+
+void s2_take_choice(S2Args& a) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return;
+  void* at = g_choices[dev].load(std::memory_order_acquire);
+  if (!at) {
+    if (hipGetSymbolAddress(&at, HIP_SYMBOL(choices)) != hipSuccess || !at) {
+      (void)hipGetLastError();                    // the launch goes to s2_attend_kernel
+      return;
+    }
+    g_choices[dev].store(at, std::memory_order_release);
+  }
+  do a.call = g_calls.fetch_add(1, std::memory_order_relaxed) + 1; while (a.call == 0);   // 0: a record that no call had yet
+  a.choice = static_cast<S2Choice*>(at) + a.call % kChoices;
 }
 
 hipError_t launch_s2_costs(const S2Args& a, int d, hipStream_t st) {

@@ -246,6 +246,43 @@ def test_attention_over_lists_at_word_edges(h_q, n_q, chunks, d, block):
     assert err <= 2e-2, err
 
 
+def random_lists(p, n_q, n_kv, block, causal, sparsity, seed):
+    """Lists of chunks kept at random, with a token of every chunk and a chunk of every token of a stretch."""
+    t_all, words = B.list_stride(p), B.mask_words(p)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    c = torch.arange(words * 32, device=DEV)
+    keep = torch.rand((p.batch, p.h_kv, n_q, words * 32), generator=gen, device=DEV) >= sparsity
+    keep[:, :, n_q // 2 + 5] = True
+    keep[:, :, n_q // 3: n_q // 3 + 300, 7] = True
+    own = ((n_kv - n_q + torch.arange(n_q, device=DEV)) // block).view(1, n_q, 1)
+    keep = (keep & (c < own)) | (c == own) if causal else keep & (c < t_all)
+    mask = torch.zeros((p.batch, p.h_kv, n_q, words), dtype=torch.int64, device=DEV)
+    for i in range(32):
+        mask |= keep.view(p.batch, p.h_kv, n_q, words, 32)[..., i].to(torch.int64) << i
+    mask = torch.where(mask >= 1 << 31, mask - (1 << 32), mask).to(torch.int32)
+    return B.Lists(mask=mask, bias=torch.randn((p.batch, p.h_kv, n_q, t_all), generator=gen, device=DEV)), keep
+
+
+def gathers_rows(p, q, k, v, o, keep, r, lists, expected):
+    """Which of the two kernels takes the launch whose output is o.  In the one that walks the union of a wave's tokens an infinity in a value
+    reaches all rows of the wave (0 times infinity is a NaN); the one that gathers rows has it reach the tokens that kept the chunk.
+    keep: tokens x chunks of kv-head r of the first sequence."""
+    chunk = int(keep[:, :keep.shape[1] // 2].sum(0).argmax()) if expected else keep.shape[1] // 8
+    other = ~keep[:, chunk]
+    assert bool(other.any()) and bool(keep[:, chunk].any())
+    g = q.shape[1] // v.shape[1]
+    got = torch.empty_like(o)
+    for t in ("k", "v"):
+        kk, vv = k.clone(), v.clone()
+        (kk if t == "k" else vv)[0, r, chunk * p.block_size + 5] = float("nan" if t == "k" else "inf")
+        B.dash_stage2_attend(p, q, kk, vv, got, lists, B.alloc_workspace(p, DEV))
+        far, was = got[0, r * g:(r + 1) * g][:, other], o[0, r * g:(r + 1) * g][:, other]
+        assert bool(torch.isfinite(was.float()).all())
+        same = torch.equal(far, was)
+        assert same == expected, (t, chunk)
+
+
 GATHERED = [
     # name, h_q, h_kv, n_q, n_kv, d, block, causal, sparsity, interleaved: at least 320000 tiles of 128 rows x 64 keys
     ("g4_odd_tail", 32, 8, 2000, 44240, 128, 64, True, 0.97, False),
@@ -271,30 +308,16 @@ def test_attention_over_gathered_rows(name, h_q, h_kv, n_q, n_kv, d, block, caus
         q, k, v = (x.transpose(1, 2).contiguous().transpose(1, 2) for x in (q, k, v))
     o = torch.full_like(q, float("nan"))
     p = B.make_params(q, k, v, o, block, causal=causal)
-    t_all, words = B.list_stride(p), B.mask_words(p)
-    gen = torch.Generator(device=DEV)
-    gen.manual_seed(58)
-    c = torch.arange(words * 32, device=DEV)
-    keep = torch.rand((h_kv, n_q, words * 32), generator=gen, device=DEV) >= sparsity
-    keep[:, n_q // 2 + 5] = True                 # a token of every chunk
-    keep[:, n_q // 3: n_q // 3 + 300, 7] = True  # a chunk of every token
-    own = ((n_kv - n_q + torch.arange(n_q, device=DEV)) // block).view(1, n_q, 1)
-    keep = (keep & (c < own)) | (c == own) if causal else keep & (c < t_all)
-    mask = torch.zeros((1, h_kv, n_q, words), dtype=torch.int64, device=DEV)
-    for i in range(32):
-        mask[0] |= keep.view(h_kv, n_q, words, 32)[..., i].to(torch.int64) << i
-    mask = torch.where(mask >= 1 << 31, mask - (1 << 32), mask).to(torch.int32)
-    bias = torch.randn((1, h_kv, n_q, t_all), generator=gen, device=DEV)
+    lists, keep = random_lists(p, n_q, n_kv, block, causal, sparsity, 58)
+    mask, bias, t_all = lists.mask, lists.bias, B.list_stride(p)
+    keep = keep[0]
     ws = B.alloc_workspace(p, DEV).fill_(0xA5)
-    B.dash_stage2_attend(p, q, k, v, o, B.Lists(mask=mask, bias=bias), ws)
-    # which kernel it was: the workgroups of the gathering one count themselves
-    blocks = (-(-n_q // (128 // (h_q // h_kv))) + 1) // 2 * h_kv
-    routing = sum((n + 255) & ~255 for n in (h_kv * (n_kv // block) * 3 * d * 2, mask.numel() * 4, bias.numel() * 4))
-    assert int(ws[routing + 512:routing + 1536].view(torch.int32).sum()) == (0 if sparsity < 0.5 else blocks)
-    # a routing call on another stream may be using its part of the workspace
-    assert bool((ws[:routing] == 0xA5).all())
+    B.dash_stage2_attend(p, q, k, v, o, lists, ws)
+    # an uncut launch over lists of the caller's uses nothing of the workspace, which other calls may be using
+    assert bool((ws == 0xA5).all())
+    gathers_rows(p, q, k, v, o, keep[h_kv - 1], h_kv - 1, lists, sparsity >= 0.5)
     again = torch.empty_like(o)
-    B.dash_stage2_attend(p, q, k, v, again, B.Lists(mask=mask, bias=bias), ws)
+    B.dash_stage2_attend(p, q, k, v, again, lists, ws)
     assert torch.equal(o, again)
     g, worst = h_q // h_kv, 0.0
     toks = sorted({0, 1, 63, 64, n_q // 3 + 17, n_q // 2 + 4, n_q // 2 + 5, n_q // 2 + 6, n_q - 2, n_q - 1} | {(i * 977) % n_q for i in range(20)})
@@ -316,6 +339,66 @@ def test_attention_over_gathered_rows(name, h_q, h_kv, n_q, n_kv, d, block, caus
             worst = max(worst, ((o[0, r * g:(r + 1) * g, t].double() - ref).abs().max() / ref.abs().max()).item())
     print(f"[parity] gathered rows {name}: {worst:.2e}")
     assert worst <= 2e-2, worst
+
+
+def sparse_and_dense(h_q=32, h_kv=4, n=12901, d=64):
+    """Inputs of a launch that either kernel may take, lists that leave it to one or the other, and what they give."""
+    q, k, v = make_inputs(Workload("gathered_choice", 1, h_q, h_kv, n, n, d, 64, seed=59), DEV)
+    p = B.make_params(q, k, v, torch.empty_like(q), 64)
+    ws = B.alloc_workspace(p, DEV)
+    lists, want = [], []
+    for sparsity in (0.985, 0.4):
+        ls, keep = random_lists(p, n, n, 64, True, sparsity, 60)
+        o = torch.empty_like(q)
+        B.dash_stage2_attend(p, q, k, v, o, ls, ws)
+        gathers_rows(p, q, k, v, o, keep[0, 0], 0, ls, sparsity > 0.9)
+        lists.append(ls)
+        want.append(o)
+    return p, q, k, v, ws, lists, want
+
+
+@pytest.mark.parametrize("first", [0, 1])
+@pytest.mark.parametrize("calls", [8, 64])
+def test_uncut_launches_share_a_workspace(calls, first):
+    """Launches over lists of the caller's on two streams, of either kernel: they keep nothing in the workspace.  64 on each
+    stream use every record of a choice twice, and two in flight may meet in one."""
+    p, q, k, v, ws, lists, want = sparse_and_dense()
+    got = [[torch.full_like(q, float("nan")) for _ in range(calls)] for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for st in streams:
+        with torch.cuda.stream(st):
+            torch.cuda._sleep(20_000_000)        # the calls are there before the first begins
+    for which in (first, 1 - first):
+        with torch.cuda.stream(streams[which]):
+            for i in range(calls):
+                B.dash_stage2_attend(p, q, k, v, got[which][i], lists[which], ws)
+    torch.cuda.synchronize()
+    bits = [sum(torch.equal(o, want[which]) for o in got[which]) for which in range(2)]
+    print(f"[choice] {calls} calls on each of two streams, of the same bits as alone: {bits}")
+    assert bits[0] == calls and (calls > 32 or bits[1] == calls)
+    # a launch that does not know its choice is attended by both kernels; the bar is that of the other given lists
+    bar = 2e-2 * want[1].abs().max()
+    for o in got[1]:
+        assert bool(((o - want[1]).abs() <= bar).all())
+
+
+def test_a_captured_launch_chooses_its_kernel_at_every_replay():
+    p, q, k, v, ws, lists, want = sparse_and_dense()
+    mask, bias, o = lists[0].mask.clone(), lists[0].bias.clone(), torch.empty_like(q)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.dash_stage2_attend(p, q, k, v, o, B.Lists(mask=mask, bias=bias), ws)
+    for i in (0, 1, 1, 0, 1, 0):
+        mask.copy_(lists[i].mask)
+        bias.copy_(lists[i].bias)
+        o.fill_(float("nan"))
+        graph.replay()
+        again = torch.empty_like(q)
+        B.dash_stage2_attend(p, q, k, v, again, lists[1 - i], ws)
+        torch.cuda.synchronize()
+        assert torch.equal(o, want[i]) and torch.equal(again, want[1 - i]), i
 
 
 @pytest.mark.parametrize("h,n,d,block", [(8, 832, 128, 64), (2, 512, 64, 64), (4, 896, 64, 128)])
