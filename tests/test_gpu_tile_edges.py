@@ -1,6 +1,8 @@
 """GPU parity at the sizes where the tilings change: the ranges of the decode step's kernels, the
 128-key tiles and the cut row ranges of the backward pass, the 16-row tiles of the fp32 kernels.
 Oracle and tolerances are those of parity_util and test_gpu_backward."""
+import itertools
+
 import numpy as np
 import pytest
 import torch
@@ -247,7 +249,8 @@ def test_attention_over_lists_at_word_edges(h_q, n_q, chunks, d, block):
 
 
 def random_lists(p, n_q, n_kv, block, causal, sparsity, seed):
-    """Lists of chunks kept at random, with a token of every chunk and a chunk of every token of a stretch."""
+    """Lists of chunks kept at random, with a token of every chunk and a chunk of every token of a stretch; without a causal mask
+    a token of no chunk."""
     t_all, words = B.list_stride(p), B.mask_words(p)
     gen = torch.Generator(device=DEV)
     gen.manual_seed(seed)
@@ -255,6 +258,7 @@ def random_lists(p, n_q, n_kv, block, causal, sparsity, seed):
     keep = torch.rand((p.batch, p.h_kv, n_q, words * 32), generator=gen, device=DEV) >= sparsity
     keep[:, :, n_q // 2 + 5] = True
     keep[:, :, n_q // 3: n_q // 3 + 300, 7] = True
+    keep[:, :, n_q // 4 + 3] &= causal
     own = ((n_kv - n_q + torch.arange(n_q, device=DEV)) // block).view(1, n_q, 1)
     keep = (keep & (c < own)) | (c == own) if causal else keep & (c < t_all)
     mask = torch.zeros((p.batch, p.h_kv, n_q, words), dtype=torch.int64, device=DEV)
@@ -284,7 +288,7 @@ def gathers_rows(p, q, k, v, o, keep, r, lists, expected):
 
 
 GATHERED = [
-    # name, h_q, h_kv, n_q, n_kv, d, block, causal, sparsity, interleaved: at least 320000 tiles of 128 rows x 64 keys
+    # name, h_q, h_kv, n_q, n_kv, d, block, causal, sparsity, interleaved, batch (1): at least 320000 tiles of 128 rows x 64 keys
     ("g4_odd_tail", 32, 8, 2000, 44240, 128, 64, True, 0.97, False),
     ("g4_interleaved_b128", 32, 8, 4097, 4097 + 64 * 300, 128, 128, True, 0.95, True),
     ("g4_d64_dense", 32, 8, 2000, 44240, 64, 64, True, 0.3, False),
@@ -293,15 +297,19 @@ GATHERED = [
     ("g2_d64_interleaved", 16, 8, 18432, 18432, 64, 64, True, 0.95, True),
     ("g2_one_token_over", 32, 16, 12865, 12865, 128, 64, True, 0.9, False),
     ("g8", 32, 4, 12901, 12901, 128, 64, True, 0.985, False),
+    ("g4_d64", 32, 8, 2000, 44240, 64, 64, True, 0.97, False),
+    ("g8_d64_interleaved", 32, 4, 12901, 12901, 64, 64, True, 0.985, True),
+    ("g4_two_sequences", 16, 4, 2000, 44240, 128, 64, True, 0.97, False, 2),
 ]
 
 
-@pytest.mark.parametrize("name,h_q,h_kv,n_q,n_kv,d,block,causal,sparsity,interleaved", GATHERED, ids=[c[0] for c in GATHERED])
-def test_attention_over_gathered_rows(name, h_q, h_kv, n_q, n_kv, d, block, causal, sparsity, interleaved):
+@pytest.mark.parametrize("case", GATHERED, ids=[c[0] for c in GATHERED])
+def test_attention_over_gathered_rows(case):
     """Launches large enough to be left to the kernel that gathers the rows of a chunk; tokens that keep every chunk, and chunks that
     every token of a stretch keeps, among sparse ones; logits that grow along the keys.  Reference in fp64 on sampled tokens.  The bar is
     that of the other given lists."""
-    w = Workload("gathered_" + name, 1, h_q, h_kv, n_q, n_kv, d, block, causal=causal, seed=57)
+    name, h_q, h_kv, n_q, n_kv, d, block, causal, sparsity, interleaved, batch = (*case, 1)[:11]
+    w = Workload("gathered_" + name, batch, h_q, h_kv, n_q, n_kv, d, block, causal=causal, seed=57)
     q, k, v = make_inputs(w, DEV)
     k *= torch.linspace(0.5, 3.0, n_kv, device=DEV).view(1, 1, n_kv, 1).to(k.dtype)
     if interleaved:                              # [batch, token, head, d] in memory
@@ -309,36 +317,71 @@ def test_attention_over_gathered_rows(name, h_q, h_kv, n_q, n_kv, d, block, caus
     o = torch.full_like(q, float("nan"))
     p = B.make_params(q, k, v, o, block, causal=causal)
     lists, keep = random_lists(p, n_q, n_kv, block, causal, sparsity, 58)
-    mask, bias, t_all = lists.mask, lists.bias, B.list_stride(p)
-    keep = keep[0]
+    t_all = B.list_stride(p)
     ws = B.alloc_workspace(p, DEV).fill_(0xA5)
     B.dash_stage2_attend(p, q, k, v, o, lists, ws)
     # an uncut launch over lists of the caller's uses nothing of the workspace, which other calls may be using
     assert bool((ws == 0xA5).all())
-    gathers_rows(p, q, k, v, o, keep[h_kv - 1], h_kv - 1, lists, sparsity >= 0.5)
+    gathers_rows(p, q, k, v, o, keep[0, h_kv - 1], h_kv - 1, lists, sparsity >= 0.5)
     again = torch.empty_like(o)
     B.dash_stage2_attend(p, q, k, v, again, lists, ws)
     assert torch.equal(o, again)
     g, worst = h_q // h_kv, 0.0
     toks = sorted({0, 1, 63, 64, n_q // 3 + 17, n_q // 2 + 4, n_q // 2 + 5, n_q // 2 + 6, n_q - 2, n_q - 1} | {(i * 977) % n_q for i in range(20)})
-    assert bool(torch.isfinite(o[0].float()).all())
-    for r in range(h_kv):
+    assert bool(torch.isfinite(o.float()).all())
+    if not causal:
+        assert bool((o[:, :, n_q // 4 + 3] == 0).all())
+    for s, r in itertools.product(range(batch), range(h_kv)):
         for t in toks:
             pos = n_kv - n_q + t
-            kept = keep[r, t, :t_all]
+            kept = keep[s, r, t, :t_all]
             add = torch.full((t_all,), float("-inf"), device=DEV, dtype=torch.float64)
-            add[kept] = bias[0, r, t, :int(kept.sum())].double()
+            add[kept] = lists.bias[s, r, t, :int(kept.sum())].double()
             if causal:
                 add[pos // block] = 0.0
             add = add.repeat_interleave(block)[:n_kv]
             if causal:
                 add[pos + 1:] = float("-inf")
             j = add > float("-inf")
-            z = q[0, r * g:(r + 1) * g, t].double() @ k[0, r, j].double().T / d ** 0.5 + add[j]
-            ref = torch.softmax(z, -1) @ v[0, r, j].double()
-            worst = max(worst, ((o[0, r * g:(r + 1) * g, t].double() - ref).abs().max() / ref.abs().max()).item())
+            z = q[s, r * g:(r + 1) * g, t].double() @ k[s, r, j].double().T / d ** 0.5 + add[j]
+            ref = torch.softmax(z, -1) @ v[s, r, j].double()
+            worst = max(worst, ((o[s, r * g:(r + 1) * g, t].double() - ref).abs().max() / ref.abs().max()).item())
     print(f"[parity] gathered rows {name}: {worst:.2e}")
     assert worst <= 2e-2, worst
+
+
+@pytest.mark.parametrize("batch,h_q,h_kv,n_q,n_kv,d", [(1, 32, 8, 2000, 44240, 128), (2, 16, 2, 2003, 44243, 64)])
+def test_gathered_rows_behind_the_end_of_a_padded_buffer(batch, h_q, h_kv, n_q, n_kv, d):
+    """NaN behind the last token of every head of a larger buffer, with a last chunk that is not full: nobody reads it."""
+    q, k, v = make_inputs(Workload("gathered_padded", batch, h_q, h_kv, n_q, n_kv, d, 64, seed=61), DEV)
+    p = B.make_params(q, k, v, torch.empty_like(q), 64)
+    lists, keep = random_lists(p, n_q, n_kv, 64, True, 0.985, 62)
+
+    def padded(x):
+        big = torch.full((*x.shape[:2], x.shape[2] + 40, d), float("nan"), dtype=x.dtype, device=DEV)
+        big[:, :, :x.shape[2]] = x
+        return big[:, :, :x.shape[2]]
+
+    out = []
+    for qq, kk, vv in ((q, k, v), (padded(q), padded(k), padded(v))):
+        o = torch.full_like(q, float("nan"))
+        pp = B.make_params(qq, kk, vv, o, 64)
+        B.dash_stage2_attend(pp, qq, kk, vv, o, lists, B.alloc_workspace(pp, DEV))
+        out.append(o)
+    gathers_rows(p, q, k, v, out[0], keep[0, h_kv - 1], h_kv - 1, lists, True)
+    assert bool(torch.isfinite(out[1].float()).all())
+    assert torch.equal(out[0], out[1])
+
+
+def test_prefill_that_gathers_rows():
+    """The whole prefill, two sequences, a window beside the routed chunks.  Oracle and tolerances are those of the other prefills."""
+    w = Workload("gathered_prefill", 2, 16, 4, 12901, 12901, 128, 64, alpha=2.0, gamma=4.0, window=1, offset_sigma=1.0, seed=63)
+    q, k, v = make_inputs(w, DEV)
+    run = U.run_prefill(w, q, k, v)
+    rep, _ = U.check_against_oracle(w, q, k, v, run, rows=U.sample_rows(w, 24, heads=[(0, 0), (0, 3), (1, 1)]))
+    print(f"[parity] gathered prefill: sparsity {rep.sparsity:.3f} {rep.errors()}")
+    keep = torch.stack([(run.lists.mask[0, 3, :, c // 32] >> (c % 32)) & 1 for c in range(B.list_stride(run.params))], 1).bool()
+    gathers_rows(run.params, q, k, v, run.o, keep, 3, run.lists, True)
 
 
 def sparse_and_dense(h_q=32, h_kv=4, n=12901, d=64):
