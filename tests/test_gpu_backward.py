@@ -111,6 +111,9 @@ CASES = [
     ("f32_mha_d64_b64", 1, 2, 2, 320, 64, 64, {"dtype": "fp32", "offset_sigma": 0.8}),
     # the shape of the fp32 single-head non-causal configuration
     ("f32_single_head_1024", 1, 1, 1, 1024, 64, 64, {"dtype": "fp32", "causal": False, "offset_sigma": 0.5}),
+    # row tiles cut into five parts, whose records are added four at a time; a weak prior, so that ill-conditioned rows do not hide them
+    ("f32_five_parts", 1, 1, 1, 1300, 64, 64, {"dtype": "fp32", "offset_sigma": 1.0, "sigma": 1e3}),
+    ("f32_five_parts_d128", 1, 1, 1, 1537, 128, 64, {"dtype": "fp32", "offset_sigma": 1.0, "sigma": 1e3}),
     ("f32_window2_b128", 1, 4, 2, 768, 128, 128, {"dtype": "fp32", "window": 2, "offset_sigma": 0.8}),
     ("f32_sparse_gamma3_sigma03", 1, 4, 2, 512, 128, 64, {"dtype": "fp32", "gamma": 3.0, "sigma": 0.3, "offset_sigma": 1.0}),
     ("f32_alpha3", 1, 4, 2, 512, 128, 64, {"dtype": "fp32", "alpha": 3.0, "offset_sigma": 0.8}),
