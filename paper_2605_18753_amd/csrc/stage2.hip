@@ -86,7 +86,7 @@ constexpr int kMaxParts = 1536;    // records of a launch
 // second the other, and they add up through LDS.  For launches that leave every CU at most one workgroup (see s2_paired): a
 // lone wave per SIMD takes three times a tile's matrix time, so the longest list is what such a launch takes.
 // WAVES: per SIMD.  At head dimension 64 three fit with operands of the first product read two steps ahead instead of four (168
-// registers; see launch_s2_t).
+// registers, and three spilled that only masked keys, a rising maximum and the end of the walk reload; see launch_s2_t).
 template <int D, bool DENSE, bool PAIR, int WAVES = 2>
 __global__ __launch_bounds__(PAIR ? 512 : 256, WAVES) void s2_attend_kernel(S2Args a) {
   using C = S2Cfg<D>;

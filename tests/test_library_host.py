@@ -353,6 +353,17 @@ def test_threshold_solvers_use_no_scratch_memory():
     assert not {n: b for n, b in {**routing, **decode}.items() if b}
 
 
+def test_prefill_attention_keeps_its_registers():
+    """Stage 2 of the prefill holds sums and operands in registers up to what its waves per SIMD leave.  The build with three waves per SIMD spills three of
+    them, reloaded where keys are masked, where a maximum rises and behind the tiles; the gathering kernel at head dimension 128 twelve to fifteen, most of
+    them reloaded once per item."""
+    scratch = kernel_scratch(B.LIB_PATH)
+    kernels = {n: b for n, b in scratch.items() if re.search(r"(16s2_attend|16s2_gather|15s2_merge|15s2_costs)_kernel", n)}
+    assert len(kernels) == 10 + 8 + 2 + 1
+    allowed = {n: 64 if "s2_gather_kernelILi128E" in n else 16 if "s2_attend_kernelILi64ELb0ELb0ELi3E" in n else 0 for n in kernels}
+    assert not {n: b for n, b in kernels.items() if b > allowed[n]}
+
+
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 WRITES_VECTOR_REGISTERS = re.compile(r"v_(?!writelane|readlane|readfirstlane|cmp)|scratch_|global_|buffer_|flat_|ds_")
 
