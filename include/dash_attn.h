@@ -25,6 +25,9 @@
  *     Entry points may be called from several threads.  A workspace belongs to one call at a time: calls that are in
  *     flight together (several streams) need one each, or must not use it.  dash_stage2_attend of a bf16 prefill uses
  *     it for lists that are not given, and for parts where few rows meet a long cache.
+ *     A call repeated on the same inputs gives the same bits, with two exceptions: fp32 gradients are added up in no fixed order, and
+ *     while more than 64 large bf16 prefills are in flight on a GPU, one may be given the bits of the other Stage-2 kernel.  Which of the two
+ *     such a prefill takes depends on the lists of all its sequences and heads: the last bits of a sequence may change with those beside it.
  *   - Tensors are [batch, head, token, head_dim] with head_dim contiguous; the
  *     other three strides are given in ELEMENTS in dash_params.  Rows must be
  *     16-byte aligned (base pointers 16-byte aligned, strides multiples of 8

@@ -21,9 +21,9 @@
 // clock: 3250 of them per item instead of 1340.  So four adjacent lanes load 64 bytes of a row, and the LDS crossbar moves them to their lanes (with
 // selects between neighbouring lanes instead the vector pipe has 27 % more to do: 3.20 -> 3.10 ms at 32k tokens, group of 4, 9 % kept).
 //
-// What bounds it: a wave's chain of loads, products and vector work, two waves per SIMD (256 registers; head dimension 64: three, 1.97 -> 1.79 ms
-// there).  128k tokens, 32 / 8 heads, chunks of 128, 12 % of them kept: 87 -> 40 ms for Stage 2 alone, vector pipe half and matrix pipe a fifth
-// busy, 19 TB/s out of L2.  Copies without one part: no loads but an item's first -18 %, no sums in LDS -10, no wait for a token's earlier entries -7
+// What bounds it: a wave's chain of loads, products and vector work, two waves per SIMD (256 registers and twelve to fifteen spilled, most of
+// them reloaded once per item; head dimension 64: three waves, none spilled, 1.97 -> 1.79 ms there).  128k tokens, 32 / 8 heads, chunks of 128, 12 % of them kept:
+// 87 -> 40 ms for Stage 2 alone, vector pipe two fifths and matrix pipe a fifth busy, 20 TB/s out of L2.  Copies without one part: no loads but an item's first -18 %, no sums in LDS -10, no wait for a token's earlier entries -7
 // (before tiles were added one by one), no exponentials -2.
 #include <type_traits>
 
@@ -36,10 +36,11 @@ namespace dash {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// Launches of fewer 128-row tiles times 64-key tiles of a row (half of them for a whole causal prompt) are not looked at: finding out
-// what the lists hold and the launch not used cost 7 us (4096 tokens, 32 / 8 heads, dense 160 -> 167 us; 16k tokens, 1.5 ms, less than
-// one run differs from the next; 8192 tokens of 16 heads, 66k of these, would gain 279 -> 189 us with 5 % of the chunks kept and lose 290 -> 301
-// with 20 %).
+// Launches of fewer 128-row tiles times 64-key tiles of a row (half of them for a whole causal prompt) are not looked at, so that no launch under
+// 1 ms pays for finding out what the lists hold and for the launch not used: 6 to 12 us (4096 tokens, 32 / 8 heads, dense 160 -> 167 us; 8192, 43 % kept,
+// 483 -> 494; 12000, a third kept, 974 -> 985; at 32k tokens, 7.7 ms, 13 us).  The line is drawn for the launches that stay, and those below it that
+// the costs would send here are left out.  Stage 2, there -> here: 2000 tokens against a 32k cache (249k of these) with 12 % kept 681 -> 414 us, 20 % 803 -> 598, correlated
+// queries and 2.5 % 199 -> 174, head dimension 64 and 12 % 498 -> 246; 8192 tokens, 32 / 8 heads (131k), 12 % 356 -> 284; 16000 tokens of 16 heads (250k), 8 % 829 -> 511.
 constexpr int64_t kMinTiles = 320000;
 
 template <int D, int G> struct GatherCfg {
@@ -76,7 +77,8 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
   const int blk = (a.n_tiles + 1) / 2 - 1 - bid / a.hb;                   // longest rows first
   const int r = hbi % a.h_kv, b = hbi / a.h_kv;
   // Workgroups dispatched together (256, one per CU) begin their walks together: the 32 of a die read the same head's chunks at the same
-  // time, out of its L2 (128k tokens in chunks of 128: L2 misses 62 % of the requests -> 5 %).
+  // time, out of its L2 (128k tokens in chunks of 128: L2 misses 6.8 % of the requests -> 4.7, 38.5 -> 38.4 ms for Stage 2; chunks of 64 17.49 -> 17.54,
+  // 32k tokens 2.08 -> 2.09: by now it is worth nothing where a head fits the L2, and little where it does not).
   int* arrived = a.choice->arrived + (bid & 7) * 32;
   if (wave == 0) {                                                        // one wave asks: what the record says may change between two looks
     const int c = s2_choice(a, lane);
@@ -440,7 +442,7 @@ __global__ __launch_bounds__((GatherCfg<D, G>::WAVES * 64), (GatherCfg<D, G>::WA
 // of 128 keys 3.9 (4.0) per 64.  An item holds up to 32 / g_q tokens of a chunk, and on average three tenths of the chunks have one that is
 // not full.  Fitted to both kernels' times over 94 launches (16k and 32k tokens and 2000 against a 32k cache, groups of 1 to 8, both head dimensions and chunk
 // sizes, 2 to 60 % of the chunks kept, queries independent and correlated): the choice takes 0.7 % more time than the faster kernel of each, and
-// none of them more than s2_attend_kernel.  32k tokens, there -> here: group of 4, 9 % kept 4.50 -> 3.00 ms, 26 % 6.72 -> 6.05 (not taken), 41 % 7.3 -> 8.5 (not
+// none of them more than s2_attend_kernel.  The 12 launches of 2000 tokens lie below kMinTiles and are not given the choice.  32k tokens, there -> here: group of 4, 9 % kept 4.50 -> 3.00 ms, 26 % 6.72 -> 6.05 (not taken), 41 % 7.3 -> 8.5 (not
 // taken); 9 % with correlated queries 2.44 -> 2.65 (not taken); chunks of 128, 16 % 5.84 -> 3.26; group of 1, 3 % 5.42 -> 2.9, 8 % 7.48 -> 3.66; head
 // dimension 64, 9 % 3.06 -> 1.69.
 __global__ __launch_bounds__(256) void s2_costs_kernel(S2Args a, float per_item) {
