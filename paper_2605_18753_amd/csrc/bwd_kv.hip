@@ -50,7 +50,8 @@ template <typename V> __device__ __forceinline__ V kbar_sum(const BwdArgs& a, co
 // TAIL: several heads and a last row tile that is not full.  The rows behind its last token are then copied as
 // zeros: the buffer resources reach over what lies between the heads (the padding of a larger buffer, another
 // head's rows), and 0 times what it holds could be a NaN.  In every launch the selection costs 0.5 % at d = 128
-// (8.04 against 8.00 ms, forward and backward of the shape above), nothing at d = 64, where there is no other build.
+// (8.04 against 8.00 ms, forward and backward of the shape above), nothing at d = 64, where there is no other build.  No vector register is spilled, 14 to 16
+// scalar ones are, to lanes of one.
 // At d = 64 three waves per SIMD (168 registers, operands read one step ahead instead of two; the build without the selection would spill
 // six): 2 x 16 / 4 heads x 3001 tokens 441 -> 408 us, forward and backward, 16 / 4 heads x 8000 1193 -> 1099, 8 heads x 4000 323 -> 309.
 template <int D, bool TAIL>
